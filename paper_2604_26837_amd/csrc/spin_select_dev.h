@@ -1,30 +1,23 @@
 // Device code of stage 2 (register-resident variant) shared by the stand-alone
 // kernel and the fused launch.
 #pragma once
+#include <type_traits>
+
 #include "spin_common.h"
 
 struct sel_plan {
   int P, nf_lo, first_hi, kprime, take;
 };
 
-// forced prefix / suffix and k' of a row of uniform partitions (same rules as select_reg_row)
-__device__ inline sel_plan select_plan(int N, int PP, int tp, int topk, int includes_forced, int sink_pages,
-                                       int recent_pages, int sel_stride) {
+// k' and the selection's length of a row of P partitions whose forced ones are [0, nf_lo) and [first_hi, P)
+__device__ inline sel_plan plan_of(int P, int nf_lo, int first_hi, int topk, int includes_forced, int sel_stride) {
   sel_plan pl;
-  int P = N > 0 ? (N + tp - 1) / tp : 0;
-  if (P > PP) P = PP;
-  const int pages = (N + 15) >> 4;
-  int sink_end = min(sink_pages, pages);
-  int recent_begin = max(pages - recent_pages, 0);
-  if (sink_end >= recent_begin) { sink_end = pages; recent_begin = pages; }
-  int nf_lo = (N <= sink_end * 16) ? P : min((sink_end * 16) / tp, P);
-  int first_hi = min((recent_begin * 16 + tp - 1) / tp, P);
   if (first_hi <= nf_lo) { nf_lo = P; first_hi = P; }
   const int nforced = nf_lo + (P - first_hi);
   int kprime = includes_forced ? max(topk - nforced, 0) : topk;
   kprime = min(kprime, P - nforced);
   int take = nforced + kprime;
-  if (take > sel_stride) {
+  if (take > sel_stride) {   // cannot happen for strides from spin_sel_stride(); keep stores in range
     kprime = max(sel_stride - nforced, 0);
     take = min(nforced + kprime, sel_stride);
   }
@@ -32,11 +25,293 @@ __device__ inline sel_plan select_plan(int N, int PP, int tp, int topk, int incl
   return pl;
 }
 
+// the same of a row of uniform partitions
+__device__ inline sel_plan select_plan(int N, int PP, int tp, int topk, int includes_forced, int sink_pages,
+                                       int recent_pages, int sel_stride) {
+  int P = N > 0 ? (N + tp - 1) / tp : 0;
+  if (P > PP) P = PP;
+  const int pages = (N + 15) >> 4;
+  int sink_end = min(sink_pages, pages);
+  int recent_begin = max(pages - recent_pages, 0);
+  if (sink_end >= recent_begin) { sink_end = pages; recent_begin = pages; }
+  const int nf_lo = (N <= sink_end * 16) ? P : min((sink_end * 16) / tp, P);
+  const int first_hi = min((recent_begin * 16 + tp - 1) / tp, P);
+  return plan_of(P, nf_lo, first_hi, topk, includes_forced, sel_stride);
+}
+
+// ---------------------------------------------------------------------------
+// Keys held in registers: KPT consecutive ones per thread, a bit mask says which of them count.
+template <int KPT>
+struct key_bits {
+  typedef typename std::conditional<(KPT > 32), uint64_t, uint32_t>::type type;
+};
+__device__ inline int popc_bits(uint32_t m) { return __popc(m); }
+__device__ inline int popc_bits(uint64_t m) { return __popcll(m); }
+__device__ inline int ffs_bits(uint32_t m) { return __ffs(m); }
+__device__ inline int ffs_bits(uint64_t m) { return __ffsll((unsigned long long)m); }
+// bits k of 0 .. KPT-1 with c0 + k in [a, b)
+template <int KPT>
+__device__ inline typename key_bits<KPT>::type range_bits(int c0, int a, int b) {
+  typedef typename key_bits<KPT>::type M;
+  constexpr M all = KPT == (int)(8 * sizeof(M)) ? ~(M)0 : (((M)1 << (KPT & (int)(8 * sizeof(M) - 1))) - 1);
+  const int lo = min(max(a - c0, 0), KPT), hi = min(max(b - c0, 0), KPT);
+  const M from = lo >= KPT ? (M)0 : (all << lo) & all;
+  const M upto = hi >= KPT ? all : ((M)1 << hi) - 1;
+  return from & upto;
+}
+
+template <int BLOCK>
+struct kth_lds {
+  int hist[4][256];   // one histogram per digit: no buffer is cleared while others read it
+  uint32_t wmax[BLOCK / 64], wmin[BLOCK / 64];
+};
+
+// Radix select over the workgroup's valid keys, most significant digit first: finds the threshold T and the
+// number `need_eq` of keys equal to T such that the keys above T and the first need_eq keys equal to T are the
+// k largest (lowest position first among equals), 1 <= k <= number of valid keys.  With slack > 0 the search
+// stops as soon as the keys at or above the digits settled so far number at most k + slack, and those are all
+// taken.  The digits start at the highest bit in which the keys differ at all (one min/max reduction): scores
+// of one row usually share sign, exponent and leading mantissa bits, so this saves a pass or two and, above
+// all, spreads the first histogram over many bins instead of piling every key onto one LDS counter.  Every
+// wavefront scans the 256 bins for itself: one barrier per digit.  A workgroup barrier must lie between two
+// uses of the same kth_lds.
+template <int BLOCK, int KPT>
+__device__ inline void block_kth(const uint32_t (&key)[KPT], typename key_bits<KPT>::type valid, int k, int slack,
+                                 kth_lds<BLOCK> &s, uint32_t &T, unsigned &need_eq) {
+  constexpr int NW = BLOCK / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  for (int i = tid; i < 4 * 256; i += BLOCK) (&s.hist[0][0])[i] = 0;
+  uint32_t kmx = 0u, kmn = 0xffffffffu;
+#pragma unroll
+  for (int j = 0; j < KPT; ++j)
+    if ((valid >> j) & 1u) { kmx = max(kmx, key[j]); kmn = min(kmn, key[j]); }
+  kmx = spin_wave_max_u32(kmx);
+  kmn = spin_wave_min_u32(kmn);
+  if (lane == 0) { s.wmax[wave] = kmx; s.wmin[wave] = kmn; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { kmx = max(kmx, s.wmax[w]); kmn = min(kmn, s.wmin[w]); }
+  int hi = kmx == kmn ? 0 : 32 - __clz((int)(kmx ^ kmn));   // the low `hi` bits are the ones that vary
+  uint32_t prefix = hi < 32 ? kmx >> hi : 0u;
+  int remaining = k;
+#pragma unroll
+  for (int pass = 0; pass < 4; ++pass) {
+    if (hi <= 0) break;                                  // block-uniform
+    const int lo = max(hi - 8, 0), width = hi - lo;
+    const uint32_t dmask = (1u << width) - 1u;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j)
+      if (((valid >> j) & 1u) && (pass == 0 || (key[j] >> hi) == prefix))
+        atomicAdd(&s.hist[pass][(key[j] >> lo) & dmask], 1);
+    __syncthreads();
+    // suffix scan: lane handles digits 255-4*lane .. 252-4*lane, in descending order
+    int hv[4], local = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) { hv[j] = s.hist[pass][255 - 4 * lane - j]; local += hv[j]; }
+    int running = spin_wave_inclusive_scan(local) - local;
+    int my_digit = -1, my_rem = 0, my_cnt = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (running < remaining && running + hv[j] >= remaining) {
+        my_digit = 255 - 4 * lane - j;
+        my_rem = remaining - running;
+        my_cnt = hv[j];
+      }
+      running += hv[j];
+    }
+    const unsigned long long found = __ballot(my_digit >= 0);
+    if (!found) break;                                   // fewer than k valid keys: not a call this function takes
+    const int src = __ffsll((long long)found) - 1;
+    const int digit = __builtin_amdgcn_readlane(my_digit, src), in_digit = __builtin_amdgcn_readlane(my_cnt, src);
+    remaining = __builtin_amdgcn_readlane(my_rem, src);
+    prefix = (prefix << width) | (uint32_t)digit;
+    hi = lo;
+    // every key that shares this prefix is wanted (or may be taken as well): the digits below cannot change
+    // the outcome.  The threshold becomes the smallest key with the prefix, of which there may be several or
+    // none: all are wanted, and the count of the prefix covers them.
+    if (in_digit - remaining <= slack && hi > 0) {       // block-uniform
+      prefix <<= hi;
+      remaining = in_digit;
+      break;
+    }
+  }
+  T = prefix;
+  need_eq = (unsigned)remaining;
+}
+
+// of `eq`, the bits that fall within the first `quota` in order
+template <typename M>
+__device__ inline M first_bits(M eq, unsigned quota) {
+  M out = 0;
+  while (eq && quota) {
+    const M b = eq & (M)(~eq + 1);
+    out |= b;
+    eq ^= b;
+    --quota;
+  }
+  return out;
+}
+
+// Turns every thread's `sure` bits (taken) and `eq` bits (taken while fewer than need_eq of them precede) into
+// its final pick mask and the output position of its first pick (positions follow thread, then bit order).
+template <int BLOCK, typename M>
+__device__ inline M ordered_picks(M sure, M eq, unsigned need_eq, unsigned long long *s_wtot, int &pos) {
+  constexpr int NW = BLOCK / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n_sure = popc_bits(sure), n_eq = popc_bits(eq);
+  // the two counts never carry into one another: scanned separately, passed on in one word
+  const uint32_t i_sure = (uint32_t)spin_wave_inclusive_scan(n_sure), i_eq = (uint32_t)spin_wave_inclusive_scan(n_eq);
+  if (lane == 63) s_wtot[wave] = (unsigned long long)i_sure | ((unsigned long long)i_eq << 32);
+  __syncthreads();
+  unsigned sure_before = i_sure - n_sure, eq_before = i_eq - n_eq;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    const unsigned long long t = s_wtot[w];
+    if (w < wave) { sure_before += (uint32_t)t; eq_before += (uint32_t)(t >> 32); }
+  }
+  pos = (int)(sure_before + min(eq_before, need_eq));
+  return sure | first_bits(eq, need_eq > eq_before ? need_eq - eq_before : 0u);
+}
+
+// The smallest score whose key is at least K (keys as in score_key).  Bit patterns that are no
+// ordered number: below -inf every real key of the bin is at least key(-inf), so `low_end` asks
+// for -inf there; above +inf no key exists and the NaN returned fails every comparison.
+__device__ inline float key_floor_score(uint32_t K, bool low_end) {
+  const uint32_t u = (K & 0x80000000u) ? (K ^ 0x80000000u) : ~K;
+  if ((u & 0x7fffffffu) > 0x7f800000u) return (low_end && (u & 0x80000000u)) ? -__builtin_inff() : __builtin_nanf("");
+  return __uint_as_float(u);
+}
+#define SPIN_KEY_MINUS_INF 0x007fffffu
+
+// LDS of select_elements: the candidates that are left, in partition order
+template <int BLOCK, int CAP>
+struct elements_lds {
+  kth_lds<BLOCK> kth;
+  unsigned long long wtot[BLOCK / 64];
+  uint32_t key[CAP > 0 ? CAP : 1];
+  int32_t id[CAP > 0 ? CAP : 1];
+};
+
+// Picks the kprime best of the candidates a workgroup holds in registers (KPT scores per thread, bit k of `cand`:
+// f[k] is a candidate; thread, then k is ascending partition order; id(k) names its partition) and stores their
+// ids at rsel[first ..], ascending.  `bound`: a key that at least kprime of the candidates reach (0: none known).
+// What the one compute unit of a row spends its time on is instructions per score (at 1024 threads one
+// instruction on every thread's score takes the unit 6.7 ns), so a score is only compared as a float with the
+// bound (key order is float order) and the few that pass form a list in LDS, on which the exact search runs with
+// one to CAP / BLOCK keys per thread.  A row with more than CAP of them (every row where CAP is 0: few scores per
+// thread, for which the list does not pay) searches its registers.
+template <int BLOCK, int KPT, int CAP, typename ID>
+__device__ inline void select_elements(const float (&f)[KPT], typename key_bits<KPT>::type cand, uint32_t bound,
+                                       int kprime, int first, int sel_stride, int32_t *__restrict__ rsel,
+                                       elements_lds<BLOCK, CAP> &s, ID id) {
+  typedef typename key_bits<KPT>::type M;
+  [[maybe_unused]] constexpr int NW = BLOCK / 64;
+  [[maybe_unused]] const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  M valid = cand;
+  if (bound > SPIN_KEY_MINUS_INF) {            // (at -inf NaN scores, which rank there, would fail the comparison)
+    const float bf = key_floor_score(bound, true);
+    M above = 0;
+#pragma unroll
+    for (int k = 0; k < KPT; ++k) above |= f[k] >= bf ? (M)1 << k : (M)0;
+    valid &= above;
+  }
+  uint32_t T;
+  unsigned need_eq;
+  if constexpr (CAP > 0) {
+    // ordered list of the candidates left
+    const int mine = popc_bits(valid);
+    const int inc = spin_wave_inclusive_scan(mine);
+    if (lane == 63) s.wtot[wave] = (unsigned)inc;
+    __syncthreads();
+    int before = inc - mine, total = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int t = (int)s.wtot[w];
+      if (w < wave) before += t;
+      total += t;
+    }
+    if (total <= CAP) {                          // block-uniform
+      if (valid) {
+        int pos = before;
+#pragma unroll
+        for (int k = 0; k < KPT; ++k)
+          if ((valid >> k) & 1u) {
+            s.key[pos] = score_key(f[k]);
+            s.id[pos] = id(k);
+            ++pos;
+          }
+      }
+      __syncthreads();
+      constexpr int LPT = CAP / BLOCK;           // list entries per thread
+      auto pick_list = [&](auto entries) {
+        constexpr int E = decltype(entries)::value;
+        uint32_t key[E];
+#pragma unroll
+        for (int j = 0; j < E; ++j) key[j] = tid * E + j < total ? s.key[tid * E + j] : 0u;
+        const uint32_t have = range_bits<E>(tid * E, 0, total);
+        block_kth<BLOCK, E>(key, have, kprime, 0, s.kth, T, need_eq);
+        uint32_t gt = 0, eq = 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+          gt |= key[j] > T ? 1u << j : 0u;
+          eq |= key[j] == T ? 1u << j : 0u;
+        }
+        int pos;
+        uint32_t pick = ordered_picks<BLOCK>(gt & have, eq & have, need_eq, s.wtot, pos);
+        pos += first;
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+          if ((pick >> j) & 1u) {
+            if (pos < sel_stride) rsel[pos] = s.id[tid * E + j];
+            ++pos;
+          }
+      };
+      if (total <= BLOCK) pick_list(std::integral_constant<int, 1>());
+      else pick_list(std::integral_constant<int, LPT>());
+      return;
+    }
+  }
+  uint32_t key[KPT];
+#pragma unroll
+  for (int k = 0; k < KPT; ++k) key[k] = score_key(f[k]);
+  block_kth<BLOCK, KPT>(key, valid, kprime, 0, s.kth, T, need_eq);
+  M gt = 0, eq = 0;
+#pragma unroll
+  for (int k = 0; k < KPT; ++k) {
+    gt |= key[k] > T ? (M)1 << k : (M)0;
+    eq |= key[k] == T ? (M)1 << k : (M)0;
+  }
+  int pos;
+  const M pick = ordered_picks<BLOCK>((M)(gt & valid), (M)(eq & valid), need_eq, s.wtot, pos);
+  pos += first;
+#pragma unroll
+  for (int k = 0; k < KPT; ++k)
+    if ((pick >> k) & 1u) {
+      if (pos < sel_stride) rsel[pos] = id(k);
+      ++pos;
+    }
+}
+
+// forced partitions (a prefix and a suffix of the row) around the kprime candidates, and the padding
+template <int BLOCK>
+__device__ inline void emit_forced(const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
+                                   int32_t *__restrict__ nsel, int row) {
+  const int tid = threadIdx.x;
+  for (int i = tid; i < min(pl.nf_lo, sel_stride); i += BLOCK) rsel[i] = i;
+  const int at = pl.nf_lo + pl.kprime;
+  for (int i = tid; i < pl.P - pl.first_hi && at + i < sel_stride; i += BLOCK) rsel[at + i] = pl.first_hi + i;
+  for (int i = pl.take + tid; i < sel_stride; i += BLOCK) rsel[i] = -1;
+  if (tid == 0) nsel[row] = pl.take;
+}
+
 // Register-resident variant for rows of at most BLOCK * KPT partitions: every
-// thread keeps KPT consecutive keys in registers, so scores are read once; each
-// digit has its own LDS histogram, every wavefront does the 256-bin suffix scan
-// for itself (one barrier per digit), and the two compaction prefix sums share
-// one scan.
+// thread keeps KPT consecutive scores in registers, so they are read once.
+// With 16 or more of them per thread most are ruled out first: the k'-th largest of the threads' largest keys
+// is a lower bound of the threshold (k' threads hold a key at least that large).
+// Latency bounds this kernel: dependent loads, a barrier per digit, and the instructions per score on the row's
+// one compute unit.  Stages 2+3, top 128, before (every score in every histogram) and after: 8 rows of 8192
+// 14.7 -> 9.4 us, 8 rows of 16384 16.2 -> 11.5, 256 ragged rows of up to 16384 17.4 -> 13.4; rows of 62500 in the
+// long-row kernel's multi-pass fall-back 69 -> 29.
 // Returns the number of selected partitions.
 template <int BLOCK, int KPT>
 __device__ inline int select_reg_row(
@@ -44,217 +319,64 @@ __device__ inline int select_reg_row(
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
     int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, int row,
     spin_var var) {
-  constexpr int NW = BLOCK / 64;
-  __shared__ int s_hist[4][256];   // one histogram per digit: no buffer is cleared while others read it
-  __shared__ unsigned long long s_wtot[NW];
+  typedef typename key_bits<KPT>::type M;
+  constexpr int CAP = KPT >= 16 ? 2 * BLOCK : 0;
+  __shared__ elements_lds<BLOCK, CAP> s;
 
   const int b = row / Hkv, h = row - b * Hkv;
   const int N = seq_lens[b];
   const int off_b = part_offsets[b];
   const int PP = part_offsets[b + 1] - off_b;
-  const float *rs = scores + (size_t)Hkv * off_b + (size_t)h * PP;
-  int32_t *rsel = sel + (size_t)row * sel_stride;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const size_t vbase = (size_t)Hkv * off_b + (size_t)h * PP;
-  int P = var.count ? var.count[row] : (N > 0 ? (N + tp - 1) / tp : 0);
-  if (P < 0) P = 0;
-  if (P > PP) P = PP;
-  if (P > BLOCK * KPT) P = BLOCK * KPT;   // the host picks a variant that fits; keep indexing in range
-
-  // keys of partitions c0 .. c0+KPT-1
-  const int c0 = tid * KPT;
-  uint32_t key[KPT];
+  const float *rs = scores + vbase;
+  int32_t *rsel = sel + (size_t)row * sel_stride;
+  const int c0 = threadIdx.x * KPT;   // this thread's partitions: c0 .. c0 + KPT - 1
+  float f[KPT];
 #pragma unroll
   for (int k4 = 0; k4 < KPT; k4 += 4) {
-    float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (c0 + k4 < PP) f = *(const float4 *)(rs + c0 + k4);
-    key[k4] = score_key(f.x); key[k4 + 1] = score_key(f.y); key[k4 + 2] = score_key(f.z); key[k4 + 3] = score_key(f.w);
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (c0 + k4 < PP) v = *(const float4 *)(rs + c0 + k4);
+    f[k4] = v.x; f[k4 + 1] = v.y; f[k4 + 2] = v.z; f[k4 + 3] = v.w;
   }
 
   // forced partitions: a prefix [0, nf_lo) and a suffix [first_hi, P)
-  const int pages = var.count ? spin_var_row_pages(var, vbase, P) : ((N + 15) >> 4);
-  int sink_end = min(sink_pages, pages);
-  int recent_begin = max(pages - recent_pages, 0);
-  if (sink_end >= recent_begin) { sink_end = pages; recent_begin = pages; }
-  int nf_lo, first_hi;
+  sel_plan pl;
   if (var.count) {
-    nf_lo = spin_var_count_end_le(var, vbase, P, sink_end);
-    first_hi = spin_var_lower_bound_start(var, vbase, P, recent_begin);
+    int P = var.count[row];
+    P = P < 0 ? 0 : (P > PP ? PP : P);
+    const int pages = spin_var_row_pages(var, vbase, P);
+    int sink_end = min(sink_pages, pages);
+    int recent_begin = max(pages - recent_pages, 0);
+    if (sink_end >= recent_begin) { sink_end = pages; recent_begin = pages; }
+    pl = plan_of(P, spin_var_count_end_le(var, vbase, P, sink_end), spin_var_lower_bound_start(var, vbase, P, recent_begin),
+                 topk, includes_forced, sel_stride);
   } else {
-    nf_lo = (N <= sink_end * 16) ? P : min((sink_end * 16) / tp, P);
-    first_hi = min((recent_begin * 16 + tp - 1) / tp, P);
+    pl = select_plan(N, PP, tp, topk, includes_forced, sink_pages, recent_pages, sel_stride);
   }
-  if (first_hi <= nf_lo) { nf_lo = P; first_hi = P; }
-  const int nforced = nf_lo + (P - first_hi);
-  const int ncand = P - nforced;
-  int kprime = includes_forced ? max(topk - nforced, 0) : topk;
-  kprime = min(kprime, ncand);
-  int take = nforced + kprime;
-  if (take > sel_stride) {
-    kprime = max(sel_stride - nforced, 0);
-    take = min(nforced + kprime, sel_stride);
+  if (pl.P > BLOCK * KPT) {           // the host picks a variant that fits; keep indexing in range
+    pl.P = BLOCK * KPT;
+    pl.nf_lo = min(pl.nf_lo, pl.P);
+    pl.first_hi = max(min(pl.first_hi, pl.P), pl.nf_lo);
+    pl.kprime = min(pl.kprime, pl.first_hi - pl.nf_lo);
+    pl.take = min(pl.nf_lo + pl.kprime + pl.P - pl.first_hi, sel_stride);
   }
-  // candidates of this thread form the index range [ca, cb)
-  const int ca = max(c0, nf_lo), cb = min(c0 + KPT, first_hi);
-
-  uint32_t prefix = 0;
-  int remaining = kprime;
-  // Radix select of the k'-th largest candidate key, most significant digit first.  The digits
-  // start at the highest bit in which the row's candidate keys differ at all (one min/max
-  // reduction): scores of one row usually share sign, exponent and leading mantissa bits, so
-  // this saves a pass or two and, above all, spreads the first histogram over many bins
-  // instead of piling every key onto one LDS counter.
-  // Rows with many keys per thread: for the first digit every thread counts, in one packed
-  // register, its keys in the 8 highest digit values at or below the row's largest one; the full
-  // histogram is only built when the k'-th candidate lies below them.
-  constexpr bool TOP8 = KPT >= 16 && KPT <= 255;
-  __shared__ uint32_t s_wmax[NW], s_wmin[NW];
-  if (kprime > 0) {
-    for (int i = tid; i < 4 * 256; i += BLOCK) (&s_hist[0][0])[i] = 0;
-    uint32_t kmx = 0u, kmn = 0xffffffffu;
+  emit_forced<BLOCK>(pl, sel_stride, rsel, nsel, row);   // under way while the scores are still coming
+  if (pl.kprime > 0) {
+    const M cand = range_bits<KPT>(c0, pl.nf_lo, pl.first_hi);
+    uint32_t bound = 0;
+    if (KPT >= 16) {
+      const int holders = (pl.first_hi - 1) / KPT - pl.nf_lo / KPT + 1;   // threads that hold a candidate
+      if (holders >= pl.kprime + (pl.kprime >> 1)) {                      // block-uniform
+        float mx = -__builtin_inff();                                     // NaN scores rank as -inf: dropped
 #pragma unroll
-    for (int k = 0; k < KPT; ++k) {
-      const int p = c0 + k;
-      if (p >= ca && p < cb) { kmx = max(kmx, key[k]); kmn = min(kmn, key[k]); }
-    }
-    kmx = spin_wave_max_u32(kmx);
-    kmn = spin_wave_min_u32(kmn);
-    if (lane == 0) { s_wmax[wave] = kmx; s_wmin[wave] = kmn; }
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < NW; ++w) { kmx = max(kmx, s_wmax[w]); kmn = min(kmn, s_wmin[w]); }
-    int hi = kmx == kmn ? 0 : 32 - __clz((int)(kmx ^ kmn));   // the low `hi` bits are the ones that vary
-    prefix = hi < 32 ? kmx >> hi : 0u;
-    // Suffix scan of the 256-bin histogram `buf`, done by every wavefront for itself: digit of the
-    // remaining-th largest candidate (and how many are still wanted inside it), or -1 when the
-    // histogram holds fewer.  The result is uniform over the workgroup.
-    auto find_digit = [&](int buf, int &digit, int &in_digit) {
-      __syncthreads();
-      // lane handles digits 255-4*lane .. 252-4*lane, in descending order
-      int hv[4], local = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { hv[j] = s_hist[buf][255 - 4 * lane - j]; local += hv[j]; }
-      int running = spin_wave_inclusive_scan(local) - local;
-      int my_digit = -1, my_rem = 0, my_cnt = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        if (running < remaining && running + hv[j] >= remaining) {
-          my_digit = 255 - 4 * lane - j;
-          my_rem = remaining - running;
-          my_cnt = hv[j];
-        }
-        running += hv[j];
-      }
-      const unsigned long long found = __ballot(my_digit >= 0);
-      digit = -1;
-      in_digit = 0;
-      if (found) {
-        const int src = __ffsll((long long)found) - 1;
-        digit = __builtin_amdgcn_readlane(my_digit, src);
-        remaining = __builtin_amdgcn_readlane(my_rem, src);
-        in_digit = __builtin_amdgcn_readlane(my_cnt, src);
-      }
-    };
-#pragma unroll
-    for (int pass = 0; pass < 4; ++pass) {
-      if (hi <= 0) break;                                  // block-uniform
-      const int lo = max(hi - 8, 0), width = hi - lo;
-      const uint32_t dmask = (1u << width) - 1u;
-      const uint32_t top_digit = (kmx >> lo) & dmask;      // pass 0: the largest digit present
-      if (TOP8 && pass == 0) {
-        unsigned long long acc = 0;                  // 8 counters of 8 bits: digit top_digit - j in byte j
-#pragma unroll
-        for (int k = 0; k < KPT; ++k) {
-          const int p = c0 + k;
-          const uint32_t o = top_digit - ((key[k] >> lo) & dmask);
-          if (p >= ca && p < cb && o < 8u) acc += 1ull << (8u * o);
-        }
-        // widen to 16-bit fields (a wavefront holds at most 64 * 255 keys of one digit) and add up
-        unsigned long long even = acc & 0x00ff00ff00ff00ffull, odd = (acc >> 8) & 0x00ff00ff00ff00ffull;
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-          even += __shfl_xor(even, d);
-          odd += __shfl_xor(odd, d);
-        }
-        if (lane < 8) {
-          const unsigned long long v = (lane & 1) ? odd : even;
-          const int c = (int)((v >> (16 * (lane >> 1))) & 0xffffull);
-          if (c && (uint32_t)lane <= top_digit) atomicAdd(&s_hist[0][top_digit - lane], c);
-        }
-      } else {
-#pragma unroll
-        for (int k = 0; k < KPT; ++k) {
-          const int p = c0 + k;
-          if (p >= ca && p < cb && (pass == 0 || (key[k] >> hi) == prefix))
-            atomicAdd(&s_hist[pass][(key[k] >> lo) & dmask], 1);
-        }
-      }
-      int digit, in_digit;
-      find_digit(pass, digit, in_digit);
-      if (TOP8 && pass == 0 && digit < 0) {          // block-uniform: add the digits not counted yet
-        __syncthreads();                             // every wavefront has scanned the partial histogram
-#pragma unroll
-        for (int k = 0; k < KPT; ++k) {
-          const int p = c0 + k;
-          const uint32_t dg = (key[k] >> lo) & dmask;
-          if (p >= ca && p < cb && top_digit - dg >= 8u) atomicAdd(&s_hist[0][dg], 1);
-        }
-        find_digit(0, digit, in_digit);
-      }
-      prefix = (prefix << width) | (uint32_t)digit;
-      hi = lo;
-      // every candidate that shares this prefix is wanted: the digits below cannot change the outcome.  The
-      // threshold becomes the smallest key with the prefix, of which there may be several or none: all are
-      // wanted, and `remaining` (the candidates with the prefix) covers them.
-      if (in_digit == remaining && hi > 0) {         // block-uniform
-        prefix <<= hi;
-        break;
+        for (int k = 0; k < KPT; ++k) mx = fmaxf(mx, ((cand >> k) & 1u) ? f[k] : mx);
+        const uint32_t top[1] = {score_key(mx)};
+        unsigned at_bound;
+        block_kth<BLOCK, 1>(top, cand ? 1u : 0u, pl.kprime, pl.kprime >> 2, s.kth, bound, at_bound);
       }
     }
+    select_elements<BLOCK, KPT, CAP>(f, cand, bound, pl.kprime, pl.nf_lo, sel_stride, rsel, s,
+                                     [&](int k) { return c0 + k; });
   }
-  const uint32_t T = prefix;
-  // (after the early exit above, keys above T that share the prefix are picked as `key > T` and keys equal to T
-  // within the quota, which is as large as the whole prefix: the same set either way)
-  const unsigned need_eq = kprime > 0 ? (unsigned)remaining : 0u;
-
-  // counts of this thread: low half = forced or above threshold, high half = equal to it
-  unsigned long long mine = 0;
-#pragma unroll
-  for (int k = 0; k < KPT; ++k) {
-    const int p = c0 + k;
-    if (p >= P) continue;
-    if (p < nf_lo || p >= first_hi) { mine += 1ull; continue; }
-    if (kprime == 0) continue;
-    mine += (key[k] > T) ? 1ull : 0ull;
-    mine += (key[k] == T) ? (1ull << 32) : 0ull;
-  }
-  // the two counts never carry into one another: scan the halves separately
-  const unsigned long long inc = (unsigned long long)(uint32_t)spin_wave_inclusive_scan((int)(uint32_t)mine) |
-                                 ((unsigned long long)(uint32_t)spin_wave_inclusive_scan((int)(mine >> 32)) << 32);
-  if (lane == 63) s_wtot[wave] = inc;
-  __syncthreads();
-  unsigned long long before = inc - mine;
-#pragma unroll
-  for (int w = 0; w < NW; ++w)
-    if (w < wave) before += s_wtot[w];
-  const unsigned gt_before = (unsigned)(before & 0xffffffffull), eq_before = (unsigned)(before >> 32);
-  unsigned eq_quota = need_eq > eq_before ? need_eq - eq_before : 0u;
-  int pos = (int)(gt_before + min(eq_before, need_eq));
-#pragma unroll
-  for (int k = 0; k < KPT; ++k) {
-    const int p = c0 + k;
-    if (p >= P) continue;
-    bool pick;
-    if (p < nf_lo || p >= first_hi) pick = true;
-    else if (kprime == 0) pick = false;
-    else {
-      pick = key[k] > T;
-      if (key[k] == T && eq_quota > 0) { pick = true; --eq_quota; }
-    }
-    if (pick && pos < sel_stride) rsel[pos++] = p;
-  }
-  for (int i = take + tid; i < sel_stride; i += BLOCK) rsel[i] = -1;
-  if (tid == 0) nsel[row] = take;
-  return take;
+  return pl.take;
 }
-

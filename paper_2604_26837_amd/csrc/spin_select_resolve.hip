@@ -219,6 +219,8 @@ static int select_resolve_impl(spin_ctx *ctx, int32_t batch, const float *scores
     spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<512, 4>, dim3((unsigned)rows), dim3(512), SPIN_SR_ARGS);
   else if (ctx->max_parts <= 4096)
     spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<512, 8>, dim3((unsigned)rows), dim3(512), SPIN_SR_ARGS);
+  else if (ctx->max_parts <= 8192)   // 512 x 16 against 1024 x 8 and 1024 x 16, stages 2+3 of 8 rows: 9.0 / 10.4 / 11.8 us
+    spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<512, 16>, dim3((unsigned)rows), dim3(512), SPIN_SR_ARGS);
   else
     spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<1024, 16>, dim3((unsigned)rows), dim3(1024),
                 SPIN_SR_ARGS);
