@@ -595,7 +595,7 @@ def main():
                                                score_tiles_per_wg=args.score_tiles)
     # rows of at most 16384 partitions: stage 2 is one launch, which also resolves
     one_launch_23 = max(w.partitions(b) for b in range(w.batch)) <= 16384
-    # longer rows: stages 1-3 in one call (stage 1 takes stage 2's histogram along, stage 2's last launch resolves)
+    # longer rows: stages 1-3 in one call (stage 1 stores its tiles' maxima for stage 2, stage 2's launch resolves)
     fused_12 = not one_launch_23 and not args.four_calls
     sp = layer.spin
 
@@ -872,7 +872,7 @@ def main():
         "attended_kv_pct_peak": attended["pct_peak"] if attended else None,
         "attended_kv": attended,
         "step_launches": "four stage calls" if args.four_calls else (
-            "stages 1-3 in one call (stage 1 counts stage 2's histogram, stage 2's launch resolves), attention (3 launches)" if fused_12
+            "stages 1-3 in one call (stage 1 stores its tiles' maxima for stage 2, stage 2's launch resolves), attention (3 launches)" if fused_12
             else ("score, select+resolve with the sink / recent pages attended on the side, attention over the "
                   "other pages (3 launches)" if forced_split else "score, select+resolve, attention (3 launches)")),
         "kernels_plain_three_launch_step": plain_kernels or None,

@@ -236,9 +236,8 @@ int spin_score_partitions(spin_ctx *ctx, int32_t batch, const void *q, const voi
  * (topk_includes_forced) or topk; ties go to the lower id, +0 and -0 tie, NaN
  * ranks lowest.  sel (DEVICE int32 [rows][sel_stride]) ascending, padded with
  * -1; nsel (DEVICE int32 [rows]).  Contexts configured for rows of 16385 to
- * 131072 partitions run two launches (a histogram of the leading key bits kept
- * in `workspace`, then the selection); the workspace must have been cleared by
- * spin_workspace_init once and is left cleared. */
+ * 131072 partitions run two launches (the maxima of the rows' score tiles, kept
+ * in `workspace`, then the selection). */
 int spin_select_topk(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
                      const int32_t *seq_lens, int32_t *sel, int32_t *nsel, void *workspace,
                      void *stream);
@@ -257,8 +256,8 @@ int spin_pin_partitions(spin_ctx *ctx, int32_t batch, float *scores, const int32
 /* Stages 1 and 2 in ONE call: arguments and results are exactly those of
  * spin_score_partitions followed by spin_select_topk, bit for bit (the scores
  * are still written).  With contexts whose stage 2 takes two
- * launches (rows of 16385 to 131072 uniform partitions) stage 1 counts the leading key
- * bits of its scores while it still holds them, so the histogram launch over
+ * launches (rows of 16385 to 131072 uniform partitions) stage 1 stores the maximum of
+ * every score tile while it still holds the scores, so the launch that takes them from
  * the score array is saved; every other configuration simply runs the two
  * stages one after the other.  The workspace is needed as for the two calls.
  * (Pinned partitions go between the two stages: use the separate calls then.) */
@@ -315,7 +314,7 @@ int spin_advance_step(spin_ctx *ctx, void *workspace, void *stream);
 
 /* Stages 2 and 3 together (all-resident mode): ONE launch for rows of at most 16384
  * partitions; for uniform partitions, rows of up to 131072 partitions take stage 2's
- * histogram launch first and the launch that finishes stage 2 resolves.  Anything
+ * launch for the tiles' maxima first and the launch that finishes stage 2 resolves.  Anything
  * else is SPIN_ERR_UNSUPPORTED before a kernel is issued, and the two calls above apply.
  * Arguments and results are exactly those of spin_select_topk followed by
  * spin_resolve_slots, bit for bit: the workgroup that selected a row resolves it. */
@@ -324,8 +323,8 @@ int spin_select_resolve(spin_ctx *ctx, int32_t batch, const float *scores, const
                         const int32_t *leaf_pool, int64_t leaf_chunks, int32_t *slots, int32_t *page_ids,
                         uint16_t *valid_mask, int32_t *npages, void *workspace, void *stream);
 
-/* Stages 1, 2 and 3 in two launches: spin_score_partitions (taking stage 2's first
- * histogram along where spin_score_select_topk would) followed by spin_select_resolve.
+/* Stages 1, 2 and 3 in two launches: spin_score_partitions (storing the score tiles'
+ * maxima where spin_score_select_topk would) followed by spin_select_resolve.
  * Arguments, results and refusals are those of the stage calls, bit for bit. */
 int spin_score_select_resolve(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries,
                               const int32_t *chan_idx, const int32_t *part_offsets, const int32_t *seq_lens,

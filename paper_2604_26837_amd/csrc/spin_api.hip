@@ -114,12 +114,15 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   x->ws_ticket_off = off;                       // one arrival counter per row, zero between launches
   off += (size_t)x->max_rows * sizeof(int32_t);
   off = (off + 255) & ~(size_t)255;
-  // stage 2 of long rows: 4096 counters per row, zero between launches
-  if (x->max_parts > 16384 && x->max_parts <= 131072 && !c->variable_partitions) {
-    x->ws_hist_off = off;
-    off += (size_t)x->max_rows * 4096 * sizeof(int32_t);
-  }
   x->ws_zero_bytes = off;
+  // stage 2 of rows beyond 16384 partitions: the maxima of the rows' score tiles
+  x->tile_log = x->rows_per_part == 4 ? 2 : x->rows_per_part == 2 ? 3 : 4;
+  if (x->max_parts > 16384 && x->max_parts <= 131072 && !c->variable_partitions) {
+    x->max_stride = ((cdiv32(x->max_parts, 16) * 16 >> x->tile_log) + 3) & ~3;
+    x->ws_max_off = off;
+    off += (size_t)x->max_rows * x->max_stride * sizeof(float);
+    off = (off + 255) & ~(size_t)255;
+  }
   x->ws_skip_off = off;
   off += (size_t)x->max_rows * 2 * sizeof(int32_t);
   off = (off + 255) & ~(size_t)255;

@@ -48,7 +48,9 @@ struct spin_ctx {
   float scale;
   size_t ws_bytes;
   size_t ws_ticket_off, ws_ml_off, ws_acc_off;
-  size_t ws_hist_off;     // per-row first-digit histograms of stage 2 for long rows; 0 = not used
+  size_t ws_max_off;      // maxima of the rows' score tiles, [max_rows][max_stride]; 0 = not used
+  int32_t max_stride;     // tiles of the longest row, rounded up to a multiple of 4
+  int32_t tile_log;       // log2 of the partitions in a summary tile of 16 rows
   size_t ws_zero_bytes;   // leading part of the workspace that spin_workspace_init clears
   size_t ws_skip_off;     // [max_rows][2] list positions attended by the launch of stages 2+3 (always-attended pages)
   spin_var var;           // registered partition tables (all NULL: uniform partitions)
@@ -83,12 +85,12 @@ static inline int spin_launch_status() {
 }
 
 // host-side bodies of stages 1 and 2, shared by the stage calls and the combined call.
-// hist != NULL: stage 1 also counts the leading 12 key bits of every candidate's score into the
-// per-row histograms stage 2 of long rows starts from; hist_ready: stage 2 finds them filled.
+// maxima != NULL: stage 1 also stores the maximum of every summary tile's scores there, which stage 2 of rows
+// beyond 4096 partitions starts from; maxima_ready: stage 2 finds them in the workspace.
 int spin_score_impl(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries, const int32_t *chan_idx,
                     const int32_t *part_offsets, const int32_t *seq_lens, float *scores, void *workspace,
-                    void *stream, int32_t *hist);
-// `res` != NULL (all-resident mode, rows of 16385 - 131072 partitions only): the launch that finishes
+                    void *stream, float *maxima);
+// `res` != NULL (all-resident mode, rows that go by their tiles' maxima only): the launch that finishes
 // stage 2 also runs stage 3 for its row and stores the results there; SPIN_ERR_UNSUPPORTED elsewhere.
 struct spin_resolve_args {
   const int32_t *dir;
@@ -103,7 +105,7 @@ struct spin_resolve_args {
 int spin_static_scratch_prepare(void);
 int spin_select_impl(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
                      const int32_t *seq_lens, int32_t *sel, int32_t *nsel, void *workspace, void *stream,
-                     bool hist_ready, const spin_resolve_args *res);
+                     bool maxima_ready, const spin_resolve_args *res);
 
 #ifdef __HIPCC__
 // Launch `kernel` on `st`; when timing is enabled the launch carries a start
@@ -243,7 +245,4 @@ __device__ inline uint32_t score_key(float f) {
   if (u == 0x80000000u) u = 0u;                          // -0 ties +0
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
-
-// bins of the chip-wide histogram of the leading 12 key bits (stage 2 of long rows)
-#define BIG_BINS 4096
 #endif

@@ -146,323 +146,116 @@ __global__ __launch_bounds__(BLOCK) void spin_select_reg_kernel(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
     int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, spin_var var) {
+  __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
   (void)select_reg_row<BLOCK, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
-                                          recent_pages, sel_stride, sel, nsel, (int)blockIdx.x, var);
+                                   recent_pages, sel_stride, sel, nsel, (int)blockIdx.x, var, s);
 }
 
 // ---------------------------------------------------------------------------
-// Long rows (more than 16384 partitions, e.g. token partitions of a 64K context).
-//
-// A single workgroup spends most of its time walking a long row several times,
-// so the first digit is settled by the whole chip instead: a first launch, many
-// workgroups per row, histograms the top 12 key bits of the candidates into the
-// workspace.  The second launch, one workgroup per row, finds the bin D of the
-// k'-th candidate from it, walks the row ONCE (coalesced, order does not
-// matter): partitions above bin D and forced partitions set their bit in an LDS
-// bitmap, the few keys inside bin D go to an LDS list, where three short radix
-// passes over the remaining 20 bits find the threshold key T.  List entries
-// above T join the bitmap, entries equal to T a second bitmap; one ordered walk
-// over both emits the indices ascending, taking the lowest-index ties first.
-// A row whose bin D does not fit the list (heavy ties) falls back, inside the
-// same launch, to the multi-pass algorithms above; the results are the same.
-#define BIG_CHUNK 8192
-#define BIG_BLOCK 1024
-#define BIG_CAP 3072
-
-__global__ __launch_bounds__(256) void spin_select_hist_kernel(
-    const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
-    const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
-    int recent_pages, int sel_stride, int32_t *__restrict__ hist) {
-  __shared__ int s_h[BIG_BINS];
-  const int row = blockIdx.y, tid = threadIdx.x;
+// Rows that go by their tiles' maxima (select_by_tile_maxima): always beyond 16384 partitions, where the row does not
+// fit the workgroup's registers, and beyond 4096 where stage 1 of the same call has left the maxima.  For scores
+// that come from elsewhere this launch, many workgroups per row, takes them first.
+__global__ __launch_bounds__(256) void spin_tile_max_kernel(const float *__restrict__ scores,
+                                                            const int32_t *__restrict__ part_offsets, int Hkv,
+                                                            int gs_log, float *__restrict__ maxima, int max_stride) {
+  const int row = blockIdx.y;
   const int b = row / Hkv, h = row - b * Hkv;
   const int PP = part_offsets[b + 1] - part_offsets[b];
   const float *rs = scores + (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
-  const sel_plan pl = select_plan(seq_lens[b], PP, tp, topk, includes_forced, sink_pages, recent_pages, sel_stride);
-  const int lo = max((int)blockIdx.x * BIG_CHUNK, pl.nf_lo);
-  const int hi = min(((int)blockIdx.x + 1) * BIG_CHUNK, pl.first_hi);
-  if (lo >= hi || pl.kprime == 0) return;
-  for (int i = tid; i < BIG_BINS; i += 256) s_h[i] = 0;
-  __syncthreads();
-  // the chunk's 8192 scores as 8 aligned 16-byte loads per thread, all issued before the first use
-  // (rows are padded to a multiple of 16 partitions, so a load never leaves the row)
-  float4 f[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int p4 = (int)blockIdx.x * BIG_CHUNK + (i * 256 + tid) * 4;
-    f[i] = p4 < PP ? *(const float4 *)(rs + p4) : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int p4 = (int)blockIdx.x * BIG_CHUNK + (i * 256 + tid) * 4;
-    const float v[4] = {f[i].x, f[i].y, f[i].z, f[i].w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (p4 + e >= lo && p4 + e < hi) atomicAdd(&s_h[score_key(v[e]) >> 20], 1);
-  }
-  __syncthreads();
-  for (int i = tid; i < BIG_BINS; i += 256) {
-    const int c = s_h[i];
-    if (c) atomicAdd(&hist[(size_t)row * BIG_BINS + i], c);
-  }
+  // a quad of scores per lane (one contiguous KiB per wavefront); a tile is 1, 2 or 4 neighbouring lanes
+  const int p = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4;
+  if (p >= PP) return;                                   // PP is a multiple of 16: whole tiles leave
+  const float4 v = *(const float4 *)(rs + p);
+  float m = fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w));     // NaN only where all four are: ranks as -inf
+  if (gs_log >= 3) m = fmaxf(m, spin_dpp<SPIN_DPP_XOR1>(m));
+  if (gs_log >= 4) m = fmaxf(m, spin_dpp<SPIN_DPP_XOR2>(m));
+  const int t = p >> gs_log;
+  if ((p & ((1 << gs_log) - 1)) == 0 && t < max_stride) maxima[(size_t)row * max_stride + t] = m;
 }
 
-// The multi-pass algorithms for a row the one-walk path cannot take.  Kept out of line: they keep
-// up to 64 keys per thread in registers, which must not shape the register allocation of the
-// common path (measured: 18.6 -> 18.0 us on 64 rows of 65536 tokens).
-__device__ __attribute__((noinline)) void select_big_fallback(
-    const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
-    const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
-    int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, int row, int P) {
-  if (P <= BIG_BLOCK * 64) {
-    spin_var none = {};
-    (void)select_reg_row<BIG_BLOCK, 64>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
-                                               recent_pages, sel_stride, sel, nsel, row, none);
-  } else {
-    select_generic_row<BIG_BLOCK>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
-                                  recent_pages, sel_stride, sel, nsel, row);
-  }
-}
-
-// RESOLVE: the workgroup goes on to stage 3 for its row (same device function as the stage call).
-template <bool RESOLVE>
-__global__ __launch_bounds__(BIG_BLOCK) void spin_select_big_kernel(
-    const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
-    const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
-    int recent_pages, int sel_stride, int32_t *sel, int32_t *__restrict__ nsel, int32_t *hist,
-    int words_max, spin_resolve_args ra, int page_stride, int dir_stride, int leaf_entries, int32_t *status) {
-  extern __shared__ uint32_t s_dyn[];
-  uint32_t *s_main = s_dyn;                              // [words_max] bit p: partition p is selected
-  uint32_t *s_eq = s_dyn + words_max;                    // [words_max] bit p: candidate p has the threshold key
-  uint2 *s_list = (uint2 *)(s_dyn + 2 * words_max);      // [BIG_CAP] {key, partition} of the keys in bin D
-  __shared__ int s_wave[BIG_BLOCK / 64];
-  __shared__ unsigned long long s_wtot[BIG_BLOCK / 64];
-  __shared__ int s_h[256];
-  __shared__ int s_D, s_r, s_cntD, s_n, s_digit, s_remaining;
-
-  const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// One workgroup per row.  MPT: maxima per thread.  RESOLVE: the workgroup goes on to stage 3 for its row (same device
+// function as the stage call).
+// Latency bounds it: a dependent load each for maxima, scores and leaf entries, about 14 barriers, and whatever every
+// wavefront does for itself.  With a chip-wide histogram of the leading 12 key bits in its place one compute unit
+// walked the row's scores, and rows with many scores in the threshold's bin were searched whole: stages 2+3, 8 rows
+// of 62500, k' = 244: 28.8 -> 12.7 us; 64 rows of 65536, k' = 1024: 22.8 -> 20.0; and stage 1, which counted the
+// histogram in LDS, 42.7 -> 39.5 us on 8 rows of 62500.
+template <int BLOCK, int MPT, bool RESOLVE>
+__global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
+    const float *__restrict__ scores, const float *__restrict__ maxima, int max_stride, int gs_log,
+    const int32_t *__restrict__ part_offsets, const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk,
+    int includes_forced, int sink_pages, int recent_pages, int sel_stride, int32_t *sel, int32_t *__restrict__ nsel,
+    spin_resolve_args ra, int page_stride, int dir_stride, int leaf_entries, int32_t *status) {
+  constexpr int CAP = 4096;
+  __shared__ tiles_lds<BLOCK, CAP> s;
+  const int row = blockIdx.x;
   const int b = row / Hkv, h = row - b * Hkv;
   const int PP = part_offsets[b + 1] - part_offsets[b];
   const float *rs = scores + (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
   int32_t *rsel = sel + (size_t)row * sel_stride;
   const sel_plan pl = select_plan(seq_lens[b], PP, tp, topk, includes_forced, sink_pages, recent_pages, sel_stride);
-  const int P = pl.P, kprime = pl.kprime;
-  const int W = (P + 31) >> 5;
-
-  // bin of the k'-th candidate: thread t owns bins 4095-4t .. 4092-4t, highest first
-  int4 *rh4 = (int4 *)(hist + (size_t)row * BIG_BINS) + (BIG_BINS / 4 - 1 - tid);   // one 16-byte load and store
-  const int4 h4 = *rh4;
-  *rh4 = make_int4(0, 0, 0, 0);                            // ready for the next launch
-  const int hv[4] = {h4.w, h4.z, h4.y, h4.x};
-  const int local = h4.x + h4.y + h4.z + h4.w;
-  if (tid == 0) { s_D = BIG_BINS; s_r = 0; s_cntD = 0; s_n = 0; }
-  int total;
-  int running = block_exclusive_scan<BIG_BLOCK>(local, s_wave, total);   // its barriers order the lines above
-  if (kprime > 0) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (running < kprime && running + hv[j] >= kprime) {
-        s_D = BIG_BINS - 1 - 4 * tid - j;
-        s_r = kprime - running;
-        s_cntD = hv[j];
-      }
-      running += hv[j];
-    }
-  }
-  __syncthreads();
-  const int D = s_D;
-  // (bin 7 holds -inf and the NaN scores, which rank as -inf: the walk below compares scores as
-  // floats and would not see the NaNs, so that bin goes the multi-pass way as well)
-  if (kprime > 0 && (D == BIG_BINS || D == 7 || s_cntD > BIG_CAP || W > words_max)) {
-    // heavy ties in the threshold bin (or a histogram that does not cover the row): multi-pass algorithms
-    select_big_fallback(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages, recent_pages,
-                        sel_stride, sel, nsel, row, P);
-    if (RESOLVE) {
-      __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here
-      resolve_row<BIG_BLOCK>(row, pl.take, sel, seq_lens, ra.dir, ra.leaf_pool, ra.leaf_chunks, Hkv, tp, sink_pages,
-                             recent_pages, sel_stride, page_stride, dir_stride, leaf_entries, ra.slots, ra.page_ids,
-                             ra.valid_mask, ra.npages, status, spin_var{});
-    }
-    return;
-  }
-
-  // the bitmaps start with the forced partitions [0, nf_lo) and [first_hi, P) set
-  for (int i = tid; i < W; i += BIG_BLOCK) {
-    const int p0 = i * 32;
-    uint32_t m = 0;
-    if (p0 < pl.nf_lo) m |= pl.nf_lo - p0 >= 32 ? 0xffffffffu : (1u << (pl.nf_lo - p0)) - 1u;
-    if (p0 + 32 > pl.first_hi) {
-      const uint32_t from = p0 >= pl.first_hi ? 0xffffffffu : ~((1u << (pl.first_hi - p0)) - 1u);
-      const uint32_t upto = P - p0 >= 32 ? 0xffffffffu : (1u << (P - p0)) - 1u;   // P > p0: i < W
-      m |= from & upto;
-    }
-    s_main[i] = m;
-    s_eq[i] = 0;
-  }
-  __syncthreads();
-
-  // One walk over the row, 16-byte loads, eight per thread in flight.  Membership of a score in
-  // bin D or above is decided on the float itself: the key is monotone in the score, so
-  // key >= K  <=>  score >= (the score whose key is K); a NaN score fails every comparison, which is
-  // right above the bin of -inf (the rank NaN has as a key).  The exact key is only formed for the
-  // few scores that join the list.
-  const float f_lo = key_floor_score((uint32_t)D << 20, true);
-  const float f_hi = D + 1 < BIG_BINS ? key_floor_score(((uint32_t)D + 1u) << 20, false) : __builtin_nanf("");
-  for (int base = 0; base < P && kprime > 0; base += BIG_BLOCK * 32) {
-    float4 f[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int p4 = base + (i * BIG_BLOCK + tid) * 4;
-      f[i] = p4 < PP ? *(const float4 *)(rs + p4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-    // non-candidates (forced partitions, the padding past P) become NaN, which fails every comparison;
-    // only the loads that straddle an end of the candidate range have any
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int p4 = base + (i * BIG_BLOCK + tid) * 4;
-      if (!(p4 >= pl.nf_lo && p4 + 4 <= pl.first_hi)) {
-        if (p4 + 0 < pl.nf_lo || p4 + 0 >= pl.first_hi) f[i].x = __builtin_nanf("");
-        if (p4 + 1 < pl.nf_lo || p4 + 1 >= pl.first_hi) f[i].y = __builtin_nanf("");
-        if (p4 + 2 < pl.nf_lo || p4 + 2 >= pl.first_hi) f[i].z = __builtin_nanf("");
-        if (p4 + 3 < pl.nf_lo || p4 + 3 >= pl.first_hi) f[i].w = __builtin_nanf("");
-      }
-    }
-    // classify the thread's 32 scores: bit 4i+e of `above` / `in_d` = score e of load i lies above bin D /
-    // in it.  One comparison per score; the rest only runs when some lane of the wavefront passes it.
-    uint32_t above = 0, in_d = 0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float v[4] = {f[i].x, f[i].y, f[i].z, f[i].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const bool ge_lo = v[e] >= f_lo;
-        if (__ballot(ge_lo) == 0ull) continue;
-        const bool ge_hi = v[e] >= f_hi;
-        above |= (ge_lo && ge_hi) ? 1u << (4 * i + e) : 0u;
-        in_d |= (ge_lo && !ge_hi) ? 1u << (4 * i + e) : 0u;
-      }
-    }
-    if (above) {
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int p4 = base + (i * BIG_BLOCK + tid) * 4;
-        const uint32_t bits = (above >> (4 * i)) & 0xfu;
-        if (bits) atomicOr(&s_main[p4 >> 5], bits << (p4 & 31));   // p4 is a multiple of 4: the bits stay in one word
-      }
-    }
-    // the scores in bin D join the list: one counter update per wavefront and batch
-    if (__ballot(in_d != 0u)) {
-      const int mine = __popc(in_d);
-      const int inc = spin_wave_inclusive_scan(mine);
-      int first = 0;
-      if (lane == 63) first = atomicAdd(&s_n, inc);
-      int pos = __builtin_amdgcn_readlane(first, 63) + inc - mine;
-      if (in_d) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const float v[4] = {f[i].x, f[i].y, f[i].z, f[i].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if ((in_d >> (4 * i + e)) & 1u) {
-              if (pos < BIG_CAP) s_list[pos] = make_uint2(score_key(v[e]), (uint32_t)(base + (i * BIG_BLOCK + tid) * 4 + e));
-              ++pos;
-            }
-        }
-      }
-    }
-  }
-  __syncthreads();
-  const int n = min(s_n, BIG_CAP);
-
-  // threshold key among the list: digits of 8, 8 and 4 bits below the 12 settled ones
-  uint32_t low = 0;                 // settled bits below bit 20, right-aligned
-  int remaining = s_r;
-  if (kprime > 0) {
-#pragma unroll
-    for (int pass = 0; pass < 3; ++pass) {
-      const int shift = pass == 0 ? 12 : (pass == 1 ? 4 : 0);
-      const int width = pass == 2 ? 4 : 8;
-      if (tid < 256) s_h[tid] = 0;
-      __syncthreads();
-      for (int i = tid; i < n; i += BIG_BLOCK) {
-        const uint32_t k20 = s_list[i].x & 0xfffffu;
-        if (pass == 0 || (k20 >> (shift + width)) == low) atomicAdd(&s_h[(k20 >> shift) & ((1u << width) - 1u)], 1);
-      }
-      __syncthreads();
-      if (wave == 0) {
-        int v4[4], loc = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { v4[j] = s_h[255 - 4 * lane - j]; loc += v4[j]; }
-        const int inc = spin_wave_inclusive_scan(loc);
-        int run = inc - loc;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (run < remaining && run + v4[j] >= remaining) {
-            s_digit = 255 - 4 * lane - j;
-            s_remaining = remaining - run;
-          }
-          run += v4[j];
-        }
-      }
-      __syncthreads();
-      low = (low << width) | (uint32_t)s_digit;
-      remaining = s_remaining;
-    }
-  }
-  const uint32_t T = ((uint32_t)D << 20) | low;
-  const unsigned need_eq = kprime > 0 ? (unsigned)remaining : 0u;
-  for (int i = tid; i < n; i += BIG_BLOCK) {
-    const uint2 e = s_list[i];
-    if (e.x > T) atomicOr(&s_main[e.y >> 5], 1u << (e.y & 31));
-    else if (e.x == T) atomicOr(&s_eq[e.y >> 5], 1u << (e.y & 31));
-  }
-  __syncthreads();
-
-  // ordered emission: thread t owns the words [t * wpt, (t + 1) * wpt)
-  const int wpt = (W + BIG_BLOCK - 1) / BIG_BLOCK;
-  const int w0 = min(tid * wpt, W), w1 = min(w0 + wpt, W);
-  unsigned long long mine = 0;
-  for (int w = w0; w < w1; ++w) mine += (unsigned long long)__popc(s_main[w]) + ((unsigned long long)__popc(s_eq[w]) << 32);
-  const unsigned long long inc = (unsigned long long)(uint32_t)spin_wave_inclusive_scan((int)(uint32_t)mine) |
-                                 ((unsigned long long)(uint32_t)spin_wave_inclusive_scan((int)(mine >> 32)) << 32);
-  if (lane == 63) s_wtot[wave] = inc;
-  __syncthreads();
-  unsigned long long before = inc - mine;
-  for (int w = 0; w < wave; ++w) before += s_wtot[w];
-  const unsigned main_before = (unsigned)(before & 0xffffffffull), eq_before = (unsigned)(before >> 32);
-  unsigned eq_quota = need_eq > eq_before ? need_eq - eq_before : 0u;
-  int pos = (int)(main_before + min(eq_before, need_eq));
-  for (int w = w0; w < w1; ++w) {
-    const uint32_t m = s_main[w], e = s_eq[w];
-    uint32_t both = m | e;
-    while (both) {
-      const int bit = __ffs(both) - 1;
-      both &= both - 1;
-      bool pick = (m >> bit) & 1u;
-      if (!pick && eq_quota > 0) { pick = true; --eq_quota; }
-      if (pick && pos < sel_stride) rsel[pos++] = w * 32 + bit;
-    }
-  }
-  for (int i = pl.take + tid; i < sel_stride; i += BIG_BLOCK) rsel[i] = -1;
-  if (tid == 0) nsel[row] = pl.take;
-  if (RESOLVE) {
+  emit_forced<BLOCK>(pl, sel_stride, rsel, nsel, row);
+  if (pl.kprime > 0 &&
+      ((pl.P >> gs_log) > min(max_stride, BLOCK * MPT) ||
+       !select_by_tile_maxima<BLOCK, MPT, CAP>(rs, maxima + (size_t)row * max_stride, max_stride, gs_log, pl,
+                                               sel_stride, rsel, s))) {
     __syncthreads();
-    resolve_row<BIG_BLOCK>(row, pl.take, sel, seq_lens, ra.dir, ra.leaf_pool, ra.leaf_chunks, Hkv, tp, sink_pages,
-                           recent_pages, sel_stride, page_stride, dir_stride, leaf_entries, ra.slots, ra.page_ids,
-                           ra.valid_mask, ra.npages, status, spin_var{});
+    select_generic_row<BLOCK>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
+                              recent_pages, sel_stride, sel, nsel, row);
+  }
+  if (RESOLVE) {
+    __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here
+    resolve_row<BLOCK>(row, pl.take, sel, seq_lens, ra.dir, ra.leaf_pool, ra.leaf_chunks, Hkv, tp, sink_pages,
+                       recent_pages, sel_stride, page_stride, dir_stride, leaf_entries, ra.slots, ra.page_ids,
+                       ra.valid_mask, ra.npages, status, spin_var{});
   }
 }
 
 int spin_select_impl(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
                      const int32_t *seq_lens, int32_t *sel, int32_t *nsel, void *workspace, void *stream,
-                     bool hist_ready, const spin_resolve_args *res) {
+                     bool maxima_ready, const spin_resolve_args *res) {
   if (!ctx || batch < 0 || batch > ctx->cfg.max_batch) return SPIN_ERR_INVALID;
   if (batch == 0) return SPIN_OK;
   if (!scores || !part_offsets || !seq_lens || !sel || !nsel) return SPIN_ERR_INVALID;
   const spin_config &c = ctx->cfg;
   const int rows = batch * c.num_kv_heads;
-  // stage 3 in the same launch exists for the long-row path below only
-  if (res && !(ctx->max_parts > 16384 && ctx->ws_hist_off && workspace && rows <= 65535)) return SPIN_ERR_UNSUPPORTED;
+  // (rows are the second dimension of the grid that takes the maxima)
+  const bool by_maxima = ctx->ws_max_off && workspace && rows <= 65535 && ctx->max_parts > 16384;
+  // stage 3 in the same launch exists for the path by the tiles' maxima only
+  if (res && !by_maxima) return SPIN_ERR_UNSUPPORTED;
+  if (by_maxima) {
+    float *maxima = (float *)((char *)workspace + ctx->ws_max_off);
+    const int stride = ctx->max_stride, gs_log = ctx->tile_log;
+    if (!maxima_ready)
+      spin_launch(ctx, SPIN_K_SELECT_HIST, spin_tile_max_kernel,
+                  dim3((unsigned)((ctx->max_parts + 1023) / 1024), (unsigned)rows), dim3(256), 0, (hipStream_t)stream,
+                  scores, part_offsets, c.num_kv_heads, gs_log, maxima, stride);
+#define SPIN_TILES_LAUNCH(BLOCK, MPT)                                                                           \
+  do {                                                                                                        \
+    if (res)                                                                                                  \
+      spin_launch(ctx, SPIN_K_SELECT, spin_select_tiles_kernel<BLOCK, MPT, true>, dim3((unsigned)rows),       \
+                  dim3(BLOCK), 0, (hipStream_t)stream, scores, (const float *)maxima, stride, gs_log,         \
+                  part_offsets, seq_lens, c.num_kv_heads, c.partition_tokens, c.topk, c.topk_includes_forced, \
+                  c.sink_pages, c.recent_pages, ctx->sel_stride, sel, nsel, *res, ctx->page_stride,           \
+                  ctx->dir_stride, c.leaf_entries, (int32_t *)workspace);                                     \
+    else                                                                                                      \
+      spin_launch(ctx, SPIN_K_SELECT, spin_select_tiles_kernel<BLOCK, MPT, false>, dim3((unsigned)rows),      \
+                  dim3(BLOCK), 0, (hipStream_t)stream, scores, (const float *)maxima, stride, gs_log,         \
+                  part_offsets, seq_lens, c.num_kv_heads, c.partition_tokens, c.topk, c.topk_includes_forced, \
+                  c.sink_pages, c.recent_pages, ctx->sel_stride, sel, nsel, spin_resolve_args{}, 0, 0, 0,     \
+                  (int32_t *)nullptr);                                                                        \
+  } while (0)
+    // What every wavefront does for itself favours few of them, the lines of many tiles many: 512 against 1024
+    // threads, 8 rows of 62500 and k' = 244: 12.7 / 13.4 us; 64 rows of 65536 and k' = 1024: 21.2 / 19.9 us.
+    const bool few = c.topk <= 512;
+    if (stride <= 4096 && few) SPIN_TILES_LAUNCH(512, 8);
+    else if (stride <= 4096) SPIN_TILES_LAUNCH(1024, 4);
+    else if (stride <= 8192 && few) SPIN_TILES_LAUNCH(512, 16);
+    else if (stride <= 8192) SPIN_TILES_LAUNCH(1024, 8);
+    else SPIN_TILES_LAUNCH(1024, 32);
+#undef SPIN_TILES_LAUNCH
+    return spin_launch_status();
+  }
 #define SPIN_SELECT_ARGS                                                                                      \
   0, (hipStream_t)stream, scores, part_offsets, seq_lens, c.num_kv_heads, c.partition_tokens, c.topk,         \
       c.topk_includes_forced, c.sink_pages, c.recent_pages, ctx->sel_stride, sel, nsel
@@ -475,31 +268,7 @@ int spin_select_impl(spin_ctx *ctx, int32_t batch, const float *scores, const in
   else if (ctx->max_parts <= 16384)
     spin_launch(ctx, SPIN_K_SELECT, spin_select_reg_kernel<1024, 16>, dim3((unsigned)rows), dim3(1024),
                 SPIN_SELECT_ARGS, ctx->var);
-  else if (ctx->ws_hist_off && workspace && rows <= 65535) {   // rows are the histogram grid's second dimension
-    // two launches: histogram of the first 12 key bits by many workgroups per row, then one workgroup per row
-    int32_t *hist = (int32_t *)((char *)workspace + ctx->ws_hist_off);
-    const int words_max = ((ctx->max_parts + 63) / 64) * 2;
-    const size_t lds = (size_t)words_max * 8 + (size_t)BIG_CAP * 8;
-    // at most 56 KiB for rows of 131072 partitions; the kernel's static arrays (under 8 KiB) come on top
-    if (lds + 8192 > 64 * 1024) return SPIN_ERR_UNSUPPORTED;
-    if (!hist_ready)   // stage 1 may have counted the bins already while it produced the scores
-      spin_launch(ctx, SPIN_K_SELECT_HIST, spin_select_hist_kernel,
-                  dim3((unsigned)((ctx->max_parts + BIG_CHUNK - 1) / BIG_CHUNK), (unsigned)rows), dim3(256), 0,
-                  (hipStream_t)stream, scores, part_offsets, seq_lens, c.num_kv_heads, c.partition_tokens, c.topk,
-                  c.topk_includes_forced, c.sink_pages, c.recent_pages, ctx->sel_stride, hist);
-#define SPIN_BIG_ARGS                                                                                         \
-  dim3((unsigned)rows), dim3(BIG_BLOCK), lds, (hipStream_t)stream, scores, part_offsets, seq_lens, c.num_kv_heads, \
-      c.partition_tokens, c.topk, c.topk_includes_forced, c.sink_pages, c.recent_pages, ctx->sel_stride, sel, nsel,  \
-      hist, words_max
-    if (res)
-      spin_launch(ctx, SPIN_K_SELECT, spin_select_big_kernel<true>, SPIN_BIG_ARGS, *res, ctx->page_stride,
-                  ctx->dir_stride, c.leaf_entries, (int32_t *)workspace);
-    else
-      spin_launch(ctx, SPIN_K_SELECT, spin_select_big_kernel<false>, SPIN_BIG_ARGS, spin_resolve_args{}, 0, 0, 0,
-                  (int32_t *)nullptr);
-#undef SPIN_BIG_ARGS
-    return spin_launch_status();
-  } else if (ctx->max_parts <= 65536)
+  else if (ctx->max_parts <= 65536)
     spin_launch(ctx, SPIN_K_SELECT, spin_select_reg_kernel<1024, 64>, dim3((unsigned)rows), dim3(1024),
                 SPIN_SELECT_ARGS, ctx->var);
   else if (ctx->var.count)
@@ -516,9 +285,8 @@ extern "C" int spin_select_topk(spin_ctx *ctx, int32_t batch, const float *score
   return spin_select_impl(ctx, batch, scores, part_offsets, seq_lens, sel, nsel, workspace, stream, false, nullptr);
 }
 
-// Stages 1 and 2 in one call.  Where stage 2 takes two launches and stage 1 can count the leading
-// key bits of its scores as it produces them, the histogram launch is saved; otherwise the two
-// stages are simply issued one after the other.  Same results as the two calls, bit for bit.
+// Stages 1 and 2 in one call: for rows of 4097 to 131072 partitions stage 1 leaves its tiles' maxima for stage 2;
+// otherwise the two stages are simply issued one after the other.  Same results as the two calls, bit for bit.
 extern "C" int spin_score_select_topk(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries,
                                       const int32_t *chan_idx, const int32_t *part_offsets,
                                       const int32_t *seq_lens, float *scores, int32_t *sel, int32_t *nsel,
@@ -526,11 +294,11 @@ extern "C" int spin_score_select_topk(spin_ctx *ctx, int32_t batch, const void *
   if (!ctx || batch < 0 || batch > ctx->cfg.max_batch) return SPIN_ERR_INVALID;
   if (batch == 0) return SPIN_OK;
   if (!sel || !nsel) return SPIN_ERR_INVALID;
-  // (same condition as the two-launch path of stage 2: the histogram must be consumed by the launch that follows)
-  const bool fuse = ctx->ws_hist_off && workspace && batch * ctx->cfg.num_kv_heads <= 65535;
-  int32_t *hist = fuse ? (int32_t *)((char *)workspace + ctx->ws_hist_off) : nullptr;
+  // (same condition as in stage 2)
+  const bool fuse = ctx->ws_max_off && workspace && batch * ctx->cfg.num_kv_heads <= 65535;
+  float *maxima = fuse ? (float *)((char *)workspace + ctx->ws_max_off) : nullptr;
   const int st = spin_score_impl(ctx, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, workspace, stream,
-                                 hist);
+                                 maxima);
   if (st != SPIN_OK) return st;
   return spin_select_impl(ctx, batch, scores, part_offsets, seq_lens, sel, nsel, workspace, stream, fuse, nullptr);
 }

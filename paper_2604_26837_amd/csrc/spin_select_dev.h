@@ -60,6 +60,33 @@ __device__ inline typename key_bits<KPT>::type range_bits(int c0, int a, int b) 
   return from & upto;
 }
 
+// The digit in whose bin the element of rank `rank` (1: the largest) falls, from the 256 bins of a histogram, with
+// the rank inside that bin and its count; -1 where the bins hold fewer.  Every wavefront computes it for itself.
+// Lane handles digits 255-4*lane .. 252-4*lane, in descending order.
+__device__ inline int digit_of_rank(const int *hist, int &rank, int &in_digit) {
+  const int lane = threadIdx.x & 63;
+  int hv[4], local = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { hv[j] = hist[255 - 4 * lane - j]; local += hv[j]; }
+  int running = spin_wave_inclusive_scan(local) - local;
+  int my_digit = -1, my_rem = 0, my_cnt = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (running < rank && running + hv[j] >= rank) {
+      my_digit = 255 - 4 * lane - j;
+      my_rem = rank - running;
+      my_cnt = hv[j];
+    }
+    running += hv[j];
+  }
+  const unsigned long long found = __ballot(my_digit >= 0);
+  if (!found) return -1;
+  const int src = __ffsll((long long)found) - 1;
+  rank = __builtin_amdgcn_readlane(my_rem, src);
+  in_digit = __builtin_amdgcn_readlane(my_cnt, src);
+  return __builtin_amdgcn_readlane(my_digit, src);
+}
+
 template <int BLOCK>
 struct kth_lds {
   int hist[4][256];   // one histogram per digit: no buffer is cleared while others read it
@@ -79,7 +106,7 @@ template <int BLOCK, int KPT>
 __device__ inline void block_kth(const uint32_t (&key)[KPT], typename key_bits<KPT>::type valid, int k, int slack,
                                  kth_lds<BLOCK> &s, uint32_t &T, unsigned &need_eq) {
   constexpr int NW = BLOCK / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   for (int i = tid; i < 4 * 256; i += BLOCK) (&s.hist[0][0])[i] = 0;
   uint32_t kmx = 0u, kmn = 0xffffffffu;
 #pragma unroll
@@ -104,26 +131,9 @@ __device__ inline void block_kth(const uint32_t (&key)[KPT], typename key_bits<K
       if (((valid >> j) & 1u) && (pass == 0 || (key[j] >> hi) == prefix))
         atomicAdd(&s.hist[pass][(key[j] >> lo) & dmask], 1);
     __syncthreads();
-    // suffix scan: lane handles digits 255-4*lane .. 252-4*lane, in descending order
-    int hv[4], local = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) { hv[j] = s.hist[pass][255 - 4 * lane - j]; local += hv[j]; }
-    int running = spin_wave_inclusive_scan(local) - local;
-    int my_digit = -1, my_rem = 0, my_cnt = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (running < remaining && running + hv[j] >= remaining) {
-        my_digit = 255 - 4 * lane - j;
-        my_rem = remaining - running;
-        my_cnt = hv[j];
-      }
-      running += hv[j];
-    }
-    const unsigned long long found = __ballot(my_digit >= 0);
-    if (!found) break;                                   // fewer than k valid keys: not a call this function takes
-    const int src = __ffsll((long long)found) - 1;
-    const int digit = __builtin_amdgcn_readlane(my_digit, src), in_digit = __builtin_amdgcn_readlane(my_cnt, src);
-    remaining = __builtin_amdgcn_readlane(my_rem, src);
+    int in_digit = 0;
+    const int digit = digit_of_rank(s.hist[pass], remaining, in_digit);
+    if (digit < 0) break;                                // fewer than k valid keys: not a call this function takes
     prefix = (prefix << width) | (uint32_t)digit;
     hi = lo;
     // every key that shares this prefix is wanted (or may be taken as well): the digits below cannot change
@@ -192,6 +202,43 @@ struct elements_lds {
   int32_t id[CAP > 0 ? CAP : 1];
 };
 
+// The kprime best of the `total` entries of an ordered list in LDS, stored ascending at rsel[first ..].
+template <int BLOCK, int CAP>
+__device__ inline void pick_from_list(int total, int kprime, int first, int sel_stride, int32_t *__restrict__ rsel,
+                                      elements_lds<BLOCK, CAP> &s) {
+  const int tid = threadIdx.x;
+  auto pick_list = [&](auto entries) {
+    constexpr int E = decltype(entries)::value;  // list entries per thread
+    uint32_t T;
+    unsigned need_eq;
+    uint32_t key[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) key[j] = tid * E + j < total ? s.key[tid * E + j] : 0u;
+    const uint32_t have = range_bits<E>(tid * E, 0, total);
+    block_kth<BLOCK, E>(key, have, kprime, 0, s.kth, T, need_eq);
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      gt |= key[j] > T ? 1u << j : 0u;
+      eq |= key[j] == T ? 1u << j : 0u;
+    }
+    int pos;
+    uint32_t pick = ordered_picks<BLOCK>(gt & have, eq & have, need_eq, s.wtot, pos);
+    pos += first;
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+      if ((pick >> j) & 1u) {
+        if (pos < sel_stride) rsel[pos] = s.id[tid * E + j];
+        ++pos;
+      }
+  };
+  constexpr int LPT = CAP / BLOCK;
+  if (total <= BLOCK) pick_list(std::integral_constant<int, 1>());
+  else if (LPT > 2 && total <= 2 * BLOCK) pick_list(std::integral_constant<int, 2>());
+  else if (LPT > 4 && total <= 4 * BLOCK) pick_list(std::integral_constant<int, 4>());
+  else pick_list(std::integral_constant<int, LPT>());
+}
+
 // Picks the kprime best of the candidates a workgroup holds in registers (KPT scores per thread, bit k of `cand`:
 // f[k] is a candidate; thread, then k is ascending partition order; id(k) names its partition) and stores their
 // ids at rsel[first ..], ascending.  `bound`: a key that at least kprime of the candidates reach (0: none known).
@@ -242,32 +289,7 @@ __device__ inline void select_elements(const float (&f)[KPT], typename key_bits<
           }
       }
       __syncthreads();
-      constexpr int LPT = CAP / BLOCK;           // list entries per thread
-      auto pick_list = [&](auto entries) {
-        constexpr int E = decltype(entries)::value;
-        uint32_t key[E];
-#pragma unroll
-        for (int j = 0; j < E; ++j) key[j] = tid * E + j < total ? s.key[tid * E + j] : 0u;
-        const uint32_t have = range_bits<E>(tid * E, 0, total);
-        block_kth<BLOCK, E>(key, have, kprime, 0, s.kth, T, need_eq);
-        uint32_t gt = 0, eq = 0;
-#pragma unroll
-        for (int j = 0; j < E; ++j) {
-          gt |= key[j] > T ? 1u << j : 0u;
-          eq |= key[j] == T ? 1u << j : 0u;
-        }
-        int pos;
-        uint32_t pick = ordered_picks<BLOCK>(gt & have, eq & have, need_eq, s.wtot, pos);
-        pos += first;
-#pragma unroll
-        for (int j = 0; j < E; ++j)
-          if ((pick >> j) & 1u) {
-            if (pos < sel_stride) rsel[pos] = s.id[tid * E + j];
-            ++pos;
-          }
-      };
-      if (total <= BLOCK) pick_list(std::integral_constant<int, 1>());
-      else pick_list(std::integral_constant<int, LPT>());
+      pick_from_list<BLOCK, CAP>(total, kprime, first, sel_stride, rsel, s);
       return;
     }
   }
@@ -310,19 +332,19 @@ __device__ inline void emit_forced(const sel_plan &pl, int sel_stride, int32_t *
 // is a lower bound of the threshold (k' threads hold a key at least that large).
 // Latency bounds this kernel: dependent loads, a barrier per digit, and the instructions per score on the row's
 // one compute unit.  Stages 2+3, top 128, before (every score in every histogram) and after: 8 rows of 8192
-// 14.7 -> 9.4 us, 8 rows of 16384 16.2 -> 11.5, 256 ragged rows of up to 16384 17.4 -> 13.4; rows of 62500 in the
-// long-row kernel's multi-pass fall-back 69 -> 29.
+// 14.7 -> 9.4 us, 8 rows of 16384 16.2 -> 11.5, 256 ragged rows of up to 16384 17.4 -> 13.4.
 // Returns the number of selected partitions.
+template <int BLOCK, int KPT>
+constexpr int reg_row_cap() { return KPT >= 16 ? 2 * BLOCK : 0; }
+
 template <int BLOCK, int KPT>
 __device__ inline int select_reg_row(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
     int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, int row,
-    spin_var var) {
+    spin_var var, elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> &s) {
   typedef typename key_bits<KPT>::type M;
-  constexpr int CAP = KPT >= 16 ? 2 * BLOCK : 0;
-  __shared__ elements_lds<BLOCK, CAP> s;
-
+  constexpr int CAP = reg_row_cap<BLOCK, KPT>();
   const int b = row / Hkv, h = row - b * Hkv;
   const int N = seq_lens[b];
   const int off_b = part_offsets[b];
@@ -379,4 +401,224 @@ __device__ inline int select_reg_row(
                                      [&](int k) { return c0 + k; });
   }
   return pl.take;
+}
+
+// ---------------------------------------------------------------------------
+// Rows whose scores come with the maximum of every tile (2^gs_log consecutive partitions; 16, 8 or 4): stage 1
+// writes it as it holds the scores, or a launch of its own takes it from the score array.
+//
+// The k'-th largest maximum T0 bounds the threshold from below (k' tiles hold a score at least that large), so
+// candidates above T0 lie in the fewer than k' tiles whose maximum is above it, and of the tiles whose maximum
+// equals T0 only the first that make up k' can matter: each holds a candidate with exactly that key, and among
+// equals the lowest partitions win.  The row's one workgroup therefore reads one value per tile and then the scores
+// of k' tiles, whatever the row's length and however many scores tie; tiles that hold forced partitions are no
+// bound for anything and are read as well.  T0 then rules most of those scores out and the rest form the list.
+#define TILE_LIST 4098     // tiles a row may read (16-bit ids: rows of up to 131072 partitions, 4 or more to a tile)
+template <int BLOCK, int CAP>
+struct tiles_lds : elements_lds<BLOCK, CAP> {
+  uint16_t tile[TILE_LIST];
+};
+
+// Stores the kprime best candidates ascending at rsel[nf_lo ..].  A row with fewer than k' tiles reads them all; where
+// more scores reach the bound than the list holds, the search and the selection re-read them per pass instead.
+// False (for the whole workgroup, nothing stored): k' beyond what the tile list holds.
+template <int BLOCK, int MPT, int CAP>
+__device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const float *__restrict__ maxima,
+                                             int maxima_stride, int gs_log, const sel_plan &pl, int sel_stride,
+                                             int32_t *__restrict__ rsel, tiles_lds<BLOCK, CAP> &s) {
+  constexpr int NW = BLOCK / 64;
+  typedef typename key_bits<MPT>::type M;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int gs = 1 << gs_log, kprime = pl.kprime;
+  if (kprime + (kprime >> 3) + 2 > TILE_LIST) return false;                       // block-uniform
+  const int t_lo = (pl.nf_lo + gs - 1) >> gs_log, t_hi = pl.first_hi >> gs_log;   // tiles of candidates only
+  const int m0 = tid * MPT;
+  uint32_t top[MPT];
+#pragma unroll
+  for (int j = 0; j < MPT; j += 4) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (m0 + j < maxima_stride) v = *(const float4 *)(maxima + m0 + j);   // the stride is a multiple of 4
+    top[j] = score_key(v.x);
+    top[j + 1] = score_key(v.y);
+    top[j + 2] = score_key(v.z);
+    top[j + 3] = score_key(v.w);
+  }
+  const M cand = range_bits<MPT>(m0, t_lo, t_hi);
+  uint32_t T0 = 0;
+  unsigned need_eq = 0;
+  if (t_hi - t_lo >= kprime) block_kth<BLOCK, MPT>(top, cand, kprime, kprime >> 3, s.kth, T0, need_eq);
+  // ascending list of the tiles to read, the one that straddles either end of the candidates among them (both
+  // ends in one tile: that one)
+  const int has_lo = (pl.nf_lo & (gs - 1)) ? 1 : 0, has_hi = (pl.first_hi & (gs - 1)) && t_hi >= t_lo ? 1 : 0;
+  M gt = 0, eq = 0;
+#pragma unroll
+  for (int j = 0; j < MPT; ++j) {
+    gt |= top[j] > T0 ? (M)1 << j : (M)0;
+    eq |= top[j] == T0 ? (M)1 << j : (M)0;
+  }
+  int pos;
+  M pick = ordered_picks<BLOCK>((M)(gt & cand), (M)(eq & cand), need_eq, s.wtot, pos);
+  unsigned n_gt = 0, n_eq = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    n_gt += (uint32_t)s.wtot[w];
+    n_eq += (uint32_t)(s.wtot[w] >> 32);
+  }
+  int ntiles = has_lo + (int)(n_gt + min(n_eq, need_eq));
+  pos += has_lo;
+  while (pick) {
+    const int j = ffs_bits(pick) - 1;
+    pick &= pick - 1;
+    if (pos < TILE_LIST) s.tile[pos] = (uint16_t)(m0 + j);
+    ++pos;
+  }
+  if (tid == 0) {
+    if (has_lo) s.tile[0] = (uint16_t)(t_lo - 1);
+    if (has_hi && ntiles < TILE_LIST) s.tile[ntiles] = (uint16_t)t_hi;
+  }
+  ntiles = min(ntiles + has_hi, TILE_LIST);
+  __syncthreads();
+  const bool all = T0 <= SPIN_KEY_MINUS_INF;           // (NaN scores rank at -inf and would fail the comparison)
+  const float bf = key_floor_score(T0, true);
+  const int q_log = gs_log - 2, nquads = ntiles << q_log;
+  // Four scores (a quad) per lane and load, neighbouring lanes neighbouring quads: a wavefront's load touches as few
+  // lines as there are, which matters because the one compute unit that fetches k' scattered lines is bound by them
+  // (1024 tiles: 6.5 us; 7.0 with four quads in a row per lane).  A round is V loads per lane; wavefront w has the
+  // quads [64 V w, 64 V (w + 1)) of it, so order is wavefront, load, lane, score.
+  auto load_quad = [&](int qd, int &p, float4 &v) {
+    p = -4;                                            // no candidates
+    v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (qd < nquads) {
+      p = ((int)s.tile[qd >> q_log] << gs_log) + ((qd & ((1 << q_log) - 1)) << 2);
+      v = *(const float4 *)(rs + p);
+    }
+  };
+  // which of a quad's scores are candidates above the bound
+  auto quad_bits = [&](int p, const float4 &v) {
+    const float f[4] = {v.x, v.y, v.z, v.w};
+    uint32_t bits = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bits |= (all || f[e] >= bf) ? 1u << e : 0u;
+    return bits & range_bits<4>(p, pl.nf_lo, pl.first_hi);
+  };
+  int total = 0;
+  auto gather = [&](auto loads) {
+    constexpr int V = decltype(loads)::value;
+    for (int q0 = 0; q0 < nquads; q0 += BLOCK * V) {
+      float4 v[V];
+      int p[V];
+#pragma unroll
+      for (int j = 0; j < V; ++j) load_quad(q0 + (wave * V + j) * 64 + lane, p[j], v[j]);
+      // the loads' counts (at most 256 each over the wavefront) share words for the prefix sums, two to a word
+      uint32_t keep[V], inc[(V + 1) / 2];
+#pragma unroll
+      for (int j = 0; j < V; j += 2) {
+        keep[j] = quad_bits(p[j], v[j]);
+        uint32_t cnt = (uint32_t)__popc(keep[j]);
+        if (j + 1 < V) {
+          keep[j + 1] = quad_bits(p[j + 1], v[j + 1]);
+          cnt |= (uint32_t)__popc(keep[j + 1]) << 16;
+        }
+        inc[j / 2] = (uint32_t)spin_wave_inclusive_scan((int)cnt);
+      }
+      int at[V], wave_total = 0;
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        const int sh = (j & 1) * 16;
+        at[j] = wave_total + (int)((inc[j / 2] >> sh) & 0xffffu) - __popc(keep[j]);
+        wave_total += (int)(((uint32_t)__builtin_amdgcn_readlane((int)inc[j / 2], 63) >> sh) & 0xffffu);
+      }
+      if (lane == 0) s.wtot[wave] = (unsigned)wave_total;
+      __syncthreads();
+      int before = total;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const int t = (int)s.wtot[w];
+        if (w < wave) before += t;
+        total += t;
+      }
+      if (total > CAP) return;                         // block-uniform
+#pragma unroll
+      for (int j = 0; j < V; ++j) {
+        if (!keep[j]) continue;
+        const float f[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+        int to = before + at[j];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if ((keep[j] >> e) & 1u) {
+            s.key[to] = score_key(f[e]);
+            s.id[to] = p[j] + e;
+            ++to;
+          }
+      }
+      __syncthreads();                                 // the list is whole, and s.wtot may be written again
+    }
+  };
+  if (nquads <= BLOCK * 2) gather(std::integral_constant<int, 2>());
+  else gather(std::integral_constant<int, 8>());
+  if (total <= CAP) {
+    pick_from_list<BLOCK, CAP>(total, kprime, pl.nf_lo, sel_stride, rsel, s);
+    return true;
+  }
+  // More scores than the list holds (ties, or hardly more than k' tiles in all): radix search over the tiles' scores
+  uint32_t prefix = 0;
+  int remaining = kprime;
+  for (int shift = 24; shift >= 0; shift -= 8) {
+    __syncthreads();
+    for (int i = tid; i < 256; i += BLOCK) s.kth.hist[0][i] = 0;
+    __syncthreads();
+    for (int qd = tid; qd < nquads; qd += BLOCK) {
+      float4 v;
+      int p;
+      load_quad(qd, p, v);
+      const uint32_t keep = quad_bits(p, v);
+      const float f[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t k = score_key(f[e]);
+        if (((keep >> e) & 1u) && (shift == 24 || (k >> (shift + 8)) == prefix))
+          atomicAdd(&s.kth.hist[0][(k >> shift) & 255u], 1);
+      }
+    }
+    __syncthreads();
+    int in_digit = 0;
+    const int digit = digit_of_rank(s.kth.hist[0], remaining, in_digit);
+    prefix = (prefix << 8) | (uint32_t)(digit & 255);
+  }
+  int first = pl.nf_lo;
+  unsigned quota = (unsigned)remaining;                // scores equal to the threshold still wanted
+  for (int q0 = 0; q0 < nquads; q0 += BLOCK) {
+    float4 v;
+    int p;
+    load_quad(q0 + tid, p, v);
+    const uint32_t keep = quad_bits(p, v);
+    const float f[4] = {v.x, v.y, v.z, v.w};
+    uint32_t above = 0, equal = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t k = score_key(f[e]);
+      above |= k > prefix ? 1u << e : 0u;
+      equal |= k == prefix ? 1u << e : 0u;
+    }
+    __syncthreads();
+    int at;
+    const uint32_t taken = ordered_picks<BLOCK>(above & keep, equal & keep, quota, s.wtot, at);
+    at += first;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if ((taken >> e) & 1u) {
+        if (at < sel_stride) rsel[at] = p + e;
+        ++at;
+      }
+    unsigned sure = 0, eqs = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      sure += (uint32_t)s.wtot[w];
+      eqs += (uint32_t)(s.wtot[w] >> 32);
+    }
+    eqs = min(eqs, quota);
+    first += (int)(sure + eqs);
+    quota -= eqs;
+  }
+  return true;
 }

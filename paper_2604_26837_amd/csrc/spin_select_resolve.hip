@@ -15,9 +15,10 @@ __global__ __launch_bounds__(BLOCK) void spin_select_resolve_kernel(
     const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks, int page_stride, int dir_stride, int leaf_entries,
     int32_t *__restrict__ slots, int32_t *__restrict__ page_ids, uint16_t *__restrict__ valid_mask,
     int32_t *__restrict__ npages, int32_t *status, spin_var var) {
+  __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
   const int row = blockIdx.x;
   const int take = select_reg_row<BLOCK, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced,
-                                                     sink_pages, recent_pages, sel_stride, sel, nsel, row, var);
+                                              sink_pages, recent_pages, sel_stride, sel, nsel, row, var, s);
   __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here
   resolve_row<BLOCK>(row, take, sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages, recent_pages,
                      sel_stride, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status, var);
@@ -146,9 +147,10 @@ __global__ __launch_bounds__(512) void spin_select_resolve_forced_kernel(
                          fa.scale_log2e, fa.part_ml, fa.part_acc, fa.skip);
     return;
   }
+  __shared__ elements_lds<512, reg_row_cap<512, KPT>()> s;
   const int row = blockIdx.x;
   const int take = select_reg_row<512, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced,
-                                            sink_pages, recent_pages, sel_stride, sel, nsel, row, spin_var{});
+                                            sink_pages, recent_pages, sel_stride, sel, nsel, row, spin_var{}, s);
   __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here
   resolve_row<512>(row, take, sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages, recent_pages,
                    sel_stride, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status,
@@ -190,12 +192,12 @@ extern "C" int spin_select_resolve_forced(spin_ctx *ctx, int32_t batch, const fl
   return spin_launch_status();
 }
 
-// hist_ready: stage 1 of this step has filled the long-row histograms already
+// maxima_ready: stage 1 of this step has left its tiles' maxima in the workspace
 static int select_resolve_impl(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
                                const int32_t *seq_lens, int32_t *sel, int32_t *nsel, const int32_t *dir,
                                const int32_t *leaf_pool, int64_t leaf_chunks, int32_t *slots, int32_t *page_ids,
                                uint16_t *valid_mask, int32_t *npages, void *workspace, void *stream,
-                               bool hist_ready) {
+                               bool maxima_ready) {
   if (!ctx || batch < 0 || batch > ctx->cfg.max_batch || leaf_chunks <= 0) return SPIN_ERR_INVALID;
   if (batch == 0) return SPIN_OK;
   if (!scores || !part_offsets || !seq_lens || !sel || !nsel || !dir || !leaf_pool || !slots || !page_ids ||
@@ -206,9 +208,9 @@ static int select_resolve_impl(spin_ctx *ctx, int32_t batch, const float *scores
   if (c.lru_timestamps > 0) return SPIN_ERR_UNSUPPORTED;
   const int rows = batch * c.num_kv_heads;
   if (ctx->max_parts > 16384) {
-    // long rows: the launch that finishes stage 2 resolves its row (refused where that path does not apply)
+    // from the tiles' maxima: the launch that finishes stage 2 resolves its row (refused where that path does not apply)
     const spin_resolve_args res{dir, leaf_pool, leaf_chunks, slots, page_ids, valid_mask, npages};
-    return spin_select_impl(ctx, batch, scores, part_offsets, seq_lens, sel, nsel, workspace, stream, hist_ready, &res);
+    return spin_select_impl(ctx, batch, scores, part_offsets, seq_lens, sel, nsel, workspace, stream, maxima_ready, &res);
   }
 #define SPIN_SR_ARGS                                                                                          \
   0, (hipStream_t)stream, scores, part_offsets, seq_lens, c.num_kv_heads, c.partition_tokens, c.topk,         \
@@ -237,8 +239,8 @@ extern "C" int spin_select_resolve(spin_ctx *ctx, int32_t batch, const float *sc
                              page_ids, valid_mask, npages, workspace, stream, false);
 }
 
-// Stages 1, 2 and 3 in two launches: spin_score_partitions (which, for rows of more than 16384 partitions, counts
-// stage 2's first histogram as it goes) followed by spin_select_resolve.  Same results as the three stage calls.
+// Stages 1, 2 and 3 in two launches: spin_score_partitions (which, for rows of more than 16384 partitions, leaves
+// its tiles' maxima for stage 2) followed by spin_select_resolve.  Same results as the three stage calls.
 extern "C" int spin_score_select_resolve(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries,
                                          const int32_t *chan_idx, const int32_t *part_offsets,
                                          const int32_t *seq_lens, float *scores, int32_t *sel, int32_t *nsel,
@@ -253,11 +255,11 @@ extern "C" int spin_score_select_resolve(spin_ctx *ctx, int32_t batch, const voi
   const int rows = batch * c.num_kv_heads;
   const bool long_rows = ctx->max_parts > 16384;
   // refuse before stage 1 is issued what the second launch would refuse
-  if (c.lru_timestamps > 0 || (long_rows && !(ctx->ws_hist_off && rows <= 65535))) return SPIN_ERR_UNSUPPORTED;
-  const bool fuse = long_rows;   // stage 1 of every score kind counts stage 2's first histogram for long rows
-  int32_t *hist = fuse ? (int32_t *)((char *)workspace + ctx->ws_hist_off) : nullptr;
+  if (c.lru_timestamps > 0 || (long_rows && !(ctx->ws_max_off && rows <= 65535))) return SPIN_ERR_UNSUPPORTED;
+  const bool fuse = ctx->ws_max_off != 0 && rows <= 65535;
+  float *maxima = fuse ? (float *)((char *)workspace + ctx->ws_max_off) : nullptr;
   const int st = spin_score_impl(ctx, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, workspace, stream,
-                                 hist);
+                                 maxima);
   if (st != SPIN_OK) return st;
   return select_resolve_impl(ctx, batch, scores, part_offsets, seq_lens, sel, nsel, dir, leaf_pool, leaf_chunks, slots,
                              page_ids, valid_mask, npages, workspace, stream, fuse);

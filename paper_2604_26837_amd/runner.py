@@ -144,13 +144,10 @@ class LayerState:
                               self.ws)
 
     def step_fused(self, q: torch.Tensor, summaries: Optional[torch.Tensor] = None):
-        """The step in the fewest launches the row length allows (what ``bench.py`` times): stages 2+3 in one
-        launch for rows of at most 16384 partitions (with the sink / recent pages attended beside them where
-        that applies), stages 1-3 in one call for longer ones."""
+        """The step in three launches (what ``bench.py`` times): stages 1-3 in two, with the sink / recent pages
+        attended beside stages 2+3 where that applies, then attention."""
         if self.spin.forced_split_supported and self.layouts_none:
             self.step3f(q, summaries)
-        elif max(self.w.partitions(b) for b in range(self.w.batch)) <= 16384:
-            self.step3(q, summaries)
         else:
             self.step123(q, summaries)
 

@@ -1,0 +1,77 @@
+"""Stage 2 by the maxima of the score tiles: bit-exact against the oracle at the row lengths and selection sizes where
+a tile straddles the candidates' ends, the tiles become too few for k', the list of scores overflows, or another
+kernel variant takes over; and the combined call (maxima from stage 1) against the stage calls."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_26837_amd import runner, synth
+from test_gpu_stages import _check_select
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# (partitions, k, sink pages, recent pages) of the longest row; pages of 16 tokens, one partition each
+SIZES = [(16385, 1, 0, 0), (16385, 1024, 15, 17), (16400, 1025, 16, 16), (20000, 1249, 3, 8), (20000, 1300, 3, 8),
+         (32768, 2040, 0, 1), (62500, 256, 4, 8), (65535, 3600, 1, 1), (65536, 3700, 0, 0), (65537, 128, 4, 8),
+         (131071, 700, 7, 9), (131072, 40, 0, 16)]
+
+
+@pytest.mark.parametrize("parts,topk,sink,recent", SIZES)
+def test_rows_by_tile_maxima(parts, topk, sink, recent):
+    rng = np.random.default_rng(parts * 3 + topk)
+    lens = (parts * 16, parts * 16 - 5, max(parts // 3, 1) * 16 + 3, 40 * 16)
+    w = synth.config0().with_(num_q_heads=4, num_kv_heads=1, seq_lens=lens, topk=topk, topk_includes_forced=True,
+                              sink_pages=sink, recent_pages=recent, name="tiles")
+    smooth = [(rng.standard_normal(w.partitions(b)) * 10 + 150).astype(np.float32) for b in range(4)]
+    ties = [np.round(x / 4).astype(np.float32) for x in smooth]
+    equal = [np.full(len(x), 2.0, dtype=np.float32) for x in smooth]
+    # whole tiles of large scores: every score of the k' tiles is a candidate
+    clustered = [np.where(np.arange(len(x)) // 16 % 37 == 5, x + 1000, -x).astype(np.float32) for x in smooth]
+    nans = [np.where(rng.random(len(x)) < 0.995, np.nan, x).astype(np.float32) for x in smooth]
+    low = [np.where(rng.random(len(x)) < 0.999, -np.inf, np.where(rng.random(len(x)) < 0.5, np.nan, x)).astype(np.float32)
+           for x in smooth]
+    for rows in (smooth, ties, equal, clustered, nans, low):
+        _check_select(w, rows)
+
+
+# kernel variants by row length and representatives per partition (tiles of 16, 8 and 4 partitions)
+CALLS = [(16385, 1, 120, 1, 1), (20000, 1, 1500, 0, 0), (65536, 1, 2048, 0, 1), (70000, 1, 90, 1, 0),
+         (16400, 2, 300, 2, 21), (17000, 4, 1025, 0, 0), (33000, 4, 200, 3, 5)]
+
+
+@pytest.mark.parametrize("parts,reps,topk,sink,recent", CALLS)
+def test_combined_call_by_tile_maxima(parts, reps, topk, sink, recent):
+    tp = 16 if reps > 1 else 1
+    lens = (parts * tp, parts * tp - 3, parts * tp // 5, 90 * tp)
+    kind = synth.SCORE_REPMAX if reps > 1 else synth.SCORE_SKETCH
+    if tp == 1:
+        sink = recent = min(sink, 1)
+    w = synth.config0().with_(num_q_heads=5, num_kv_heads=1, seq_lens=lens, partition_tokens=tp, score_kind=kind,
+                              reps_per_partition=reps if reps > 1 else 4, topk=topk, sink_pages=sink,
+                              recent_pages=recent, name="tiles_call")
+    data = synth.generate(w)
+    natural = torch.from_numpy(data.pool_bits.view(np.int16).copy()).to(DEV).view(torch.bfloat16)
+    layer = runner.LayerState.from_natural_pool(w, data.slot_of, natural)
+    if kind == synth.SCORE_SKETCH:
+        layer.set_channels(synth.sketch_channels(data))
+    layer.build_summaries()
+    names = ("scores", "sel", "nsel", "slots", "page_ids", "valid_mask", "npages", "out", "lse")
+    for seed in range(3):
+        q = torch.from_numpy(synth.make_queries(w, 40 + seed).view(np.int16)).to(DEV).view(torch.bfloat16)
+        layer.step(q)
+        torch.cuda.synchronize()
+        want = {n: getattr(layer, n).clone() for n in names}
+        layer.ws.fill_(0x7f)                       # nothing may depend on what the workspace held, tickets aside
+        layer.spin.workspace_init(layer.ws)
+        for n in names[1:]:
+            getattr(layer, n).fill_(-3)
+        layer.step123(q)
+        torch.cuda.synchronize()
+        assert layer.status() == 0
+        keep = torch.arange(layer.slots.shape[1], device=DEV)[None, :] < layer.npages[:, None]
+        for n in names:
+            got, ref = getattr(layer, n), want[n]
+            if n in ("slots", "page_ids", "valid_mask"):
+                got, ref = got[keep], ref[keep]
+            assert torch.equal(got, ref), (seed, n)
