@@ -5,9 +5,9 @@
 // a side stream (needs the miss list on the host).  The device-driven one is
 // the paper's copy kernel (Section 5.5): one wavefront copies one page with
 // 16-byte lane transactions straight out of pinned host memory; a fixed, small number of
-// workgroups walks the (row, chunk of misses) pairs with a grid stride, so pages are spread over
-// the wavefronts whatever row owns them, and the miss list never leaves the device.  The same
-// kernel run the other way is Offload's copy (slot -> host page).
+// workgroups deals all rows' pages to its wavefronts one by one, whatever row owns them, and the
+// miss list never leaves the device.  The same kernel run the other way is Offload's copy (slot ->
+// host page).
 #include "spin_common.h"
 
 extern "C" int spin_copy_misses_host(spin_ctx *ctx, int32_t batch, const void *host_kv,
@@ -45,12 +45,11 @@ extern "C" int spin_copy_misses_host(spin_ctx *ctx, int32_t batch, const void *h
 }
 
 #define GATHER_WAVES 4
-#define GATHER_PAGES_PER_WG 16
-// Workgroups of a copy launch.  The host link is the limit (about 54 GB/s), and it takes about 64 compute units
-// to saturate it (measured per step of the budget workload, 6.4 K pages: 8 / 16 / 32 / 64 / 128 / 512 / 2048
-// workgroups -> 2605 / 1489 / 1092 / 1001 / 1000 / 1032 / 1032 us); more only crowd the units that other
-// launches could use meanwhile.
-#define GATHER_MAX_WGS 64
+// Workgroups of a copy launch.  The host link is the limit and 64 wavefronts with a page each in flight fill it; more
+// requests at a time slow it down (64 rows that miss 1010 pages: 4 / 8 / 12 / 16 / 32 / 64 / 128 / 256 workgroups ->
+// 250 / 167 / 165 / 163-165 / 166 / 166 / 180 / 199 us) and crowd the units that other launches could use meanwhile.
+#define GATHER_MAX_WGS 16
+#define GATHER_ROWS 1024   // rows whose miss counts a workgroup holds as prefix sums at a time
 
 struct host_map {
   const int32_t *table;     // NULL: identity
@@ -59,49 +58,87 @@ struct host_map {
 
 // TO_HOST = false: host page -> slot (Retrieve).  TO_HOST = true: slot -> host page (Offload's copy,
 // Table 1: copy(gpu_kv, cpu_kv, map)); the lists have the same shape in both directions.
+//
+// The host link bounds it, provided that the pages are spread over the wavefronts whatever the rows' counts are: a
+// wavefront takes every (number of wavefronts)-th page of all rows' lists, found by the prefix sums of the counts.
+// (Dealt in chunks of 16 pages of one row, rows that miss 16 pages or fewer each had an eighth of 64 workgroups at
+// work.  1010 pages of 64 rows: 167.6 -> 163-165 us; 6490 of 256 rows: 1016 -> 1003 us, 53 GB/s.)
 template <bool TO_HOST>
 __global__ __launch_bounds__(GATHER_WAVES * 64) void spin_gather_kernel(
     uint4 *__restrict__ host_kv, const int64_t *__restrict__ row_base, const int32_t *__restrict__ nmiss,
     const int32_t *__restrict__ miss_pages, const int32_t *__restrict__ miss_slots, uint4 *__restrict__ pool,
-    int64_t pool_slots, int page_stride, int chunks_per_row, int total_items, int32_t *status, host_map hm) {
+    int64_t pool_slots, int page_stride, int rows, int32_t *status, host_map hm) {
+  __shared__ int s_end[GATHER_ROWS];     // pages of the rows up to and including this one
+  __shared__ int s_wtot[GATHER_WAVES];
+  constexpr int RPT = GATHER_ROWS / (GATHER_WAVES * 64);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  // (row, chunk of the row's list) pairs are dealt to the workgroups with a grid stride: the link needs few
-  // pages in flight, so the launch stays small and leaves the compute units to whatever runs beside it
-  for (int item = blockIdx.x; item < total_items; item += gridDim.x) {
-  const int row = item / chunks_per_row, chunk = item - row * chunks_per_row;
-  int n = nmiss[row];
-  n = n < 0 ? 0 : (n > page_stride ? page_stride : n);
-  const int begin = chunk * GATHER_PAGES_PER_WG;
-  const int end = min(begin + GATHER_PAGES_PER_WG, n);
-  const int64_t rb = row_base[row];
-  for (int i = begin + wave; i < end; i += GATHER_WAVES) {
-    const int32_t pg = miss_pages[(size_t)row * page_stride + i];
-    const int32_t slot = miss_slots[(size_t)row * page_stride + i];
-    if (pg < 0 || slot < 0 || (int64_t)slot >= pool_slots) {
-      if (lane == 0) spin_raise(status, SPIN_ERR_SLOT_RANGE);
-      continue;
-    }
-    int64_t hpage = rb + pg;
-    if (hm.table) {                         // CPU page table: offset of the page in the row's list -> physical host page
-      const bool in_table = hpage >= 0 && hpage < hm.entries;
-      hpage = in_table ? hm.table[hpage] : -1;
-    }
-    // the host pool's size, when one was registered (with or without a table), bounds the page
-    if (hpage < 0 || (hm.pages > 0 && hpage >= hm.pages)) {
-      if (lane == 0) spin_raise(status, SPIN_ERR_SLOT_RANGE);
-      continue;
-    }
-    uint4 *hp = host_kv + (size_t)hpage * SPIN_SLOT_U4 + lane;
-    uint4 *dp = pool + (size_t)slot * SPIN_SLOT_U4 + lane;
-    const uint4 *src = TO_HOST ? dp : hp;
-    uint4 *dst = TO_HOST ? hp : dp;
-    uint4 v[8];
+  const int nwaves = gridDim.x * GATHER_WAVES;
+  int item = wave * gridDim.x + blockIdx.x;            // neighbouring pages go to different compute units
+  for (int row0 = 0; row0 < rows; row0 += GATHER_ROWS) {
+    int cnt[RPT], mine = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = src[k * 64];
+    for (int j = 0; j < RPT; ++j) {
+      const int row = row0 + threadIdx.x * RPT + j;
+      const int n = row < rows ? nmiss[row] : 0;
+      cnt[j] = n < 0 ? 0 : (n > page_stride ? page_stride : n);
+      mine += cnt[j];
+    }
+    const int inc = spin_wave_inclusive_scan(mine);
+    if (row0) __syncthreads();                         // the sums of the rows before have been read
+    if (lane == 63) s_wtot[wave] = inc;
+    __syncthreads();
+    int run = inc - mine, total = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) dst[k * 64] = v[k];
+    for (int w = 0; w < GATHER_WAVES; ++w) {
+      if (w < wave) run += s_wtot[w];
+      total += s_wtot[w];
+    }
+#pragma unroll
+    for (int j = 0; j < RPT; ++j) {
+      run += cnt[j];
+      s_end[threadIdx.x * RPT + j] = run;
+    }
+    __syncthreads();
+    for (; item < total; item += nwaves) {
+      int lo = 0, hi = GATHER_ROWS - 1;                // the first row whose pages end behind `item`
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (s_end[mid] > item) hi = mid; else lo = mid + 1;
+      }
+      const int row = row0 + lo, i = item - (lo ? s_end[lo - 1] : 0);
+      const int32_t pg = miss_pages[(size_t)row * page_stride + i];
+      const int32_t slot = miss_slots[(size_t)row * page_stride + i];
+      if (pg < 0 || slot < 0 || (int64_t)slot >= pool_slots) {
+        if (lane == 0) spin_raise(status, SPIN_ERR_SLOT_RANGE);
+        continue;
+      }
+      int64_t hpage = row_base[row] + pg;
+      if (hm.table) {                       // CPU page table: offset of the page in the row's list -> physical host page
+        const bool in_table = hpage >= 0 && hpage < hm.entries;
+        hpage = in_table ? hm.table[hpage] : -1;
+      }
+      // the host pool's size, when one was registered (with or without a table), bounds the page
+      if (hpage < 0 || (hm.pages > 0 && hpage >= hm.pages)) {
+        if (lane == 0) spin_raise(status, SPIN_ERR_SLOT_RANGE);
+        continue;
+      }
+      uint4 *hp = host_kv + (size_t)hpage * SPIN_SLOT_U4 + lane;
+      uint4 *dp = pool + (size_t)slot * SPIN_SLOT_U4 + lane;
+      const uint4 *src = TO_HOST ? dp : hp;
+      uint4 *dst = TO_HOST ? hp : dp;
+      uint4 v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = src[k * 64];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) dst[k * 64] = v[k];
+    }
+    item -= total;
   }
-  }
+}
+
+static unsigned gather_workgroups(int64_t most_pages) {
+  const int64_t wgs = (most_pages + GATHER_WAVES - 1) / GATHER_WAVES;
+  return (unsigned)(wgs < GATHER_MAX_WGS ? wgs : GATHER_MAX_WGS);
 }
 
 extern "C" int spin_gather_misses(spin_ctx *ctx, int32_t batch, const void *host_kv, const int64_t *row_base,
@@ -112,10 +149,9 @@ extern "C" int spin_gather_misses(spin_ctx *ctx, int32_t batch, const void *host
   if (!host_kv || !row_base || !nmiss || !miss_pages || !miss_slots || !kv_pool) return SPIN_ERR_INVALID;
   if (!workspace) return SPIN_ERR_WORKSPACE;
   const int rows = batch * ctx->cfg.num_kv_heads;
-  const int chunks = (ctx->page_stride + GATHER_PAGES_PER_WG - 1) / GATHER_PAGES_PER_WG;
-  spin_launch(ctx, SPIN_K_GATHER, spin_gather_kernel<false>, dim3((unsigned)min(rows * chunks, GATHER_MAX_WGS)), dim3(GATHER_WAVES * 64), 0,
+  spin_launch(ctx, SPIN_K_GATHER, spin_gather_kernel<false>, dim3(gather_workgroups((int64_t)rows * ctx->page_stride)), dim3(GATHER_WAVES * 64), 0,
               (hipStream_t)stream, (uint4 *)const_cast<void *>(host_kv), row_base, nmiss, miss_pages, miss_slots,
-              (uint4 *)kv_pool, pool_slots, ctx->page_stride, chunks, rows * chunks, (int32_t *)workspace,
+              (uint4 *)kv_pool, pool_slots, ctx->page_stride, rows, (int32_t *)workspace,
               host_map{ctx->cpu_table, ctx->cpu_table_entries, ctx->cpu_pages});
   return spin_launch_status();
 }
@@ -128,10 +164,9 @@ extern "C" int spin_offload_pages(spin_ctx *ctx, int32_t batch, const void *kv_p
   if (!host_kv || !row_base || !count || !pages || !slots || !kv_pool) return SPIN_ERR_INVALID;
   if (!workspace) return SPIN_ERR_WORKSPACE;
   const int rows = batch * ctx->cfg.num_kv_heads;
-  const int chunks = (ctx->page_stride + GATHER_PAGES_PER_WG - 1) / GATHER_PAGES_PER_WG;
-  spin_launch(ctx, SPIN_K_OFFLOAD, spin_gather_kernel<true>, dim3((unsigned)min(rows * chunks, GATHER_MAX_WGS)), dim3(GATHER_WAVES * 64), 0,
+  spin_launch(ctx, SPIN_K_OFFLOAD, spin_gather_kernel<true>, dim3(gather_workgroups((int64_t)rows * ctx->page_stride)), dim3(GATHER_WAVES * 64), 0,
               (hipStream_t)stream, (uint4 *)host_kv, row_base, count, pages, slots,
-              (uint4 *)const_cast<void *>(kv_pool), pool_slots, ctx->page_stride, chunks, rows * chunks, (int32_t *)workspace,
+              (uint4 *)const_cast<void *>(kv_pool), pool_slots, ctx->page_stride, rows, (int32_t *)workspace,
               host_map{ctx->cpu_table, ctx->cpu_table_entries, ctx->cpu_pages});
   return spin_launch_status();
 }
