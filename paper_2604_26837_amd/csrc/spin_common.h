@@ -186,14 +186,26 @@ __device__ inline int spin_var_lower_bound_start(const spin_var &v, size_t base,
   }
   return lo;
 }
-// number of leading partitions that end at or before `page`
-__device__ inline int spin_var_count_end_le(const spin_var &v, size_t base, int P, int page) {
-  int lo = 0, hi = P;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (v.first_page[base + mid] + spin_var_npages(v, base, mid) <= page) lo = mid + 1; else hi = mid;
-  }
-  return lo;
+// How the always-attended windows lie in a row of variable-length partitions: the pages [0, sink_end) and
+// [recent_begin, pages), and the last partitions that start before sink_end / at or before recent_begin (-1: none).
+struct spin_var_span {
+  int P, pages, sink_end, recent_begin, at_sink, at_recent;
+};
+__device__ inline void spin_var_windows(spin_var_span &w, int sink_pages, int recent_pages) {
+  w.sink_end = min(sink_pages, w.pages);
+  w.recent_begin = max(w.pages - recent_pages, 0);
+  if (w.sink_end >= w.recent_begin) { w.sink_end = w.pages; w.recent_begin = w.pages; }
+}
+// the same by searches in the row's tables
+__device__ inline spin_var_span spin_var_span_of(const spin_var &v, size_t base, int row, int PP, int sink_pages,
+                                                 int recent_pages) {
+  spin_var_span w;
+  w.P = min(max(v.count[row], 0), PP);
+  w.pages = spin_var_row_pages(v, base, w.P);
+  spin_var_windows(w, sink_pages, recent_pages);
+  w.at_sink = spin_var_lower_bound_start(v, base, w.P, w.sink_end) - 1;
+  w.at_recent = spin_var_lower_bound_start(v, base, w.P, w.recent_begin + 1) - 1;
+  return w;
 }
 
 // DPP lane exchanges inside a row of 16 lanes

@@ -147,8 +147,9 @@ __global__ __launch_bounds__(BLOCK) void spin_select_reg_kernel(
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
     int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, spin_var var) {
   __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
+  spin_var_span span;
   (void)select_reg_row<BLOCK, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
-                                   recent_pages, sel_stride, sel, nsel, (int)blockIdx.x, var, s);
+                                   recent_pages, sel_stride, sel, nsel, (int)blockIdx.x, var, span, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -326,6 +326,59 @@ __device__ inline void emit_forced(const sel_plan &pl, int sel_stride, int32_t *
   if (tid == 0) nsel[row] = pl.take;
 }
 
+// The windows of a row of at most BLOCK * KPT variable-length partitions, and its forced prefix and suffix
+// [0, nf_lo) and [first_hi, P).  Every thread holds the table entries of its KPT partitions, so one round of loads and
+// two barriers stand for four binary searches of a dozen dependent loads each.
+template <int BLOCK, int KPT>
+__device__ inline spin_var_span block_var_span(const spin_var &var, size_t vbase, int row, int PP, int sink_pages,
+                                               int recent_pages, int &nf_lo, int &first_hi) {
+  constexpr int NW = BLOCK / 64;
+  __shared__ int s_pages;
+  __shared__ uint2 s_cnt[NW];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c0 = threadIdx.x * KPT;
+  spin_var_span w;
+  int start[KPT], tokens[KPT];
+#pragma unroll
+  for (int k = 0; k < KPT; ++k) {
+    const bool in = c0 + k < PP;                       // the tables are as long as the score array
+    start[k] = in ? var.first_page[vbase + c0 + k] : 0;
+    tokens[k] = in ? var.tokens[vbase + c0 + k] : 0;
+  }
+  w.P = min(min(max(var.count[row], 0), PP), BLOCK * KPT);
+  if (w.P == 0 && threadIdx.x == 0) s_pages = 0;
+#pragma unroll
+  for (int k = 0; k < KPT; ++k)
+    if (c0 + k == w.P - 1) s_pages = start[k] + ((tokens[k] + 15) >> 4);
+  __syncthreads();
+  w.pages = s_pages;
+  spin_var_windows(w, sink_pages, recent_pages);
+  // partitions that end by sink_end | start before it, start before recent_begin | at or before it; two counts to a
+  // word (at most 16384 each)
+  uint32_t lo = 0, hi = 0;
+#pragma unroll
+  for (int k = 0; k < KPT; ++k)
+    if (c0 + k < w.P) {
+      const int end = start[k] + ((tokens[k] + 15) >> 4);
+      lo += (end <= w.sink_end ? 1u : 0u) + (start[k] < w.sink_end ? 0x10000u : 0u);
+      hi += (start[k] < w.recent_begin ? 1u : 0u) + (start[k] <= w.recent_begin ? 0x10000u : 0u);
+    }
+  lo = (uint32_t)spin_wave_inclusive_scan((int)lo);
+  hi = (uint32_t)spin_wave_inclusive_scan((int)hi);
+  if (lane == 63) s_cnt[wave] = make_uint2(lo, hi);
+  __syncthreads();
+  lo = hi = 0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    lo += s_cnt[i].x;
+    hi += s_cnt[i].y;
+  }
+  nf_lo = (int)(lo & 0xffffu);
+  w.at_sink = (int)(lo >> 16) - 1;
+  first_hi = (int)(hi & 0xffffu);
+  w.at_recent = (int)(hi >> 16) - 1;
+  return w;
+}
+
 // Register-resident variant for rows of at most BLOCK * KPT partitions: every
 // thread keeps KPT consecutive scores in registers, so they are read once.
 // With 16 or more of them per thread most are ruled out first: the k'-th largest of the threads' largest keys
@@ -333,7 +386,7 @@ __device__ inline void emit_forced(const sel_plan &pl, int sel_stride, int32_t *
 // Latency bounds this kernel: dependent loads, a barrier per digit, and the instructions per score on the row's
 // one compute unit.  Stages 2+3, top 128, before (every score in every histogram) and after: 8 rows of 8192
 // 14.7 -> 9.4 us, 8 rows of 16384 16.2 -> 11.5, 256 ragged rows of up to 16384 17.4 -> 13.4.
-// Returns the number of selected partitions.
+// Returns the number of selected partitions (and, with variable-length partitions, the row's windows in `span`).
 template <int BLOCK, int KPT>
 constexpr int reg_row_cap() { return KPT >= 16 ? 2 * BLOCK : 0; }
 
@@ -342,7 +395,7 @@ __device__ inline int select_reg_row(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
     int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, int row,
-    spin_var var, elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> &s) {
+    spin_var var, spin_var_span &span, elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> &s) {
   typedef typename key_bits<KPT>::type M;
   constexpr int CAP = reg_row_cap<BLOCK, KPT>();
   const int b = row / Hkv, h = row - b * Hkv;
@@ -364,14 +417,9 @@ __device__ inline int select_reg_row(
   // forced partitions: a prefix [0, nf_lo) and a suffix [first_hi, P)
   sel_plan pl;
   if (var.count) {
-    int P = var.count[row];
-    P = P < 0 ? 0 : (P > PP ? PP : P);
-    const int pages = spin_var_row_pages(var, vbase, P);
-    int sink_end = min(sink_pages, pages);
-    int recent_begin = max(pages - recent_pages, 0);
-    if (sink_end >= recent_begin) { sink_end = pages; recent_begin = pages; }
-    pl = plan_of(P, spin_var_count_end_le(var, vbase, P, sink_end), spin_var_lower_bound_start(var, vbase, P, recent_begin),
-                 topk, includes_forced, sel_stride);
+    int nf_lo, first_hi;
+    span = block_var_span<BLOCK, KPT>(var, vbase, row, PP, sink_pages, recent_pages, nf_lo, first_hi);
+    pl = plan_of(span.P, nf_lo, first_hi, topk, includes_forced, sel_stride);
   } else {
     pl = select_plan(N, PP, tp, topk, includes_forced, sink_pages, recent_pages, sel_stride);
   }

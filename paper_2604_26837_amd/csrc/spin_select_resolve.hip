@@ -17,11 +17,13 @@ __global__ __launch_bounds__(BLOCK) void spin_select_resolve_kernel(
     int32_t *__restrict__ npages, int32_t *status, spin_var var) {
   __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
   const int row = blockIdx.x;
+  spin_var_span span = {};
   const int take = select_reg_row<BLOCK, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced,
-                                              sink_pages, recent_pages, sel_stride, sel, nsel, row, var, s);
+                                              sink_pages, recent_pages, sel_stride, sel, nsel, row, var, span, s);
   __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here
   resolve_row<BLOCK>(row, take, sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages, recent_pages,
-                     sel_stride, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status, var);
+                     sel_stride, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status, var,
+                     &span);
 }
 
 // ---------------------------------------------------------------------------
@@ -149,8 +151,9 @@ __global__ __launch_bounds__(512) void spin_select_resolve_forced_kernel(
   }
   __shared__ elements_lds<512, reg_row_cap<512, KPT>()> s;
   const int row = blockIdx.x;
+  spin_var_span span;                // (uniform partitions)
   const int take = select_reg_row<512, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced,
-                                            sink_pages, recent_pages, sel_stride, sel, nsel, row, spin_var{}, s);
+                                            sink_pages, recent_pages, sel_stride, sel, nsel, row, spin_var{}, span, s);
   __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here
   resolve_row<512>(row, take, sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages, recent_pages,
                    sel_stride, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status,

@@ -141,3 +141,51 @@ def test_uniform_tables_give_the_uniform_results():
         assert torch.equal(ref.slots[r, :n[r]], var.slots[r, :n[r]])
         assert torch.equal(ref.valid_mask[r, :n[r]], var.valid_mask[r, :n[r]])
     assert torch.equal(ref.out.view(torch.int16), var.out.view(torch.int16))
+
+
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("pages,topk,largest,sink,recent", [
+    (2500, 24, 256, 4, 16), (5000, 700, 64, 3, 1), (9000, 1100, 32, 0, 9), (4100, 5, 256, 40, 70), (16000, 520, 16, 1, 1),
+    (30, 3, 256, 20, 9), (40, 3, 256, 0, 0)])
+def test_windows_and_page_lists_of_long_rows(pages, topk, largest, sink, recent, fused):
+    """Stages 2 and 3 alone on rows of every register width, more selected partitions than one round of threads, and
+    windows that straddle a partition: whole numbers, so the lists must be the oracle's."""
+    hkv = 2
+    lens = (16 * pages - 5, 16 * max(pages // 3, 1))
+    w = synth.config0().with_(seq_lens=lens, num_q_heads=hkv, num_kv_heads=hkv, partition_tokens=largest, topk=topk,
+                              topk_includes_forced=False, sink_pages=sink, recent_pages=recent, name="vlong")
+    layouts = synth.variable_layouts(w, seed=pages)
+    rng = np.random.default_rng(pages)
+    slot_of, nslots = [], 0
+    perm = rng.permutation(hkv * sum(w.pages(b) for b in range(w.batch))).astype(np.int32)
+    for b in range(w.batch):
+        n = hkv * w.pages(b)
+        slot_of.append(perm[nslots:nslots + n].reshape(hkv, -1))
+        nslots += n
+    pool = torch.zeros((nslots, 4096), dtype=torch.bfloat16, device=DEV)
+    layer = runner.LayerState(w, slot_of, pool, layouts=layouts)
+    layer.scores.copy_(torch.from_numpy(rng.integers(0, 300, layer.scores.numel()).astype(np.float32)))   # many ties
+    sp = layer.spin
+    if fused:
+        sp.select_resolve(w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.dir,
+                          layer.leaf_pool, layer.slots, layer.page_ids, layer.valid_mask, layer.npages, layer.ws)
+    else:
+        sp.select_topk(w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.ws)
+        sp.resolve_slots(w.batch, 0, layer.sel, layer.nsel, layer.seq_lens, layer.dir, layer.leaf_pool, layer.slots,
+                         layer.page_ids, layer.valid_mask, layer.npages, layer.ws)
+    torch.cuda.synchronize()
+    assert layer.status() == 0
+    scores, sel, nsel = layer.scores.cpu().numpy(), layer.sel.cpu().numpy(), layer.nsel.cpu().numpy()
+    slots, ids, npages = layer.slots.cpu().numpy(), layer.page_ids.cpu().numpy(), layer.npages.cpu().numpy()
+    masks = layer.valid_mask.cpu().numpy().view(np.uint16)
+    for r in range(w.rows):
+        b, h = divmod(r, hkv)
+        first, toks = layouts[b][h]
+        base = layer.row_base(b, h)
+        want = varpart.select_topk(scores[base:base + len(first)], first, toks, 16, topk, False, sink, recent)
+        assert sel[r, :nsel[r]].tolist() == want
+        page_map = {(r, pg): int(s) for pg, s in enumerate(slot_of[b][h])}
+        pg_w, sl_w, mk_w = varpart.resolve_slots(want, first, toks, 16, sink, recent, page_map, r)
+        n = npages[r]
+        assert ids[r, :n].tolist() == pg_w and slots[r, :n].tolist() == sl_w and masks[r, :n].tolist() == mk_w
+        assert (ids[r, n:] == -1).all() and (masks[r, n:] == 0).all()
