@@ -1,8 +1,11 @@
-"""ctypes binding of ``libspin.so``: same names as the C ABI, argument
-marshalling only.  torch supplies device memory and the current stream."""
+"""Binding of ``libspin.so``: same names as the C ABI, argument marshalling
+only.  torch supplies device memory and the current stream.  Set-up and
+bookkeeping calls go through ctypes, the stage calls through the extension
+module ``_spin_torch``, which checks and converts their tensors natively."""
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import Optional
 
@@ -11,6 +14,7 @@ import torch
 from . import build as _build
 
 _LIB: Optional[C.CDLL] = None
+_call = None          # the extension module, bound to the loaded library
 
 SPIN_OK = 0
 STATUS_NAMES = {0: "SPIN_OK", -1: "SPIN_ERR_INVALID", -2: "SPIN_ERR_UNSUPPORTED", -3: "SPIN_ERR_WORKSPACE",
@@ -47,12 +51,14 @@ class SpinError(RuntimeError):
 
 def load_library() -> C.CDLL:
     """Load the in-tree library; there is no fallback if it is missing."""
-    global _LIB
+    global _LIB, _call
     if _LIB is not None:
         return _LIB
     if not os.path.exists(_build.LIB_PATH):
         raise RuntimeError(f"{_build.LIB_PATH} is not built: run `python -m paper_2604_26837_amd.build` "
                            "(the HIP library is required; there is no CPU fallback)")
+    if not os.path.exists(_build.MODULE_PATH):
+        raise RuntimeError(f"{_build.MODULE_PATH} is not built: run `python -m paper_2604_26837_amd.build`")
     lib = C.CDLL(_build.LIB_PATH)
     vp, i32, i64 = C.c_void_p, C.c_int32, C.c_int64
     lib.spin_create.argtypes = [C.POINTER(SpinConfig), C.POINTER(vp)]
@@ -99,6 +105,12 @@ def load_library() -> C.CDLL:
     lib.spin_copy_misses_host.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp, i64, vp, C.POINTER(i64)]
     lib.spin_gather_misses.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp, i64, vp, vp]
     lib.spin_offload_pages.argtypes = [vp, i32, vp, i64, vp, vp, vp, vp, vp, vp, vp]
+    spec = importlib.util.spec_from_file_location("_spin_torch", _build.MODULE_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    for name in module.ENTRIES.split(",")[:-1]:
+        module.bind(name, C.cast(getattr(lib, name), vp).value)
+    _call = module
     _LIB = lib
     return lib
 
@@ -140,6 +152,7 @@ class Spin:
         if st != SPIN_OK:
             raise SpinError(st, "spin_create")
         self.h = h
+        self._ctx = h.value
         self.sel_stride = self.lib.spin_sel_stride(h)
         self.page_stride = self.lib.spin_page_stride(h)
         self.dir_stride = self.lib.spin_dir_stride(h)
@@ -163,6 +176,7 @@ class Spin:
             if getattr(self, "h", None):
                 self.lib.spin_destroy(self.h)
                 self.h = None
+                self._ctx = 0
         except Exception:
             pass
 
@@ -201,30 +215,18 @@ class Spin:
     # -- set-up calls -----------------------------------------------------
     def pack_kv_pages(self, src_k, src_v, slots, kv_pool):
         n = src_k.shape[0]
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
-        self._check(self.lib.spin_pack_kv_pages(
-            self.h, n, _ptr(src_k, torch.bfloat16, "src_k"), _ptr(src_v, torch.bfloat16, "src_v"),
-            _ptr(slots, torch.int32, "slots"), _ptr(kv_pool, None, "kv_pool"), pool_slots, _stream()),
-            "spin_pack_kv_pages")
+        self._check(_call.spin_pack_kv_pages(self._ctx, n, src_k, src_v, slots, kv_pool), "spin_pack_kv_pages")
 
     def build_summaries(self, batch, kv_pool, dir_, leaf_pool, part_offsets, seq_lens, chan_idx, summaries, ws):
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
-        self._check(self.lib.spin_build_summaries(
-            self.h, batch, _ptr(kv_pool), pool_slots, _ptr(dir_, torch.int32, "dir"),
-            _ptr(leaf_pool, torch.int32, "leaf_pool"), leaf_pool.shape[0],
-            _ptr(part_offsets, torch.int32, "part_offsets"), _ptr(seq_lens, torch.int32, "seq_lens"),
-            _ptr(chan_idx, torch.int32, "chan_idx"), _ptr(summaries), _ptr(ws), _stream()),
-            "spin_build_summaries")
+        self._check(_call.spin_build_summaries(
+            self._ctx, batch, kv_pool, dir_, leaf_pool, part_offsets, seq_lens, chan_idx, summaries,
+            ws), "spin_build_summaries")
 
     def append_kv(self, batch, k_new, v_new, seq_lens, kv_pool, dir_, leaf_pool, part_offsets, chan_idx,
                   summaries, ws):
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
-        self._check(self.lib.spin_append_kv(
-            self.h, batch, _ptr(k_new, torch.bfloat16, "k_new"), _ptr(v_new, torch.bfloat16, "v_new"),
-            _ptr(seq_lens, torch.int32, "seq_lens"), _ptr(kv_pool), pool_slots, _ptr(dir_, torch.int32, "dir"),
-            _ptr(leaf_pool, torch.int32, "leaf_pool"), leaf_pool.shape[0],
-            _ptr(part_offsets, torch.int32, "part_offsets"), _ptr(chan_idx, torch.int32, "chan_idx"),
-            _ptr(summaries), _ptr(ws), _stream()), "spin_append_kv")
+        self._check(_call.spin_append_kv(
+            self._ctx, batch, k_new, v_new, seq_lens, kv_pool, dir_, leaf_pool, part_offsets, chan_idx, summaries,
+            ws), "spin_append_kv")
 
     def probe_stream_read(self, buf, nbytes, ws):
         self._check(self.lib.spin_probe_stream_read(self.h, _ptr(buf), nbytes, _ptr(ws), _stream()),
@@ -278,16 +280,12 @@ class Spin:
 
     # -- the four stages --------------------------------------------------
     def score_partitions(self, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, ws):
-        self._check(self.lib.spin_score_partitions(
-            self.h, batch, _ptr(q, torch.bfloat16, "q"), _ptr(summaries), _ptr(chan_idx, torch.int32, "chan_idx"),
-            _ptr(part_offsets, torch.int32, "part_offsets"), _ptr(seq_lens, torch.int32, "seq_lens"),
-            _ptr(scores, torch.float32, "scores"), _ptr(ws), _stream()), "spin_score_partitions")
+        self._check(_call.spin_score_partitions(
+            self._ctx, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, ws), "spin_score_partitions")
 
     def select_topk(self, batch, scores, part_offsets, seq_lens, sel, nsel, ws):
-        self._check(self.lib.spin_select_topk(
-            self.h, batch, _ptr(scores, torch.float32, "scores"), _ptr(part_offsets, torch.int32, "part_offsets"),
-            _ptr(seq_lens, torch.int32, "seq_lens"), _ptr(sel, torch.int32, "sel"),
-            _ptr(nsel, torch.int32, "nsel"), _ptr(ws), _stream()), "spin_select_topk")
+        self._check(_call.spin_select_topk(
+            self._ctx, batch, scores, part_offsets, seq_lens, sel, nsel, ws), "spin_select_topk")
 
     def pin_partitions(self, batch, scores, part_offsets, pinned, npinned):
         self._check(self.lib.spin_pin_partitions(
@@ -296,44 +294,27 @@ class Spin:
             "spin_pin_partitions")
 
     def score_select_topk(self, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, sel, nsel, ws):
-        self._check(self.lib.spin_score_select_topk(
-            self.h, batch, _ptr(q, torch.bfloat16, "q"), _ptr(summaries), _ptr(chan_idx, torch.int32, "chan_idx"),
-            _ptr(part_offsets, torch.int32, "part_offsets"), _ptr(seq_lens, torch.int32, "seq_lens"),
-            _ptr(scores, torch.float32, "scores"), _ptr(sel, torch.int32, "sel"), _ptr(nsel, torch.int32, "nsel"),
-            _ptr(ws), _stream()), "spin_score_select_topk")
+        self._check(_call.spin_score_select_topk(
+            self._ctx, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, sel, nsel,
+            ws), "spin_score_select_topk")
 
     def resolve_slots(self, batch, step, sel, nsel, seq_lens, dir_, leaf_pool, slots, page_ids, valid_mask,
                       npages, ws, rev_table=None, slot_base=None, miss_pages=None, miss_slots=None, nmiss=None):
-        self._check(self.lib.spin_resolve_slots(
-            self.h, batch, step, _ptr(sel, torch.int32, "sel"), _ptr(nsel, torch.int32, "nsel"),
-            _ptr(seq_lens, torch.int32, "seq_lens"), _ptr(dir_, torch.int32, "dir"),
-            _ptr(leaf_pool, torch.int32, "leaf_pool"), leaf_pool.shape[0],
-            _ptr(rev_table, torch.int32, "rev_table"), _ptr(slot_base, torch.int32, "slot_base"),
-            _ptr(slots, torch.int32, "slots"), _ptr(page_ids, torch.int32, "page_ids"),
-            _ptr(valid_mask, torch.int16, "valid_mask"), _ptr(npages, torch.int32, "npages"),
-            _ptr(miss_pages, torch.int32, "miss_pages"), _ptr(miss_slots, torch.int32, "miss_slots"),
-            _ptr(nmiss, torch.int32, "nmiss"), _ptr(ws), _stream()), "spin_resolve_slots")
+        self._check(_call.spin_resolve_slots(
+            self._ctx, batch, step, sel, nsel, seq_lens, dir_, leaf_pool, rev_table, slot_base, slots, page_ids,
+            valid_mask, npages, miss_pages, miss_slots, nmiss, ws), "spin_resolve_slots")
 
     def select_resolve(self, batch, scores, part_offsets, seq_lens, sel, nsel, dir_, leaf_pool, slots, page_ids,
                        valid_mask, npages, ws):
-        self._check(self.lib.spin_select_resolve(
-            self.h, batch, _ptr(scores, torch.float32, "scores"), _ptr(part_offsets, torch.int32, "part_offsets"),
-            _ptr(seq_lens, torch.int32, "seq_lens"), _ptr(sel, torch.int32, "sel"), _ptr(nsel, torch.int32, "nsel"),
-            _ptr(dir_, torch.int32, "dir"), _ptr(leaf_pool, torch.int32, "leaf_pool"), leaf_pool.shape[0],
-            _ptr(slots, torch.int32, "slots"), _ptr(page_ids, torch.int32, "page_ids"),
-            _ptr(valid_mask, torch.int16, "valid_mask"), _ptr(npages, torch.int32, "npages"), _ptr(ws), _stream()),
-            "spin_select_resolve")
+        self._check(_call.spin_select_resolve(
+            self._ctx, batch, scores, part_offsets, seq_lens, sel, nsel, dir_, leaf_pool, slots, page_ids,
+            valid_mask, npages, ws), "spin_select_resolve")
 
     def score_select_resolve(self, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, sel, nsel, dir_,
                              leaf_pool, slots, page_ids, valid_mask, npages, ws):
-        self._check(self.lib.spin_score_select_resolve(
-            self.h, batch, _ptr(q, torch.bfloat16, "q"), _ptr(summaries), _ptr(chan_idx, torch.int32, "chan_idx"),
-            _ptr(part_offsets, torch.int32, "part_offsets"), _ptr(seq_lens, torch.int32, "seq_lens"),
-            _ptr(scores, torch.float32, "scores"), _ptr(sel, torch.int32, "sel"), _ptr(nsel, torch.int32, "nsel"),
-            _ptr(dir_, torch.int32, "dir"), _ptr(leaf_pool, torch.int32, "leaf_pool"), leaf_pool.shape[0],
-            _ptr(slots, torch.int32, "slots"), _ptr(page_ids, torch.int32, "page_ids"),
-            _ptr(valid_mask, torch.int16, "valid_mask"), _ptr(npages, torch.int32, "npages"), _ptr(ws), _stream()),
-            "spin_score_select_resolve")
+        self._check(_call.spin_score_select_resolve(
+            self._ctx, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, sel, nsel, dir_, leaf_pool,
+            slots, page_ids, valid_mask, npages, ws), "spin_score_select_resolve")
 
     def copy_misses_host(self, batch, host_kv, host_row_base, nmiss, miss_pages, miss_slots, kv_pool,
                          copy_stream) -> int:
@@ -352,84 +333,50 @@ class Spin:
 
     def gather_misses(self, batch, host_kv, row_base, nmiss, miss_pages, miss_slots, kv_pool, ws):
         """host_kv: pinned CPU tensor (read by the kernel); the lists are DEVICE tensors."""
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
         if not host_kv.is_pinned():
             raise ValueError("host_kv must be pinned host memory")
-        self._check(self.lib.spin_gather_misses(
-            self.h, batch, host_kv.data_ptr(), _ptr(row_base, torch.int64, "row_base"),
-            _ptr(nmiss, torch.int32, "nmiss"), _ptr(miss_pages, torch.int32, "miss_pages"),
-            _ptr(miss_slots, torch.int32, "miss_slots"), _ptr(kv_pool), pool_slots, _ptr(ws), _stream()),
-            "spin_gather_misses")
+        self._check(_call.spin_gather_misses(
+            self._ctx, batch, host_kv.data_ptr(), row_base, nmiss, miss_pages, miss_slots, kv_pool,
+            ws), "spin_gather_misses")
 
     def offload_pages(self, batch, kv_pool, host_kv, row_base, count, pages, slots, ws):
         """host_kv: pinned CPU tensor (written by the kernel); the lists are DEVICE tensors."""
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
         if not host_kv.is_pinned():
             raise ValueError("host_kv must be pinned host memory")
-        self._check(self.lib.spin_offload_pages(
-            self.h, batch, _ptr(kv_pool), pool_slots, host_kv.data_ptr(), _ptr(row_base, torch.int64, "row_base"),
-            _ptr(count, torch.int32, "count"), _ptr(pages, torch.int32, "pages"),
-            _ptr(slots, torch.int32, "slots"), _ptr(ws), _stream()), "spin_offload_pages")
+        self._check(_call.spin_offload_pages(
+            self._ctx, batch, kv_pool, host_kv.data_ptr(), row_base, count, pages, slots, ws), "spin_offload_pages")
 
     def sparse_decode(self, batch, q, kv_pool, slots, valid_mask, npages, out, lse, ws):
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
-        self._check(self.lib.spin_sparse_decode(
-            self.h, batch, _ptr(q, torch.bfloat16, "q"), _ptr(kv_pool), pool_slots,
-            _ptr(slots, torch.int32, "slots"), _ptr(valid_mask, torch.int16, "valid_mask"),
-            _ptr(npages, torch.int32, "npages"), _ptr(out, torch.bfloat16, "out"),
-            _ptr(lse, torch.float32, "lse"), _ptr(ws), _stream()), "spin_sparse_decode")
+        self._check(_call.spin_sparse_decode(
+            self._ctx, batch, q, kv_pool, slots, valid_mask, npages, out, lse, ws), "spin_sparse_decode")
 
     def sparse_decode_static(self, batch, q, kv_pool, slots, valid_mask, npages, out, lse, status=None):
         """Stage 4 with the split-K scratch in the library's own device array (no workspace argument)."""
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
-        self._check(self.lib.spin_sparse_decode_static(
-            self.h, batch, _ptr(q, torch.bfloat16, "q"), _ptr(kv_pool), pool_slots,
-            _ptr(slots, torch.int32, "slots"), _ptr(valid_mask, torch.int16, "valid_mask"),
-            _ptr(npages, torch.int32, "npages"), _ptr(out, torch.bfloat16, "out"),
-            _ptr(lse, torch.float32, "lse"), _ptr(status, torch.int32, "status"), _stream()),
-            "spin_sparse_decode_static")
+        self._check(_call.spin_sparse_decode_static(
+            self._ctx, batch, q, kv_pool, slots, valid_mask, npages, out, lse, status), "spin_sparse_decode_static")
 
     def select_resolve_forced(self, batch, scores, part_offsets, seq_lens, sel, nsel, dir_, leaf_pool, slots, page_ids,
                               valid_mask, npages, q, kv_pool, ws):
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
-        self._check(self.lib.spin_select_resolve_forced(
-            self.h, batch, _ptr(scores, torch.float32, "scores"), _ptr(part_offsets, torch.int32, "part_offsets"),
-            _ptr(seq_lens, torch.int32, "seq_lens"), _ptr(sel, torch.int32, "sel"), _ptr(nsel, torch.int32, "nsel"),
-            _ptr(dir_, torch.int32, "dir"), _ptr(leaf_pool, torch.int32, "leaf_pool"), leaf_pool.shape[0],
-            _ptr(slots, torch.int32, "slots"), _ptr(page_ids, torch.int32, "page_ids"),
-            _ptr(valid_mask, torch.int16, "valid_mask"), _ptr(npages, torch.int32, "npages"),
-            _ptr(q, torch.bfloat16, "q"), _ptr(kv_pool), pool_slots, _ptr(ws), _stream()),
-            "spin_select_resolve_forced")
+        self._check(_call.spin_select_resolve_forced(
+            self._ctx, batch, scores, part_offsets, seq_lens, sel, nsel, dir_, leaf_pool, slots, page_ids,
+            valid_mask, npages, q, kv_pool, ws), "spin_select_resolve_forced")
 
     def sparse_decode_rest(self, batch, q, kv_pool, slots, valid_mask, npages, out, lse, ws):
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
-        self._check(self.lib.spin_sparse_decode_rest(
-            self.h, batch, _ptr(q, torch.bfloat16, "q"), _ptr(kv_pool), pool_slots,
-            _ptr(slots, torch.int32, "slots"), _ptr(valid_mask, torch.int16, "valid_mask"),
-            _ptr(npages, torch.int32, "npages"), _ptr(out, torch.bfloat16, "out"),
-            _ptr(lse, torch.float32, "lse"), _ptr(ws), _stream()), "spin_sparse_decode_rest")
+        self._check(_call.spin_sparse_decode_rest(
+            self._ctx, batch, q, kv_pool, slots, valid_mask, npages, out, lse, ws), "spin_sparse_decode_rest")
 
     def split_hits_misses(self, batch, page_ids, valid_mask, npages, miss_pages, nmiss, mask_hits, mask_misses):
-        self._check(self.lib.spin_split_hits_misses(
-            self.h, batch, _ptr(page_ids, torch.int32, "page_ids"), _ptr(valid_mask, torch.int16, "valid_mask"),
-            _ptr(npages, torch.int32, "npages"), _ptr(miss_pages, torch.int32, "miss_pages"),
-            _ptr(nmiss, torch.int32, "nmiss"), _ptr(mask_hits, torch.int16, "mask_hits"),
-            _ptr(mask_misses, torch.int16, "mask_misses"), _stream()), "spin_split_hits_misses")
+        self._check(_call.spin_split_hits_misses(
+            self._ctx, batch, page_ids, valid_mask, npages, miss_pages, nmiss, mask_hits,
+            mask_misses), "spin_split_hits_misses")
 
     def sparse_decode_begin(self, batch, q, kv_pool, slots, valid_mask, npages, ws):
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
-        self._check(self.lib.spin_sparse_decode_begin(
-            self.h, batch, _ptr(q, torch.bfloat16, "q"), _ptr(kv_pool), pool_slots, _ptr(slots, torch.int32, "slots"),
-            _ptr(valid_mask, torch.int16, "valid_mask"), _ptr(npages, torch.int32, "npages"), _ptr(ws), _stream()),
-            "spin_sparse_decode_begin")
+        self._check(_call.spin_sparse_decode_begin(
+            self._ctx, batch, q, kv_pool, slots, valid_mask, npages, ws), "spin_sparse_decode_begin")
 
     def sparse_decode_finish(self, batch, q, kv_pool, slots, valid_mask, npages, out, lse, ws):
-        pool_slots = kv_pool.numel() * kv_pool.element_size() // 8192
-        self._check(self.lib.spin_sparse_decode_finish(
-            self.h, batch, _ptr(q, torch.bfloat16, "q"), _ptr(kv_pool), pool_slots, _ptr(slots, torch.int32, "slots"),
-            _ptr(valid_mask, torch.int16, "valid_mask"), _ptr(npages, torch.int32, "npages"),
-            _ptr(out, torch.bfloat16, "out"), _ptr(lse, torch.float32, "lse"), _ptr(ws), _stream()),
-            "spin_sparse_decode_finish")
+        self._check(_call.spin_sparse_decode_finish(
+            self._ctx, batch, q, kv_pool, slots, valid_mask, npages, out, lse, ws), "spin_sparse_decode_finish")
 
     @property
     def forced_split_supported(self) -> bool:

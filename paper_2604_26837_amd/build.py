@@ -13,6 +13,9 @@ PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
 # SPIN_LIB_PATH lets a developer load an experimental build instead of the in-tree one
 LIB_PATH = os.environ.get("SPIN_LIB_PATH") or os.path.join(PKG_DIR, "libspin.so")
+# Python extension module: the stage calls with torch tensors as arguments (host code only)
+MODULE_SRC = os.path.join(PKG_DIR, "csrc", "spin_torch.cpp")
+MODULE_PATH = os.path.join(PKG_DIR, "_spin_torch.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -39,7 +42,29 @@ def build_library(verbose: bool = False) -> str:
     if verbose and err.strip():
         print(err, file=sys.stderr)
     os.replace(LIB_PATH + ".tmp", LIB_PATH)
+    build_module()
     return LIB_PATH
+
+
+def build_module() -> str:
+    """The extension module that takes torch tensors to the stage entry points."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"],
+           "-isystem", os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), MODULE_SRC,
+           "-L", os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+           "-o", MODULE_PATH + ".tmp"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("the extension module does not build:\n" + res.stderr)
+    os.replace(MODULE_PATH + ".tmp", MODULE_PATH)
+    return MODULE_PATH
 
 
 EXAMPLE_SRC = os.path.join(PKG_DIR, "examples", "one_step.cpp")
