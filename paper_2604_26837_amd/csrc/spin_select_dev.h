@@ -328,54 +328,71 @@ __device__ inline void emit_forced(const sel_plan &pl, int sel_stride, int32_t *
 
 // The windows of a row of at most BLOCK * KPT variable-length partitions, and its forced prefix and suffix
 // [0, nf_lo) and [first_hi, P).  Every thread holds the table entries of its KPT partitions, so one round of loads and
-// two barriers stand for four binary searches of a dozen dependent loads each.
+// two barriers stand for four binary searches of a dozen dependent loads each.  (With more than 16 per thread, which
+// the registers would not hold beside the scores, the entries are read where they are used.)
 template <int BLOCK, int KPT>
 __device__ inline spin_var_span block_var_span(const spin_var &var, size_t vbase, int row, int PP, int sink_pages,
                                                int recent_pages, int &nf_lo, int &first_hi) {
-  constexpr int NW = BLOCK / 64;
+  constexpr int NW = BLOCK / 64, HELD = KPT <= 16 ? KPT : 1;
   __shared__ int s_pages;
-  __shared__ uint2 s_cnt[NW];
+  __shared__ int4 s_cnt[NW];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c0 = threadIdx.x * KPT;
   spin_var_span w;
-  int start[KPT], tokens[KPT];
+  struct entry { int start, end; };
+  auto load = [&](int k) {                             // the tables are as long as the score array
+    entry e = {0, 0};
+    if (c0 + k < PP) {
+      e.start = var.first_page[vbase + c0 + k];
+      e.end = e.start + spin_var_npages(var, vbase, c0 + k);
+    }
+    return e;
+  };
+  entry held[HELD];
+  if (HELD == KPT) {
 #pragma unroll
-  for (int k = 0; k < KPT; ++k) {
-    const bool in = c0 + k < PP;                       // the tables are as long as the score array
-    start[k] = in ? var.first_page[vbase + c0 + k] : 0;
-    tokens[k] = in ? var.tokens[vbase + c0 + k] : 0;
+    for (int k = 0; k < HELD; ++k) held[k] = load(k);
   }
   w.P = min(min(max(var.count[row], 0), PP), BLOCK * KPT);
   if (w.P == 0 && threadIdx.x == 0) s_pages = 0;
+  if (HELD == KPT) {
 #pragma unroll
-  for (int k = 0; k < KPT; ++k)
-    if (c0 + k == w.P - 1) s_pages = start[k] + ((tokens[k] + 15) >> 4);
+    for (int k = 0; k < HELD; ++k)
+      if (c0 + k == w.P - 1) s_pages = held[k].end;
+  } else if (w.P > 0 && (w.P - 1) / KPT == (int)threadIdx.x) {
+    s_pages = load((w.P - 1) % KPT).end;
+  }
   __syncthreads();
   w.pages = s_pages;
   spin_var_windows(w, sink_pages, recent_pages);
-  // partitions that end by sink_end | start before it, start before recent_begin | at or before it; two counts to a
-  // word (at most 16384 each)
-  uint32_t lo = 0, hi = 0;
+  // partitions that end by sink_end, start before it, start before recent_begin, start at or before it
+  int4 n = make_int4(0, 0, 0, 0);
 #pragma unroll
   for (int k = 0; k < KPT; ++k)
     if (c0 + k < w.P) {
-      const int end = start[k] + ((tokens[k] + 15) >> 4);
-      lo += (end <= w.sink_end ? 1u : 0u) + (start[k] < w.sink_end ? 0x10000u : 0u);
-      hi += (start[k] < w.recent_begin ? 1u : 0u) + (start[k] <= w.recent_begin ? 0x10000u : 0u);
+      const entry e = HELD == KPT ? held[k < HELD ? k : 0] : load(k);
+      n.x += e.end <= w.sink_end;
+      n.y += e.start < w.sink_end;
+      n.z += e.start < w.recent_begin;
+      n.w += e.start <= w.recent_begin;
     }
-  lo = (uint32_t)spin_wave_inclusive_scan((int)lo);
-  hi = (uint32_t)spin_wave_inclusive_scan((int)hi);
-  if (lane == 63) s_cnt[wave] = make_uint2(lo, hi);
+  n.x = spin_wave_inclusive_scan(n.x);
+  n.y = spin_wave_inclusive_scan(n.y);
+  n.z = spin_wave_inclusive_scan(n.z);
+  n.w = spin_wave_inclusive_scan(n.w);
+  if (lane == 63) s_cnt[wave] = n;
   __syncthreads();
-  lo = hi = 0;
+  n = make_int4(0, 0, 0, 0);
 #pragma unroll
   for (int i = 0; i < NW; ++i) {
-    lo += s_cnt[i].x;
-    hi += s_cnt[i].y;
+    n.x += s_cnt[i].x;
+    n.y += s_cnt[i].y;
+    n.z += s_cnt[i].z;
+    n.w += s_cnt[i].w;
   }
-  nf_lo = (int)(lo & 0xffffu);
-  w.at_sink = (int)(lo >> 16) - 1;
-  first_hi = (int)(hi & 0xffffu);
-  w.at_recent = (int)(hi >> 16) - 1;
+  nf_lo = n.x;
+  w.at_sink = n.y - 1;
+  first_hi = n.z;
+  w.at_recent = n.w - 1;
   return w;
 }
 

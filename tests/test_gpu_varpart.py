@@ -146,7 +146,7 @@ def test_uniform_tables_give_the_uniform_results():
 @pytest.mark.parametrize("fused", [False, True])
 @pytest.mark.parametrize("pages,topk,largest,sink,recent", [
     (2500, 24, 256, 4, 16), (5000, 700, 64, 3, 1), (9000, 1100, 32, 0, 9), (4100, 5, 256, 40, 70), (16000, 520, 16, 1, 1),
-    (30, 3, 256, 20, 9), (40, 3, 256, 0, 0)])
+    (30, 3, 256, 20, 9), (40, 3, 256, 0, 0), (20000, 9, 32, 7, 3), (65536, 40, 16, 0, 0)])
 def test_windows_and_page_lists_of_long_rows(pages, topk, largest, sink, recent, fused):
     """Stages 2 and 3 alone on rows of every register width, more selected partitions than one round of threads, and
     windows that straddle a partition: whole numbers, so the lists must be the oracle's."""
@@ -166,6 +166,8 @@ def test_windows_and_page_lists_of_long_rows(pages, topk, largest, sink, recent,
     layer = runner.LayerState(w, slot_of, pool, layouts=layouts)
     layer.scores.copy_(torch.from_numpy(rng.integers(0, 300, layer.scores.numel()).astype(np.float32)))   # many ties
     sp = layer.spin
+    if fused and sp.cfg.max_context > 16 * 16384:
+        pytest.skip("stages 2+3 in one launch take rows of at most 16384 variable-length partitions")
     if fused:
         sp.select_resolve(w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.dir,
                           layer.leaf_pool, layer.slots, layer.page_ids, layer.valid_mask, layer.npages, layer.ws)
