@@ -239,6 +239,20 @@ __device__ inline int spin_wave_inclusive_scan(int v) {
   const int row = (threadIdx.x & 63) >> 4;
   return v + (row >= 1 ? t0 : 0) + (row >= 2 ? t1 : 0) + (row >= 3 ? t2 : 0);
 }
+// One word per wavefront of a workgroup, lane l % NW holding wavefront l's (NW: 4, 8 or 16): the sum over the
+// wavefronts before `wave` (uniform), and over all of them.  A scan over lanes instead of NW additions, since every
+// wavefront does this for itself and an instruction on all of a 1024-thread workgroup's takes its compute unit 6.7 ns.
+template <int NW>
+__device__ inline int spin_waves_before(int v, int wave, int &total) {
+  static_assert(NW == 4 || NW == 8 || NW == 16, "one row of 16 lanes");
+  int inc = v;
+  inc += spin_dpp_i<0x111>(inc);               // row_shr:1
+  inc += spin_dpp_i<0x112>(inc);               // row_shr:2
+  if (NW > 4) inc += spin_dpp_i<0x114>(inc);   // row_shr:4
+  if (NW > 8) inc += spin_dpp_i<0x118>(inc);   // row_shr:8
+  total = __builtin_amdgcn_readlane(inc, NW - 1);
+  return __builtin_amdgcn_readlane(inc - v, wave);
+}
 // maximum / minimum of an unsigned word over the wavefront, result uniform
 __device__ inline uint32_t spin_wave_max_u32(uint32_t v) {
   v = max(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, SPIN_DPP_XOR1, 0xf, 0xf, false));

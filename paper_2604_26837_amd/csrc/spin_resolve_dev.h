@@ -6,20 +6,12 @@
 template <int RES_BLOCK>
 __device__ inline int res_block_exclusive_scan(int v, int *s_wave, int &total) {
   constexpr int RES_WAVES = RES_BLOCK / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int inc = spin_wave_inclusive_scan(v);
   __syncthreads();
   if (lane == 63) s_wave[wave] = inc;
   __syncthreads();
-  int off = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < RES_WAVES; ++w) {
-    const int x = s_wave[w];
-    if (w < wave) off += x;
-    tot += x;
-  }
-  total = tot;
-  return off + inc - v;
+  return spin_waves_before<RES_WAVES>(s_wave[lane % RES_WAVES], wave, total) + inc - v;
 }
 
 __device__ inline uint32_t page_mask(int page, int N) {

@@ -190,6 +190,8 @@ __global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
   constexpr int CAP = 4096;
   __shared__ tiles_lds<BLOCK, CAP> s;
   const int row = blockIdx.x;
+  float4 mine[MPT / 4];
+  load_tile_maxima<MPT>(mine, maxima + (size_t)row * max_stride, max_stride);
   const int b = row / Hkv, h = row - b * Hkv;
   const int PP = part_offsets[b + 1] - part_offsets[b];
   const float *rs = scores + (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
@@ -198,8 +200,7 @@ __global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
   emit_forced<BLOCK>(pl, sel_stride, rsel, nsel, row);
   if (pl.kprime > 0 &&
       ((pl.P >> gs_log) > min(max_stride, BLOCK * MPT) ||
-       !select_by_tile_maxima<BLOCK, MPT, CAP>(rs, maxima + (size_t)row * max_stride, max_stride, gs_log, pl,
-                                               sel_stride, rsel, s))) {
+       !select_by_tile_maxima<BLOCK, MPT, CAP>(rs, mine, gs_log, pl, sel_stride, rsel, s))) {
     __syncthreads();
     select_generic_row<BLOCK>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
                               recent_pages, sel_stride, sel, nsel, row);

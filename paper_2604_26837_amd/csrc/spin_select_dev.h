@@ -65,9 +65,9 @@ __device__ inline typename key_bits<KPT>::type range_bits(int c0, int a, int b) 
 // Lane handles digits 255-4*lane .. 252-4*lane, in descending order.
 __device__ inline int digit_of_rank(const int *hist, int &rank, int &in_digit) {
   const int lane = threadIdx.x & 63;
-  int hv[4], local = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) { hv[j] = hist[255 - 4 * lane - j]; local += hv[j]; }
+  const int4 bins = *(const int4 *)(hist + 252 - 4 * lane);
+  const int hv[4] = {bins.w, bins.z, bins.y, bins.x};
+  const int local = (hv[0] + hv[1]) + (hv[2] + hv[3]);
   int running = spin_wave_inclusive_scan(local) - local;
   int my_digit = -1, my_rem = 0, my_cnt = 0;
 #pragma unroll
@@ -89,7 +89,7 @@ __device__ inline int digit_of_rank(const int *hist, int &rank, int &in_digit) {
 
 template <int BLOCK>
 struct kth_lds {
-  int hist[4][256];   // one histogram per digit: no buffer is cleared while others read it
+  alignas(16) int hist[4][256];   // one histogram per digit: no buffer is cleared while others read it
   uint32_t wmax[BLOCK / 64], wmin[BLOCK / 64];
 };
 
@@ -116,8 +116,8 @@ __device__ inline void block_kth(const uint32_t (&key)[KPT], typename key_bits<K
   kmn = spin_wave_min_u32(kmn);
   if (lane == 0) { s.wmax[wave] = kmx; s.wmin[wave] = kmn; }
   __syncthreads();
-#pragma unroll
-  for (int w = 0; w < NW; ++w) { kmx = max(kmx, s.wmax[w]); kmn = min(kmn, s.wmin[w]); }
+  kmx = spin_wave_max_u32(s.wmax[lane % NW]);
+  kmn = spin_wave_min_u32(s.wmin[lane % NW]);
   int hi = kmx == kmn ? 0 : 32 - __clz((int)(kmx ^ kmn));   // the low `hi` bits are the ones that vary
   uint32_t prefix = hi < 32 ? kmx >> hi : 0u;
   int remaining = k;
@@ -163,22 +163,22 @@ __device__ inline M first_bits(M eq, unsigned quota) {
 }
 
 // Turns every thread's `sure` bits (taken) and `eq` bits (taken while fewer than need_eq of them precede) into
-// its final pick mask and the output position of its first pick (positions follow thread, then bit order).
+// its final pick mask and the output position of its first pick (positions follow thread, then bit order); `picked`:
+// all threads' picks, `eq_picked`: those of equal keys.
 template <int BLOCK, typename M>
-__device__ inline M ordered_picks(M sure, M eq, unsigned need_eq, unsigned long long *s_wtot, int &pos) {
+__device__ inline M ordered_picks(M sure, M eq, unsigned need_eq, uint2 *s_wtot, int &pos, int &picked, int &eq_picked) {
   constexpr int NW = BLOCK / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_sure = popc_bits(sure), n_eq = popc_bits(eq);
-  // the two counts never carry into one another: scanned separately, passed on in one word
-  const uint32_t i_sure = (uint32_t)spin_wave_inclusive_scan(n_sure), i_eq = (uint32_t)spin_wave_inclusive_scan(n_eq);
-  if (lane == 63) s_wtot[wave] = (unsigned long long)i_sure | ((unsigned long long)i_eq << 32);
+  const int i_sure = spin_wave_inclusive_scan(n_sure), i_eq = spin_wave_inclusive_scan(n_eq);
+  if (lane == 63) s_wtot[wave] = make_uint2((uint32_t)i_sure, (uint32_t)i_eq);
   __syncthreads();
-  unsigned sure_before = i_sure - n_sure, eq_before = i_eq - n_eq;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    const unsigned long long t = s_wtot[w];
-    if (w < wave) { sure_before += (uint32_t)t; eq_before += (uint32_t)(t >> 32); }
-  }
+  const uint2 t = s_wtot[lane % NW];
+  int all_sure, all_eq;
+  const unsigned sure_before = (unsigned)(spin_waves_before<NW>((int)t.x, wave, all_sure) + i_sure - n_sure);
+  const unsigned eq_before = (unsigned)(spin_waves_before<NW>((int)t.y, wave, all_eq) + i_eq - n_eq);
+  eq_picked = (int)min((unsigned)all_eq, need_eq);
+  picked = all_sure + eq_picked;
   pos = (int)(sure_before + min(eq_before, need_eq));
   return sure | first_bits(eq, need_eq > eq_before ? need_eq - eq_before : 0u);
 }
@@ -197,7 +197,7 @@ __device__ inline float key_floor_score(uint32_t K, bool low_end) {
 template <int BLOCK, int CAP>
 struct elements_lds {
   kth_lds<BLOCK> kth;
-  unsigned long long wtot[BLOCK / 64];
+  uint2 wtot[BLOCK / 64];
   uint32_t key[CAP > 0 ? CAP : 1];
   int32_t id[CAP > 0 ? CAP : 1];
 };
@@ -222,8 +222,8 @@ __device__ inline void pick_from_list(int total, int kprime, int first, int sel_
       gt |= key[j] > T ? 1u << j : 0u;
       eq |= key[j] == T ? 1u << j : 0u;
     }
-    int pos;
-    uint32_t pick = ordered_picks<BLOCK>(gt & have, eq & have, need_eq, s.wtot, pos);
+    int pos, picked, eq_picked;
+    uint32_t pick = ordered_picks<BLOCK>(gt & have, eq & have, need_eq, s.wtot, pos, picked, eq_picked);
     pos += first;
 #pragma unroll
     for (int j = 0; j < E; ++j)
@@ -253,7 +253,7 @@ __device__ inline void select_elements(const float (&f)[KPT], typename key_bits<
                                        elements_lds<BLOCK, CAP> &s, ID id) {
   typedef typename key_bits<KPT>::type M;
   [[maybe_unused]] constexpr int NW = BLOCK / 64;
-  [[maybe_unused]] const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  [[maybe_unused]] const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   M valid = cand;
   if (bound > SPIN_KEY_MINUS_INF) {            // (at -inf NaN scores, which rank there, would fail the comparison)
     const float bf = key_floor_score(bound, true);
@@ -268,15 +268,10 @@ __device__ inline void select_elements(const float (&f)[KPT], typename key_bits<
     // ordered list of the candidates left
     const int mine = popc_bits(valid);
     const int inc = spin_wave_inclusive_scan(mine);
-    if (lane == 63) s.wtot[wave] = (unsigned)inc;
+    if (lane == 63) s.wtot[wave].x = (unsigned)inc;
     __syncthreads();
-    int before = inc - mine, total = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      const int t = (int)s.wtot[w];
-      if (w < wave) before += t;
-      total += t;
-    }
+    int total;
+    const int before = spin_waves_before<NW>((int)s.wtot[lane % NW].x, wave, total) + inc - mine;
     if (total <= CAP) {                          // block-uniform
       if (valid) {
         int pos = before;
@@ -303,8 +298,8 @@ __device__ inline void select_elements(const float (&f)[KPT], typename key_bits<
     gt |= key[k] > T ? (M)1 << k : (M)0;
     eq |= key[k] == T ? (M)1 << k : (M)0;
   }
-  int pos;
-  const M pick = ordered_picks<BLOCK>((M)(gt & valid), (M)(eq & valid), need_eq, s.wtot, pos);
+  int pos, picked, eq_picked;
+  const M pick = ordered_picks<BLOCK>((M)(gt & valid), (M)(eq & valid), need_eq, s.wtot, pos, picked, eq_picked);
   pos += first;
 #pragma unroll
   for (int k = 0; k < KPT; ++k)
@@ -487,26 +482,32 @@ struct tiles_lds : elements_lds<BLOCK, CAP> {
 // Stores the kprime best candidates ascending at rsel[nf_lo ..].  A row with fewer than k' tiles reads them all; where
 // more scores reach the bound than the list holds, the search and the selection re-read them per pass instead.
 // False (for the whole workgroup, nothing stored): k' beyond what the tile list holds.
+// `maxima`: the calling thread's MPT of the row (load_tile_maxima, whose loads need not wait for the row's plan).
+template <int MPT>
+__device__ inline void load_tile_maxima(float4 (&v)[MPT / 4], const float *__restrict__ maxima, int maxima_stride) {
+  const int m0 = threadIdx.x * MPT;
+#pragma unroll
+  for (int j = 0; j < MPT / 4; ++j)                    // the stride is a multiple of 4
+    v[j] = m0 + 4 * j < maxima_stride ? *(const float4 *)(maxima + m0 + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
+}
 template <int BLOCK, int MPT, int CAP>
-__device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const float *__restrict__ maxima,
-                                             int maxima_stride, int gs_log, const sel_plan &pl, int sel_stride,
-                                             int32_t *__restrict__ rsel, tiles_lds<BLOCK, CAP> &s) {
+__device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const float4 (&maxima)[MPT / 4], int gs_log,
+                                             const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
+                                             tiles_lds<BLOCK, CAP> &s) {
   constexpr int NW = BLOCK / 64;
   typedef typename key_bits<MPT>::type M;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gs = 1 << gs_log, kprime = pl.kprime;
   if (kprime + (kprime >> 3) + 2 > TILE_LIST) return false;                       // block-uniform
   const int t_lo = (pl.nf_lo + gs - 1) >> gs_log, t_hi = pl.first_hi >> gs_log;   // tiles of candidates only
   const int m0 = tid * MPT;
   uint32_t top[MPT];
 #pragma unroll
-  for (int j = 0; j < MPT; j += 4) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (m0 + j < maxima_stride) v = *(const float4 *)(maxima + m0 + j);   // the stride is a multiple of 4
-    top[j] = score_key(v.x);
-    top[j + 1] = score_key(v.y);
-    top[j + 2] = score_key(v.z);
-    top[j + 3] = score_key(v.w);
+  for (int j = 0; j < MPT / 4; ++j) {
+    top[4 * j] = score_key(maxima[j].x);
+    top[4 * j + 1] = score_key(maxima[j].y);
+    top[4 * j + 2] = score_key(maxima[j].z);
+    top[4 * j + 3] = score_key(maxima[j].w);
   }
   const M cand = range_bits<MPT>(m0, t_lo, t_hi);
   uint32_t T0 = 0;
@@ -521,15 +522,9 @@ __device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const
     gt |= top[j] > T0 ? (M)1 << j : (M)0;
     eq |= top[j] == T0 ? (M)1 << j : (M)0;
   }
-  int pos;
-  M pick = ordered_picks<BLOCK>((M)(gt & cand), (M)(eq & cand), need_eq, s.wtot, pos);
-  unsigned n_gt = 0, n_eq = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    n_gt += (uint32_t)s.wtot[w];
-    n_eq += (uint32_t)(s.wtot[w] >> 32);
-  }
-  int ntiles = has_lo + (int)(n_gt + min(n_eq, need_eq));
+  int pos, ntiles, eq_tiles;
+  M pick = ordered_picks<BLOCK>((M)(gt & cand), (M)(eq & cand), need_eq, s.wtot, pos, ntiles, eq_tiles);
+  ntiles += has_lo;
   pos += has_lo;
   while (pick) {
     const int j = ffs_bits(pick) - 1;
@@ -593,15 +588,11 @@ __device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const
         at[j] = wave_total + (int)((inc[j / 2] >> sh) & 0xffffu) - __popc(keep[j]);
         wave_total += (int)(((uint32_t)__builtin_amdgcn_readlane((int)inc[j / 2], 63) >> sh) & 0xffffu);
       }
-      if (lane == 0) s.wtot[wave] = (unsigned)wave_total;
+      if (lane == 0) s.wtot[wave].x = (unsigned)wave_total;
       __syncthreads();
-      int before = total;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const int t = (int)s.wtot[w];
-        if (w < wave) before += t;
-        total += t;
-      }
+      int round_total;
+      const int before = total + spin_waves_before<NW>((int)s.wtot[lane % NW].x, wave, round_total);
+      total += round_total;
       if (total > CAP) return;                         // block-uniform
 #pragma unroll
       for (int j = 0; j < V; ++j) {
@@ -619,7 +610,9 @@ __device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const
       __syncthreads();                                 // the list is whole, and s.wtot may be written again
     }
   };
-  if (nquads <= BLOCK * 2) gather(std::integral_constant<int, 2>());
+  // loads per lane: a quad that is not there costs as many instructions as one that is
+  if (nquads <= BLOCK * 3) gather(std::integral_constant<int, 3>());
+  else if (nquads <= BLOCK * 5) gather(std::integral_constant<int, 5>());
   else gather(std::integral_constant<int, 8>());
   if (total <= CAP) {
     pick_from_list<BLOCK, CAP>(total, kprime, pl.nf_lo, sel_stride, rsel, s);
@@ -666,8 +659,8 @@ __device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const
       equal |= k == prefix ? 1u << e : 0u;
     }
     __syncthreads();
-    int at;
-    const uint32_t taken = ordered_picks<BLOCK>(above & keep, equal & keep, quota, s.wtot, at);
+    int at, picked, eq_picked;
+    const uint32_t taken = ordered_picks<BLOCK>(above & keep, equal & keep, quota, s.wtot, at, picked, eq_picked);
     at += first;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
@@ -675,15 +668,8 @@ __device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const
         if (at < sel_stride) rsel[at] = p + e;
         ++at;
       }
-    unsigned sure = 0, eqs = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      sure += (uint32_t)s.wtot[w];
-      eqs += (uint32_t)(s.wtot[w] >> 32);
-    }
-    eqs = min(eqs, quota);
-    first += (int)(sure + eqs);
-    quota -= eqs;
+    first += picked;
+    quota -= (unsigned)eq_picked;
   }
   return true;
 }
