@@ -91,6 +91,7 @@ template <int BLOCK>
 struct kth_lds {
   alignas(16) int hist[4][256];   // one histogram per digit: no buffer is cleared while others read it
   uint32_t wmax[BLOCK / 64], wmin[BLOCK / 64];
+  alignas(16) int4 found[4];
 };
 
 // Radix select over the workgroup's valid keys, most significant digit first: finds the threshold T and the
@@ -131,8 +132,20 @@ __device__ inline void block_kth(const uint32_t (&key)[KPT], typename key_bits<K
       if (((valid >> j) & 1u) && (pass == 0 || (key[j] >> hi) == prefix))
         atomicAdd(&s.hist[pass][(key[j] >> lo) & dmask], 1);
     __syncthreads();
-    int in_digit = 0;
-    const int digit = digit_of_rank(s.hist[pass], remaining, in_digit);
+    int in_digit = 0, digit;
+    if (BLOCK >= 1024) {
+      if (wave == 0) {
+        digit = digit_of_rank(s.hist[pass], remaining, in_digit);
+        if (lane == 0) s.found[pass] = make_int4(digit, remaining, in_digit, 0);
+      }
+      __syncthreads();
+      const int4 f = s.found[pass];
+      digit = __builtin_amdgcn_readfirstlane(f.x);
+      remaining = __builtin_amdgcn_readfirstlane(f.y);
+      in_digit = __builtin_amdgcn_readfirstlane(f.z);
+    } else {
+      digit = digit_of_rank(s.hist[pass], remaining, in_digit);
+    }
     if (digit < 0) break;                                // fewer than k valid keys: not a call this function takes
     prefix = (prefix << width) | (uint32_t)digit;
     hi = lo;
