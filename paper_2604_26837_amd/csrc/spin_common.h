@@ -136,6 +136,16 @@ __device__ inline float spin_dev_load(const float *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// two floats at an address that is a multiple of 8, in one access
+__device__ inline void spin_dev_store2(float *p, float2 v) {
+  __hip_atomic_store((unsigned long long *)p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline float2 spin_dev_load2(const float *p) {
+  return __builtin_bit_cast(float2, __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT));
+}
+
 // 16-byte load marked non-temporal (streamed once, not worth keeping in cache)
 typedef __attribute__((ext_vector_type(4))) unsigned int spin_u32x4;
 __device__ inline uint4 spin_nt_load(const uint4 *p) {

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_tokens_kernel(
     const int32_t *__restrict__ npages, int page_stride, int G, int Hq, int Hkv, int nsplit, int pstride,
     const int32_t *__restrict__ skip, float scale_log2e, float *part_ml, float *part_acc, int32_t *tickets,
     uint16_t *__restrict__ out, float *__restrict__ lse, int32_t *status) {
-  extern __shared__ float smem[];
+  extern __shared__ __align__(16) float smem[];
   // the token lists live behind the merge buffers of decode_finish
   uint32_t *tok = (uint32_t *)(smem + WAVES * G * (SPIN_HEAD_DIM + 2)) + (threadIdx.x >> 6) * TOK_LIST;
 
