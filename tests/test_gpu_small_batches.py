@@ -1,0 +1,48 @@
+"""Stage 4's split-K factor follows the batch of the call: a context sized for many requests gives the same lists and,
+to the tolerance of a bf16 output of two summation orders, the same attention for any batch, in every form of the
+stage (plain, after the always-attended pages, in two passes, with the static scratch)."""
+import pytest
+import torch
+
+from paper_2604_26837_amd import runner, synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("batch,max_batch,heads,kv,topk,tp", [(1, 16, 8, 2, 32, 16), (3, 16, 32, 8, 64, 16), (1, 1, 16, 1, 200, 16),
+                                                              (2, 40, 128, 8, 40, 16), (2, 9, 8, 2, 6, 128), (5, 5, 8, 8, 9, 16)])
+def test_any_batch_of_a_larger_context(batch, max_batch, heads, kv, topk, tp):
+    w = synth.config0().with_(seq_lens=tuple(4003 + 517 * b for b in range(batch)), num_q_heads=heads, num_kv_heads=kv,
+                              topk=topk, partition_tokens=tp, sink_pages=2, recent_pages=5, topk_includes_forced=tp == 16,
+                              name="small_batch")
+    one, _ = runner.build_device_layer(w, decode_splits=1)
+    many, _ = runner.build_device_layer(w, max_batch=max_batch)
+    one.step(one.q0)
+    want = one.out.float()
+
+    def check(out):
+        torch.cuda.synchronize()
+        assert many.status() == 0
+        # probabilities are rounded to bf16 (2^-9) before they meet the values, the output once more: two orders of
+        # the same sum differ by a few units of the last place of the largest term
+        assert (out.float() - want).abs().max() <= 2 ** -6 * want.abs().max()
+        assert torch.equal(many.slots, one.slots) and torch.equal(many.npages, one.npages)
+
+    sp, args = many.spin, (w.batch, many.q0, many.kv_pool, many.slots, many.valid_mask, many.npages)
+    for form in (many.step, many.step_fused, many.step_fused):       # (twice: the tickets are left cleared)
+        many.out.zero_()
+        form(many.q0)
+        check(many.out)
+    sp.sparse_decode(*args, many.out, many.lse, many.ws)
+    plain = many.out.clone()
+    check(plain)
+    static = torch.zeros_like(plain)
+    sp.sparse_decode_static(*args, static, None)
+    check(static)
+    assert torch.equal(static, plain)
+    first = many.valid_mask.clone()
+    first[:, 1::2] = 0
+    sp.sparse_decode_begin(*args[:4], first, many.npages, many.ws)
+    sp.sparse_decode_finish(*args[:4], many.valid_mask - first, many.npages, many.out, many.lse, many.ws)
+    check(many.out)
