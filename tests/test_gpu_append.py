@@ -49,6 +49,20 @@ def test_append_tokens(kind):
     _check_append(w, start)
 
 
+@pytest.mark.parametrize("tp,reps,start,final", [
+    (128, 1, (125, 190), (131, 257)),       # a whole partition: eight pages, two rounds of four
+    (80, 1, (60, 78), (97, 162)),           # five pages: a round with one page left
+    (1024, 2, (500,), (530,)),              # a second representative that starts on page 32
+    (2048, 1, (1005, 2040), (1042, 2052)),  # more pages than a wavefront has lanes
+])
+def test_append_pages_of_a_representative(tp, reps, start, final):
+    """The keys of a representative's pages are read four pages at a time, the page table one page per lane."""
+    w = synth.config0().with_(seq_lens=final, num_q_heads=8, num_kv_heads=2, partition_tokens=tp, reps_per_partition=reps,
+                              score_kind=synth.SCORE_REPMAX, topk=2, topk_includes_forced=False, sink_pages=1,
+                              recent_pages=1, block_mean_std=0.5, name="append_pages")
+    _check_append(w, start)
+
+
 @pytest.mark.parametrize("seed", range(16))
 def test_append_random_workloads(seed):
     """Summary kind, partition size (down to single tokens: token-major slots), representative count,
