@@ -141,7 +141,7 @@ int32_t spin_sel_stride(const spin_ctx *ctx);     /* entries per row of `sel` */
 int32_t spin_page_stride(const spin_ctx *ctx);    /* entries per row of slots / page_ids / valid_mask */
 int32_t spin_dir_stride(const spin_ctx *ctx);     /* entries per row of `dir` */
 int32_t spin_decode_splits(const spin_ctx *ctx);  /* the split-K factor of a call with max_batch requests; with
-                                                     decode_splits = 0 a smaller batch gets up to 8 */
+                                                     decode_splits = 0 a smaller batch may get more */
 /* bytes of the summary array for `padded_partitions` = part_offsets[batch] */
 size_t spin_summary_bytes(const spin_ctx *ctx, int64_t padded_partitions);
 

@@ -86,7 +86,10 @@ static inline bool spin_forced_split_supported(const spin_ctx *ctx) { return ctx
 
 // Split-K factor of stage 4 for a launch of `rows` rows: about one workgroup on each of the 256 compute units, all
 // resident at once; at least one page per wavefront (four, where partitions are smaller than a page and a tile is
-// gathered from 16 of them); and at most as many partials as the row's last workgroup asks for at once.
+// gathered from 16 of them); and at most as many partials as the row's last workgroup asks for at once, unless the rows
+// are so long that half as many again leave four pages per wavefront: then one workgroup's share of the pages takes
+// longer than the merge's further rounds (steps: 2 rows of 580 pages in blocks 25.9 us, 8 rows of 1036 pages in
+// clusters 33.5).
 // A row's pages cross one compute unit at 45 GB/s, so that few rows want many splits although every one lengthens the
 // merge.  Measured, splits 1 / 2 / 4 / 6 / 8 / 12 / 16: 2 rows of 32 pages 7.6 / 7.4 / 7.0 / 6.9 / 6.9 / 9.1 / 9.8 us,
 // 24 rows of 64 pages 12.1 / 10.5 / 9.5 / 9.2 / 9.2 / 14.7 / 18.0, 8 rows of 128 pages 21.8 / 15.4 / 10.8 / 9.5 / 9.2 / 11.0 / 11.9.
@@ -95,9 +98,11 @@ static inline int32_t spin_splits_for(const spin_ctx *x, int32_t rows) {
   int32_t splits = x->cfg.decode_splits;
   if (splits == 0) {
     const int32_t pages = x->page_stride / ((x->k_token_major ? 4 : 1) * x->waves);
+    const int32_t four_pages = x->page_stride / (4 * x->waves);
+    const int32_t most = four_pages >= SPIN_MERGE_AT_ONCE * 3 / 2 ? four_pages
+                         : pages < SPIN_MERGE_AT_ONCE ? pages : SPIN_MERGE_AT_ONCE;
     splits = 256 / rows;
-    if (splits > pages) splits = pages;
-    if (splits > SPIN_MERGE_AT_ONCE) splits = SPIN_MERGE_AT_ONCE;
+    if (splits > most) splits = most;
     if (splits < 1) splits = 1;
   }
   return splits > 64 ? 64 : splits;
