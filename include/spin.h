@@ -140,8 +140,7 @@ size_t spin_workspace_bytes(const spin_ctx *ctx); /* DEVICE scratch, 256-byte al
 int32_t spin_sel_stride(const spin_ctx *ctx);     /* entries per row of `sel` */
 int32_t spin_page_stride(const spin_ctx *ctx);    /* entries per row of slots / page_ids / valid_mask */
 int32_t spin_dir_stride(const spin_ctx *ctx);     /* entries per row of `dir` */
-int32_t spin_decode_splits(const spin_ctx *ctx);  /* the split-K factor of a call with max_batch requests; with
-                                                     decode_splits = 0 a smaller batch may get more */
+int32_t spin_decode_splits(const spin_ctx *ctx);  /* the split-K factor in use, whatever a call's batch */
 /* bytes of the summary array for `padded_partitions` = part_offsets[batch] */
 size_t spin_summary_bytes(const spin_ctx *ctx, int64_t padded_partitions);
 
@@ -442,7 +441,8 @@ int spin_offload_pages(spin_ctx *ctx, int32_t batch, const void *kv_pool, int64_
 /* Stage 4.  out[b][hq] (DEVICE bf16 [batch][num_q_heads][128]) =
  * softmax(scale * q K_S^T) V_S over the tokens whose mask bit is set in the
  * row's resolved pages; fp32 online softmax, split over the page list and
- * merged in a fixed order.  lse (DEVICE fp32 [batch][num_q_heads], natural log;
+ * merged in a fixed order (a request's bits do not depend on the others of the
+ * call).  lse (DEVICE fp32 [batch][num_q_heads], natural log;
  * may be NULL).  A row with no valid token gives out = 0, lse = -inf.
  * Only the bytes of attended tokens are fetched: a page with a partial mask
  * loads the K rows and V quads its mask names; with partition_tokens < 16
@@ -483,13 +483,10 @@ int spin_sparse_decode_finish(spin_ctx *ctx, int32_t batch, const void *q, const
  * clearing kernel plus the attention kernel on `stream`.  The array's device address is looked
  * up once per device: by spin_create for the device that is current then, otherwise by the
  * first call on that device.
- * A shape is taken if 256 + 4 * rows + 8 * P + 512 * P bytes (each term rounded up to 256) fit the
- * array, with rows = batch * num_kv_heads, P = rows * (n + m) * (num_q_heads / num_kv_heads), n =
- * decode_splits or, where that is 0, min(256 / (max_batch * num_kv_heads), spin_page_stride / (4 *
- * decode_waves)), at least 1, and m = 1 (or one per 16 always-attended pages, up to n, where
- * spin_select_resolve_forced applies); a larger shape returns SPIN_ERR_STATIC_LIMIT before anything
- * is launched.  (Where decode_splits is 0 and the splits of spin_sparse_decode need more than the array
- * holds, fewer are used, and the output may differ from spin_sparse_decode's in the last bit.)
+ * A call needs 256 + 4 * rows + 8 * P + 512 * P bytes of it (each term rounded up to 256), with
+ * rows = batch * num_kv_heads and P = rows * (2 * spin_decode_splits(ctx)) * (num_q_heads /
+ * num_kv_heads) at most (the workspace's layout of partials is kept); a larger shape returns
+ * SPIN_ERR_STATIC_LIMIT before anything is launched.
  * status (DEVICE int32, may be NULL): receives the first device-detected fault (a slot id
  * outside the pool: SPIN_ERR_SLOT_RANGE) if it held 0 before; the caller clears and reads it.
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different

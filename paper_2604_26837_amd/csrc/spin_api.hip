@@ -87,7 +87,17 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   // partitions smaller than a page: most pages are fetched in part (a few KiB), so a wavefront
   // keeps two pages in flight instead of one (measured: 53 -> 42 us on 64 rows x 65536 tokens)
   x->depth = c->decode_depth ? c->decode_depth : (tp < 16 ? 3 : 2);
-  x->splits = spin_splits_for(x, x->max_rows);
+  int32_t splits = c->decode_splits;
+  if (splits == 0) {
+    // about one 8-wave workgroup on each of the 256 compute units, all resident
+    // at once, and at least four pages per wavefront (measured best on MI355X)
+    splits = 256 / x->max_rows;
+    int32_t cap = x->page_stride / (4 * x->waves);
+    if (splits > cap) splits = cap;
+    if (splits < 1) splits = 1;
+  }
+  if (splits > 64) splits = 64;
+  x->splits = splits;
   x->scale = c->softmax_scale > 0.f ? c->softmax_scale : 1.0f / sqrtf((float)c->head_dim);
   // the always-attended pages beside stages 2+3: about 16 pages per side workgroup, at most one per split
   // (each leaves a partial that one split's first wavefront starts from)
@@ -96,26 +106,9 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   if (c->lru_timestamps == 0 && tp >= SPIN_PAGE_TOKENS && !c->variable_partitions && x->max_parts <= 4096 &&
       forced_pages >= 1 && forced_pages <= 1024) {
     int32_t s_wgs = (forced_pages + 15) / 16;
-    x->side_wgs = s_wgs > x->splits ? x->splits : s_wgs;   // (a smaller batch has no fewer splits)
+    x->side_wgs = s_wgs > splits ? splits : s_wgs;
   }
-  // spin_sparse_decode_static promises to take the shapes whose partials fit its array at this many per row
-  int32_t promised = c->decode_splits;
-  if (promised == 0) {
-    promised = 256 / x->max_rows;
-    if (promised > x->page_stride / (4 * x->waves)) promised = x->page_stride / (4 * x->waves);
-    if (promised < 1) promised = 1;
-  }
-  if (promised > 64) promised = 64;
-  const int32_t side = x->side_wgs ? (forced_pages + 15) / 16 : 1;
-  x->static_partials = promised + (side > promised ? promised : side);
-  // partials of stage 4: those of the splits (of whichever batch has the most), then the spare ones
-  x->spare_stride = x->side_wgs > 1 ? x->side_wgs : 1;
-  x->spare_at = 0;
-  for (int32_t n = 1; n <= c->max_batch; ++n) {
-    const int32_t used = n * c->num_kv_heads * spin_splits_for(x, n * c->num_kv_heads);
-    if (used > x->spare_at) x->spare_at = used;
-  }
-  const size_t partials = (size_t)x->spare_at + (size_t)x->max_rows * x->spare_stride;
+  x->pstride = splits + (x->side_wgs > 1 ? x->side_wgs : 1);
 
   size_t off = SPIN_WS_HEADER;
   x->ws_ticket_off = off;                       // one arrival counter per row, zero between launches
@@ -133,11 +126,13 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   x->ws_skip_off = off;
   off += (size_t)x->max_rows * 2 * sizeof(int32_t);
   off = (off + 255) & ~(size_t)255;
+  // workgroup partials of stage 4: one per split, plus those of the always-attended pages when the launch of
+  // stages 2+3 attends them (at least one: the first of two passes over a page list leaves its result there)
   x->ws_ml_off = off;
-  off += partials * group * 2 * sizeof(float);
+  off += (size_t)x->max_rows * x->pstride * group * 2 * sizeof(float);
   off = (off + 255) & ~(size_t)255;
   x->ws_acc_off = off;
-  off += partials * group * SPIN_HEAD_DIM * sizeof(float);
+  off += (size_t)x->max_rows * x->pstride * group * SPIN_HEAD_DIM * sizeof(float);
   x->ws_bytes = (off + 255) & ~(size_t)255;
   // set-up for spin_sparse_decode_static on the device that is current now: its first call then asks the
   // runtime for nothing (a caller may be capturing by then).  Best effort: a context may be created with no

@@ -38,13 +38,9 @@ struct spin_ctx {
   int32_t sel_stride;
   int32_t page_stride;
   int32_t dir_stride;
-  int32_t splits;         // of a launch of max_batch requests; spin_splits_for() has them for fewer
+  int32_t splits;
   int32_t side_wgs;       // workgroups per row that attend the always-attended pages beside stages 2+3 (0: not supported)
-  // stage 4's partials in the workspace: those of a launch's splits (row * nsplit + split), and from index spare_at on
-  // spare_stride per row that a launch leaves for a later one (one per side_wgs, at least one: the first of two
-  // passes over a page list leaves its result there)
-  int32_t spare_at, spare_stride;
-  int32_t static_partials;   // partials per row that spin_sparse_decode_static's limit is stated for
+  int32_t pstride;        // stage 4's partials per row in the workspace: one per split, then one per such workgroup
   int32_t waves;          // wavefronts per decode workgroup
   int32_t depth;          // page buffers per decode wavefront
   int32_t kd;             // contraction length of one summary row
@@ -83,30 +79,6 @@ typedef __attribute__((ext_vector_type(4))) short spin_s16x4;
 // attention over a row's always-attended pages beside stages 2+3, the rest in stage 4: all-resident mode,
 // uniform partitions of whole pages, rows short enough for the 512-thread selection
 static inline bool spin_forced_split_supported(const spin_ctx *ctx) { return ctx->side_wgs > 0; }
-
-// Split-K factor of stage 4 for a launch of `rows` rows: about one workgroup on each of the 256 compute units, all
-// resident at once; at least one page per wavefront (four, where partitions are smaller than a page and a tile is
-// gathered from 16 of them); and at most as many partials as the row's last workgroup asks for at once, unless the rows
-// are so long that half as many again leave four pages per wavefront: then one workgroup's share of the pages takes
-// longer than the merge's further rounds (steps: 2 rows of 580 pages in blocks 25.9 us, 8 rows of 1036 pages in
-// clusters 33.5).
-// A row's pages cross one compute unit at 45 GB/s, so that few rows want many splits although every one lengthens the
-// merge.  Measured, splits 1 / 2 / 4 / 6 / 8 / 12 / 16: 2 rows of 32 pages 7.6 / 7.4 / 7.0 / 6.9 / 6.9 / 9.1 / 9.8 us,
-// 24 rows of 64 pages 12.1 / 10.5 / 9.5 / 9.2 / 9.2 / 14.7 / 18.0, 8 rows of 128 pages 21.8 / 15.4 / 10.8 / 9.5 / 9.2 / 11.0 / 11.9.
-#define SPIN_MERGE_AT_ONCE 8
-static inline int32_t spin_splits_for(const spin_ctx *x, int32_t rows) {
-  int32_t splits = x->cfg.decode_splits;
-  if (splits == 0) {
-    const int32_t pages = x->page_stride / ((x->k_token_major ? 4 : 1) * x->waves);
-    const int32_t four_pages = x->page_stride / (4 * x->waves);
-    const int32_t most = four_pages >= SPIN_MERGE_AT_ONCE * 3 / 2 ? four_pages
-                         : pages < SPIN_MERGE_AT_ONCE ? pages : SPIN_MERGE_AT_ONCE;
-    splits = 256 / rows;
-    if (splits > most) splits = most;
-    if (splits < 1) splits = 1;
-  }
-  return splits > 64 ? 64 : splits;
-}
 
 static inline int spin_launch_status() {
   return hipGetLastError() == hipSuccess ? SPIN_OK : SPIN_ERR_HIP;

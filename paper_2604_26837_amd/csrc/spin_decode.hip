@@ -22,15 +22,14 @@
 
 #include "spin_decode_dev.h"
 
-#define SPIN_DECODE_FROM_PARTIAL 1   // the first wavefronts of a row's splits start from its spare partials
+#define SPIN_DECODE_FROM_PARTIAL 1   // the row's first wavefront starts from the partial at index nsplit
 #define SPIN_DECODE_TO_PARTIAL 2     // the row's merged result goes there instead of to `out`
 
 template <int WAVES, int DEPTH>
 __global__ __launch_bounds__(WAVES * 64) void spin_decode_kernel(
     const uint16_t *__restrict__ q, const uint4 *__restrict__ pool, int64_t pool_slots,
     const int32_t *__restrict__ slots, const uint16_t *__restrict__ masks,
-    const int32_t *__restrict__ npages, int page_stride, int G, int Hq, int Hkv, int nsplit,
-    int spare_at, int spare_stride,
+    const int32_t *__restrict__ npages, int page_stride, int G, int Hq, int Hkv, int nsplit, int pstride,
     const int32_t *__restrict__ skip, int mode, int nside, float scale_log2e, float *part_ml, float *part_acc, int32_t *tickets,
     uint16_t *__restrict__ out, float *__restrict__ lse, int32_t *status) {
   const int row = blockIdx.x / nsplit;
@@ -69,7 +68,7 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_kernel(
   // the row (its always-attended pages, or the first of two passes over the page list) instead of from the
   // empty state: that partial then is part of the ordinary merge.
   if ((mode & SPIN_DECODE_FROM_PARTIAL) && split < nside && wave == 0) {
-    const size_t pf = ((size_t)spare_at + (size_t)row * spare_stride + split) * G;
+    const size_t pf = ((size_t)row * pstride + nsplit + split) * G;
     if (n < G) {
       st.m = part_ml[(pf + n) * 2];
       if (c == 0) st.l = part_ml[(pf + n) * 2 + 1];   // the lanes' denominators are summed over c at the end
@@ -108,8 +107,8 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_kernel(
     attend_lane_pages<DEPTH>(st, pool, myslot, mymask, cnt, lane, c, qf, scale_log2e);
   }
 
-  decode_finish<WAVES>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, spare_at + row * spare_stride,
-                       part_ml, part_acc, tickets, out, lse, (mode & SPIN_DECODE_TO_PARTIAL) != 0);
+  decode_finish<WAVES>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, pstride, part_ml, part_acc, tickets, out,
+                       lse, (mode & SPIN_DECODE_TO_PARTIAL) != 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -168,8 +167,7 @@ template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void spin_decode_tokens_kernel(
     const uint16_t *__restrict__ q, const uint4 *__restrict__ pool, int64_t pool_slots,
     const int32_t *__restrict__ slots, const uint16_t *__restrict__ masks,
-    const int32_t *__restrict__ npages, int page_stride, int G, int Hq, int Hkv, int nsplit,
-    int spare_at, int spare_stride,
+    const int32_t *__restrict__ npages, int page_stride, int G, int Hq, int Hkv, int nsplit, int pstride,
     const int32_t *__restrict__ skip, float scale_log2e, float *part_ml, float *part_acc, int32_t *tickets,
     uint16_t *__restrict__ out, float *__restrict__ lse, int32_t *status) {
   extern __shared__ __align__(16) float smem[];
@@ -254,8 +252,8 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_tokens_kernel(
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // before the next batch overwrites the list
   }
   __syncthreads();   // the merge buffers are separate from the lists, but keep the phases apart
-  decode_finish<WAVES>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, spare_at + row * spare_stride,
-                       part_ml, part_acc, tickets, out, lse);
+  decode_finish<WAVES>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, pstride, part_ml, part_acc, tickets, out,
+                       lse);
 }
 
 // Host side of stage 4: checks, then the launch; the split-K scratch (row tickets, (m, l) pairs and
@@ -265,9 +263,10 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_tokens_kernel(
 static int decode_launch(spin_ctx *ctx, int32_t batch, const void *q, const void *kv_pool, int64_t pool_slots,
                          const int32_t *slots, const uint16_t *valid_mask, const int32_t *npages, void *out,
                          float *lse, float *part_ml, float *part_acc, int32_t *tickets, int32_t *status,
-                         int nsplit, const int32_t *skip, int mode, int nside, void *stream) {
+                         const int32_t *skip, int mode, int nside, void *stream) {
   const int rows = batch * ctx->cfg.num_kv_heads;
-  const int G = ctx->group, spare_at = ctx->spare_at, spare_stride = ctx->spare_stride;
+  const int G = ctx->group, nsplit = ctx->splits;
+  const int pstride = ctx->pstride;
   const float scale_log2e = ctx->scale * 1.4426950408889634f;
   const int W = ctx->waves;
   const size_t lds = (size_t)W * G * (SPIN_HEAD_DIM + 2) * sizeof(float);
@@ -278,15 +277,15 @@ static int decode_launch(spin_ctx *ctx, int32_t batch, const void *q, const void
     const size_t lds_tok = (size_t)8 * G * (SPIN_HEAD_DIM + 2) * sizeof(float) + (size_t)8 * TOK_LIST * sizeof(uint32_t);
     spin_launch(ctx, SPIN_K_DECODE, spin_decode_tokens_kernel<8>, dim3((unsigned)(rows * nsplit)), dim3(512), lds_tok,
                 (hipStream_t)stream, (const uint16_t *)q, (const uint4 *)kv_pool, pool_slots, slots, valid_mask, npages,
-                ctx->page_stride, G, ctx->cfg.num_q_heads, ctx->cfg.num_kv_heads, nsplit, spare_at, spare_stride,
-                skip, scale_log2e, part_ml, part_acc, tickets, (uint16_t *)out, lse, status);
+                ctx->page_stride, G, ctx->cfg.num_q_heads, ctx->cfg.num_kv_heads, nsplit, pstride, skip, scale_log2e,
+                part_ml, part_acc, tickets, (uint16_t *)out, lse, status);
     return spin_launch_status();
   }
 #define SPIN_DECODE_LAUNCH2(WV, DP)                                                                              \
   spin_launch(ctx, SPIN_K_DECODE, spin_decode_kernel<WV, DP>, dim3((unsigned)(rows * nsplit)), dim3(WV * 64), lds, \
               (hipStream_t)stream, (const uint16_t *)q, (const uint4 *)kv_pool, pool_slots, slots, valid_mask,   \
-              npages, ctx->page_stride, G, ctx->cfg.num_q_heads, ctx->cfg.num_kv_heads, nsplit, spare_at,       \
-              spare_stride, skip, mode, nside, scale_log2e, part_ml, part_acc, tickets, (uint16_t *)out, lse, status)
+              npages, ctx->page_stride, G, ctx->cfg.num_q_heads, ctx->cfg.num_kv_heads, nsplit, pstride, skip,   \
+              mode, nside, scale_log2e, part_ml, part_acc, tickets, (uint16_t *)out, lse, status)
 #define SPIN_DECODE_LAUNCH(WV)                          \
   do {                                                  \
     if (ctx->depth == 2) SPIN_DECODE_LAUNCH2(WV, 2);    \
@@ -312,8 +311,7 @@ extern "C" int spin_sparse_decode(spin_ctx *ctx, int32_t batch, const void *q, c
   char *ws = (char *)workspace;
   return decode_launch(ctx, batch, q, kv_pool, pool_slots, slots, valid_mask, npages, out, lse,
                        (float *)(ws + ctx->ws_ml_off), (float *)(ws + ctx->ws_acc_off),
-                       (int32_t *)(ws + ctx->ws_ticket_off), (int32_t *)workspace,
-                       spin_splits_for(ctx, batch * ctx->cfg.num_kv_heads), nullptr, 0, 0, stream);
+                       (int32_t *)(ws + ctx->ws_ticket_off), (int32_t *)workspace, nullptr, 0, 0, stream);
 }
 
 // Attention in two passes over one page list: the first attends the tokens its masks name and leaves
@@ -330,8 +328,7 @@ static int decode_two_pass(spin_ctx *ctx, int32_t batch, const void *q, const vo
   char *ws = (char *)workspace;
   return decode_launch(ctx, batch, q, kv_pool, pool_slots, slots, valid_mask, npages, out, lse,
                        (float *)(ws + ctx->ws_ml_off), (float *)(ws + ctx->ws_acc_off),
-                       (int32_t *)(ws + ctx->ws_ticket_off), (int32_t *)workspace,
-                       spin_splits_for(ctx, batch * ctx->cfg.num_kv_heads), nullptr, mode, 1, stream);
+                       (int32_t *)(ws + ctx->ws_ticket_off), (int32_t *)workspace, nullptr, mode, 1, stream);
 }
 
 extern "C" int spin_sparse_decode_begin(spin_ctx *ctx, int32_t batch, const void *q, const void *kv_pool,
@@ -364,8 +361,7 @@ extern "C" int spin_sparse_decode_rest(spin_ctx *ctx, int32_t batch, const void 
   return decode_launch(ctx, batch, q, kv_pool, pool_slots, slots, valid_mask, npages, out, lse,
                        (float *)(ws + ctx->ws_ml_off), (float *)(ws + ctx->ws_acc_off),
                        (int32_t *)(ws + ctx->ws_ticket_off), (int32_t *)workspace,
-                       spin_splits_for(ctx, batch * ctx->cfg.num_kv_heads), (const int32_t *)(ws + ctx->ws_skip_off),
-                       SPIN_DECODE_FROM_PARTIAL, ctx->side_wgs, stream);
+                       (const int32_t *)(ws + ctx->ws_skip_off), SPIN_DECODE_FROM_PARTIAL, ctx->side_wgs, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -416,18 +412,12 @@ extern "C" int spin_sparse_decode_static(spin_ctx *ctx, int32_t batch, const voi
   if (!q || !kv_pool || !slots || !valid_mask || !npages || !out) return SPIN_ERR_INVALID;
   // layout inside the array, sized for this call's rows: [status word, 256 B][tickets][(m, l)][accumulators]
   const size_t rows = (size_t)batch * ctx->cfg.num_kv_heads;
+  const size_t partials = rows * ctx->pstride * ctx->group;   // the layout of the workspace (spare partials are not used here)
   const size_t ticket_off = SPIN_WS_HEADER;
   const size_t ml_off = (ticket_off + rows * sizeof(int32_t) + 255) & ~(size_t)255;
-  const auto acc_off = [&](int n) {      // with n partials per row
-    return (ml_off + rows * n * ctx->group * 2 * sizeof(float) + 255) & ~(size_t)255;
-  };
-  const auto fits = [&](int n) {
-    return acc_off(n) + rows * n * ctx->group * SPIN_HEAD_DIM * sizeof(float) <= SPIN_STATIC_SCRATCH_BYTES;
-  };
-  if (!fits(ctx->static_partials)) return SPIN_ERR_STATIC_LIMIT;
-  // the splits of spin_sparse_decode, or as many as fit the array (one always does)
-  int nsplit = spin_splits_for(ctx, (int32_t)rows);
-  while (!fits(nsplit)) --nsplit;
+  const size_t acc_off = (ml_off + partials * 2 * sizeof(float) + 255) & ~(size_t)255;
+  const size_t need = acc_off + partials * SPIN_HEAD_DIM * sizeof(float);
+  if (need > SPIN_STATIC_SCRATCH_BYTES) return SPIN_ERR_STATIC_LIMIT;
   void *base = nullptr;
   const int rc = static_scratch(&base);
   if (rc != SPIN_OK) return rc;
@@ -438,6 +428,6 @@ extern "C" int spin_sparse_decode_static(spin_ctx *ctx, int32_t batch, const voi
                      (int32_t *)sc, nclear);
   if (hipGetLastError() != hipSuccess) return SPIN_ERR_HIP;
   return decode_launch(ctx, batch, q, kv_pool, pool_slots, slots, valid_mask, npages, out, lse,
-                       (float *)(sc + ml_off), (float *)(sc + acc_off(nsplit)), (int32_t *)(sc + ticket_off),
-                       status ? status : (int32_t *)sc, nsplit, nullptr, 0, 0, stream);
+                       (float *)(sc + ml_off), (float *)(sc + acc_off), (int32_t *)(sc + ticket_off),
+                       status ? status : (int32_t *)sc, nullptr, 0, 0, stream);
 }

@@ -150,18 +150,17 @@ __device__ inline void write_out(uint16_t *__restrict__ out, float *__restrict__
 
 // After a workgroup's wavefronts have consumed their tiles: merge the wavefront partials through
 // LDS and, with several splits, the workgroup partials through the workspace (see the header).
-// Partial `s` of a row lives at index row * nsplit + s; the row's output is the merge, in index order, of the
-// nsplit partials of the calling launch.  `spare`: index of the row's first spare partial, which a launch leaves for a
-// later one.
+// Partial `s` of a row lives at index row * pstride + s (pstride = splits + the partials earlier launches may leave); the row's output is
+// the merge, in index order, of the partials 0 .. nsplit-1 of the calling launch.
 // ONLY_PARTIAL (then `split` is the index j of the calling workgroup among those that attend a row's
-// always-attended pages): the workgroup only stores its partial, the row's spare one j, for a later
+// always-attended pages): the workgroup only stores its partial, at index nsplit + j, for a later
 // launch on the same stream to start from.
 // to_partial: the merged result of the row is stored there as well, unnormalised, instead of being
 // written to `out` (the first of two attention passes over one page list).
 // Returns true in the workgroup that wrote the row's output.
 template <int WAVES, bool ONLY_PARTIAL = false>
 __device__ __forceinline__ bool decode_finish(softmax_state &st, int row, int split, int b, int h, int lane, int wave,
-                                              int n, int c, int G, int Hq, int nsplit, int spare,
+                                              int n, int c, int G, int Hq, int nsplit, int pstride,
                                               float *part_ml, float *part_acc, int32_t *tickets,
                                               uint16_t *__restrict__ out, float *__restrict__ lse,
                                               bool to_partial = false) {
@@ -215,14 +214,14 @@ __device__ __forceinline__ bool decode_finish(softmax_state &st, int row, int sp
     }
     if (ONLY_PARTIAL || (nsplit == 1 && to_partial)) {
       // read by a later launch on the same stream: plain stores
-      const size_t pi = ((size_t)spare + (ONLY_PARTIAL ? split : 0)) * G + g;
+      const size_t pi = ((size_t)row * pstride + nsplit + (ONLY_PARTIAL ? split : 0)) * G + g;
       *(float2 *)(part_acc + pi * SPIN_HEAD_DIM + d) = O;
       if (d == 0) *(float2 *)(part_ml + pi * 2) = make_float2(M, L);
     } else if (nsplit == 1) {
       write_out(out, lse, b * Hq + h * G + g, d, M, L, O);
     } else {
       // device-scope stores: written through to where every compute die sees them
-      const size_t pi = ((size_t)row * nsplit + split) * G + g;
+      const size_t pi = ((size_t)row * pstride + split) * G + g;
       spin_dev_store2(part_acc + pi * SPIN_HEAD_DIM + d, O);
       if (d == 0) spin_dev_store2(part_ml + pi * 2, make_float2(M, L));
     }
@@ -245,8 +244,8 @@ __device__ __forceinline__ bool decode_finish(softmax_state &st, int row, int sp
   // splits a lane asks for all its accumulators and all (m, l) pairs (the same ones in a whole wavefront) at once, and
   // nothing passes through LDS.  From the ticket to the output: 2 splits 1.8 -> 1.3 us, 8 splits 2.6 -> 1.8, against
   // one channel per lane, four rounds of predicated loads and the pairs staged in LDS behind a barrier.
-  const size_t pbase = (size_t)row * nsplit * G;
-  constexpr int CH = SPIN_MERGE_AT_ONCE;
+  const size_t pbase = (size_t)row * pstride * G;
+  constexpr int CH = 8;
   for (int idx = threadIdx.x; idx < G * (SPIN_HEAD_DIM / 2); idx += WAVES * 64) {
     const int g = __builtin_amdgcn_readfirstlane(idx >> 6), d = (idx & 63) * 2;
     const float *acc_at = part_acc + (pbase + g) * SPIN_HEAD_DIM + d, *ml_at = part_ml + (pbase + g) * 2;
@@ -281,7 +280,7 @@ __device__ __forceinline__ bool decode_finish(softmax_state &st, int row, int sp
       }
     }
     if (to_partial) {
-      const size_t pi = (size_t)spare * G + g;
+      const size_t pi = ((size_t)row * pstride + nsplit) * G + g;
       *(float2 *)(part_acc + pi * SPIN_HEAD_DIM + d) = O;
       if (d == 0) *(float2 *)(part_ml + pi * 2) = make_float2(M, L);
     } else {

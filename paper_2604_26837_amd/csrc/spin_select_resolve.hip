@@ -83,7 +83,7 @@ __device__ inline void attend_forced_row(
     int row, int side, int nside, const uint16_t *__restrict__ q, const uint4 *__restrict__ pool, int64_t pool_slots,
     const int32_t *__restrict__ seq_lens, const int32_t *__restrict__ dir, const int32_t *__restrict__ leaf_pool,
     int64_t leaf_chunks, int Hkv, int G, int Hq, int sink_pages, int recent_pages, int dir_stride, int leaf_entries,
-    int spare, float scale_log2e, float *part_ml, float *part_acc, int32_t *skip) {
+    int nsplit, int pstride, float scale_log2e, float *part_ml, float *part_acc, int32_t *skip) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, c = lane >> 4;
@@ -118,7 +118,7 @@ __device__ inline void attend_forced_row(
                   leaf_chunks, row, dir_stride, leaf_entries, pool_slots, myslot, mymask);
     attend_lane_pages<2>(st, pool, myslot, mymask, cnt, lane, c, qf, scale_log2e);
   }
-  decode_finish<WAVES, true>(st, row, side, b, h, lane, wave, n, c, G, Hq, 0, spare, part_ml,
+  decode_finish<WAVES, true>(st, row, side, b, h, lane, wave, n, c, G, Hq, nsplit, pstride, part_ml,
                        part_acc, nullptr, nullptr, nullptr);
 }
 
@@ -126,7 +126,7 @@ struct spin_forced_args {
   const uint16_t *q;
   const uint4 *pool;
   int64_t pool_slots;
-  int G, Hq, spare_at, spare_stride, nside;
+  int G, Hq, nsplit, pstride, nside;
   float scale_log2e;
   float *part_ml, *part_acc;
   int32_t *skip;
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(512) void spin_select_resolve_forced_kernel(
   if ((int)blockIdx.x >= rows) {
     const int idx = (int)blockIdx.x - rows, srow = idx / fa.nside;
     attend_forced_row<8>(srow, idx - srow * fa.nside, fa.nside, fa.q, fa.pool, fa.pool_slots, seq_lens, dir, leaf_pool, leaf_chunks, Hkv,
-                         fa.G, fa.Hq, sink_pages, recent_pages, dir_stride, leaf_entries, fa.spare_at + srow * fa.spare_stride,
+                         fa.G, fa.Hq, sink_pages, recent_pages, dir_stride, leaf_entries, fa.nsplit, fa.pstride,
                          fa.scale_log2e, fa.part_ml, fa.part_acc, fa.skip);
     return;
   }
@@ -177,7 +177,7 @@ extern "C" int spin_select_resolve_forced(spin_ctx *ctx, int32_t batch, const fl
   const int rows = batch * c.num_kv_heads;
   char *ws = (char *)workspace;
   const spin_forced_args fa = {(const uint16_t *)q, (const uint4 *)kv_pool, pool_slots, ctx->group, c.num_q_heads,
-                               ctx->spare_at, ctx->spare_stride, ctx->side_wgs, ctx->scale * 1.4426950408889634f,
+                               ctx->splits, ctx->pstride, ctx->side_wgs, ctx->scale * 1.4426950408889634f,
                                (float *)(ws + ctx->ws_ml_off), (float *)(ws + ctx->ws_acc_off),
                                (int32_t *)(ws + ctx->ws_skip_off)};
   // dynamic LDS: the merge buffers of the attention workgroups (8 wavefronts)

@@ -54,6 +54,13 @@ def test_create_validates_and_sizes(lib):
             binding.Spin(**cfg)
 
 
+@pytest.mark.parametrize("splits,batch,kv,topk,context", [(1, 1, 2, 32, 4096), (2, 16, 8, 64, 32768), (4, 1, 8, 128, 131072),
+                                                          (2, 12, 8, 128, 20096), (18, 1, 2, 580, 65536), (64, 1, 2, 2048, 65536)])
+def test_default_splits_leave_four_pages_per_wavefront(lib, splits, batch, kv, topk, context):
+    sp = binding.Spin(max_batch=batch, num_q_heads=4 * kv, num_kv_heads=kv, topk=topk, max_context=context)
+    assert sp.decode_splits == splits == max(min(256 // (batch * kv), sp.page_stride // 32, 64), 1)
+
+
 def test_stage_calls_reject_bad_arguments_before_launching(lib):
     sp = binding.Spin(max_batch=2, num_q_heads=8, num_kv_heads=2, topk=8, max_context=1024)
     h = sp.h

@@ -1,6 +1,6 @@
-"""Stage 4's split-K factor follows the batch of the call: a context sized for many requests gives the same lists and,
-to the tolerance of a bf16 output of two summation orders, the same attention for any batch, in every form of the
-stage (plain, after the always-attended pages, in two passes, with the static scratch)."""
+"""Small batches in a context sized for many requests, in every form of stage 4 (plain, after the always-attended
+pages, in two passes, with the static scratch): to the tolerance of a bf16 output of two summation orders the attention
+of a context with one split, and a request's output bits do not depend on how many others share its call."""
 import pytest
 import torch
 
@@ -11,7 +11,7 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("batch,max_batch,heads,kv,topk,tp", [(1, 16, 8, 2, 32, 16), (3, 16, 32, 8, 64, 16), (1, 1, 16, 1, 200, 16),
-                                                              (2, 40, 128, 8, 40, 16), (2, 9, 8, 2, 6, 128), (5, 5, 8, 8, 9, 16)])
+                                                              (2, 40, 128, 8, 40, 16), (2, 9, 8, 2, 6, 128), (5, 5, 8, 8, 9, 16), (4, 4, 128, 8, 128, 16)])
 def test_any_batch_of_a_larger_context(batch, max_batch, heads, kv, topk, tp):
     w = synth.config0().with_(seq_lens=tuple(4003 + 517 * b for b in range(batch)), num_q_heads=heads, num_kv_heads=kv,
                               topk=topk, partition_tokens=tp, sink_pages=2, recent_pages=5, topk_includes_forced=tp == 16,
@@ -46,3 +46,38 @@ def test_any_batch_of_a_larger_context(batch, max_batch, heads, kv, topk, tp):
     sp.sparse_decode_begin(*args[:4], first, many.npages, many.ws)
     sp.sparse_decode_finish(*args[:4], many.valid_mask - first, many.npages, many.out, many.lse, many.ws)
     check(many.out)
+
+
+@pytest.mark.parametrize("batch,heads,kv,topk,tp", [(16, 32, 8, 64, 16), (16, 8, 2, 70, 16), (5, 128, 8, 128, 16),
+                                                    (16, 8, 2, 6, 128)])
+def test_bits_of_a_request_in_any_batch(batch, heads, kv, topk, tp):
+    w = synth.config0().with_(seq_lens=tuple(4003 + 17 * b for b in range(batch)), num_q_heads=heads, num_kv_heads=kv,
+                              topk=topk, partition_tokens=tp, sink_pages=2, recent_pages=5, topk_includes_forced=tp == 16,
+                              name="any_batch")
+    layer, _ = runner.build_device_layer(w)
+    sp = layer.spin
+
+    def static(q):
+        layer.step(q)
+        sp.sparse_decode_static(layer.w.batch, q, layer.kv_pool, layer.slots, layer.valid_mask, layer.npages, layer.out,
+                                layer.lse)
+
+    def two_passes(q):
+        layer.step(q)
+        args = (layer.w.batch, q, layer.kv_pool, layer.slots)
+        first = layer.valid_mask.clone()
+        first[:, 1::2] = 0
+        sp.sparse_decode_begin(*args, first, layer.npages, layer.ws)
+        sp.sparse_decode_finish(*args, layer.valid_mask - first, layer.npages, layer.out, layer.lse, layer.ws)
+
+    for form in (layer.step, layer.step_fused, static, two_passes):
+        layer.w = w
+        form(layer.q0)
+        out, lse = layer.out.clone(), layer.lse.clone()
+        for n in (1, 3, batch // 2):                                 # the first n requests alone
+            layer.w = w.with_(seq_lens=w.seq_lens[:n])
+            layer.out.zero_()
+            form(layer.q0[:n].contiguous())
+            assert torch.equal(layer.out[:n], out[:n]) and torch.equal(layer.lse[:n], lse[:n])
+    torch.cuda.synchronize()
+    assert layer.status() == 0
