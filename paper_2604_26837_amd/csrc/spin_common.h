@@ -128,15 +128,8 @@ __device__ inline void spin_raise(int32_t *status, int32_t err) { atomicCAS(stat
 __device__ inline float spin_bf16_to_f32(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
 
 // device-scope (all compute dies) relaxed accesses: written through / read from
-// the level every die sees, without cache-wide write-back or invalidate
-__device__ inline void spin_dev_store(float *p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline float spin_dev_load(const float *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// two floats at an address that is a multiple of 8, in one access
+// the level every die sees, without cache-wide write-back or invalidate; two floats
+// at an address that is a multiple of 8, in one access
 __device__ inline void spin_dev_store2(float *p, float2 v) {
   __hip_atomic_store((unsigned long long *)p, __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
@@ -262,6 +255,17 @@ __device__ inline int spin_waves_before(int v, int wave, int &total) {
   if (NW > 8) inc += spin_dpp_i<0x118>(inc);   // row_shr:8
   total = __builtin_amdgcn_readlane(inc, NW - 1);
   return __builtin_amdgcn_readlane(inc - v, wave);
+}
+// lane `lane`'s value (uniform), and the maximum over the wavefront
+__device__ inline float spin_readlane(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ inline float spin_wave_max(float v) {
+  v = fmaxf(v, spin_dpp<SPIN_DPP_XOR1>(v));
+  v = fmaxf(v, spin_dpp<SPIN_DPP_XOR2>(v));
+  v = fmaxf(v, spin_dpp<SPIN_DPP_HALF_MIRROR>(v));
+  v = fmaxf(v, spin_dpp<SPIN_DPP_MIRROR>(v));
+  return fmaxf(fmaxf(spin_readlane(v, 0), spin_readlane(v, 16)), fmaxf(spin_readlane(v, 32), spin_readlane(v, 48)));
 }
 // maximum / minimum of an unsigned word over the wavefront, result uniform
 __device__ inline uint32_t spin_wave_max_u32(uint32_t v) {

@@ -240,43 +240,70 @@ __device__ __forceinline__ bool decode_finish(softmax_state &st, int row, int sp
     s_last = (__hip_atomic_fetch_add(&tickets[row], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nsplit - 1);
   __syncthreads();
   if (!s_last) return false;
-  // A chain of dependent steps on one compute unit ends every row, so this is written for latency: with up to CH
-  // splits a lane asks for all its accumulators and all (m, l) pairs (the same ones in a whole wavefront) at once, and
-  // nothing passes through LDS.  From the ticket to the output: 2 splits 1.8 -> 1.3 us, 8 splits 2.6 -> 1.8, against
-  // one channel per lane, four rounds of predicated loads and the pairs staged in LDS behind a barrier.
+  // A chain of dependent steps on one compute unit ends every row, so this is written for latency: nothing passes
+  // through LDS, and no load waits for another.  With up to CH splits a lane asks for all its accumulators and all
+  // (m, l) pairs (the same ones in a whole wavefront) at once.  From the ticket to the output: 2 splits 1.8 -> 1.3 us,
+  // 8 splits 2.6 -> 1.8, against one channel per lane, four rounds of predicated loads and the pairs staged in LDS
+  // behind a barrier.  With more, lane s asks for the pair of split s (there are at most 64) beside the first 2 * CH
+  // accumulators, and the next ones are under way while the ones before are summed.  Stage 4, against a loop over the
+  // pairs ahead of rounds of eight and against the pairs staged in LDS: 2 rows of 580 pages, 18 splits 15.3 / 14.1 ->
+  // 11.9 us; 8 rows of 1036 pages, 32 splits 23.7 / 20.9 -> 18.3; 24 rows of 64 pages, 16 splits 16.5 / 15.9 -> 13.6;
+  // 8 rows of 384 pages, groups of 16, 12 splits 20.2 / 21.0 -> 13.8; 2 rows of 65536 tokens, 64 splits 22.6 / 15.7 -> 13.2.
   const size_t pbase = (size_t)row * pstride * G;
   constexpr int CH = 8;
   for (int idx = threadIdx.x; idx < G * (SPIN_HEAD_DIM / 2); idx += WAVES * 64) {
     const int g = __builtin_amdgcn_readfirstlane(idx >> 6), d = (idx & 63) * 2;
     const float *acc_at = part_acc + (pbase + g) * SPIN_HEAD_DIM + d, *ml_at = part_ml + (pbase + g) * 2;
     float M = NEG_INF, L = 0.f;
-    float2 O = make_float2(0.f, 0.f), a[CH], ml[CH];
-    auto load = [&](int s0) {
+    float2 O = make_float2(0.f, 0.f);
+    auto load = [&](float2 (&a)[CH], int s0) {
 #pragma unroll
       for (int s = 0; s < CH; ++s) {
         if (s0 + s >= nsplit) break;                     // uniform
-        ml[s] = spin_dev_load2(ml_at + (size_t)(s0 + s) * G * 2);
-        a[s] = spin_dev_load2(acc_at + (size_t)(s0 + s) * G * SPIN_HEAD_DIM);
+        a[s] = spin_dev_load2(acc_at + (unsigned)((s0 + s) * G * SPIN_HEAD_DIM));
       }
     };
-    if (nsplit > CH)
-      for (int s = 0; s < nsplit; ++s) M = fmaxf(M, spin_dev_load(ml_at + (size_t)s * G * 2));
-    load(0);
+    auto add = [&](float wgt, float l_of, const float2 &a) {
+      L += l_of * wgt;
+      O.x += a.x * wgt;
+      O.y += a.y * wgt;
+    };
     if (nsplit <= CH) {
+      float2 a[CH], ml[CH];
+#pragma unroll
+      for (int s = 0; s < CH; ++s) {
+        if (s >= nsplit) break;
+        ml[s] = spin_dev_load2(ml_at + (unsigned)(s * G * 2));
+        a[s] = spin_dev_load2(acc_at + (unsigned)(s * G * SPIN_HEAD_DIM));
+      }
 #pragma unroll
       for (int s = 0; s < CH; ++s)
         if (s < nsplit) M = fmaxf(M, ml[s].x);
-    }
-    const float Ms = (M == NEG_INF) ? 0.f : M;
-    for (int s0 = 0; s0 < nsplit; s0 += CH) {            // the splits in split order
-      if (s0) load(s0);
+      const float Ms = (M == NEG_INF) ? 0.f : M;
 #pragma unroll
-      for (int s = 0; s < CH; ++s) {
-        if (s0 + s >= nsplit) break;
-        const float wgt = __builtin_amdgcn_exp2f(ml[s].x - Ms);
-        L += ml[s].y * wgt;
-        O.x += a[s].x * wgt;
-        O.y += a[s].y * wgt;
+      for (int s = 0; s < CH; ++s) {                     // the splits in split order
+        if (s >= nsplit) break;
+        add(__builtin_amdgcn_exp2f(ml[s].x - Ms), ml[s].y, a[s]);
+      }
+    } else {
+      float2 ml = make_float2(NEG_INF, 0.f), a[2][CH];
+      if (lane < nsplit) ml = spin_dev_load2(ml_at + (unsigned)(lane * G * 2));
+      load(a[0], 0);
+      load(a[1], CH);
+      M = fmaxf(spin_wave_max(ml.x), NEG_INF);
+      const float wgt = __builtin_amdgcn_exp2f(ml.x - (M == NEG_INF ? 0.f : M));
+      auto add_all = [&](float2 (&a_of)[CH], int s0) {
+#pragma unroll
+        for (int s = 0; s < CH; ++s) {
+          if (s0 + s >= nsplit) break;
+          add(spin_readlane(wgt, s0 + s), spin_readlane(ml.y, s0 + s), a_of[s]);
+        }
+      };
+      for (int s0 = 0; s0 < nsplit; s0 += 2 * CH) {
+        add_all(a[0], s0);
+        load(a[0], s0 + 2 * CH);
+        add_all(a[1], s0 + CH);
+        load(a[1], s0 + 3 * CH);
       }
     }
     if (to_partial) {

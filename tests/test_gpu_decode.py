@@ -243,7 +243,47 @@ def test_random_launch_shapes_and_page_lists(seed):
     _compare(got, np.nan_to_num(ref), lgot, lref)
 
 
-@pytest.mark.parametrize("splits,waves", [(0, 0), (1, 8), (3, 4), (2, 2)])
+@pytest.mark.parametrize("token_major", [False, True])
+@pytest.mark.parametrize("splits,group", [(8, 4), (9, 4), (15, 1), (16, 16), (17, 4), (24, 3), (25, 8), (32, 2), (33, 16), (64, 4)])
+def test_many_splits(splits, group, token_major):
+    """The row's last workgroup merges up to eight partials in one round, more in rounds of sixteen: factors around
+    the rounds' edges, with lists of all pages (splits of several wavefronts, of one, and empty ones), one page, no
+    page and no attended token.  A partial that is left out or counted twice moves lse by its share of the row, far
+    more than the tolerance of the sums."""
+    from gpu_harness import DeviceWorkload
+    w = synth.config0().with_(seq_lens=(700, 16, 4090, 333, 2049), num_q_heads=2 * group, num_kv_heads=2,
+                              topk=256 * (4 if token_major else 1), partition_tokens=4 if token_major else 16,
+                              name=f"splits{splits}")
+    dw = DeviceWorkload(synth.generate(w, spare_slots=3), decode_splits=splits)
+    assert dw.spin.decode_splits == splits
+    rng = np.random.default_rng(splits)
+    pl, ml = _random_selection(w, rng, 256, ragged_masks=True)
+    pl[0], ml[0] = [], []
+    ml[1] = [0] * len(pl[1])
+    pl[6], ml[6] = pl[6][:1], [1 << 3]
+    pl[7], ml[7] = pl[7][:splits - 1], ml[7][:splits - 1]
+    ref, lref = _oracle_rows(dw, pl, ml)
+    got, lgot = _run_decode(dw, pl, ml)
+    _compare(got, np.nan_to_num(ref), lgot, lref)
+    got2, lgot2 = _run_decode(dw, pl, ml)                       # (the tickets are left cleared)
+    assert np.array_equal(got, got2) and np.array_equal(lgot, lgot2)
+
+
+def test_default_split_factor_of_long_lists():
+    """Few rows with long page lists get more than eight splits without being asked."""
+    from gpu_harness import DeviceWorkload
+    for pages, splits in ((383, 11), (384, 12), (580, 18)):
+        w = synth.config0().with_(seq_lens=(16 * pages,), topk=pages, name=f"long{pages}")
+        dw = DeviceWorkload(synth.generate(w))
+        assert dw.spin.decode_splits == splits
+        pl = [list(range(pages))] * w.rows
+        ml = [[0xFFFF] * pages] * w.rows
+        ref, lref = _oracle_rows(dw, pl, ml)
+        got, lgot = _run_decode(dw, pl, ml)
+        _compare(got, ref, lgot, lref)
+
+
+@pytest.mark.parametrize("splits,waves", [(0, 0), (1, 8), (3, 4), (2, 2), (9, 0), (17, 4), (64, 8)])
 def test_two_pass_attention_over_a_split_page_list(splits, waves):
     """spin_sparse_decode_begin + spin_sparse_decode_finish over any two-way split of the token masks (a page in
     one pass, the other, both in part, or neither) equal attention over the union: oracle tolerance, and the

@@ -70,6 +70,10 @@ CASES = {
     "many_recent_pages": (synth.config0().with_(seq_lens=(30000, 12000), num_q_heads=8, num_kv_heads=2, topk=300,
                                                 sink_pages=16, recent_pages=200, name="forced_many"),
                           dict(decode_splits=3)),
+    "seventeen_splits": (synth.config0().with_(seq_lens=(5000, 900, 40), num_q_heads=8, num_kv_heads=2, topk=120,
+                                               sink_pages=4, recent_pages=40, name="forced_17"), dict(decode_splits=17)),
+    "long_lists_default_splits": (synth.config0().with_(seq_lens=(16 * 900,), num_q_heads=8, num_kv_heads=2, topk=640,
+                                                        sink_pages=4, recent_pages=30, name="forced_640"), {}),
     "rows_up_to_4096_pages": (synth.config0().with_(seq_lens=(65536, 40000), num_q_heads=8, num_kv_heads=2, topk=64,
                                                     sink_pages=8, recent_pages=56, name="forced_long"), {}),
 }
