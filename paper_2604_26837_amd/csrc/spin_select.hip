@@ -188,7 +188,7 @@ __global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
     int includes_forced, int sink_pages, int recent_pages, int sel_stride, int32_t *sel, int32_t *__restrict__ nsel,
     spin_resolve_args ra, int page_stride, int dir_stride, int leaf_entries, int32_t *status) {
   constexpr int CAP = 4096;
-  __shared__ tiles_lds<BLOCK, CAP> s;
+  __shared__ tiles_row_lds<BLOCK, CAP> s;
   const int row = blockIdx.x;
   float4 mine[MPT / 4];
   load_tile_maxima<MPT>(mine, maxima + (size_t)row * max_stride, max_stride);
@@ -198,12 +198,13 @@ __global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
   int32_t *rsel = sel + (size_t)row * sel_stride;
   const sel_plan pl = select_plan(seq_lens[b], PP, tp, topk, includes_forced, sink_pages, recent_pages, sel_stride);
   emit_forced<BLOCK>(pl, sel_stride, rsel, nsel, row);
-  if (pl.kprime > 0 &&
-      ((pl.P >> gs_log) > min(max_stride, BLOCK * MPT) ||
-       !select_by_tile_maxima<BLOCK, MPT, CAP>(rs, mine, gs_log, pl, sel_stride, rsel, s))) {
+  // (a row that is longer than the context's longest one has no maxima for all its tiles)
+  if (pl.kprime > 0 && ((pl.P >> gs_log) > min(max_stride, BLOCK * MPT) || pl.P > ROW_PARTS)) {
     __syncthreads();
     select_generic_row<BLOCK>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
                               recent_pages, sel_stride, sel, nsel, row);
+  } else if (pl.kprime > 0) {
+    select_by_tile_maxima<BLOCK, MPT, CAP>(rs, mine, gs_log, pl, sel_stride, rsel, s);
   }
   if (RESOLVE) {
     __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here

@@ -487,42 +487,201 @@ __device__ inline int select_reg_row(
 // of k' tiles, whatever the row's length and however many scores tie; tiles that hold forced partitions are no
 // bound for anything and are read as well.  T0 then rules most of those scores out and the rest form the list.
 #define TILE_LIST 4098     // tiles a row may read (16-bit ids: rows of up to 131072 partitions, 4 or more to a tile)
+#define ROW_PARTS 131072   // partitions of the longest row
+#define ROW_BINS 4096
+#define ROW_LIST 2048
 template <int BLOCK, int CAP>
 struct tiles_lds : elements_lds<BLOCK, CAP> {
   uint16_t tile[TILE_LIST];
 };
+// LDS of select_whole_row
+template <int BLOCK>
+struct row_lds {
+  kth_lds<BLOCK> kth;
+  uint2 wtot[BLOCK / 64];
+  alignas(16) int4 found;
+  int listed;
+  uint32_t above[ROW_PARTS / 32], equal[ROW_PARTS / 32];   // one bit per partition
+  union {
+    alignas(16) int bins[ROW_BINS];
+    struct { uint32_t key[ROW_LIST]; int32_t id[ROW_LIST]; } list;
+  };
+};
+template <int BLOCK, int CAP>
+union tiles_row_lds {
+  tiles_lds<BLOCK, CAP> tiles;
+  row_lds<BLOCK> row;
+};
 
-// Stores the kprime best candidates ascending at rsel[nf_lo ..].  A row with fewer than k' tiles reads them all; where
-// more scores reach the bound than the list holds, the search and the selection re-read them per pass instead.
-// False (for the whole workgroup, nothing stored): k' beyond what the tile list holds.
-// `maxima`: the calling thread's MPT of the row (load_tile_maxima, whose loads need not wait for the row's plan).
-template <int MPT>
-__device__ inline void load_tile_maxima(float4 (&v)[MPT / 4], const float *__restrict__ maxima, int maxima_stride) {
-  const int m0 = threadIdx.x * MPT;
+// The kprime best candidates of a row of at most ROW_PARTS partitions, stored ascending at rsel[nf_lo ..], from walks
+// over all its scores (a quad per lane and load): a histogram of the keys from `lo` to `hi`, which
+// is repeated inside the bin of the k'-th candidate while that holds too many scores (ties, or a row whose scores lie
+// close together), then one walk that marks the scores above the bin in a bitmap and lists those inside it.
+// No candidate's key is known to be above hi (one that is counts in the last bin); fewer than kprime may reach `lo`,
+// and then the keys below it are searched.
+// This is the path of rows whose k' tiles hold more scores than a list takes.  The one compute unit is bound by
+// instructions per score: about ten for the histogram, four for the bitmap.  Against a radix search that read the tiles'
+// scores five times and, for k' beyond the tile list, one contiguous stretch of scores per thread: stages 2+3, 2 rows of
+// 65536 token partitions, k' 2560 / 3600 / 4096 / 8192: 67 / 82 / 202 / 217 -> 34 / 37 / 38 / 53 us; 2 rows of 20000,
+// k' 2048 / 8192: 44 / 90 -> 22 / 64.  (Being in the kernel it costs rows that do not come here 0.2 to 0.3 us, out of
+// line as well; four quads under way as good as eight, which take 30 more registers.)
+template <int BLOCK>
+__device__ inline void select_whole_row(const float *__restrict__ rs, uint32_t lo, uint32_t hi, const sel_plan &pl,
+                                        int sel_stride, int32_t *__restrict__ rsel, row_lds<BLOCK> &s) {
+  constexpr int NW = BLOCK / 64, V = 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int words = (pl.first_hi + 31) >> 5;
+  for (int i = tid; i < words; i += BLOCK) s.above[i] = s.equal[i] = 0u;
+  if (tid == 0) s.listed = 0;
+  // `use` gets V quads of scores, the partition of the first (load i: i * BLOCK * 4 further on) and a bit per candidate
+  auto walk = [&](auto use) {
+    for (int base = pl.nf_lo & ~3; base < pl.first_hi; base += BLOCK * 4 * V) {
+      const int p0 = base + tid * 4;
+      float4 v[V];
+      uint32_t have = 0;
 #pragma unroll
-  for (int j = 0; j < MPT / 4; ++j)                    // the stride is a multiple of 4
-    v[j] = m0 + 4 * j < maxima_stride ? *(const float4 *)(maxima + m0 + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int i = 0; i < V; ++i) {
+        const int p = p0 + i * BLOCK * 4;                // the row's scores are padded to a multiple of 16
+        v[i] = p < pl.first_hi ? *(const float4 *)(rs + p) : make_float4(0.f, 0.f, 0.f, 0.f);
+        have |= range_bits<4>(p, pl.nf_lo, pl.first_hi) << (4 * i);
+      }
+      use(v, p0, have);
+    }
+  };
+  int rank = pl.kprime;                                  // of the threshold among the keys of [lo, hi)
+  bool open = true;                                      // keys from hi on belong to the last bin
+  // settles 12 bits a time, after one walk in vain at most
+  for (int pass = 0; pass < 4; ++pass) {
+    const int shift = max(20 - __clz((int)(hi - lo - 1)), 0);
+    const uint32_t span = open ? 0xffffffffu - lo : hi - lo, last = (hi - lo - 1) >> shift;
+    for (int i = tid; i < ROW_BINS; i += BLOCK) s.bins[i] = 0;
+    __syncthreads();
+    walk([&](const float4 (&v)[V], int, uint32_t have) {
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const float f[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t d = score_key(f[e]) - lo;       // (below lo: wraps to more than any span)
+          if (((have >> (4 * i + e)) & 1u) && d < span) atomicAdd(&s.bins[min(d >> shift, last)], 1);
+        }
+      }
+    });
+    __syncthreads();
+    // thread t has the bins from ROW_BINS - 1 - t * BPT down
+    constexpr int BPT = ROW_BINS / BLOCK;
+    int c[BPT], local = 0, total;
+#pragma unroll
+    for (int j = 0; j < BPT; ++j) { c[j] = s.bins[ROW_BINS - 1 - tid * BPT - j]; local += c[j]; }
+    const int inc = spin_wave_inclusive_scan(local);
+    if (lane == 63) s.wtot[wave].x = (unsigned)inc;
+    __syncthreads();
+    int running = spin_waves_before<NW>((int)s.wtot[lane % NW].x, wave, total) + inc - local;
+#pragma unroll
+    for (int j = 0; j < BPT; ++j) {
+      if (running < rank && running + c[j] >= rank) s.found = make_int4(ROW_BINS - 1 - tid * BPT - j, rank - running, c[j], 0);
+      running += c[j];
+    }
+    __syncthreads();
+    if (total < rank) {                                  // uniform
+      if (lo == 0) break;                                // (cannot be: every candidate was counted)
+      rank -= total;
+      hi = lo;
+      lo = 0;
+      open = false;
+      continue;
+    }
+    const int4 f = s.found;
+    const uint32_t bin = (uint32_t)__builtin_amdgcn_readfirstlane(f.x);
+    rank = __builtin_amdgcn_readfirstlane(f.y);
+    open = open && bin == last;
+    lo += bin << shift;
+    hi = open ? 0xffffffffu : lo + min(1u << shift, hi - lo);
+    if (__builtin_amdgcn_readfirstlane(f.z) <= ROW_LIST || hi - lo == 1) break;
+  }
+  // key order is float order, but NaN scores, which rank as -inf, fail every comparison
+  const bool all = lo <= SPIN_KEY_MINUS_INF, one = hi - lo == 1;
+  const float f_lo = key_floor_score(lo, true), f_hi = key_floor_score(hi, false);
+  walk([&](const float4 (&v)[V], int p0, uint32_t have) {
+    uint32_t above = 0, within = 0;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const float f[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        within |= (all || f[e] >= f_lo) ? 1u << (4 * i + e) : 0u;
+        above |= f[e] >= f_hi ? 1u << (4 * i + e) : 0u;
+      }
+    }
+    above &= have;
+    within &= have & ~above;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {                        // (p is a multiple of 4: a quad's bits lie in one word)
+      const int p = p0 + i * BLOCK * 4;
+      const uint32_t bits = (above >> (4 * i)) & 15u, eq = (within >> (4 * i)) & 15u;
+      if (bits) atomicOr(&s.above[p >> 5], bits << (p & 31));
+      if (one && eq) atomicOr(&s.equal[p >> 5], eq << (p & 31));
+    }
+    if (!one && __ballot(within != 0u)) {
+      const int inc = spin_wave_inclusive_scan(__popc(within));
+      int to = 0;
+      if (lane == 63) to = atomicAdd(&s.listed, inc);
+      to = __builtin_amdgcn_readlane(to, 63) + inc - __popc(within);
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const float f[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if ((within >> (4 * i + e)) & 1u) {
+            if (to < ROW_LIST) {
+              s.list.key[to] = score_key(f[e]);
+              s.list.id[to] = p0 + i * BLOCK * 4 + e;
+            }
+            ++to;
+          }
+      }
+    }
+  });
+  __syncthreads();
+  unsigned quota = (unsigned)rank;                       // scores equal to the threshold that are wanted
+  if (!one) {
+    constexpr int E = ROW_LIST / BLOCK;
+    const int n = min(s.listed, ROW_LIST);
+    uint32_t key[E], T;
+#pragma unroll
+    for (int j = 0; j < E; ++j) key[j] = tid * E + j < n ? s.list.key[tid * E + j] : 0u;
+    block_kth<BLOCK, E>(key, range_bits<E>(tid * E, 0, n), rank, 0, s.kth, T, quota);
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      if (tid * E + j >= n || key[j] < T) continue;
+      const int p = s.list.id[tid * E + j];
+      atomicOr(key[j] > T ? &s.above[p >> 5] : &s.equal[p >> 5], 1u << (p & 31));
+    }
+  }
+  int first = pl.nf_lo;
+  for (int w0 = 0; w0 < words; w0 += BLOCK) {
+    __syncthreads();
+    const int w = w0 + tid;
+    int at, picked, eq_picked;
+    uint32_t taken = ordered_picks<BLOCK>(w < words ? s.above[w] : 0u, w < words ? s.equal[w] : 0u, quota, s.wtot, at,
+                                          picked, eq_picked);
+    for (at += first; taken; taken &= taken - 1, ++at)
+      if (at < sel_stride) rsel[at] = w * 32 + __ffs((int)taken) - 1;
+    first += picked;
+    quota -= (unsigned)eq_picked;
+  }
 }
+
+// False (for the whole workgroup, nothing stored): more scores than the list holds.
 template <int BLOCK, int MPT, int CAP>
-__device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const float4 (&maxima)[MPT / 4], int gs_log,
-                                             const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
-                                             tiles_lds<BLOCK, CAP> &s) {
+__device__ inline bool list_by_tile_maxima(const float *__restrict__ rs, const uint32_t (&top)[MPT],
+                                           typename key_bits<MPT>::type cand, int t_lo, int t_hi, int gs_log,
+                                           const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
+                                           tiles_lds<BLOCK, CAP> &s) {
   constexpr int NW = BLOCK / 64;
   typedef typename key_bits<MPT>::type M;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int gs = 1 << gs_log, kprime = pl.kprime;
-  if (kprime + (kprime >> 3) + 2 > TILE_LIST) return false;                       // block-uniform
-  const int t_lo = (pl.nf_lo + gs - 1) >> gs_log, t_hi = pl.first_hi >> gs_log;   // tiles of candidates only
-  const int m0 = tid * MPT;
-  uint32_t top[MPT];
-#pragma unroll
-  for (int j = 0; j < MPT / 4; ++j) {
-    top[4 * j] = score_key(maxima[j].x);
-    top[4 * j + 1] = score_key(maxima[j].y);
-    top[4 * j + 2] = score_key(maxima[j].z);
-    top[4 * j + 3] = score_key(maxima[j].w);
-  }
-  const M cand = range_bits<MPT>(m0, t_lo, t_hi);
+  const int gs = 1 << gs_log, kprime = pl.kprime, m0 = tid * MPT;
   uint32_t T0 = 0;
   unsigned need_eq = 0;
   if (t_hi - t_lo >= kprime) block_kth<BLOCK, MPT>(top, cand, kprime, kprime >> 3, s.kth, T0, need_eq);
@@ -627,62 +786,61 @@ __device__ inline bool select_by_tile_maxima(const float *__restrict__ rs, const
   if (nquads <= BLOCK * 3) gather(std::integral_constant<int, 3>());
   else if (nquads <= BLOCK * 5) gather(std::integral_constant<int, 5>());
   else gather(std::integral_constant<int, 8>());
-  if (total <= CAP) {
-    pick_from_list<BLOCK, CAP>(total, kprime, pl.nf_lo, sel_stride, rsel, s);
-    return true;
-  }
-  // More scores than the list holds (ties, or hardly more than k' tiles in all): radix search over the tiles' scores
-  uint32_t prefix = 0;
-  int remaining = kprime;
-  for (int shift = 24; shift >= 0; shift -= 8) {
-    __syncthreads();
-    for (int i = tid; i < 256; i += BLOCK) s.kth.hist[0][i] = 0;
-    __syncthreads();
-    for (int qd = tid; qd < nquads; qd += BLOCK) {
-      float4 v;
-      int p;
-      load_quad(qd, p, v);
-      const uint32_t keep = quad_bits(p, v);
-      const float f[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint32_t k = score_key(f[e]);
-        if (((keep >> e) & 1u) && (shift == 24 || (k >> (shift + 8)) == prefix))
-          atomicAdd(&s.kth.hist[0][(k >> shift) & 255u], 1);
-      }
-    }
-    __syncthreads();
-    int in_digit = 0;
-    const int digit = digit_of_rank(s.kth.hist[0], remaining, in_digit);
-    prefix = (prefix << 8) | (uint32_t)(digit & 255);
-  }
-  int first = pl.nf_lo;
-  unsigned quota = (unsigned)remaining;                // scores equal to the threshold still wanted
-  for (int q0 = 0; q0 < nquads; q0 += BLOCK) {
-    float4 v;
-    int p;
-    load_quad(q0 + tid, p, v);
-    const uint32_t keep = quad_bits(p, v);
-    const float f[4] = {v.x, v.y, v.z, v.w};
-    uint32_t above = 0, equal = 0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t k = score_key(f[e]);
-      above |= k > prefix ? 1u << e : 0u;
-      equal |= k == prefix ? 1u << e : 0u;
-    }
-    __syncthreads();
-    int at, picked, eq_picked;
-    const uint32_t taken = ordered_picks<BLOCK>(above & keep, equal & keep, quota, s.wtot, at, picked, eq_picked);
-    at += first;
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if ((taken >> e) & 1u) {
-        if (at < sel_stride) rsel[at] = p + e;
-        ++at;
-      }
-    first += picked;
-    quota -= (unsigned)eq_picked;
-  }
+  if (total > CAP) return false;
+  pick_from_list<BLOCK, CAP>(total, kprime, pl.nf_lo, sel_stride, rsel, s);
   return true;
+}
+
+// Stores the kprime best candidates ascending at rsel[nf_lo ..].  A row with fewer than k' tiles reads them all; one
+// with more scores above the bound than the list holds is walked whole.
+// `maxima`: the calling thread's MPT of the row (load_tile_maxima, whose loads need not wait for the row's plan).
+template <int MPT>
+__device__ inline void load_tile_maxima(float4 (&v)[MPT / 4], const float *__restrict__ maxima, int maxima_stride) {
+  const int m0 = threadIdx.x * MPT;
+#pragma unroll
+  for (int j = 0; j < MPT / 4; ++j)                    // the stride is a multiple of 4
+    v[j] = m0 + 4 * j < maxima_stride ? *(const float4 *)(maxima + m0 + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
+}
+template <int BLOCK, int MPT, int CAP>
+__device__ inline void select_by_tile_maxima(const float *__restrict__ rs, const float4 (&maxima)[MPT / 4], int gs_log,
+                                             const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
+                                             tiles_row_lds<BLOCK, CAP> &lds) {
+  constexpr int NW = BLOCK / 64;
+  typedef typename key_bits<MPT>::type M;
+  tiles_lds<BLOCK, CAP> &s = lds.tiles;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int gs = 1 << gs_log, kprime = pl.kprime;
+  const int t_lo = (pl.nf_lo + gs - 1) >> gs_log, t_hi = pl.first_hi >> gs_log;   // tiles of candidates only
+  const int m0 = tid * MPT;
+  uint32_t top[MPT];
+#pragma unroll
+  for (int j = 0; j < MPT / 4; ++j) {
+    top[4 * j] = score_key(maxima[j].x);
+    top[4 * j + 1] = score_key(maxima[j].y);
+    top[4 * j + 2] = score_key(maxima[j].z);
+    top[4 * j + 3] = score_key(maxima[j].w);
+  }
+  const M cand = range_bits<MPT>(m0, t_lo, t_hi);
+  // Scores above the bound: all candidates where there is none, else a share of 1 - k'/T of the T tiles holds none, so
+  // that there are about T ln(T / (T - k')) where scores come in no order (k' with the search's slack).
+  const int T = t_hi - t_lo, most = kprime + (kprime >> 3);
+  const bool whole = pl.first_hi - pl.nf_lo > CAP &&                               // block-uniform
+      (most >= T || most + 2 > TILE_LIST ||
+       (float)T * (__builtin_amdgcn_logf((float)T) - __builtin_amdgcn_logf((float)(T - most))) > CAP * 1.4427f);
+  if (whole) {
+    uint32_t kmx = 0u, kmn = 0xffffffffu;
+#pragma unroll
+    for (int j = 0; j < MPT; ++j)
+      if ((cand >> j) & 1u) { kmx = max(kmx, top[j]); kmn = min(kmn, top[j]); }
+    kmx = spin_wave_max_u32(kmx);
+    kmn = spin_wave_min_u32(kmn);
+    if (lane == 0) { s.kth.wmax[wave] = kmx; s.kth.wmin[wave] = kmn; }
+  } else if (list_by_tile_maxima<BLOCK, MPT, CAP>(rs, top, cand, t_lo, t_hi, gs_log, pl, sel_stride, rsel, s)) {
+    return;
+  }
+  __syncthreads();
+  // from the least to the greatest of the tiles' maxima, which block_kth leaves in LDS as well
+  const uint32_t kmx = spin_wave_max_u32(s.kth.wmax[lane % NW]), kmn = spin_wave_min_u32(s.kth.wmin[lane % NW]);
+  __syncthreads();
+  select_whole_row<BLOCK>(rs, min(kmn, kmx), kmx + 1, pl, sel_stride, rsel, lds.row);
 }

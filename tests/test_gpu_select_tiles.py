@@ -14,7 +14,10 @@ DEV = "cuda:0"
 # (partitions, k, sink pages, recent pages) of the longest row; pages of 16 tokens, one partition each
 SIZES = [(16385, 1, 0, 0), (16385, 1024, 15, 17), (16400, 1025, 16, 16), (20000, 1249, 3, 8), (20000, 1300, 3, 8),
          (32768, 2040, 0, 1), (62500, 256, 4, 8), (65535, 3600, 1, 1), (65536, 3700, 0, 0), (65537, 128, 4, 8),
-         (131071, 700, 7, 9), (131072, 40, 0, 16)]
+         (131071, 700, 7, 9), (131072, 40, 0, 16),
+         # k' hardly below, at and beyond the number of tiles, and nearly all partitions: rows that are walked whole
+         (16385, 1000, 0, 0), (16400, 16380, 5, 7), (20000, 6000, 3, 8), (65536, 4095, 0, 0), (65536, 12000, 2, 3),
+         (131072, 8192, 1, 1), (131072, 131000, 3, 0)]
 
 
 @pytest.mark.parametrize("parts,topk,sink,recent", SIZES)
@@ -29,15 +32,37 @@ def test_rows_by_tile_maxima(parts, topk, sink, recent):
     # whole tiles of large scores: every score of the k' tiles is a candidate
     clustered = [np.where(np.arange(len(x)) // 16 % 37 == 5, x + 1000, -x).astype(np.float32) for x in smooth]
     nans = [np.where(rng.random(len(x)) < 0.995, np.nan, x).astype(np.float32) for x in smooth]
+    # most scores lie close together, so that a bin of the first histogram holds more than the list
+    narrow = [np.where(rng.random(len(x)) < 0.01, x * 10, 150 + x / 1000).astype(np.float32) for x in smooth]
     low = [np.where(rng.random(len(x)) < 0.999, -np.inf, np.where(rng.random(len(x)) < 0.5, np.nan, x)).astype(np.float32)
            for x in smooth]
-    for rows in (smooth, ties, equal, clustered, nans, low):
+    for rows in (smooth, ties, equal, clustered, nans, low, narrow):
         _check_select(w, rows)
+
+
+@pytest.mark.parametrize("parts", [20000, 65536])
+def test_time_of_large_selections(parts):
+    """Stage 2 takes longer for a larger k', for the walks over all scores and the longer output, but not by the many
+    times that a path for exceptions costs: the least of 30 launches of k' = half the row's tiles (few scores read)
+    against k' = one and a half times the tiles (all read three times).  Measured 1.5 times; scores re-read per digit,
+    or by each thread a stretch of its own, 3.7 and 10.6 times."""
+    least = []
+    for topk in (parts // 32, parts * 3 // 32):
+        w = synth.config0().with_(num_q_heads=4, num_kv_heads=1, seq_lens=(parts,) * 2, partition_tokens=1,
+                                  score_kind=synth.SCORE_SKETCH, topk=topk, sink_pages=0, recent_pages=0, name="large")
+        layer = runner.build_device_layer(w)[0]
+        layer.step(layer.q0)
+        layer.spin.profile_enable(64)
+        for _ in range(30):
+            layer.spin.select_topk(w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.ws)
+        torch.cuda.synchronize()
+        least.append(layer.spin.profile_read("select")[2])
+    assert least[1] < 2.5 * least[0]
 
 
 # kernel variants by row length and representatives per partition (tiles of 16, 8 and 4 partitions)
 CALLS = [(16385, 1, 120, 1, 1), (20000, 1, 1500, 0, 0), (65536, 1, 2048, 0, 1), (70000, 1, 90, 1, 0),
-         (16400, 2, 300, 2, 21), (17000, 4, 1025, 0, 0), (33000, 4, 200, 3, 5)]
+         (65536, 1, 5000, 0, 1), (20000, 1, 2048, 1, 0), (33000, 4, 9000, 3, 5), (16400, 2, 300, 2, 21), (17000, 4, 1025, 0, 0), (33000, 4, 200, 3, 5)]
 
 
 @pytest.mark.parametrize("parts,reps,topk,sink,recent", CALLS)
