@@ -517,8 +517,7 @@ union tiles_row_lds {
 // over all its scores (a quad per lane and load): a histogram of the keys from `lo` to `hi`, which
 // is repeated inside the bin of the k'-th candidate while that holds too many scores (ties, or a row whose scores lie
 // close together), then one walk that marks the scores above the bin in a bitmap and lists those inside it.
-// No candidate's key is known to be above hi (one that is counts in the last bin); fewer than kprime may reach `lo`,
-// and then the keys below it are searched.
+// No candidate's key reaches `hi`; fewer than kprime may reach `lo`, and then the keys below it are searched.
 // This is the path of rows whose k' tiles hold more scores than a list takes.  The one compute unit is bound by
 // instructions per score: about ten for the histogram, four for the bitmap.  Against a radix search that read the tiles'
 // scores five times and, for k' beyond the tile list, one contiguous stretch of scores per thread: stages 2+3, 2 rows of
@@ -549,11 +548,11 @@ __device__ inline void select_whole_row(const float *__restrict__ rs, uint32_t l
     }
   };
   int rank = pl.kprime;                                  // of the threshold among the keys of [lo, hi)
-  bool open = true;                                      // keys from hi on belong to the last bin
   // settles 12 bits a time, after one walk in vain at most
   for (int pass = 0; pass < 4; ++pass) {
     const int shift = max(20 - __clz((int)(hi - lo - 1)), 0);
-    const uint32_t span = open ? 0xffffffffu - lo : hi - lo, last = (hi - lo - 1) >> shift;
+    const uint32_t span = hi - lo;
+    int same = 0;                                        // of one key: counted by the thread, not one by one in LDS
     for (int i = tid; i < ROW_BINS; i += BLOCK) s.bins[i] = 0;
     __syncthreads();
     walk([&](const float4 (&v)[V], int, uint32_t have) {
@@ -563,10 +562,13 @@ __device__ inline void select_whole_row(const float *__restrict__ rs, uint32_t l
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const uint32_t d = score_key(f[e]) - lo;       // (below lo: wraps to more than any span)
-          if (((have >> (4 * i + e)) & 1u) && d < span) atomicAdd(&s.bins[min(d >> shift, last)], 1);
+          const bool in = ((have >> (4 * i + e)) & 1u) && d < span;
+          if (span == 1) same += in;
+          else if (in) atomicAdd(&s.bins[d >> shift], 1);
         }
       }
     });
+    if (span == 1) atomicAdd(&s.bins[0], same);
     __syncthreads();
     // thread t has the bins from ROW_BINS - 1 - t * BPT down
     constexpr int BPT = ROW_BINS / BLOCK;
@@ -588,15 +590,13 @@ __device__ inline void select_whole_row(const float *__restrict__ rs, uint32_t l
       rank -= total;
       hi = lo;
       lo = 0;
-      open = false;
       continue;
     }
     const int4 f = s.found;
     const uint32_t bin = (uint32_t)__builtin_amdgcn_readfirstlane(f.x);
     rank = __builtin_amdgcn_readfirstlane(f.y);
-    open = open && bin == last;
     lo += bin << shift;
-    hi = open ? 0xffffffffu : lo + min(1u << shift, hi - lo);
+    hi = lo + min(1u << shift, hi - lo);
     if (__builtin_amdgcn_readfirstlane(f.z) <= ROW_LIST || hi - lo == 1) break;
   }
   // key order is float order, but NaN scores, which rank as -inf, fail every comparison
@@ -839,8 +839,12 @@ __device__ inline void select_by_tile_maxima(const float *__restrict__ rs, const
     return;
   }
   __syncthreads();
-  // from the least to the greatest of the tiles' maxima, which block_kth leaves in LDS as well
-  const uint32_t kmx = spin_wave_max_u32(s.kth.wmax[lane % NW]), kmn = spin_wave_min_u32(s.kth.wmin[lane % NW]);
+  // from the least to the greatest of the tiles' maxima, which block_kth leaves in LDS as well; the candidates of the
+  // tiles that straddle either end may be greater
+  uint32_t kmx = spin_wave_max_u32(s.kth.wmax[lane % NW]);
+  const uint32_t kmn = spin_wave_min_u32(s.kth.wmin[lane % NW]);
+  const int p = ((lane & 16 ? t_hi : t_lo - 1) << gs_log) + (lane & (gs - 1));
+  kmx = max(kmx, spin_wave_max_u32(p >= pl.nf_lo && p < pl.first_hi ? score_key(rs[p]) : 0u));
   __syncthreads();
   select_whole_row<BLOCK>(rs, min(kmn, kmx), kmx + 1, pl, sel_stride, rsel, lds.row);
 }

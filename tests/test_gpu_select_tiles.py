@@ -36,7 +36,10 @@ def test_rows_by_tile_maxima(parts, topk, sink, recent):
     narrow = [np.where(rng.random(len(x)) < 0.01, x * 10, 150 + x / 1000).astype(np.float32) for x in smooth]
     low = [np.where(rng.random(len(x)) < 0.999, -np.inf, np.where(rng.random(len(x)) < 0.5, np.nan, x)).astype(np.float32)
            for x in smooth]
-    for rows in (smooth, ties, equal, clustered, nans, low, narrow):
+    # all tiles' maxima alike, and the greatest scores in the tiles that straddle the candidates' ends
+    ends = [np.where((np.arange(len(x)) < 16 * (sink // 16 + 1)) | (np.arange(len(x)) >= len(x) - recent - 16),
+                     np.float32(9) + (x > 150), np.float32(2)).astype(np.float32) for x in smooth]
+    for rows in (smooth, ties, equal, clustered, nans, low, narrow, ends):
         _check_select(w, rows)
 
 
@@ -45,19 +48,22 @@ def test_time_of_large_selections(parts):
     """Stage 2 takes longer for a larger k', for the walks over all scores and the longer output, but not by the many
     times that a path for exceptions costs: the least of 30 launches of k' = half the row's tiles (few scores read)
     against k' = one and a half times the tiles (all read three times).  Measured 1.5 times; scores re-read per digit,
-    or by each thread a stretch of its own, 3.7 and 10.6 times."""
+    or by each thread a stretch of its own, 3.7 and 10.6 times.  Nor for scores that are all the same (1.7 to 2.1
+    times; each counted by itself in one place 9 and 13)."""
     least = []
-    for topk in (parts // 32, parts * 3 // 32):
+    for topk, alike in ((parts // 32, False), (parts * 3 // 32, False), (parts // 32, True)):
         w = synth.config0().with_(num_q_heads=4, num_kv_heads=1, seq_lens=(parts,) * 2, partition_tokens=1,
                                   score_kind=synth.SCORE_SKETCH, topk=topk, sink_pages=0, recent_pages=0, name="large")
         layer = runner.build_device_layer(w)[0]
         layer.step(layer.q0)
+        if alike:
+            layer.scores.fill_(2.0)
         layer.spin.profile_enable(64)
         for _ in range(30):
             layer.spin.select_topk(w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.ws)
         torch.cuda.synchronize()
         least.append(layer.spin.profile_read("select")[2])
-    assert least[1] < 2.5 * least[0]
+    assert max(least[1:]) < 3 * least[0]
 
 
 # kernel variants by row length and representatives per partition (tiles of 16, 8 and 4 partitions)
