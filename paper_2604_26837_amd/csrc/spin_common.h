@@ -86,7 +86,7 @@ static inline int spin_launch_status() {
 
 // host-side bodies of stages 1 and 2, shared by the stage calls and the combined call.
 // maxima != NULL: stage 1 also stores the maximum of every summary tile's scores there, which stage 2 of rows
-// beyond 4096 partitions starts from; maxima_ready: stage 2 finds them in the workspace.
+// beyond 16384 partitions starts from; maxima_ready: stage 2 finds them in the workspace.
 int spin_score_impl(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries, const int32_t *chan_idx,
                     const int32_t *part_offsets, const int32_t *seq_lens, float *scores, void *workspace,
                     void *stream, float *maxima);

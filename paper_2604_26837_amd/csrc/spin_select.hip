@@ -153,9 +153,9 @@ __global__ __launch_bounds__(BLOCK) void spin_select_reg_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Rows that go by their tiles' maxima (select_by_tile_maxima): always beyond 16384 partitions, where the row does not
-// fit the workgroup's registers, and beyond 4096 where stage 1 of the same call has left the maxima.  For scores
-// that come from elsewhere this launch, many workgroups per row, takes them first.
+// Rows that go by their tiles' maxima (select_by_tile_maxima): contexts of 16385 to 131072 partitions, whose rows do not
+// fit the workgroup's registers.  For scores that do not come from stage 1 of the same call this launch, many workgroups
+// per row, takes the maxima first.
 __global__ __launch_bounds__(256) void spin_tile_max_kernel(const float *__restrict__ scores,
                                                             const int32_t *__restrict__ part_offsets, int Hkv,
                                                             int gs_log, float *__restrict__ maxima, int max_stride) {
@@ -288,7 +288,7 @@ extern "C" int spin_select_topk(spin_ctx *ctx, int32_t batch, const float *score
   return spin_select_impl(ctx, batch, scores, part_offsets, seq_lens, sel, nsel, workspace, stream, false, nullptr);
 }
 
-// Stages 1 and 2 in one call: for rows of 4097 to 131072 partitions stage 1 leaves its tiles' maxima for stage 2;
+// Stages 1 and 2 in one call: for contexts of 16385 to 131072 partitions stage 1 leaves its tiles' maxima for stage 2;
 // otherwise the two stages are simply issued one after the other.  Same results as the two calls, bit for bit.
 extern "C" int spin_score_select_topk(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries,
                                       const int32_t *chan_idx, const int32_t *part_offsets,

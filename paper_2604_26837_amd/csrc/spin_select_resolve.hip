@@ -1,8 +1,9 @@
-// Stages 2 and 3 in one launch (all-resident mode; rows of more than 16384
-// partitions take the long-row kernels of stage 2, whose finishing launch resolves).  Both stages work on one row per workgroup, so the workgroup
-// that selected a row resolves it straight away: the same device functions run
-// as in the two stage calls, the results are the same bits, and one launch with
-// its start-up latency chain is saved.
+// Stages 2 and 3 in one launch (all-resident mode; for rows of more than 16384
+// partitions it is the launch that selects by the tiles' maxima, see
+// spin_select_tiles_kernel).  Both stages work on one row per workgroup, so the
+// workgroup that selected a row resolves it straight away: the same device
+// functions run as in the two stage calls, the results are the same bits, and
+// one launch with its start-up latency chain is saved.
 #include "spin_decode_dev.h"
 #include "spin_resolve_dev.h"
 #include "spin_select_dev.h"

@@ -20,12 +20,12 @@ def _workloads():
         # the same with the sink / recent pages attended beside stages 2+3 (their partial travels through the workspace)
         "pages_forced_split": (c0.with_(seq_lens=(4096, 1000, 2049, 30), num_q_heads=8, num_kv_heads=2, topk=24,
                                         sink_pages=2, recent_pages=3, name="graph_forced"), "step3f"),
-        # token partitions, rows long enough for the two-launch selection (its histogram lives in the
-        # workspace and must be left cleared by every replay), partial page masks in the attention
+        # token partitions, rows long enough for the selection by tile maxima (which live in the workspace
+        # and are written anew by every replay), partial page masks in the attention
         "long_token_rows": (c0.with_(seq_lens=(20000, 17001), num_q_heads=8, num_kv_heads=2, partition_tokens=1,
                                      score_kind=synth.SCORE_SKETCH, topk=300, sink_pages=1, recent_pages=1,
                                      name="graph_tokens"), "step"),
-        # the same rows with stages 1+2 in one call: stage 1 fills the histogram stage 2 clears
+        # the same rows with stages 1+2 in one call: stage 1 stores the maxima that stage 2 reads
         "long_token_rows_stage12_call": (c0.with_(seq_lens=(20000, 17001), num_q_heads=8, num_kv_heads=2,
                                                   partition_tokens=1, score_kind=synth.SCORE_SKETCH, topk=300,
                                                   sink_pages=1, recent_pages=1, name="graph_tokens12"), "step12"),

@@ -1,8 +1,8 @@
 """Stages 1 and 2 in one call must give exactly what the two stage calls give:
 same score bits, same selection.  Rows of more than 16384 partitions take the path where
-stage 1 counts the leading key bits for stage 2 (the histogram in the workspace must be
-left cleared, so the calls are repeated and interleaved); every other shape
-simply runs the two stages."""
+stage 1 stores the maxima of its score tiles for stage 2 (a call must not depend on the maxima
+that another left in the workspace, so the calls are repeated and interleaved); every other
+shape simply runs the two stages."""
 import numpy as np
 import pytest
 import torch
@@ -18,7 +18,7 @@ def _workloads():
     c0 = synth.config0()
     tok = dict(num_q_heads=8, num_kv_heads=2, partition_tokens=1, score_kind=synth.SCORE_SKETCH)
     return {
-        # two-launch selection: histogram taken by stage 1
+        # selection by the tiles' maxima, which stage 1 stores
         "long_token_rows": c0.with_(seq_lens=(20000, 17001, 65536), topk=300, sink_pages=1, recent_pages=2,
                                     name="ss_long", **tok),
         "long_rows_no_forced": c0.with_(seq_lens=(40000, 16400), topk=1024, sink_pages=0, recent_pages=0,
@@ -26,7 +26,7 @@ def _workloads():
         # one short request in a context sized for long rows; k' = 0 for the request that is all forced
         "long_context_short_rows": c0.with_(seq_lens=(100, 32, 17000), topk=40, sink_pages=1, recent_pages=1,
                                             name="ss_mixed", **tok),
-        # long rows of page partitions: stage 1 of the other two score kinds counts the histogram too
+        # long rows of page partitions: stage 1 of the other two score kinds stores the maxima too
         "long_page_rows_minmax": c0.with_(seq_lens=(16 * 17000 + 5, 300000, 900), num_q_heads=4, num_kv_heads=1,
                                           topk=200, sink_pages=3, recent_pages=6, name="ss_long_minmax"),
         "long_page_rows_repmax": c0.with_(seq_lens=(270000, 16 * 16385), num_q_heads=6, num_kv_heads=2,
@@ -89,8 +89,8 @@ def test_combined_call_equals_the_two_stage_calls(name):
 
 @pytest.mark.parametrize("name", ["long_token_rows", "long_page_rows_minmax", "long_page_rows_repmax"])
 def test_combined_call_saves_the_histogram_launch(name):
-    """For long rows the combined call issues no histogram launch over the score array (stage 1 has counted
-    the bins), the separate stage 2 call issues one."""
+    """For long rows the combined call issues no launch over the score array ahead of the selection (stage 1 has
+    stored the tiles' maxima), the separate stage 2 call issues one."""
     w = _workloads()[name]
     data = synth.generate(w)
     natural = torch.from_numpy(data.pool_bits.view(np.int16).copy()).to(DEV).view(torch.bfloat16)
@@ -116,7 +116,8 @@ def test_combined_call_saves_the_histogram_launch(name):
 
 
 def _heavy_ties(layer, w):
-    """Scores that send a long row down the multi-pass fallback: a handful of distinct values."""
+    """Scores of which more reach the bound than a list holds, so that a long row is walked whole: a handful of
+    distinct values."""
     rng = np.random.default_rng(11)
     vals = rng.choice(np.array([0.5, 0.5, 0.25, 1.0], dtype=np.float32), size=layer.scores.numel())
     return torch.from_numpy(vals).to(DEV)
@@ -124,8 +125,8 @@ def _heavy_ties(layer, w):
 
 @pytest.mark.parametrize("name", list(_workloads()))
 def test_stages_1_to_3_in_one_call_equal_the_stage_calls(name):
-    """spin_score_select_resolve (and spin_select_resolve on its own, also for long rows and for rows that take
-    stage 2's multi-pass fallback) against the separate stage calls: every output identical."""
+    """spin_score_select_resolve (and spin_select_resolve on its own, also for long rows and for rows that
+    stage 2 walks whole) against the separate stage calls: every output identical."""
     w = _workloads()[name]
     data = synth.generate(w)
     natural = torch.from_numpy(data.pool_bits.view(np.int16).copy()).to(DEV).view(torch.bfloat16)
