@@ -162,11 +162,12 @@ bool gather_arguments(const char *kinds, const char *names, PyObject *const *arg
     }
     PyObject *o = args[at++];
     if (kind == 'n') {
-      if (!PyLong_Check(o)) {
+      if (!PyIndex_Check(o)) {            // (numpy's integers and tensors of one integer are none of Python's)
         PyErr_Format(PyExc_TypeError, "an integer is wanted, got %R", o);
         return false;
       }
       value[i] = (int64_t)PyLong_AsUnsignedLongLongMask(o);
+      if (value[i] == -1 && PyErr_Occurred()) return false;
       continue;
     }
     tensor_info t = {0, 0, 0, 0};

@@ -1,6 +1,7 @@
 """What the stage calls refuse before anything is launched: tensors that are not on the GPU, not contiguous or of
 another type than documented, and arguments that are no tensors or no integers; a tensor subclass is as good as a
 plain tensor."""
+import numpy as np
 import pytest
 import torch
 
@@ -20,9 +21,21 @@ def test_refusals_without_a_gpu():
         sp.sparse_decode(1, None, None, t, t, t, t, t, t)                 # a pool has a size, so it has to be there
     with pytest.raises(AttributeError):
         sp.select_topk(1, [1.0], t, t, t, t, t)
-    for batch in (1.0, "1", None):
+    for batch in (1.0, "1", None, np.float32(1), torch.tensor(1.0), torch.tensor([1, 1])):
         with pytest.raises(TypeError):
             sp.select_topk(batch, t.float(), t, t, t, t, t)
+
+
+def test_integers_of_any_kind():
+    """A batch or a step is often an element of a numpy array or of a tensor: it is as good as Python's integer (the
+    call goes on to the tensors behind it)."""
+    sp = _spin()
+    t = torch.zeros(64, dtype=torch.int32)
+    for one in (1, np.int32(1), np.int64(1), np.uint8(1), torch.tensor(1), np.array([1])[0]):
+        with pytest.raises(ValueError, match="scores must live on the GPU"):
+            sp.select_topk(one, t.float(), t, t, t, t, t)
+        with pytest.raises(ValueError, match="sel must live on the GPU"):
+            sp.resolve_slots(one, one, t, t, t, t, t, t, t, t, t, t)
 
 
 @pytest.mark.gpu
@@ -36,7 +49,10 @@ def test_refusals_and_subclasses_on_the_gpu():
     sp.select_topk(0, None, None, None, None, None, None)                 # an empty batch is nothing to do
     with pytest.raises(binding.SpinError):
         sp.select_topk(w.batch + 1, None, None, None, None, None, None)   # more than max_batch
-    args = [w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.ws]
+    sp.select_topk(np.int64(0), None, None, None, None, None, None)
+    with pytest.raises(binding.SpinError):
+        sp.select_topk(np.int32(-1), None, None, None, None, None, None)
+    args = [np.int64(w.batch), layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.ws]
     for at, bad, text in ((1, layer.scores.half(), "scores must be torch.float32, got torch.float16"),
                           (2, layer.part_offsets.long(), "part_offsets must be torch.int32, got torch.int64"),
                           (4, layer.sel.t().expand(-1, w.rows), "sel must be contiguous"),
