@@ -10,8 +10,9 @@
 //
 // Latency bounds it.  A representative's keys were read token by token, each behind its own walk through the page
 // table; now lanes walk its pages side by side, the new token's among them, and the keys of four pages are asked for
-// at once and added up in the same order.  Last token of a partition with one representative, 32 rows, a launch after
-// the other: 128 tokens 36.1 -> 6.8 us, 64 tokens 19.3 -> 5.4.
+// at once and added up in the same order; pages without tokens before the new one are passed over, so that the first
+// token of a sub-range costs no more than it did.  A partition with one representative, 128 rows, a launch after the
+// other: token 0 / 3 / 15 / 64 / 127 of it 2.9 / 3.7 / 6.8 / 19.9 / 36.5 -> 2.9 / 3.8 / 3.8 / 4.9 / 5.9 us.
 #include "spin_common.h"
 
 __device__ inline size_t k_elem(int token_major, int t, int d) { return ((size_t)spin_k_unit(token_major, t, d >> 3) << 3) + (d & 7); }
@@ -33,7 +34,7 @@ __global__ __launch_bounds__(128) void spin_append_kernel(
     const uint16_t *__restrict__ k_new, const uint16_t *__restrict__ v_new, const int32_t *__restrict__ seq_lens,
     uint16_t *pool, int64_t pool_slots, const int32_t *__restrict__ dir, const int32_t *__restrict__ leaf_pool,
     int64_t leaf_chunks, const int32_t *__restrict__ part_offsets, const int32_t *__restrict__ chan,
-    uint16_t *summ, int Hkv, int tp, int kind, int reps, int dir_stride, int leaf_entries, int k_token_major,
+    uint16_t *summ, int Hkv, int tp, int kind, int reps, int sub, int dir_stride, int leaf_entries, int k_token_major,
     int32_t *status) {
   const int row = blockIdx.x, d = threadIdx.x;
   const int b = row / Hkv, h = row - b * Hkv;
@@ -44,17 +45,17 @@ __global__ __launch_bounds__(128) void spin_append_kernel(
     if (d == 0) spin_raise(status, SPIN_ERR_INVALID);
     return;
   }
-  // representative: the sub-range the token lands in starts at t0; lane i of either wavefront holds the slot of its
-  // i-th page (the token's own is page `last`)
-  const int sub = kind == SPIN_SCORE_REPMAX ? tp / reps : 1;
-  const int r = kind == SPIN_SCORE_REPMAX ? (t - p * tp) / sub : 0;
-  const int t0 = p * tp + r * sub, first = t0 >> 4, last = (t >> 4) - first, lane = d & 63;
-  int32_t mine = -1;
-  if (kind == SPIN_SCORE_REPMAX && lane <= last)
+  // representative: the sub-range of `sub` tokens that the new one lands in starts at t0; lane i of either wavefront
+  // holds the slot of its i-th page (the token's own is page `last`; in the first page one walk on scalars serves)
+  const int at = kind == SPIN_SCORE_REPMAX ? t / sub : t;
+  const int r = at - p * reps, t0 = kind == SPIN_SCORE_REPMAX ? at * sub : t;
+  const int first = t0 >> 4, last = (t >> 4) - first, lane = d & 63;
+  int32_t mine = -1, slot;
+  if (last > 0 && lane <= last)
     mine = spin_walk(dir, leaf_pool, leaf_chunks, row, dir_stride, leaf_entries, first + lane);
-  const int32_t slot = kind == SPIN_SCORE_REPMAX && last < 64
-                           ? __builtin_amdgcn_readlane(mine, last)
-                           : spin_walk(dir, leaf_pool, leaf_chunks, row, dir_stride, leaf_entries, t >> 4);
+  if (last > 0 && last < 64) slot = __builtin_amdgcn_readlane(mine, last);
+  else slot = spin_walk(dir, leaf_pool, leaf_chunks, row, dir_stride, leaf_entries, t >> 4);
+  if (last == 0) mine = slot;
   if (slot < 0 || (int64_t)slot >= pool_slots) {
     if (d == 0) spin_raise(status, SPIN_ERR_NOT_RESIDENT);
     return;
@@ -81,7 +82,7 @@ __global__ __launch_bounds__(128) void spin_append_kernel(
   } else {
     // representative of the sub-range the token lands in: mean of its keys so far
     double acc = (double)spin_bf16_to_f32(kb);
-    for (int j = 0; j <= last; j += 4) {
+    for (int j = 0; t0 < t && j <= last; j += 4) {
       if (j && (j & 63) == 0)
         mine = j + lane <= last
                    ? spin_walk(dir, leaf_pool, leaf_chunks, row, dir_stride, leaf_entries, first + j + lane) : -1;
@@ -90,7 +91,7 @@ __global__ __launch_bounds__(128) void spin_append_kernel(
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         // pages that hold tokens before the new one
-        const bool wanted = j + i <= last && (first + j + i) * SPIN_PAGE_TOKENS < t && t0 < t;
+        const bool wanted = j + i <= last && (first + j + i) * SPIN_PAGE_TOKENS < t;
         const int32_t s2 = __builtin_amdgcn_readlane(mine, (j + i) & 63);
         there[i] = wanted && s2 >= 0 && (int64_t)s2 < pool_slots;
         if (there[i]) {
@@ -102,12 +103,18 @@ __global__ __launch_bounds__(128) void spin_append_kernel(
         }
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < 4; ++i) {
+        if (!there[i]) continue;                           // uniform, as are the page's bounds
+        const int u0 = (first + j + i) * SPIN_PAGE_TOKENS, lo = t0 - u0, hi = t - u0;
+        if (lo <= 0 && hi >= SPIN_PAGE_TOKENS) {
 #pragma unroll
-        for (int x = 0; x < SPIN_PAGE_TOKENS; ++x) {
-          const int u = (first + j + i) * SPIN_PAGE_TOKENS + x;
-          if (there[i] && u >= t0 && u < t) acc += (double)spin_bf16_to_f32(key[i][x]);
+          for (int x = 0; x < SPIN_PAGE_TOKENS; ++x) acc += (double)spin_bf16_to_f32(key[i][x]);
+        } else {
+#pragma unroll
+          for (int x = 0; x < SPIN_PAGE_TOKENS; ++x)
+            if (x >= lo && x < hi) acc += (double)spin_bf16_to_f32(key[i][x]);
         }
+      }
     }
     const uint16_t m = f64_to_bf16(acc / (double)(t - t0 + 1));
     const size_t R = (base + p) * reps;
@@ -135,7 +142,8 @@ extern "C" int spin_append_kv(spin_ctx *ctx, int32_t batch, const void *k_new, c
   spin_launch(ctx, SPIN_K_APPEND, spin_append_kernel, dim3((unsigned)rows), dim3(128), 0, (hipStream_t)stream,
               (const uint16_t *)k_new, (const uint16_t *)v_new, seq_lens, (uint16_t *)kv_pool, pool_slots, dir,
               leaf_pool, leaf_chunks, part_offsets, chan_idx, (uint16_t *)summaries, c.num_kv_heads,
-              c.partition_tokens, c.score_kind, c.reps_per_partition, ctx->dir_stride, c.leaf_entries,
+              c.partition_tokens, c.score_kind, c.reps_per_partition,
+              c.score_kind == SPIN_SCORE_REPMAX ? c.partition_tokens / c.reps_per_partition : 1, ctx->dir_stride, c.leaf_entries,
               ctx->k_token_major, (int32_t *)workspace);
   return spin_launch_status();
 }
