@@ -45,10 +45,13 @@ extern "C" int spin_copy_misses_host(spin_ctx *ctx, int32_t batch, const void *h
 }
 
 #define GATHER_WAVES 4
-// Workgroups of a copy launch.  The host link is the limit and 64 wavefronts with a page each in flight fill it; more
-// requests at a time slow it down (64 rows that miss 1010 pages: 4 / 8 / 12 / 16 / 32 / 64 / 128 / 256 workgroups ->
-// 250 / 167 / 165 / 163-165 / 166 / 166 / 180 / 199 us) and crowd the units that other launches could use meanwhile.
+// Workgroups of a copy launch.  The host link is the limit and, for reads of host memory, 64 wavefronts with a page each
+// in flight fill it; more requests at a time slow it down (64 rows that miss 1010 pages: 4 / 8 / 12 / 16 / 32 / 64 / 128 /
+// 256 workgroups -> 250 / 167 / 165 / 163-165 / 166 / 166 / 180 / 199 us) and crowd the units that other launches could use
+// meanwhile.  Writes to host memory want more (16 / 32 / 64 workgroups: 256 pages 45.6 / 43.1 / 41.7 us, 512 pages
+// 88.3 / 83.1 / 80.5, 1024 pages 167 / 160 / 156; from 4000 pages on they are alike).
 #define GATHER_MAX_WGS 16
+#define OFFLOAD_MAX_WGS 64
 #define GATHER_ROWS 1024   // rows whose miss counts a workgroup holds as prefix sums at a time
 
 struct host_map {
@@ -100,7 +103,7 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void spin_gather_kernel(
     }
     __syncthreads();
     for (; item < total; item += nwaves) {
-      int lo = 0, hi = GATHER_ROWS - 1;                // the first row whose pages end behind `item`
+      int lo = 0, hi = min(rows - row0, GATHER_ROWS) - 1;   // the first row whose pages end behind `item`
       while (lo < hi) {
         const int mid = (lo + hi) >> 1;
         if (s_end[mid] > item) hi = mid; else lo = mid + 1;
@@ -136,9 +139,9 @@ __global__ __launch_bounds__(GATHER_WAVES * 64) void spin_gather_kernel(
   }
 }
 
-static unsigned gather_workgroups(int64_t most_pages) {
+static unsigned copy_workgroups(int64_t most_pages, int64_t most_wgs) {
   const int64_t wgs = (most_pages + GATHER_WAVES - 1) / GATHER_WAVES;
-  return (unsigned)(wgs < GATHER_MAX_WGS ? wgs : GATHER_MAX_WGS);
+  return (unsigned)(wgs < most_wgs ? wgs : most_wgs);
 }
 
 extern "C" int spin_gather_misses(spin_ctx *ctx, int32_t batch, const void *host_kv, const int64_t *row_base,
@@ -149,7 +152,8 @@ extern "C" int spin_gather_misses(spin_ctx *ctx, int32_t batch, const void *host
   if (!host_kv || !row_base || !nmiss || !miss_pages || !miss_slots || !kv_pool) return SPIN_ERR_INVALID;
   if (!workspace) return SPIN_ERR_WORKSPACE;
   const int rows = batch * ctx->cfg.num_kv_heads;
-  spin_launch(ctx, SPIN_K_GATHER, spin_gather_kernel<false>, dim3(gather_workgroups((int64_t)rows * ctx->page_stride)), dim3(GATHER_WAVES * 64), 0,
+  spin_launch(ctx, SPIN_K_GATHER, spin_gather_kernel<false>,
+              dim3(copy_workgroups((int64_t)rows * ctx->page_stride, GATHER_MAX_WGS)), dim3(GATHER_WAVES * 64), 0,
               (hipStream_t)stream, (uint4 *)const_cast<void *>(host_kv), row_base, nmiss, miss_pages, miss_slots,
               (uint4 *)kv_pool, pool_slots, ctx->page_stride, rows, (int32_t *)workspace,
               host_map{ctx->cpu_table, ctx->cpu_table_entries, ctx->cpu_pages});
@@ -164,7 +168,8 @@ extern "C" int spin_offload_pages(spin_ctx *ctx, int32_t batch, const void *kv_p
   if (!host_kv || !row_base || !count || !pages || !slots || !kv_pool) return SPIN_ERR_INVALID;
   if (!workspace) return SPIN_ERR_WORKSPACE;
   const int rows = batch * ctx->cfg.num_kv_heads;
-  spin_launch(ctx, SPIN_K_OFFLOAD, spin_gather_kernel<true>, dim3(gather_workgroups((int64_t)rows * ctx->page_stride)), dim3(GATHER_WAVES * 64), 0,
+  spin_launch(ctx, SPIN_K_OFFLOAD, spin_gather_kernel<true>,
+              dim3(copy_workgroups((int64_t)rows * ctx->page_stride, OFFLOAD_MAX_WGS)), dim3(GATHER_WAVES * 64), 0,
               (hipStream_t)stream, (uint4 *)host_kv, row_base, count, pages, slots,
               (uint4 *)const_cast<void *>(kv_pool), pool_slots, ctx->page_stride, rows, (int32_t *)workspace,
               host_map{ctx->cpu_table, ctx->cpu_table_entries, ctx->cpu_pages});
