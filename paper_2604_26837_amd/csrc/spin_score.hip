@@ -40,7 +40,9 @@ __global__ __launch_bounds__(WAVES * 64) void spin_score_k32_single_kernel(
   score_row_single_tile<NJ, MINMAX, WAVES>(q, summ, part_offsets, Hq, Hkv, G, rows_per_part, row, chunk, scores, tm);
 }
 
-// SKETCH: one 16x16x16 instruction per tile of 16 tokens (512 bytes).
+// SKETCH: one 16x16x16 instruction per tile of 16 tokens (512 bytes).  MAXIMA: tm.at is there (asked for at
+// run time, it slows the loop: 16 rows of 16000 tokens, groups of 16, 10.0 -> 10.9 us).
+template <bool MAXIMA>
 __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
     const uint16_t *__restrict__ q, const uint2 *__restrict__ summ, const int32_t *__restrict__ chan,
     const int32_t *__restrict__ part_offsets, int Hq, int Hkv, int G, int tiles_per_wg, int wgs_per_row,
@@ -88,7 +90,7 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
       s = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qf, __builtin_bit_cast(spin_s16x4, a[u]), s, 0, 0, 0);
       const float m = spin_head_max(s, c, G);   // lane (n, c): heads 4c+i of token n
       if (c == 0) scores[base + (size_t)(t0 + u) * 16 + n] = m;
-      if (tm.at) {                              // uniform
+      if (MAXIMA) {
         const float top = spin_row16_max(m);
         if (lane == 0 && t0 + u < tm.stride) tm.at[(size_t)row * tm.stride + t0 + u] = top;
       }
@@ -246,7 +248,8 @@ int spin_score_impl(spin_ctx *ctx, int32_t batch, const void *q, const void *sum
   dim3((unsigned)rows * wgs), dim3(SCORE_WAVES * 64), 0, st, (const uint16_t *)q, (const UNIT *)summaries, chan_idx, \
       part_offsets, c.num_q_heads, c.num_kv_heads, ctx->group, tiles_per_wg, wgs, scores, tm
     if (four) spin_launch(ctx, SPIN_K_SCORE, spin_score_sketch4_kernel, SPIN_SKETCH_ARGS(uint4));
-    else spin_launch(ctx, SPIN_K_SCORE, spin_score_sketch_kernel, SPIN_SKETCH_ARGS(uint2));
+    else if (maxima) spin_launch(ctx, SPIN_K_SCORE, spin_score_sketch_kernel<true>, SPIN_SKETCH_ARGS(uint2));
+    else spin_launch(ctx, SPIN_K_SCORE, spin_score_sketch_kernel<false>, SPIN_SKETCH_ARGS(uint2));
 #undef SPIN_SKETCH_ARGS
   }
   return spin_launch_status();
