@@ -103,13 +103,14 @@ struct kth_lds {
 // all, spreads the first histogram over many bins instead of piling every key onto one LDS counter.  Every
 // wavefront scans the 256 bins for itself: one barrier per digit.  A workgroup barrier must lie between two
 // uses of the same kth_lds.
-// MANY (a row's scores, 16 or more per thread): those of a bell-shaped row still share a dozen first digits, so a
+// MANY and `many` (a row's scores, 16 per thread): those of a bell-shaped row still share a dozen first digits, so a
 // thread counts its keys of the eight largest in a register, and the others only where the k-th is among them.  Stage 2
-// of 8 rows of 16384 normal scores, k 2048 / 8192: 14.1 / 15.9 us, with one LDS addition per score 22.7 / 24.1; of scores
-// spread over many digits the detour costs up to 2.5 us (almost all close together, k 8192: 37.8 -> 40.3).
+// of 8 rows of 16384 normal scores, k 2048 / 8192: 14.3 / 16.0 us, with one LDS addition per score 22.7 / 24.1; of scores
+// spread over many digits the detour costs up to 2.5 us (almost all close together, k 8192: 37.8 -> 40.2), and with few
+// keys the additions are the shorter way (256 ragged rows, below 4096 of them: step 142.6 us against 144.9).
 template <int BLOCK, int KPT, bool MANY = false>
 __device__ inline void block_kth(const uint32_t (&key)[KPT], typename key_bits<KPT>::type valid, int k, int slack,
-                                 kth_lds<BLOCK> &s, uint32_t &T, unsigned &need_eq) {
+                                 kth_lds<BLOCK> &s, uint32_t &T, unsigned &need_eq, bool many = false) {
   constexpr int NW = BLOCK / 64;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   for (int i = tid; i < 4 * 256; i += BLOCK) (&s.hist[0][0])[i] = 0;
@@ -131,33 +132,17 @@ __device__ inline void block_kth(const uint32_t (&key)[KPT], typename key_bits<K
     if (hi <= 0) break;                                  // block-uniform
     const int lo = max(hi - 8, 0), width = hi - lo;
     const uint32_t dmask = (1u << width) - 1u;
-    int in_digit = 0, digit;
-    auto look_up = [&]() {
-      __syncthreads();
-      if (BLOCK >= 1024) {
-        if (wave == 0) {
-          digit = digit_of_rank(s.hist[pass], remaining, in_digit);
-          if (lane == 0) s.found[pass] = make_int4(digit, remaining, in_digit, 0);
-        }
-        __syncthreads();
-        const int4 f = s.found[pass];
-        digit = __builtin_amdgcn_readfirstlane(f.x);
-        remaining = __builtin_amdgcn_readfirstlane(f.y);
-        in_digit = __builtin_amdgcn_readfirstlane(f.z);
-      } else {
-        digit = digit_of_rank(s.hist[pass], remaining, in_digit);
-      }
-    };
-    if (MANY && pass == 0) {
-      const uint32_t top = (kmx >> lo) & dmask;            // the largest digit there is
+    [[maybe_unused]] const bool ahead = MANY && pass == 0 && many;   // block-uniform
+    [[maybe_unused]] const uint32_t top = (kmx >> lo) & dmask;       // in the first pass the largest digit there is
+    if (MANY && ahead) {
       unsigned long long acc = 0;                          // byte o: keys whose digit is top - o
 #pragma unroll
       for (int j = 0; j < KPT; ++j) {
         const uint32_t o = top - ((key[j] >> lo) & dmask);
         if (((valid >> j) & 1u) && o < 8u) acc += 1ull << (8u * o);
       }
-      // 16 bits each, of which a wavefront's sum needs 13 (64 keys per thread)
-      static_assert(KPT <= 255, "a thread's count fits a byte, a wavefront's 16 bits");
+      // 16 bits each, of which a wavefront's sum needs 11
+      static_assert(!MANY || KPT <= 255, "a thread's count fits a byte, a wavefront's 16 bits");
       uint32_t part[4] = {(uint32_t)acc & 0x00ff00ffu, (uint32_t)(acc >> 8) & 0x00ff00ffu,
                           (uint32_t)(acc >> 32) & 0x00ff00ffu, (uint32_t)(acc >> 40) & 0x00ff00ffu};
 #pragma unroll
@@ -170,22 +155,38 @@ __device__ inline void block_kth(const uint32_t (&key)[KPT], typename key_bits<K
           if (part[i] >> 16) atomicAdd(&s.hist[0][top - o - 2], (int)(part[i] >> 16));
         }
       }
-      look_up();
-      if (digit < 0) {                                     // block-uniform: below them
+    } else {
+#pragma unroll
+      for (int j = 0; j < KPT; ++j)
+        if (((valid >> j) & 1u) && (pass == 0 || (key[j] >> hi) == prefix))
+          atomicAdd(&s.hist[pass][(key[j] >> lo) & dmask], 1);
+    }
+    __syncthreads();
+    int in_digit = 0, digit;
+    if (BLOCK >= 1024) {
+      if (wave == 0) {
+        digit = digit_of_rank(s.hist[pass], remaining, in_digit);
+        if (lane == 0) s.found[pass] = make_int4(digit, remaining, in_digit, 0);
+      }
+      __syncthreads();
+      const int4 f = s.found[pass];
+      digit = __builtin_amdgcn_readfirstlane(f.x);
+      remaining = __builtin_amdgcn_readfirstlane(f.y);
+      in_digit = __builtin_amdgcn_readfirstlane(f.z);
+    } else {
+      digit = digit_of_rank(s.hist[pass], remaining, in_digit);
+    }
+    if constexpr (MANY) {
+      if (ahead && digit < 0) {                            // below the eight
         __syncthreads();                                   // (every wavefront has read the bins)
 #pragma unroll
         for (int j = 0; j < KPT; ++j) {
           const uint32_t dg = (key[j] >> lo) & dmask;
           if (((valid >> j) & 1u) && top - dg >= 8u) atomicAdd(&s.hist[0][dg], 1);
         }
-        look_up();
+        __syncthreads();
+        digit = digit_of_rank(s.hist[0], remaining, in_digit);
       }
-    } else {
-#pragma unroll
-      for (int j = 0; j < KPT; ++j)
-        if (((valid >> j) & 1u) && (pass == 0 || (key[j] >> hi) == prefix))
-          atomicAdd(&s.hist[pass][(key[j] >> lo) & dmask], 1);
-      look_up();
     }
     if (digit < 0) break;                                // fewer than k valid keys: not a call this function takes
     prefix = (prefix << width) | (uint32_t)digit;
@@ -308,6 +309,7 @@ __device__ inline void select_elements(const float (&f)[KPT], typename key_bits<
   typedef typename key_bits<KPT>::type M;
   [[maybe_unused]] constexpr int NW = BLOCK / 64;
   [[maybe_unused]] const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int total = 0;                                 // candidates left (counted where there is a list)
   M valid = cand;
   if (bound > SPIN_KEY_MINUS_INF) {            // (at -inf NaN scores, which rank there, would fail the comparison)
     const float bf = key_floor_score(bound, true);
@@ -324,7 +326,6 @@ __device__ inline void select_elements(const float (&f)[KPT], typename key_bits<
     const int inc = spin_wave_inclusive_scan(mine);
     if (lane == 63) s.wtot[wave].x = (unsigned)inc;
     __syncthreads();
-    int total;
     const int before = spin_waves_before<NW>((int)s.wtot[lane % NW].x, wave, total) + inc - mine;
     if (total <= CAP) {                          // block-uniform
       if (valid) {
@@ -345,7 +346,7 @@ __device__ inline void select_elements(const float (&f)[KPT], typename key_bits<
   uint32_t key[KPT];
 #pragma unroll
   for (int k = 0; k < KPT; ++k) key[k] = score_key(f[k]);
-  block_kth<BLOCK, KPT, (KPT >= 16)>(key, valid, kprime, 0, s.kth, T, need_eq);
+  block_kth<BLOCK, KPT, KPT == 16>(key, valid, kprime, 0, s.kth, T, need_eq, total >= 4096);
   M gt = 0, eq = 0;
 #pragma unroll
   for (int k = 0; k < KPT; ++k) {
