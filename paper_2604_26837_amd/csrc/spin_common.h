@@ -145,6 +145,17 @@ __device__ inline uint4 spin_nt_load(const uint4 *p) {
   return __builtin_bit_cast(uint4, __builtin_nontemporal_load((const spin_u32x4 *)p));
 }
 
+// A buffer of `bytes` bytes at a uniform address, and 16 bytes a lane from it, non-temporal.  A lane whose offset lies
+// beyond the buffer reads zeros and moves nothing, so a load that some lanes or some passes of a loop do without needs
+// no branch.  That is what software pipelines are written with here: where loads under way are joined by a path without
+// them, the compiler has to assume the path with the fewest, and waits for the ones just issued along with those it needs.
+__device__ inline __amdgpu_buffer_rsrc_t spin_buffer(const void *p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
+}
+__device__ inline uint4 spin_buffer_load(__amdgpu_buffer_rsrc_t buf, uint32_t lane_offset, uint32_t offset) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)lane_offset, (int)offset, 2 /* nt */));
+}
+
 typedef __attribute__((ext_vector_type(2))) unsigned int spin_u32x2;
 __device__ inline uint2 spin_nt_load2(const uint2 *p) {
   return __builtin_bit_cast(uint2, __builtin_nontemporal_load((const spin_u32x2 *)p));

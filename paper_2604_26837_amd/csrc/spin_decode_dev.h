@@ -10,34 +10,21 @@ struct page_regs {
   uint4 k[4], v[4];
 };
 
-// Loads of a page.  A page whose mask is not full (token partitions, the ragged last page) only
-// fetches what its attended tokens need: in the K tile a lane holds 16 bytes of ONE token, in
-// the V tile 16 bytes of ONE token quad, so lanes of unattended tokens / quads issue no load
-// and hold zeros (their logits are masked and their probabilities are exactly zero, so the
-// result has the same bits as with the whole page loaded).
-__device__ inline void load_page(page_regs &r, const uint4 *__restrict__ pool, int slot, int lane, unsigned mask) {
-  const uint4 *kp = pool + (size_t)slot * SPIN_SLOT_U4 + lane;
-  if (mask == 0xffffu) {
+// The tiles of a page.  Only what its attended tokens need is fetched: in the K tile a lane holds 16 bytes of ONE token,
+// in the V tile 16 bytes of ONE token quad, so lanes of unattended tokens / quads (all of them for an empty mask) are
+// sent beyond the slot and hold zeros (their logits are masked and their probabilities are exactly zero, so the
+// result has the same bits as with the whole page loaded).  `slot` and `mask` are uniform.
+__device__ __forceinline__ void load_k_tile(page_regs &r, const uint4 *__restrict__ pool, int slot, int lane, unsigned mask) {
+  const __amdgpu_buffer_rsrc_t buf = spin_buffer(pool + (size_t)slot * SPIN_SLOT_U4, SPIN_SLOT_U4 * 16);
+  const uint32_t at = ((mask >> (lane & 15)) & 1u) ? (uint32_t)lane * 16 : SPIN_SLOT_U4 * 16;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) r.k[j] = spin_nt_load(kp + j * 64);
+  for (int j = 0; j < 4; ++j) r.k[j] = spin_buffer_load(buf, at, j * 1024);
+}
+__device__ __forceinline__ void load_v_tile(page_regs &r, const uint4 *__restrict__ pool, int slot, int lane, unsigned mask) {
+  const __amdgpu_buffer_rsrc_t buf = spin_buffer(pool + (size_t)slot * SPIN_SLOT_U4, SPIN_SLOT_U4 * 16);
+  const uint32_t at = ((mask >> (4 * (lane >> 4))) & 0xfu) ? (uint32_t)lane * 16 : SPIN_SLOT_U4 * 16;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) r.v[j] = spin_nt_load(kp + SPIN_KTILE_U4 + j * 64);
-  } else {
-    const bool kneed = (mask >> (lane & 15)) & 1u;
-    const bool vneed = ((mask >> (4 * (lane >> 4))) & 0xfu) != 0u;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) r.k[j] = make_uint4(0, 0, 0, 0);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) r.v[j] = make_uint4(0, 0, 0, 0);
-    if (kneed) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) r.k[j] = spin_nt_load(kp + j * 64);
-    }
-    if (vneed) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) r.v[j] = spin_nt_load(kp + SPIN_KTILE_U4 + j * 64);
-    }
-  }
+  for (int j = 0; j < 4; ++j) r.v[j] = spin_buffer_load(buf, at, SPIN_KTILE_U4 * 16 + j * 1024);
 }
 
 struct softmax_state {
@@ -45,14 +32,18 @@ struct softmax_state {
   spin_f32x4 acc[8];
 };
 
-__device__ inline void consume_page(softmax_state &st, const page_regs &r, const spin_bf16x8 (&qf)[4],
-                                    unsigned mask, int c, float scale_log2e) {
-  // S[token 4c+i][head n]
+// S[token 4c+i][head n] of a tile of 16 tokens
+__device__ __forceinline__ spin_f32x4 tile_logits(const page_regs &r, const spin_bf16x8 (&qf)[4]) {
   spin_f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int j = 0; j < 4; ++j)
     s = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(spin_bf16x8, r.k[j]), qf[j], s, 0, 0, 0);
+  return s;
+}
 
+// the online softmax over a tile's logits, and its share of P V
+__device__ __forceinline__ void tile_attend(softmax_state &st, const spin_f32x4 &s, const page_regs &r, unsigned mask, int c,
+                                            float scale_log2e) {
   const unsigned mbits = (mask >> (4 * c)) & 0xFu;
   float sv[4];
 #pragma unroll
@@ -95,27 +86,38 @@ __device__ inline void consume_page(softmax_state &st, const page_regs &r, const
   }
 }
 
-// Attends `cnt` (<= 64) pages whose slot and mask are held one per lane (lane i: the i-th page), in
-// lane order, through a ring of DEPTH register buffers: DEPTH-1 pages are in flight while one is consumed.
+// Attends `cnt` (<= 64) pages whose slot and mask are held one per lane (lane i: the i-th page; a slot inside the pool
+// in every lane), in lane order, through a ring of DEPTH register buffers.  A tile's registers are loaded again as soon
+// as it has been consumed, and what lies past the end is loaded as an empty page, so that the loop is straight-line
+// code that waits for exactly the tile it is about to read (see spin_buffer).
 template <int DEPTH>
 __device__ __forceinline__ void attend_lane_pages(softmax_state &st, const uint4 *__restrict__ pool, int myslot,
                                                   unsigned mymask, int cnt, int lane, int c,
                                                   const spin_bf16x8 (&qf)[4], float scale_log2e) {
   page_regs r[DEPTH];
+  auto slot_of = [&](int i) { return __builtin_amdgcn_readlane(myslot, i < cnt ? i : 0); };
+  auto mask_of = [&](int i) { return (unsigned)__builtin_amdgcn_readlane((int)mymask, i & 63) & (i < cnt ? 0xffffu : 0u); };
 #pragma unroll
-  for (int d = 0; d < DEPTH - 1; ++d)
-    if (d < cnt) load_page(r[d], pool, __builtin_amdgcn_readlane(myslot, d), lane,
-                           (unsigned)__builtin_amdgcn_readlane((int)mymask, d));
-  for (int i = 0; i < cnt; i += DEPTH) {
+  for (int d = 0; d < DEPTH; ++d) {
+    load_k_tile(r[d], pool, slot_of(d), lane, mask_of(d));
+    __builtin_amdgcn_sched_barrier(0);   // asked for in the order in which the loop asks again
+    load_v_tile(r[d], pool, slot_of(d), lane, mask_of(d));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  int i = 0;
+  for (; i + DEPTH <= cnt; i += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
-      const int ahead = i + d + DEPTH - 1;
-      if (ahead < cnt) load_page(r[(d + DEPTH - 1) % DEPTH], pool, __builtin_amdgcn_readlane(myslot, ahead), lane,
-                                 (unsigned)__builtin_amdgcn_readlane((int)mymask, ahead));
-      if (i + d < cnt)
-        consume_page(st, r[d], qf, (unsigned)__builtin_amdgcn_readlane((int)mymask, i + d), c, scale_log2e);
+      const int ahead = i + d + DEPTH;
+      const spin_f32x4 s = tile_logits(r[d], qf);
+      load_k_tile(r[d], pool, slot_of(ahead), lane, mask_of(ahead));
+      tile_attend(st, s, r[d], mask_of(i + d), c, scale_log2e);
+      load_v_tile(r[d], pool, slot_of(ahead), lane, mask_of(ahead));
     }
   }
+#pragma unroll
+  for (int d = 0; d < DEPTH - 1; ++d)
+    if (i + d < cnt) tile_attend(st, tile_logits(r[d], qf), r[d], mask_of(i + d), c, scale_log2e);
 }
 
 // the group's queries as the second matrix operand of the logit tile: column n = head, k = channels 32j+8c..+8

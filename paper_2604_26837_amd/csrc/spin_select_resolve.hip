@@ -80,7 +80,7 @@ __device__ inline forced_span forced_pages_of(int N, int sink_pages, int recent_
 }
 
 template <int WAVES>
-__device__ inline void attend_forced_row(
+__device__ __forceinline__ void attend_forced_row(
     int row, int side, int nside, const uint16_t *__restrict__ q, const uint4 *__restrict__ pool, int64_t pool_slots,
     const int32_t *__restrict__ seq_lens, const int32_t *__restrict__ dir, const int32_t *__restrict__ leaf_pool,
     int64_t leaf_chunks, int Hkv, int G, int Hq, int sink_pages, int recent_pages, int dir_stride, int leaf_entries,
