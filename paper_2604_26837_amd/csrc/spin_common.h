@@ -156,6 +156,11 @@ __device__ inline uint4 spin_buffer_load(__amdgpu_buffer_rsrc_t buf, uint32_t la
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)lane_offset, (int)offset, 2 /* nt */));
 }
 
+// one float a lane into such a buffer; lanes beyond it store nothing
+__device__ inline void spin_buffer_store(__amdgpu_buffer_rsrc_t buf, uint32_t lane_offset, float v) {
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), buf, (int)lane_offset, 0, 0);
+}
+
 typedef __attribute__((ext_vector_type(2))) unsigned int spin_u32x2;
 __device__ inline uint2 spin_nt_load2(const uint2 *p) {
   return __builtin_bit_cast(uint2, __builtin_nontemporal_load((const spin_u32x2 *)p));
@@ -237,6 +242,21 @@ __device__ inline float spin_dpp(float v) {
 // 256 contiguous bytes, so attending to one token of a page touches two cache lines, not sixteen
 // (the V tile of such a slot is token-major too: the slot is simply K[16][128] then V[16][128]).
 __device__ inline int spin_k_unit(int token_major, int t, int ch) { return token_major ? t * 16 + ch : ch * 16 + t; }
+// Maximum with the lane 16 (32) lanes away, in every lane: the instruction swaps odd rows of 16 lanes of one register with
+// even rows of the other (the upper half with the lower), so that the two hold both partners.
+__device__ inline float spin_max_xor16(float v) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+__device__ inline float spin_max_xor32(float v) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
+// the same of two values at once: the lower half of the lanes get the maximum of a, the upper half that of b
+__device__ inline float spin_max_xor32(float a, float b) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return fmaxf(__uint_as_float(p[0]), __uint_as_float(p[1]));
+}
 template <int CTRL>
 __device__ inline int spin_dpp_i(int v) {   // lanes whose source lies outside the row read 0
   return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);

@@ -40,63 +40,100 @@ __global__ __launch_bounds__(WAVES * 64) void spin_score_k32_single_kernel(
   score_row_single_tile<NJ, MINMAX, WAVES>(q, summ, part_offsets, Hq, Hkv, G, rows_per_part, row, chunk, scores, tm);
 }
 
-// SKETCH: one 16x16x16 instruction per tile of 16 tokens (512 bytes).  MAXIMA: tm.at is there (asked for at
-// run time, it slows the loop: 16 rows of 16000 tokens, groups of 16, 10.0 -> 10.9 us).
-template <bool MAXIMA>
+// SKETCH: where a row's scores begin, how many it has, and channels 4c .. 4c+3 of its KV head's sixteen.  Scalar loads, all
+// under way together: the channels do not keep the tiles waiting.
+struct sketch_row {
+  int off, PP, ch[4];
+};
+__device__ __forceinline__ sketch_row sketch_row_of(const int32_t *__restrict__ chan, const int32_t *__restrict__ part_offsets,
+                                                    int b, int h, int c) {
+  int ch[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) ch[i] = chan[h * 16 + i];
+  const int off = part_offsets[b], end = part_offsets[b + 1];
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) ch[i] = __builtin_amdgcn_readfirstlane(ch[i]);
+  sketch_row r = {off, end - off, {}};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r.ch[i] = c < 2 ? (c == 0 ? ch[i] : ch[4 + i]) : (c == 2 ? ch[8 + i] : ch[12 + i]);
+  return r;
+}
+
+// SKETCH, groups of more than four heads: one 16x16x16 instruction per 16 tokens, 16 bytes per lane and load.  A load of a
+// KiB covers two tiles; lane (n, c) takes channels 4c .. 4c+3 of tokens 2(n%8) and 2(n%8)+1 of tile n/8, and each half
+// of it is the second operand of an instruction whose columns are those 16 tokens of the two tiles.  Rows of heads that
+// the group does not have start from -inf instead of zero, so that the maximum needs no test per head; over the lane
+// quarters it is taken of both halves at once, after which quarters 0 and 2 store 32 neighbouring scores.
+// A wavefront asks for its 16 tiles at once (ONE), no load and no store is behind a branch (see spin_buffer).  MAXIMA:
+// tm.at is there (asked for at run time, it slowed the loop).
+// 64 rows of 65536 tokens, groups of 8: 33.3 -> 25.4 us; 16 rows of 16000, groups of 16: 10.3 -> 3.5; 32 rows of 30000,
+// groups of 5: 12.4 -> 6.2; against 8-byte loads behind branches, two exchanges through LDS per tile and one tile's
+// 16 scores per store.
+template <bool MAXIMA, bool ONE>
 __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
-    const uint16_t *__restrict__ q, const uint2 *__restrict__ summ, const int32_t *__restrict__ chan,
+    const uint16_t *__restrict__ q, const uint4 *__restrict__ summ, const int32_t *__restrict__ chan,
     const int32_t *__restrict__ part_offsets, int Hq, int Hkv, int G, int tiles_per_wg, int wgs_per_row,
     float *__restrict__ scores, tile_maxima tm) {
   const int row = blockIdx.x / wgs_per_row, chunk = blockIdx.x - row * wgs_per_row;
   const int b = row / Hkv, h = row - b * Hkv;
-  const int PP = part_offsets[b + 1] - part_offsets[b];
-  const int ntiles = PP / 16;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, c = lane >> 4;
+  const sketch_row sr = sketch_row_of(chan, part_offsets, b, h, c);
+  const int ntiles = sr.PP / 16;
   const int t_begin = chunk * tiles_per_wg;
   if (t_begin >= ntiles) return;
   const int t_end = min(t_begin + tiles_per_wg, ntiles);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = lane & 15, c = lane >> 4;
-  const size_t base = (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
-
-  const uint2 *tiles = summ + base * 4;   // 16 elements = 4 units of 8 bytes per row
-  constexpr int U = 8;
-  // the first batch of tiles is requested before the query gather below (two dependent loads)
-  // has to be waited for
-  int t0 = t_begin + wave * U;
-  uint2 a[U];
+  const size_t base = (size_t)Hkv * sr.off + (size_t)h * sr.PP;
+  constexpr int U = 8;                            // pairs of tiles per wavefront and round
+  constexpr int ROUND = SCORE_WAVES * 2 * U;
+  const uint16_t *qrow = q + ((size_t)(b * Hq + h * G + min(n, G - 1))) * SPIN_HEAD_DIM;
+  uint32_t e[4];                                  // asked for ahead of the tiles
 #pragma unroll
-  for (int u = 0; u < U; ++u) a[u] = (t0 + u < t_end) ? spin_nt_load2(tiles + (size_t)(t0 + u) * 64 + lane) : make_uint2(0, 0);
-
-  // A operand: row n = head, k = sketched channels 4c..4c+3
-  spin_s16x4 qf;
-  {
-    const uint16_t *qrow = q + ((size_t)(b * Hq + h * G + (n < G ? n : 0))) * SPIN_HEAD_DIM;
-    uint16_t e[4];
+  for (int i = 0; i < 4; ++i) e[i] = qrow[sr.ch[i]];
+  // the workgroup's tiles, 512 bytes each; their scores and maxima
+  const __amdgpu_buffer_rsrc_t in = spin_buffer(summ + base * 2 + (size_t)t_begin * 32, (uint32_t)(t_end - t_begin) * 512);
+  const __amdgpu_buffer_rsrc_t out = spin_buffer(scores + base + (size_t)t_begin * 16, (uint32_t)(t_end - t_begin) * 64);
+  const __amdgpu_buffer_rsrc_t top_out =
+      spin_buffer(MAXIMA ? tm.at + (size_t)row * tm.stride + t_begin : nullptr,
+                  MAXIMA ? (uint32_t)max(min(t_end, tm.stride) - t_begin, 0) * 4 : 0);
+  uint32_t at_in = (uint32_t)(wave * 2 * U + (n >> 3)) * 512 + (uint32_t)(c * 8 + (n & 7)) * 16;
+  uint32_t at_out = c & 1 ? 0x80000000u : (uint32_t)((wave * 2 * U + (n >> 3)) * 16 + 2 * (n & 7) + (c >> 1)) * 4;
+  uint32_t at_top = (n & 7) || c ? 0x80000000u : (uint32_t)(wave * 2 * U + (n >> 3)) * 4;
+  uint4 ld[U];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) e[i] = n < G ? qrow[chan[h * 16 + 4 * c + i]] : (uint16_t)0;
-    uint2 pk = make_uint2(e[0] | ((uint32_t)e[1] << 16), e[2] | ((uint32_t)e[3] << 16));
-    qf = __builtin_bit_cast(spin_s16x4, pk);
+  for (int u = 0; u < U; ++u) {
+    ld[u] = spin_buffer_load(in, at_in, 2 * u * 512);
+    __builtin_amdgcn_sched_barrier(0);
   }
-  for (; t0 < t_end; t0 += SCORE_WAVES * U) {
-    // the next batch is in flight while this one is consumed
-    uint2 nx[U];
-    const int t1 = t0 + SCORE_WAVES * U;
+  // A operand: row n = head, k = sketched channels 4c..4c+3
+  const spin_s16x4 qf = __builtin_bit_cast(spin_s16x4, n < G ? make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16)) : make_uint2(0u, 0u));
+  spin_f32x4 start;
 #pragma unroll
-    for (int u = 0; u < U; ++u) nx[u] = (t1 + u < t_end) ? spin_nt_load2(tiles + (size_t)(t1 + u) * 64 + lane) : make_uint2(0, 0);
+  for (int i = 0; i < 4; ++i) start[i] = 4 * c + i < G ? 0.f : -__builtin_inff();
+  for (int t0 = t_begin + wave * 2 * U; t0 < t_end; t0 += ROUND) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (t0 + u >= t_end) break;
-      spin_f32x4 s = {0.f, 0.f, 0.f, 0.f};
-      s = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qf, __builtin_bit_cast(spin_s16x4, a[u]), s, 0, 0, 0);
-      const float m = spin_head_max(s, c, G);   // lane (n, c): heads 4c+i of token n
-      if (c == 0) scores[base + (size_t)(t0 + u) * 16 + n] = m;
-      if (MAXIMA) {
-        const float top = spin_row16_max(m);
-        if (lane == 0 && t0 + u < tm.stride) tm.at[(size_t)row * tm.stride + t0 + u] = top;
+      const uint2 lo = make_uint2(ld[u].x, ld[u].y), hi = make_uint2(ld[u].z, ld[u].w);
+      const spin_f32x4 s0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qf, __builtin_bit_cast(spin_s16x4, lo), start, 0, 0, 0);
+      const spin_f32x4 s1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qf, __builtin_bit_cast(spin_s16x4, hi), start, 0, 0, 0);
+      if (!ONE) ld[u] = spin_buffer_load(in, at_in, (ROUND + 2 * u) * 512);
+      const float m0 = fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3]));
+      const float m1 = fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3]));
+      float m = spin_max_xor16(spin_max_xor32(m0, m1));
+      m = fmaxf(m, -__builtin_inff());            // (NaN in every head: -inf)
+      spin_buffer_store(out, at_out + 2 * u * 64, m);
+      if (MAXIMA) {                               // a tile's tokens lie in the 8 lanes of both halves
+        float top = fmaxf(m, spin_dpp<SPIN_DPP_XOR1>(m));
+        top = fmaxf(top, spin_dpp<SPIN_DPP_XOR2>(top));
+        top = fmaxf(top, spin_dpp<SPIN_DPP_HALF_MIRROR>(top));
+        spin_buffer_store(top_out, at_top + 2 * u * 4, spin_max_xor32(top));
       }
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = nx[u];
+    if (ONE) break;
+    at_in += ROUND * 512;
+    at_out += ROUND * 64;
+    at_top += ROUND * 4;
   }
 }
 
@@ -106,85 +143,85 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
 // tiles.  The first operand of instruction j (load j/2, half j%2) holds the group's heads in rows 4j .. 4j+3 and
 // zeros elsewhere (exact zero products), so the four instructions of two loads fill one accumulator: lane (n, c) ends
 // up with the four heads' scores of one token, the maximum stays in the lane and all 64 lanes store.
-// HBM bounds it (64 rows of 65536 tokens, 151 MB read and written: 27.5 us; 28.2 with 8-byte loads in the 16x16x32
-// operand's image).
+// HBM bounds it.  A wavefront asks for its 16 tiles (8 KiB) at once, behind the group's channels and queries, and has no
+// second round (ONE); with more tiles to a workgroup a group's registers are asked for again as soon as they have been
+// consumed.  No load and no store is behind a branch (see spin_buffer).  64 rows of 65536 tokens, 151 MB read and
+// written: 25.6 us in one round, 26.4 in four; 27.1 with four rounds whose loads, behind branches, were waited for as
+// soon as they were issued.
+// MAXIMA: tm.at is there.
+template <bool MAXIMA, bool ONE>
 __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch4_kernel(
     const uint16_t *__restrict__ q, const uint4 *__restrict__ summ, const int32_t *__restrict__ chan,
     const int32_t *__restrict__ part_offsets, int Hq, int Hkv, int G, int tiles_per_wg, int wgs_per_row,
     float *__restrict__ scores, tile_maxima tm) {
   const int row = blockIdx.x / wgs_per_row, chunk = blockIdx.x - row * wgs_per_row;
   const int b = row / Hkv, h = row - b * Hkv;
-  const int PP = part_offsets[b + 1] - part_offsets[b];
-  const int ntiles = PP / 16;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, c = lane >> 4;
+  const sketch_row sr = sketch_row_of(chan, part_offsets, b, h, c);
+  const int ntiles = sr.PP / 16;
   const int t_begin = chunk * tiles_per_wg;       // tiles_per_wg is a multiple of 4
   if (t_begin >= ntiles) return;
   const int t_end = min(t_begin + tiles_per_wg, ntiles);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = lane & 15, c = lane >> 4;
-  const size_t base = (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
-  const uint4 *tiles = summ + base * 2;           // a tile: [channel quad (4)][token (16)][4 channels], 32 units of 16 bytes
-  constexpr int U = 4;                            // groups of four tiles per wavefront and batch
-  const int unit = c * 8 + (n & 7);
-  struct group4 { uint4 ld[2]; };
-  auto load_group = [&](group4 &g4, int t) {
+  const size_t base = (size_t)Hkv * sr.off + (size_t)h * sr.PP;
+  constexpr int U = 4;                            // groups of four tiles per wavefront and round
+  constexpr int ROUND = SCORE_WAVES * 4 * U;
+
+  // first operands: lane (r, c) supplies row r = 4j + g, channels 4c .. 4c+3; asked for ahead of the tiles
+  const uint16_t *qrow = q + ((size_t)(b * Hq + h * G + min(n & 3, G - 1))) * SPIN_HEAD_DIM;
+  uint32_t e[4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)                   // tiles past the end are clamped
-      g4.ld[i] = spin_nt_load(tiles + (size_t)min(t + 2 * i + (n >> 3), t_end - 1) * 32 + unit);
-  };
-  int t0 = t_begin + wave * 4 * U;
-  group4 cur[U];
+  for (int i = 0; i < 4; ++i) e[i] = qrow[sr.ch[i]];
+  // the workgroup's tiles, a tile being [channel quad (4)][token (16)][4 channels], 512 bytes; their scores and maxima
+  const __amdgpu_buffer_rsrc_t in = spin_buffer(summ + base * 2 + (size_t)t_begin * 32, (uint32_t)(t_end - t_begin) * 512);
+  const __amdgpu_buffer_rsrc_t out = spin_buffer(scores + base + (size_t)t_begin * 16, (uint32_t)(t_end - t_begin) * 64);
+  const __amdgpu_buffer_rsrc_t top_out =
+      spin_buffer(MAXIMA ? tm.at + (size_t)row * tm.stride + t_begin : nullptr,
+                  MAXIMA ? (uint32_t)max(min(t_end, tm.stride) - t_begin, 0) * 4 : 0);
+  const int tok = (c >> 1) * 32 + 2 * n + (c & 1), my_tile = 2 * (c >> 1) + (n >> 3);   // the lane's of a group of four tiles
+  uint32_t at_in = (uint32_t)(wave * 4 * U + (n >> 3)) * 512 + (uint32_t)(c * 8 + (n & 7)) * 16;
+  uint32_t at_out = (uint32_t)(wave * 4 * U * 16 + tok) * 4;
+  // a tile's tokens lie in 8 lanes of two lane rows, the first of which stores their maximum
+  uint32_t at_top = (n & 7) == 0 && !(c & 1) ? (uint32_t)(wave * 4 * U + my_tile) * 4 : 0x80000000u;
+  uint4 ld[U][2];
 #pragma unroll
   for (int u = 0; u < U; ++u)
-    if (t0 + 4 * u < t_end) load_group(cur[u], t0 + 4 * u);
-
-  // first operands: lane (r, c) supplies row r = 4j + g, channels 4c .. 4c+3
-  spin_s16x4 qa[4];
-  {
-    const int g = n & 3;
-    uint32_t w[2] = {0u, 0u};
-    if (g < G) {
-      const uint16_t *qrow = q + ((size_t)(b * Hq + h * G + g)) * SPIN_HEAD_DIM;
 #pragma unroll
-      for (int e = 0; e < 4; e += 2)
-        w[e >> 1] = (uint32_t)qrow[chan[h * 16 + 4 * c + e]] | ((uint32_t)qrow[chan[h * 16 + 4 * c + e + 1]] << 16);
+    for (int i = 0; i < 2; ++i) {
+      ld[u][i] = spin_buffer_load(in, at_in, (4 * u + 2 * i) * 512);
+      __builtin_amdgcn_sched_barrier(0);
     }
+  spin_s16x4 qa[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      qa[j] = __builtin_bit_cast(spin_s16x4, (n >> 2) == j ? make_uint2(w[0], w[1]) : make_uint2(0u, 0u));
-  }
-  // the lane's token of the group of four tiles, and whether its tile exists
-  const int tok = (c >> 1) * 32 + 2 * n + (c & 1), my_tile = 2 * (c >> 1) + (n >> 3);
-  for (; t0 < t_end; t0 += SCORE_WAVES * 4 * U) {
-    // the next batch is in flight while this one is consumed
-    group4 nxt[U];
-    const int t1 = t0 + SCORE_WAVES * 4 * U;
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (t1 + 4 * u < t_end) load_group(nxt[u], t1 + 4 * u);
+  for (int j = 0; j < 4; ++j)
+    qa[j] = __builtin_bit_cast(spin_s16x4, (n >> 2) == j && (n & 3) < G ? make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16)) : make_uint2(0u, 0u));
+  for (int t0 = t_begin + wave * 4 * U; t0 < t_end; t0 += ROUND) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int t = t0 + 4 * u;
-      if (t >= t_end) break;
       spin_f32x4 s = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const uint2 lo = make_uint2(cur[u].ld[i].x, cur[u].ld[i].y), hi = make_uint2(cur[u].ld[i].z, cur[u].ld[i].w);
+        const uint2 lo = make_uint2(ld[u][i].x, ld[u][i].y), hi = make_uint2(ld[u][i].z, ld[u][i].w);
         s = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qa[2 * i], __builtin_bit_cast(spin_s16x4, lo), s, 0, 0, 0);
         s = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qa[2 * i + 1], __builtin_bit_cast(spin_s16x4, hi), s, 0, 0, 0);
+        if (!ONE) ld[u][i] = spin_buffer_load(in, at_in, (ROUND + 4 * u + 2 * i) * 512);
       }
-      const float mx = spin_head_max(s, 0, G);    // heads 0..3 of the lane's token
-      if (t + my_tile < t_end) scores[base + (size_t)t * 16 + tok] = mx;
-      if (tm.at) {                                // uniform; a tile's tokens lie in 8 lanes of two lane rows
+      float mx = -__builtin_inff();               // heads 0..3 of the lane's token
+#pragma unroll
+      for (int i = 0; i < 4; ++i) mx = i < G ? fmaxf(mx, s[i]) : mx;
+      spin_buffer_store(out, at_out + 4 * u * 64, mx);
+      if (MAXIMA) {
         float top = fmaxf(mx, spin_dpp<SPIN_DPP_XOR1>(mx));
         top = fmaxf(top, spin_dpp<SPIN_DPP_XOR2>(top));
         top = fmaxf(top, spin_dpp<SPIN_DPP_HALF_MIRROR>(top));
         top = fmaxf(top, __shfl_xor(top, 16));
-        if ((n & 7) == 0 && !(c & 1) && t + my_tile < t_end && t + my_tile < tm.stride)
-          tm.at[(size_t)row * tm.stride + t + my_tile] = top;
+        spin_buffer_store(top_out, at_top + 4 * u * 4, top);
       }
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) cur[u] = nxt[u];
+    if (ONE) break;
+    at_in += ROUND * 512;
+    at_out += ROUND * 64;
+    at_top += ROUND * 4;
   }
 }
 
@@ -239,17 +276,24 @@ int spin_score_impl(spin_ctx *ctx, int32_t batch, const void *q, const void *sum
 #undef SPIN_SCORE_ARGS
   } else {
     if (!chan_idx) return SPIN_ERR_INVALID;
-    // groups of up to four heads: the four-tile kernel, 256 tiles per workgroup measured best (32 / 64 /
-    // 128 / 256 / 512: 28.9 / 27.7 / 28.1 / 27.4 / 28.7 us on 64 rows of 65536 tokens)
+    // groups of up to four heads: the four-tile kernel, 64 tiles per workgroup, one round (32 / 64 / 128 / 256 / 512:
+    // 26.4 / 25.6 / 26.9 / 26.4 / 28.2 us on 64 rows of 65536 tokens)
     const bool four = ctx->group <= 4 && (c.score_tiles_per_wg % 4) == 0;
-    const int tiles_per_wg = c.score_tiles_per_wg ? c.score_tiles_per_wg : (four ? 256 : 128), max_tiles = max_pp / 16;
+    const int tiles_per_wg = c.score_tiles_per_wg ? c.score_tiles_per_wg : 64, max_tiles = max_pp / 16;
     const int wgs = (max_tiles + tiles_per_wg - 1) / tiles_per_wg;
-#define SPIN_SKETCH_ARGS(UNIT)                                                                                   \
-  dim3((unsigned)rows * wgs), dim3(SCORE_WAVES * 64), 0, st, (const uint16_t *)q, (const UNIT *)summaries, chan_idx, \
+#define SPIN_SKETCH_ARGS                                                                                         \
+  dim3((unsigned)rows * wgs), dim3(SCORE_WAVES * 64), 0, st, (const uint16_t *)q, (const uint4 *)summaries, chan_idx, \
       part_offsets, c.num_q_heads, c.num_kv_heads, ctx->group, tiles_per_wg, wgs, scores, tm
-    if (four) spin_launch(ctx, SPIN_K_SCORE, spin_score_sketch4_kernel, SPIN_SKETCH_ARGS(uint4));
-    else if (maxima) spin_launch(ctx, SPIN_K_SCORE, spin_score_sketch_kernel<true>, SPIN_SKETCH_ARGS(uint2));
-    else spin_launch(ctx, SPIN_K_SCORE, spin_score_sketch_kernel<false>, SPIN_SKETCH_ARGS(uint2));
+#define SPIN_SKETCH_LAUNCH(KERNEL)                                                            \
+  do {                                                                                        \
+    if (maxima && tiles_per_wg <= 64) spin_launch(ctx, SPIN_K_SCORE, KERNEL<true, true>, SPIN_SKETCH_ARGS); \
+    else if (maxima) spin_launch(ctx, SPIN_K_SCORE, KERNEL<true, false>, SPIN_SKETCH_ARGS);   \
+    else if (tiles_per_wg <= 64) spin_launch(ctx, SPIN_K_SCORE, KERNEL<false, true>, SPIN_SKETCH_ARGS); \
+    else spin_launch(ctx, SPIN_K_SCORE, KERNEL<false, false>, SPIN_SKETCH_ARGS);              \
+  } while (0)
+    if (four) SPIN_SKETCH_LAUNCH(spin_score_sketch4_kernel);
+    else SPIN_SKETCH_LAUNCH(spin_score_sketch_kernel);
+#undef SPIN_SKETCH_LAUNCH
 #undef SPIN_SKETCH_ARGS
   }
   return spin_launch_status();

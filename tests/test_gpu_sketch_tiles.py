@@ -1,0 +1,57 @@
+"""Stage 1 of token partitions: tile counts around one round of a workgroup (64 tiles), tiles per workgroup that leave
+half a pair or several rounds, every kind of group.  The scores against sums in 64 bits to the order bound of 16
+products in 32 bits; nothing is stored past a row's last tile.  The tiles' maxima are those of the stored scores."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_26837_amd import binding, synth, tables
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("tiles_per_wg", [0, 5, 36, 128])
+@pytest.mark.parametrize("group", [1, 3, 4, 5, 8, 16])
+def test_scores_and_maxima(group, tiles_per_wg):
+    from gpu_harness import unpack_summary_rows
+    kv, lens = 2, (1, 16 * 63, 16 * 64 + 3, 16 * 193 + 1)
+    maxima = tiles_per_wg == 0                            # (rows long enough for stage 2 to go by them)
+    sp = binding.Spin(max_batch=len(lens), num_q_heads=kv * group, num_kv_heads=kv, partition_tokens=1,
+                      score_kind=synth.SCORE_SKETCH, topk=200, sink_pages=0, recent_pages=0, score_tiles_per_wg=tiles_per_wg,
+                      max_context=16400 if maxima else max(lens))
+    off = tables.part_offsets(lens, 1)
+    total = int(off[-1]) * kv
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(group)
+    summ = torch.randn(total * 16, generator=gen, device=DEV).to(torch.bfloat16)
+    q = torch.randn((len(lens), kv * group, 128), generator=gen, device=DEV).to(torch.bfloat16)
+    chan = torch.stack([torch.randperm(128, generator=gen, device=DEV)[:16] for _ in range(kv)]).to(torch.int32).contiguous()
+    scores = torch.full((total + 64,), 7.5, device=DEV)
+    seq = torch.tensor(lens, dtype=torch.int32, device=DEV)
+    offs = torch.from_numpy(off).to(DEV)
+    ws = sp.new_workspace(DEV)
+    if maxima:
+        sel = torch.zeros((len(lens) * kv, sp.sel_stride), dtype=torch.int32, device=DEV)
+        nsel = torch.zeros(len(lens) * kv, dtype=torch.int32, device=DEV)
+        sp.score_select_topk(len(lens), q, summ.view(torch.uint8), chan, offs, seq, scores, sel, nsel, ws)
+    else:
+        sp.score_partitions(len(lens), q, summ.view(torch.uint8), chan, offs, seq, scores, ws)
+    torch.cuda.synchronize()
+    assert sp.poll_status(ws) == 0
+    rows = unpack_summary_rows(summ.view(torch.uint8), 16, 4).astype(np.uint32) << 16
+    rows = rows.view(np.float32).astype(np.float64)       # [tokens][16]
+    qf, ch, got = q.double().cpu().numpy(), chan.cpu().numpy(), scores.cpu().numpy()
+    for b in range(len(lens)):
+        for h in range(kv):
+            n = int(off[b + 1] - off[b])
+            base = int(off[b]) * kv + h * n
+            heads = qf[b, h * group:(h + 1) * group][:, ch[h]]
+            terms = rows[base:base + n] @ heads.T
+            bound = 16 * 2.0 ** -24 * (np.abs(rows[base:base + n]) @ np.abs(heads).T).max(axis=1)
+            assert (np.abs(got[base:base + n] - terms.max(axis=1)) <= bound).all()
+            if maxima:                                    # the selection is the k largest of the scores, ties lowest first
+                want = np.sort(np.lexsort((np.arange(lens[b]), -got[base:base + lens[b]].astype(np.float64)))[:200])
+                r = b * kv + h
+                assert np.array_equal(sel[r, :int(nsel[r])].cpu().numpy(), want)
+    assert (got[total:] == 7.5).all()
