@@ -64,7 +64,7 @@ __device__ inline void emit_invalid(const res_out &o, int pos, int page_stride, 
 // row's selection count.  `known`: the row's windows, where the caller has them
 // (variable-length partitions).
 template <int RES_BLOCK, bool LOOKUP = true>
-__device__ inline void resolve_row(
+__device__ __forceinline__ void resolve_row(
     int row, int ns, const int32_t *__restrict__ sel, const int32_t *__restrict__ seq_lens,
     const int32_t *dir, const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks, int Hkv, int tp,
     int sink_pages, int recent_pages, int sel_stride, int page_stride, int dir_stride, int leaf_entries,

@@ -109,7 +109,7 @@ struct kth_lds {
 // spread over many digits the detour costs up to 2.5 us (almost all close together, k 8192: 37.8 -> 40.2), and with few
 // keys the additions are the shorter way (256 ragged rows, below 4096 of them: step 142.6 us against 144.9).
 template <int BLOCK, int KPT, bool MANY = false>
-__device__ inline void block_kth(const uint32_t (&key)[KPT], typename key_bits<KPT>::type valid, int k, int slack,
+__device__ __forceinline__ void block_kth(const uint32_t (&key)[KPT], typename key_bits<KPT>::type valid, int k, int slack,
                                  kth_lds<BLOCK> &s, uint32_t &T, unsigned &need_eq, bool many = false) {
   constexpr int NW = BLOCK / 64;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -259,7 +259,7 @@ struct elements_lds {
 
 // The kprime best of the `total` entries of an ordered list in LDS, stored ascending at rsel[first ..].
 template <int BLOCK, int CAP>
-__device__ inline void pick_from_list(int total, int kprime, int first, int sel_stride, int32_t *__restrict__ rsel,
+__device__ __forceinline__ void pick_from_list(int total, int kprime, int first, int sel_stride, int32_t *__restrict__ rsel,
                                       elements_lds<BLOCK, CAP> &s) {
   const int tid = threadIdx.x;
   auto pick_list = [&](auto entries) {
@@ -303,7 +303,7 @@ __device__ inline void pick_from_list(int total, int kprime, int first, int sel_
 // one to CAP / BLOCK keys per thread.  A row with more than CAP of them (every row where CAP is 0: few scores per
 // thread, for which the list does not pay) searches its registers.
 template <int BLOCK, int KPT, int CAP, typename ID>
-__device__ inline void select_elements(const float (&f)[KPT], typename key_bits<KPT>::type cand, uint32_t bound,
+__device__ __forceinline__ void select_elements(const float (&f)[KPT], typename key_bits<KPT>::type cand, uint32_t bound,
                                        int kprime, int first, int sel_stride, int32_t *__restrict__ rsel,
                                        elements_lds<BLOCK, CAP> &s, ID id) {
   typedef typename key_bits<KPT>::type M;
@@ -381,7 +381,7 @@ __device__ inline void emit_forced(const sel_plan &pl, int sel_stride, int32_t *
 // two barriers stand for four binary searches of a dozen dependent loads each.  (With more than 16 per thread, which
 // the registers would not hold beside the scores, the entries are read where they are used.)
 template <int BLOCK, int KPT>
-__device__ inline spin_var_span block_var_span(const spin_var &var, size_t vbase, int row, int PP, int sink_pages,
+__device__ __forceinline__ spin_var_span block_var_span(const spin_var &var, size_t vbase, int row, int PP, int sink_pages,
                                                int recent_pages, int &nf_lo, int &first_hi) {
   constexpr int NW = BLOCK / 64, HELD = KPT <= 16 ? KPT : 1;
   __shared__ int s_pages;
@@ -458,7 +458,7 @@ template <int BLOCK, int KPT>
 constexpr int reg_row_cap() { return KPT >= 16 ? 2 * BLOCK : 0; }
 
 template <int BLOCK, int KPT>
-__device__ inline int select_reg_row(
+__device__ __forceinline__ int select_reg_row(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
     int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, int row,
@@ -567,7 +567,7 @@ union tiles_row_lds {
 // k' 2048 / 8192: 44 / 90 -> 22 / 64.  (Being in the kernel it costs rows that do not come here 0.2 to 0.3 us, out of
 // line as well; four quads under way as good as eight, which take 30 more registers.)
 template <int BLOCK>
-__device__ inline void select_whole_row(const float *__restrict__ rs, uint32_t lo, uint32_t hi, const sel_plan &pl,
+__device__ __forceinline__ void select_whole_row(const float *__restrict__ rs, uint32_t lo, uint32_t hi, const sel_plan &pl,
                                         int sel_stride, int32_t *__restrict__ rsel, row_lds<BLOCK> &s) {
   constexpr int NW = BLOCK / 64, V = 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -716,7 +716,7 @@ __device__ inline void select_whole_row(const float *__restrict__ rs, uint32_t l
 
 // False (for the whole workgroup, nothing stored): more scores than the list holds.
 template <int BLOCK, int MPT, int CAP>
-__device__ inline bool list_by_tile_maxima(const float *__restrict__ rs, const uint32_t (&top)[MPT],
+__device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs, const uint32_t (&top)[MPT],
                                            typename key_bits<MPT>::type cand, int t_lo, int t_hi, int gs_log,
                                            const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
                                            tiles_lds<BLOCK, CAP> &s) {
@@ -844,7 +844,7 @@ __device__ inline void load_tile_maxima(float4 (&v)[MPT / 4], const float *__res
     v[j] = m0 + 4 * j < maxima_stride ? *(const float4 *)(maxima + m0 + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
 }
 template <int BLOCK, int MPT, int CAP>
-__device__ inline void select_by_tile_maxima(const float *__restrict__ rs, const float4 (&maxima)[MPT / 4], int gs_log,
+__device__ __forceinline__ void select_by_tile_maxima(const float *__restrict__ rs, const float4 (&maxima)[MPT / 4], int gs_log,
                                              const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
                                              tiles_row_lds<BLOCK, CAP> &lds) {
   constexpr int NW = BLOCK / 64;
