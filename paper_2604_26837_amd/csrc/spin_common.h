@@ -122,6 +122,9 @@ static inline void spin_launch(spin_ctx *ctx, int kid, K kernel, dim3 grid, dim3
   }
 }
 
+// words known to lie in LDS, which a pointer to ordinary memory does not say of itself
+typedef __attribute__((address_space(3))) int32_t spin_lds_i32;
+
 // first device-detected fault wins; later ones are dropped
 __device__ inline void spin_raise(int32_t *status, int32_t err) { atomicCAS(status, 0, err); }
 
@@ -154,6 +157,11 @@ __device__ inline __amdgpu_buffer_rsrc_t spin_buffer(const void *p, uint32_t byt
 }
 __device__ inline uint4 spin_buffer_load(__amdgpu_buffer_rsrc_t buf, uint32_t lane_offset, uint32_t offset) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)lane_offset, (int)offset, 2 /* nt */));
+}
+
+// the same without the hint that it is read once
+__device__ inline uint4 spin_buffer_load_kept(__amdgpu_buffer_rsrc_t buf, uint32_t lane_offset) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(buf, (int)lane_offset, 0, 0));
 }
 
 // one float a lane into such a buffer; lanes beyond it store nothing

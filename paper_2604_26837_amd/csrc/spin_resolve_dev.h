@@ -31,18 +31,41 @@ __device__ inline void res_put(const res_out &o, int pos, int32_t slot, int32_t 
 }
 
 #define RES_DIR_LDS 256
+#define SEL_HELD 2304          // a top 2048 with 256 forced ones; with these the launch by tile maxima stays under 64 KiB
 
-// `dir` points at the row's directory entries (a copy in LDS when it fits)
+// What the launch that selects a row has of it in LDS when it goes on to stage 3: the selection (where no longer than
+// SEL_HELD) and the directory entries (where at most RES_DIR_LDS).
+struct held_row {
+  int32_t sel[SEL_HELD];
+  int32_t dir[RES_DIR_LDS];
+};
+
+// a row's directory, in LDS when it fits.  (Told apart by a branch: through a pointer to either, every lookup would be
+// a generic load that waits for all memory and LDS operations under way.)
+struct row_dir {
+  const int32_t *global;
+  spin_lds_i32 *lds;
+  bool in_lds;
+  __device__ __forceinline__ int32_t at(int i) const {
+    if (in_lds) return lds[i];
+    return global[i];
+  }
+};
+
 // LOOKUP = false: only the page list and the masks are wanted (budget mode decides the slots)
 template <bool LOOKUP>
-__device__ inline void emit_page(const res_out &o, int pos, int page_stride, int page, uint32_t mask,
-                                 const int32_t *dir, const int32_t *leaf_pool, int64_t leaf_chunks, int row,
-                                 int dir_stride, int leaf_entries, int32_t *status) {
+__device__ __forceinline__ void emit_page(const res_out &o, int pos, int page_stride, int page, uint32_t mask,
+                                          const row_dir &dir, const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks,
+                                          int dir_stride, int leaf_entries, int32_t *status) {
   if (pos < 0 || pos >= page_stride) return;
-  (void)row;
   int32_t slot = -1;
   if (LOOKUP) {
-    slot = spin_walk(dir, leaf_pool, leaf_chunks, 0, dir_stride, leaf_entries, page);
+    const int ci = page < 0 ? dir_stride : page / leaf_entries;
+    if (ci < dir_stride) {
+      const int32_t chunk = dir.at(ci);
+      if (chunk >= 0 && (int64_t)chunk < leaf_chunks)
+        slot = leaf_pool[(size_t)chunk * leaf_entries + (page - ci * leaf_entries)];
+    }
     if (slot < 0) {
       spin_raise(status, SPIN_ERR_NOT_RESIDENT);
       slot = -1;
@@ -62,35 +85,42 @@ __device__ inline void emit_invalid(const res_out &o, int pos, int page_stride, 
 
 // Resolves one row with the calling workgroup of RES_BLOCK threads; `ns` = the
 // row's selection count.  `known`: the row's windows, where the caller has them
-// (variable-length partitions).
-template <int RES_BLOCK, bool LOOKUP = true>
+// (variable-length partitions).  HELD_DIR, HELD_SEL: the calling launch has staged the row's directory, or its selection,
+// in `held`.
+template <int RES_BLOCK, bool LOOKUP = true, bool HELD_DIR = false, bool HELD_SEL = false>
 __device__ __forceinline__ void resolve_row(
     int row, int ns, const int32_t *__restrict__ sel, const int32_t *__restrict__ seq_lens,
     const int32_t *dir, const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks, int Hkv, int tp,
     int sink_pages, int recent_pages, int sel_stride, int page_stride, int dir_stride, int leaf_entries,
     int32_t *__restrict__ slots, int32_t *__restrict__ page_ids, uint16_t *__restrict__ valid_mask,
-    int32_t *__restrict__ npages, int32_t *status, spin_var var, const spin_var_span *known = nullptr) {
+    int32_t *__restrict__ npages, int32_t *status, spin_var var, const spin_var_span *known = nullptr,
+    held_row *held = nullptr) {
   constexpr int RES_WAVES = RES_BLOCK / 64;
   __shared__ int s_wave[RES_WAVES];
   __shared__ int s_flagA, s_flagB, s_cntB;
-  __shared__ int32_t s_dir[RES_DIR_LDS];
+  __shared__ int32_t s_dir[HELD_DIR ? 1 : RES_DIR_LDS];
   const int tid = threadIdx.x;
   const int b = row / Hkv;
   // the row's directory entries are fetched together with its selection, so the
   // leaf lookups below are the only dependent round trip
   const int32_t *gdir = dir + (size_t)row * dir_stride;
   const bool dir_in_lds = dir_stride <= RES_DIR_LDS;
-  if (dir_in_lds)
+  if (!HELD_DIR && dir_in_lds)
     for (int i = tid; i < dir_stride; i += RES_BLOCK) s_dir[i] = gdir[i];
-  dir = dir_in_lds ? s_dir : gdir;
+  const row_dir rdir = {gdir, (spin_lds_i32 *)(HELD_DIR ? held->dir : s_dir), dir_in_lds};
   const int N = seq_lens[b];
   const int pages = (N + 15) >> 4;
   ns = ns < 0 ? 0 : (ns > sel_stride ? sel_stride : ns);
   const int32_t *rsel = sel + (size_t)row * sel_stride;
+  spin_lds_i32 *lsel = (spin_lds_i32 *)(HELD_SEL ? held->sel : s_dir);
+  auto sel_at = [&](int i) -> int32_t {
+    if (HELD_SEL) return lsel[i];
+    return rsel[i];
+  };
   res_out o = {slots + (size_t)row * page_stride, page_ids + (size_t)row * page_stride,
                valid_mask + (size_t)row * page_stride};
 
-  if (dir_in_lds) __syncthreads();
+  if (!HELD_DIR && dir_in_lds) __syncthreads();
 
   if (var.count) {
     // Variable-length partitions: the page list of partition p starts at
@@ -109,7 +139,7 @@ __device__ __forceinline__ void resolve_row(
     // selection entry i: partition (-1: names none of the row), first page, tokens
     struct part { int s, first, tokens; };
     auto entry = [&](int i) {
-      part e = {rsel[i], 0, 0};
+      part e = {sel_at(i), 0, 0};
       if (e.s < 0 || e.s >= P) e.s = -1;
       else { e.first = var.first_page[vb + e.s]; e.tokens = var.tokens[vb + e.s]; }
       return e;
@@ -138,7 +168,7 @@ __device__ __forceinline__ void resolve_row(
     const int extraB = (B >= 0 && !s_flagB) ? (endB - w.recent_begin) : 0;
     auto put = [&](int pos, const part &e, int k) {      // page k of partition e
       const int nv = min(max(e.tokens - 16 * k, 0), 16);
-      emit_page<LOOKUP>(o, pos, page_stride, e.first + k, (1u << nv) - 1u, dir, leaf_pool, leaf_chunks, row, dir_stride,
+      emit_page<LOOKUP>(o, pos, page_stride, e.first + k, (1u << nv) - 1u, rdir, leaf_pool, leaf_chunks, dir_stride,
                         leaf_entries, status);
     };
     auto shift = [&](int s) { return ((extraA && s > A) ? extraA : 0) + ((extraB && s > B) ? extraB : 0); };
@@ -183,11 +213,11 @@ __device__ __forceinline__ void resolve_row(
     // leaf lookup is the only dependent round trip.
     for (int i0 = 0; i0 < sel_stride; i0 += RES_BLOCK) {
       const int i = i0 + tid;
-      const int s = i < sel_stride ? rsel[i] : -1;
+      const int s = i < sel_stride ? sel_at(i) : -1;
       if (i < ns) {
         if (s >= 0 && s < pages)
-          emit_page<LOOKUP>(o, i, page_stride, s, page_mask(s, N), dir, leaf_pool, leaf_chunks, row, dir_stride,
-                            leaf_entries, status);
+          emit_page<LOOKUP>(o, i, page_stride, s, page_mask(s, N), rdir, leaf_pool, leaf_chunks, dir_stride,
+                        leaf_entries, status);
         else
           emit_invalid(o, i, page_stride, status);   // an entry that names no page of the row
       }
@@ -215,7 +245,7 @@ __device__ __forceinline__ void resolve_row(
     __syncthreads();
     int below_b = 0;
     for (int i = tid; i < ns; i += RES_BLOCK) {
-      const int s = rsel[i];
+      const int s = sel_at(i);
       if (s == A) s_flagA = 1;
       if (s == B) s_flagB = 1;
       below_b += (B >= 0 && s < B);
@@ -228,7 +258,7 @@ __device__ __forceinline__ void resolve_row(
     // pages of the selected partitions
     for (int idx = tid; idx < ns * m; idx += RES_BLOCK) {
       const int i = idx / m, k = idx - i * m;
-      const int s = rsel[i];
+      const int s = sel_at(i);
       const int pg = s * m + k;
       int pos = i * m + k;
       if (extraA && s > A) pos += extraA;
@@ -238,48 +268,51 @@ __device__ __forceinline__ void resolve_row(
         continue;
       }
       if (pg >= pages) continue;                     // the ragged end of the context's last partition
-      emit_page<LOOKUP>(o, pos, page_stride, pg, page_mask(pg, N), dir, leaf_pool, leaf_chunks, row, dir_stride,
-                leaf_entries, status);
+      emit_page<LOOKUP>(o, pos, page_stride, pg, page_mask(pg, N), rdir, leaf_pool, leaf_chunks, dir_stride,
+                        leaf_entries, status);
     }
     // standalone forced pages: partitions 0..A-1 are wholly forced, hence selected
     for (int k = tid; k < extraA; k += RES_BLOCK)
-      emit_page<LOOKUP>(o, A * m + k, page_stride, a0 + k, page_mask(a0 + k, N), dir, leaf_pool, leaf_chunks, row,
-                dir_stride, leaf_entries, status);
+      emit_page<LOOKUP>(o, A * m + k, page_stride, a0 + k, page_mask(a0 + k, N), rdir, leaf_pool, leaf_chunks, dir_stride,
+                        leaf_entries, status);
     for (int k = tid; k < extraB; k += RES_BLOCK)
       emit_page<LOOKUP>(o, sel_below_b * m + ((A >= 0 && A <= B) ? extraA : 0) + k, page_stride, b0 + k,
-                page_mask(b0 + k, N), dir, leaf_pool, leaf_chunks, row, dir_stride, leaf_entries, status);
+                page_mask(b0 + k, N), rdir, leaf_pool, leaf_chunks, dir_stride,
+                        leaf_entries, status);
     // total: only the context's last partition can be short
     int total = ns * m + extraA + extraB;
     if (ns > 0) {
-      const int last = rsel[ns - 1];
+      const int last = sel_at(ns - 1);
       total -= max((last + 1) * m - pages, 0);
     }
     total = min(total, page_stride);
     for (int i = total + tid; i < page_stride; i += RES_BLOCK) res_put(o, i, -1, -1, 0);
     if (tid == 0) npages[row] = total;
   } else {
-    const int ppp = 16 / tp;   // partitions per page
+    const int ppp = 16 / tp;   // partitions per page: a power of two
+    const int ppp_log = 31 - __clz(ppp);
+    auto page_of = [&](int s) { return (s + ((s >> 31) & (ppp - 1))) >> ppp_log; };   // s / ppp
     int carry = 0;
     for (int i0 = 0; i0 < ns; i0 += RES_BLOCK) {
       const int i = i0 + tid;
       int first = 0, pg = -1;
       if (i < ns) {
-        pg = rsel[i] / ppp;
-        first = (i == 0) || (rsel[i - 1] / ppp != pg);
+        pg = page_of(sel_at(i));
+        first = (i == 0) || (page_of(sel_at(i - 1)) != pg);
       }
       int tot;
       const int before = res_block_exclusive_scan<RES_BLOCK>(first, s_wave, tot);
       if (first) {
         uint32_t mk = 0;
         for (int j = i; j < ns && j < i + ppp; ++j) {
-          const int s = rsel[j];
-          if (s / ppp != pg) break;
+          const int s = sel_at(j);
+          if (page_of(s) != pg) break;
           const int t0 = s * tp, cnt = min(tp, N - t0);
           if (s < 0 || cnt <= 0) { spin_raise(status, SPIN_ERR_INVALID); continue; }   // names no token of the row
           mk |= ((1u << cnt) - 1u) << (t0 & 15);
         }
-        emit_page<LOOKUP>(o, carry + before, page_stride, pg, mk, dir, leaf_pool, leaf_chunks, row, dir_stride,
-                  leaf_entries, status);
+        emit_page<LOOKUP>(o, carry + before, page_stride, pg, mk, rdir, leaf_pool, leaf_chunks, dir_stride,
+                        leaf_entries, status);
       }
       carry += tot;
     }

@@ -9,8 +9,7 @@
 // every candidate with key > T and the lowest-index candidates with key == T
 // that are still needed.  Because emission is in index order the output is
 // ascending and ties go to the lower id without any sort.
-#include "spin_resolve_dev.h"
-#include "spin_select_dev.h"
+#include "spin_select_resolve_dev.h"
 
 #define SEL_BLOCK 512
 
@@ -149,7 +148,8 @@ __global__ __launch_bounds__(BLOCK) void spin_select_reg_kernel(
   __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
   spin_var_span span;
   (void)select_reg_row<BLOCK, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
-                                   recent_pages, sel_stride, sel, nsel, (int)blockIdx.x, var, span, s);
+                                   recent_pages, sel_row<false>{sel + (size_t)blockIdx.x * sel_stride, sel_stride, nullptr},
+                                   nsel, (int)blockIdx.x, var, span, s, [] {});
 }
 
 // ---------------------------------------------------------------------------
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(256) void spin_tile_max_kernel(const float *__restr
 // walked the row's scores, and rows with many scores in the threshold's bin were searched whole: stages 2+3, 8 rows
 // of 62500, k' = 244: 28.8 -> 12.7 us; 64 rows of 65536, k' = 1024: 22.8 -> 20.0; and stage 1, which counted the
 // histogram in LDS, 42.7 -> 39.5 us on 8 rows of 62500.
-template <int BLOCK, int MPT, bool RESOLVE>
+template <int BLOCK, int MPT, bool RESOLVE, bool HELD = false>
 __global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
     const float *__restrict__ scores, const float *__restrict__ maxima, int max_stride, int gs_log,
     const int32_t *__restrict__ part_offsets, const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk,
@@ -189,28 +189,36 @@ __global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
     spin_resolve_args ra, int page_stride, int dir_stride, int leaf_entries, int32_t *status) {
   constexpr int CAP = 4096;
   __shared__ tiles_row_lds<BLOCK, CAP> s;
+  __shared__ int32_t held_words[RESOLVE ? sizeof(held_row) / sizeof(int32_t) : 1];
+  held_row &s_held = *(held_row *)held_words;
   const int row = blockIdx.x;
+  [[maybe_unused]] int32_t mydir = 0;
+  // (with 32 maxima per thread there is no register to hold it in)
+  if (RESOLVE && MPT < 32) mydir = row_dir_entry(ra.dir, dir_stride, row);
   float4 mine[MPT / 4];
   load_tile_maxima<MPT>(mine, maxima + (size_t)row * max_stride, max_stride);
   const int b = row / Hkv, h = row - b * Hkv;
   const int PP = part_offsets[b + 1] - part_offsets[b];
   const float *rs = scores + (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
-  int32_t *rsel = sel + (size_t)row * sel_stride;
   const sel_plan pl = select_plan(seq_lens[b], PP, tp, topk, includes_forced, sink_pages, recent_pages, sel_stride);
-  emit_forced<BLOCK>(pl, sel_stride, rsel, nsel, row);
+  const sel_row<HELD> rsel = {sel + (size_t)row * sel_stride, sel_stride, (spin_lds_i32 *)s_held.sel};
   // (a row that is longer than the context's longest one has no maxima for all its tiles)
-  if (pl.kprime > 0 && ((pl.P >> gs_log) > min(max_stride, BLOCK * MPT) || pl.P > ROW_PARTS)) {
-    __syncthreads();
+  const bool no_maxima = pl.kprime > 0 && ((pl.P >> gs_log) > min(max_stride, BLOCK * MPT) || pl.P > ROW_PARTS);
+  if (!no_maxima) {
+    emit_forced<BLOCK>(pl, rsel, nsel, row);
+    if (pl.kprime > 0) select_by_tile_maxima<BLOCK, MPT, CAP>(rs, mine, gs_log, pl, rsel, s);
+  } else {
     select_generic_row<BLOCK>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
                               recent_pages, sel_stride, sel, nsel, row);
-  } else if (pl.kprime > 0) {
-    select_by_tile_maxima<BLOCK, MPT, CAP>(rs, mine, gs_log, pl, sel_stride, rsel, s);
+    __syncthreads();
+    if (HELD)
+      for (int i = threadIdx.x; i < pl.take; i += BLOCK) rsel.lds[i] = rsel.out[i];
   }
   if (RESOLVE) {
-    __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here
-    resolve_row<BLOCK>(row, pl.take, sel, seq_lens, ra.dir, ra.leaf_pool, ra.leaf_chunks, Hkv, tp, sink_pages,
-                       recent_pages, sel_stride, page_stride, dir_stride, leaf_entries, ra.slots, ra.page_ids,
-                       ra.valid_mask, ra.npages, status, spin_var{});
+    if (MPT >= 32) mydir = row_dir_entry(ra.dir, dir_stride, row);
+    resolve_selected<BLOCK>(s_held, rsel, mydir, row, pl.take, sel, seq_lens, ra.dir, ra.leaf_pool, ra.leaf_chunks, Hkv,
+                            tp, sink_pages, recent_pages, page_stride, dir_stride, leaf_entries, ra.slots, ra.page_ids,
+                            ra.valid_mask, ra.npages, status, spin_var{}, nullptr);
   }
 }
 
@@ -233,20 +241,17 @@ int spin_select_impl(spin_ctx *ctx, int32_t batch, const float *scores, const in
       spin_launch(ctx, SPIN_K_SELECT_HIST, spin_tile_max_kernel,
                   dim3((unsigned)((ctx->max_parts + 1023) / 1024), (unsigned)rows), dim3(256), 0, (hipStream_t)stream,
                   scores, part_offsets, c.num_kv_heads, gs_log, maxima, stride);
-#define SPIN_TILES_LAUNCH(BLOCK, MPT)                                                                           \
-  do {                                                                                                        \
-    if (res)                                                                                                  \
-      spin_launch(ctx, SPIN_K_SELECT, spin_select_tiles_kernel<BLOCK, MPT, true>, dim3((unsigned)rows),       \
-                  dim3(BLOCK), 0, (hipStream_t)stream, scores, (const float *)maxima, stride, gs_log,         \
-                  part_offsets, seq_lens, c.num_kv_heads, c.partition_tokens, c.topk, c.topk_includes_forced, \
-                  c.sink_pages, c.recent_pages, ctx->sel_stride, sel, nsel, *res, ctx->page_stride,           \
-                  ctx->dir_stride, c.leaf_entries, (int32_t *)workspace);                                     \
-    else                                                                                                      \
-      spin_launch(ctx, SPIN_K_SELECT, spin_select_tiles_kernel<BLOCK, MPT, false>, dim3((unsigned)rows),      \
-                  dim3(BLOCK), 0, (hipStream_t)stream, scores, (const float *)maxima, stride, gs_log,         \
-                  part_offsets, seq_lens, c.num_kv_heads, c.partition_tokens, c.topk, c.topk_includes_forced, \
-                  c.sink_pages, c.recent_pages, ctx->sel_stride, sel, nsel, spin_resolve_args{}, 0, 0, 0,     \
-                  (int32_t *)nullptr);                                                                        \
+#define SPIN_TILES_LAUNCH1(BLOCK, MPT, RESOLVE, HELD, ARGS)                                                    \
+  spin_launch(ctx, SPIN_K_SELECT, spin_select_tiles_kernel<BLOCK, MPT, RESOLVE, HELD>, dim3((unsigned)rows),   \
+              dim3(BLOCK), 0, (hipStream_t)stream, scores, (const float *)maxima, stride, gs_log,              \
+              part_offsets, seq_lens, c.num_kv_heads, c.partition_tokens, c.topk, c.topk_includes_forced,      \
+              c.sink_pages, c.recent_pages, ctx->sel_stride, sel, nsel, ARGS, ctx->page_stride,                \
+              ctx->dir_stride, c.leaf_entries, (int32_t *)workspace)
+#define SPIN_TILES_LAUNCH(BLOCK, MPT)                                                                          \
+  do {                                                                                                         \
+    if (!res) SPIN_TILES_LAUNCH1(BLOCK, MPT, false, false, spin_resolve_args{});                               \
+    else if (ctx->sel_stride <= SEL_HELD) SPIN_TILES_LAUNCH1(BLOCK, MPT, true, true, *res);                    \
+    else SPIN_TILES_LAUNCH1(BLOCK, MPT, true, false, *res);                                                    \
   } while (0)
     // What every wavefront does for itself favours few of them, the lines of many tiles many: 512 against 1024
     // threads, 8 rows of 62500 and k' = 244: 12.7 / 13.4 us; 64 rows of 65536 and k' = 1024: 21.2 / 19.9 us.
@@ -257,6 +262,7 @@ int spin_select_impl(spin_ctx *ctx, int32_t batch, const float *scores, const in
     else if (stride <= 8192) SPIN_TILES_LAUNCH(1024, 8);
     else SPIN_TILES_LAUNCH(1024, 32);
 #undef SPIN_TILES_LAUNCH
+#undef SPIN_TILES_LAUNCH1
     return spin_launch_status();
   }
 #define SPIN_SELECT_ARGS                                                                                      \

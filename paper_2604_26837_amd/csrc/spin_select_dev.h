@@ -39,6 +39,21 @@ __device__ inline sel_plan select_plan(int N, int PP, int tp, int topk, int incl
   return plan_of(P, nf_lo, first_hi, topk, includes_forced, sel_stride);
 }
 
+// Where a row's selection goes: to global memory, or (HELD: the same launch resolves the row) to LDS only, from where
+// the caller stores it.
+template <bool HELD>
+struct sel_row {
+  int32_t *__restrict__ out;
+  int stride;
+  spin_lds_i32 *lds;
+  __device__ __forceinline__ void put(int pos, int32_t id) const {
+    if (pos < stride) {
+      if (HELD) lds[pos] = id;
+      else out[pos] = id;
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Keys held in registers: KPT consecutive ones per thread, a bit mask says which of them count.
 template <int KPT>
@@ -258,8 +273,8 @@ struct elements_lds {
 };
 
 // The kprime best of the `total` entries of an ordered list in LDS, stored ascending at rsel[first ..].
-template <int BLOCK, int CAP>
-__device__ __forceinline__ void pick_from_list(int total, int kprime, int first, int sel_stride, int32_t *__restrict__ rsel,
+template <int BLOCK, int CAP, typename ROW>
+__device__ __forceinline__ void pick_from_list(int total, int kprime, int first, const ROW &rsel,
                                       elements_lds<BLOCK, CAP> &s) {
   const int tid = threadIdx.x;
   auto pick_list = [&](auto entries) {
@@ -283,7 +298,7 @@ __device__ __forceinline__ void pick_from_list(int total, int kprime, int first,
 #pragma unroll
     for (int j = 0; j < E; ++j)
       if ((pick >> j) & 1u) {
-        if (pos < sel_stride) rsel[pos] = s.id[tid * E + j];
+        rsel.put(pos, s.id[tid * E + j]);
         ++pos;
       }
   };
@@ -302,9 +317,9 @@ __device__ __forceinline__ void pick_from_list(int total, int kprime, int first,
 // bound (key order is float order) and the few that pass form a list in LDS, on which the exact search runs with
 // one to CAP / BLOCK keys per thread.  A row with more than CAP of them (every row where CAP is 0: few scores per
 // thread, for which the list does not pay) searches its registers.
-template <int BLOCK, int KPT, int CAP, typename ID>
+template <int BLOCK, int KPT, int CAP, typename ROW, typename ID>
 __device__ __forceinline__ void select_elements(const float (&f)[KPT], typename key_bits<KPT>::type cand, uint32_t bound,
-                                       int kprime, int first, int sel_stride, int32_t *__restrict__ rsel,
+                                       int kprime, int first, const ROW &rsel,
                                        elements_lds<BLOCK, CAP> &s, ID id) {
   typedef typename key_bits<KPT>::type M;
   [[maybe_unused]] constexpr int NW = BLOCK / 64;
@@ -339,7 +354,7 @@ __device__ __forceinline__ void select_elements(const float (&f)[KPT], typename 
           }
       }
       __syncthreads();
-      pick_from_list<BLOCK, CAP>(total, kprime, first, sel_stride, rsel, s);
+      pick_from_list<BLOCK, CAP>(total, kprime, first, rsel, s);
       return;
     }
   }
@@ -359,20 +374,19 @@ __device__ __forceinline__ void select_elements(const float (&f)[KPT], typename 
 #pragma unroll
   for (int k = 0; k < KPT; ++k)
     if ((pick >> k) & 1u) {
-      if (pos < sel_stride) rsel[pos] = id(k);
+      rsel.put(pos, id(k));
       ++pos;
     }
 }
 
 // forced partitions (a prefix and a suffix of the row) around the kprime candidates, and the padding
-template <int BLOCK>
-__device__ inline void emit_forced(const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
-                                   int32_t *__restrict__ nsel, int row) {
+template <int BLOCK, typename ROW>
+__device__ __forceinline__ void emit_forced(const sel_plan &pl, const ROW &rsel, int32_t *__restrict__ nsel, int row) {
   const int tid = threadIdx.x;
-  for (int i = tid; i < min(pl.nf_lo, sel_stride); i += BLOCK) rsel[i] = i;
+  for (int i = tid; i < min(pl.nf_lo, rsel.stride); i += BLOCK) rsel.put(i, i);
   const int at = pl.nf_lo + pl.kprime;
-  for (int i = tid; i < pl.P - pl.first_hi && at + i < sel_stride; i += BLOCK) rsel[at + i] = pl.first_hi + i;
-  for (int i = pl.take + tid; i < sel_stride; i += BLOCK) rsel[i] = -1;
+  for (int i = tid; i < pl.P - pl.first_hi && at + i < rsel.stride; i += BLOCK) rsel.put(at + i, pl.first_hi + i);
+  for (int i = pl.take + tid; i < rsel.stride; i += BLOCK) rsel.out[i] = -1;
   if (tid == 0) nsel[row] = pl.take;
 }
 
@@ -457,12 +471,14 @@ __device__ __forceinline__ spin_var_span block_var_span(const spin_var &var, siz
 template <int BLOCK, int KPT>
 constexpr int reg_row_cap() { return KPT >= 16 ? 2 * BLOCK : 0; }
 
-template <int BLOCK, int KPT>
+// `meanwhile` issues what the caller wants under way beside the scores.
+template <int BLOCK, int KPT, typename ROW, typename MEANWHILE>
 __device__ __forceinline__ int select_reg_row(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
-    int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, int row,
-    spin_var var, spin_var_span &span, elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> &s) {
+    int recent_pages, const ROW &rsel, int32_t *__restrict__ nsel, int row, spin_var var,
+    spin_var_span &span, elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> &s,
+    MEANWHILE meanwhile) {
   typedef typename key_bits<KPT>::type M;
   constexpr int CAP = reg_row_cap<BLOCK, KPT>();
   const int b = row / Hkv, h = row - b * Hkv;
@@ -471,15 +487,17 @@ __device__ __forceinline__ int select_reg_row(
   const int PP = part_offsets[b + 1] - off_b;
   const size_t vbase = (size_t)Hkv * off_b + (size_t)h * PP;
   const float *rs = scores + vbase;
-  int32_t *rsel = sel + (size_t)row * sel_stride;
+  const int sel_stride = rsel.stride;
   const int c0 = threadIdx.x * KPT;   // this thread's partitions: c0 .. c0 + KPT - 1
   float f[KPT];
+  const __amdgpu_buffer_rsrc_t buf = spin_buffer(rs, (uint32_t)max(PP, 0) * sizeof(float));   // zeros past the row's end
 #pragma unroll
   for (int k4 = 0; k4 < KPT; k4 += 4) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (c0 + k4 < PP) v = *(const float4 *)(rs + c0 + k4);
+    const float4 v = __builtin_bit_cast(float4, spin_buffer_load_kept(buf, (uint32_t)(c0 + k4) * sizeof(float)));
     f[k4] = v.x; f[k4 + 1] = v.y; f[k4 + 2] = v.z; f[k4 + 3] = v.w;
   }
+  __builtin_amdgcn_sched_barrier(0);
+  meanwhile();
 
   // forced partitions: a prefix [0, nf_lo) and a suffix [first_hi, P)
   sel_plan pl;
@@ -497,7 +515,7 @@ __device__ __forceinline__ int select_reg_row(
     pl.kprime = min(pl.kprime, pl.first_hi - pl.nf_lo);
     pl.take = min(pl.nf_lo + pl.kprime + pl.P - pl.first_hi, sel_stride);
   }
-  emit_forced<BLOCK>(pl, sel_stride, rsel, nsel, row);   // under way while the scores are still coming
+  emit_forced<BLOCK>(pl, rsel, nsel, row);   // under way while the scores are still coming
   if (pl.kprime > 0) {
     const M cand = range_bits<KPT>(c0, pl.nf_lo, pl.first_hi);
     uint32_t bound = 0;
@@ -512,7 +530,7 @@ __device__ __forceinline__ int select_reg_row(
         block_kth<BLOCK, 1>(top, cand ? 1u : 0u, pl.kprime, pl.kprime >> 2, s.kth, bound, at_bound);
       }
     }
-    select_elements<BLOCK, KPT, CAP>(f, cand, bound, pl.kprime, pl.nf_lo, sel_stride, rsel, s,
+    select_elements<BLOCK, KPT, CAP>(f, cand, bound, pl.kprime, pl.nf_lo, rsel, s,
                                      [&](int k) { return c0 + k; });
   }
   return pl.take;
@@ -566,9 +584,9 @@ union tiles_row_lds {
 // 65536 token partitions, k' 2560 / 3600 / 4096 / 8192: 67 / 82 / 202 / 217 -> 34 / 37 / 38 / 53 us; 2 rows of 20000,
 // k' 2048 / 8192: 44 / 90 -> 22 / 64.  (Being in the kernel it costs rows that do not come here 0.2 to 0.3 us, out of
 // line as well; four quads under way as good as eight, which take 30 more registers.)
-template <int BLOCK>
+template <int BLOCK, typename ROW>
 __device__ __forceinline__ void select_whole_row(const float *__restrict__ rs, uint32_t lo, uint32_t hi, const sel_plan &pl,
-                                        int sel_stride, int32_t *__restrict__ rsel, row_lds<BLOCK> &s) {
+                                        const ROW &rsel, row_lds<BLOCK> &s) {
   constexpr int NW = BLOCK / 64, V = 4;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int words = (pl.first_hi + 31) >> 5;
@@ -708,18 +726,17 @@ __device__ __forceinline__ void select_whole_row(const float *__restrict__ rs, u
     uint32_t taken = ordered_picks<BLOCK>(w < words ? s.above[w] : 0u, w < words ? s.equal[w] : 0u, quota, s.wtot, at,
                                           picked, eq_picked);
     for (at += first; taken; taken &= taken - 1, ++at)
-      if (at < sel_stride) rsel[at] = w * 32 + __ffs((int)taken) - 1;
+      rsel.put(at, w * 32 + __ffs((int)taken) - 1);
     first += picked;
     quota -= (unsigned)eq_picked;
   }
 }
 
 // False (for the whole workgroup, nothing stored): more scores than the list holds.
-template <int BLOCK, int MPT, int CAP>
+template <int BLOCK, int MPT, int CAP, typename ROW>
 __device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs, const uint32_t (&top)[MPT],
                                            typename key_bits<MPT>::type cand, int t_lo, int t_hi, int gs_log,
-                                           const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
-                                           tiles_lds<BLOCK, CAP> &s) {
+                                           const sel_plan &pl, const ROW &rsel, tiles_lds<BLOCK, CAP> &s) {
   constexpr int NW = BLOCK / 64;
   typedef typename key_bits<MPT>::type M;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -829,7 +846,7 @@ __device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs
   else if (nquads <= BLOCK * 5) gather(std::integral_constant<int, 5>());
   else gather(std::integral_constant<int, 8>());
   if (total > CAP) return false;
-  pick_from_list<BLOCK, CAP>(total, kprime, pl.nf_lo, sel_stride, rsel, s);
+  pick_from_list<BLOCK, CAP>(total, kprime, pl.nf_lo, rsel, s);
   return true;
 }
 
@@ -843,10 +860,9 @@ __device__ inline void load_tile_maxima(float4 (&v)[MPT / 4], const float *__res
   for (int j = 0; j < MPT / 4; ++j)                    // the stride is a multiple of 4
     v[j] = m0 + 4 * j < maxima_stride ? *(const float4 *)(maxima + m0 + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
 }
-template <int BLOCK, int MPT, int CAP>
+template <int BLOCK, int MPT, int CAP, typename ROW>
 __device__ __forceinline__ void select_by_tile_maxima(const float *__restrict__ rs, const float4 (&maxima)[MPT / 4], int gs_log,
-                                             const sel_plan &pl, int sel_stride, int32_t *__restrict__ rsel,
-                                             tiles_row_lds<BLOCK, CAP> &lds) {
+                                             const sel_plan &pl, const ROW &rsel, tiles_row_lds<BLOCK, CAP> &lds) {
   constexpr int NW = BLOCK / 64;
   typedef typename key_bits<MPT>::type M;
   tiles_lds<BLOCK, CAP> &s = lds.tiles;
@@ -877,7 +893,7 @@ __device__ __forceinline__ void select_by_tile_maxima(const float *__restrict__ 
     kmx = spin_wave_max_u32(kmx);
     kmn = spin_wave_min_u32(kmn);
     if (lane == 0) { s.kth.wmax[wave] = kmx; s.kth.wmin[wave] = kmn; }
-  } else if (list_by_tile_maxima<BLOCK, MPT, CAP>(rs, top, cand, t_lo, t_hi, gs_log, pl, sel_stride, rsel, s)) {
+  } else if (list_by_tile_maxima<BLOCK, MPT, CAP>(rs, top, cand, t_lo, t_hi, gs_log, pl, rsel, s)) {
     return;
   }
   __syncthreads();
@@ -888,5 +904,5 @@ __device__ __forceinline__ void select_by_tile_maxima(const float *__restrict__ 
   const int p = ((lane & 16 ? t_hi : t_lo - 1) << gs_log) + (lane & (gs - 1));
   kmx = max(kmx, spin_wave_max_u32(p >= pl.nf_lo && p < pl.first_hi ? score_key(rs[p]) : 0u));
   __syncthreads();
-  select_whole_row<BLOCK>(rs, min(kmn, kmx), kmx + 1, pl, sel_stride, rsel, lds.row);
+  select_whole_row<BLOCK>(rs, min(kmn, kmx), kmx + 1, pl, rsel, lds.row);
 }

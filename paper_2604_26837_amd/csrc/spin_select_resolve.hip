@@ -5,10 +5,9 @@
 // functions run as in the two stage calls, the results are the same bits, and
 // one launch with its start-up latency chain is saved.
 #include "spin_decode_dev.h"
-#include "spin_resolve_dev.h"
-#include "spin_select_dev.h"
+#include "spin_select_resolve_dev.h"
 
-template <int BLOCK, int KPT>
+template <int BLOCK, int KPT, bool HELD>
 __global__ __launch_bounds__(BLOCK) void spin_select_resolve_kernel(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
@@ -17,14 +16,17 @@ __global__ __launch_bounds__(BLOCK) void spin_select_resolve_kernel(
     int32_t *__restrict__ slots, int32_t *__restrict__ page_ids, uint16_t *__restrict__ valid_mask,
     int32_t *__restrict__ npages, int32_t *status, spin_var var) {
   __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
+  __shared__ held_row s_held;
   const int row = blockIdx.x;
+  int32_t mydir;
+  const sel_row<HELD> rsel = {sel + (size_t)row * sel_stride, sel_stride, (spin_lds_i32 *)s_held.sel};
   spin_var_span span = {};
   const int take = select_reg_row<BLOCK, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced,
-                                              sink_pages, recent_pages, sel_stride, sel, nsel, row, var, span, s);
-  __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here
-  resolve_row<BLOCK>(row, take, sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages, recent_pages,
-                     sel_stride, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status, var,
-                     &span);
+                                              sink_pages, recent_pages, rsel, nsel, row, var, span, s,
+                                              [&] { mydir = row_dir_entry(dir, dir_stride, row); });
+  resolve_selected<BLOCK>(s_held, rsel, mydir, row, take, sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages,
+                          recent_pages, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status,
+                          var, &span);
 }
 
 // ---------------------------------------------------------------------------
@@ -135,7 +137,7 @@ struct spin_forced_args {
 
 // workgroups [0, rows): stages 2+3 of a row, exactly as spin_select_resolve_kernel;
 // workgroups [rows, rows + rows * nside): attention over the always-attended pages, nside workgroups per row
-template <int KPT>
+template <int KPT, bool HELD>
 __global__ __launch_bounds__(512) void spin_select_resolve_forced_kernel(
     int rows, const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
@@ -151,14 +153,17 @@ __global__ __launch_bounds__(512) void spin_select_resolve_forced_kernel(
     return;
   }
   __shared__ elements_lds<512, reg_row_cap<512, KPT>()> s;
+  __shared__ held_row s_held;
   const int row = blockIdx.x;
+  int32_t mydir;
+  const sel_row<HELD> rsel = {sel + (size_t)row * sel_stride, sel_stride, (spin_lds_i32 *)s_held.sel};
   spin_var_span span;                // (uniform partitions)
   const int take = select_reg_row<512, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced,
-                                            sink_pages, recent_pages, sel_stride, sel, nsel, row, spin_var{}, span, s);
-  __syncthreads();   // the selection was written by this workgroup: visible to all its threads from here
-  resolve_row<512>(row, take, sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages, recent_pages,
-                   sel_stride, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status,
-                   spin_var{});
+                                            sink_pages, recent_pages, rsel, nsel, row, spin_var{}, span, s,
+                                            [&] { mydir = row_dir_entry(dir, dir_stride, row); });
+  resolve_selected<512>(s_held, rsel, mydir, row, take, sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages,
+                        recent_pages, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status,
+                        spin_var{}, nullptr);
 }
 
 extern "C" int spin_select_resolve_forced(spin_ctx *ctx, int32_t batch, const float *scores,
@@ -188,10 +193,15 @@ extern "C" int spin_select_resolve_forced(spin_ctx *ctx, int32_t batch, const fl
       c.num_kv_heads, c.partition_tokens, c.topk, c.topk_includes_forced, c.sink_pages, c.recent_pages,       \
       ctx->sel_stride, sel, nsel, dir, leaf_pool, leaf_chunks, ctx->page_stride, ctx->dir_stride,             \
       c.leaf_entries, slots, page_ids, valid_mask, npages, (int32_t *)workspace, fa
-  if (ctx->max_parts <= 2048)
-    spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_forced_kernel<4>, SPIN_SRF_ARGS);
-  else
-    spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_forced_kernel<8>, SPIN_SRF_ARGS);
+  const bool held = ctx->sel_stride <= SEL_HELD;   // selections up to this long are handed over in LDS
+#define SPIN_SRF_LAUNCH(KPT)                                                                                    \
+  do {                                                                                                          \
+    if (held) spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_forced_kernel<KPT, true>, SPIN_SRF_ARGS);     \
+    else spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_forced_kernel<KPT, false>, SPIN_SRF_ARGS);         \
+  } while (0)
+  if (ctx->max_parts <= 2048) SPIN_SRF_LAUNCH(4);
+  else SPIN_SRF_LAUNCH(8);
+#undef SPIN_SRF_LAUNCH
 #undef SPIN_SRF_ARGS
   return spin_launch_status();
 }
@@ -221,15 +231,17 @@ static int select_resolve_impl(spin_ctx *ctx, int32_t batch, const float *scores
       c.topk_includes_forced, c.sink_pages, c.recent_pages, ctx->sel_stride, sel, nsel, dir, leaf_pool,       \
       leaf_chunks, ctx->page_stride, ctx->dir_stride, c.leaf_entries, slots, page_ids, valid_mask, npages,    \
       (int32_t *)workspace, ctx->var
-  if (ctx->max_parts <= 2048)
-    spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<512, 4>, dim3((unsigned)rows), dim3(512), SPIN_SR_ARGS);
-  else if (ctx->max_parts <= 4096)
-    spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<512, 8>, dim3((unsigned)rows), dim3(512), SPIN_SR_ARGS);
-  else if (ctx->max_parts <= 8192)   // 512 x 16 against 1024 x 8 and 1024 x 16, stages 2+3 of 8 rows: 9.0 / 10.4 / 11.8 us
-    spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<512, 16>, dim3((unsigned)rows), dim3(512), SPIN_SR_ARGS);
-  else
-    spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<1024, 16>, dim3((unsigned)rows), dim3(1024),
-                SPIN_SR_ARGS);
+  const bool held = ctx->sel_stride <= SEL_HELD;
+#define SPIN_SR_LAUNCH(BLOCK, KPT)                                                                              \
+  do {                                                                                                          \
+    if (held) spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<BLOCK, KPT, true>, dim3((unsigned)rows), dim3(BLOCK), SPIN_SR_ARGS); \
+    else spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<BLOCK, KPT, false>, dim3((unsigned)rows), dim3(BLOCK), SPIN_SR_ARGS);     \
+  } while (0)
+  if (ctx->max_parts <= 2048) SPIN_SR_LAUNCH(512, 4);
+  else if (ctx->max_parts <= 4096) SPIN_SR_LAUNCH(512, 8);
+  else if (ctx->max_parts <= 8192) SPIN_SR_LAUNCH(512, 16);   // against 1024 x 8 and 1024 x 16, stages 2+3 of 8 rows: 9.0 / 10.4 / 11.8 us
+  else SPIN_SR_LAUNCH(1024, 16);
+#undef SPIN_SR_LAUNCH
 #undef SPIN_SR_ARGS
   return spin_launch_status();
 }
