@@ -121,8 +121,14 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_kernel(
 // wherever they live.  A wavefront expands the masks of its pages (dealt round-robin exactly as
 // above) into a token list in LDS -- page order, then token order, so the accumulation order is
 // fixed -- and then treats every 16 list entries as one tile: lane (n, c) fetches 64 contiguous
-// bytes of the key of tile row n per load, and the values of tile rows 4c .. 4c+3 for its 8
-// output channels with 2-byte loads that land in the operand layout of P V directly.  Per
+// bytes of the key of tile row n per load, and 16 bytes of each of the value rows 4c .. 4c+3, which
+// it transposes in registers into the operands of P V (a lane's output channels then are 8n .. 8n+7,
+// eight neighbours, where the page kernel's are 16 apart).  The gather of 256-byte rows bounds this.
+// Against 2-byte loads straight into the operands (32 a tile, whose packing waited for all of them
+// before the next tile was asked for), whole steps, us: 64 rows of 65536 tokens, 1024 attended
+// 54.5 -> 53.7; 96 rows, 2048 attended 91.9 -> 90.3; 8 rows, 2048 attended 41.9 -> 41.1; 16 rows of
+// 8003, 300 attended 21.6 -> 21.3.  Three tiles under way are worse than two (55.0 / 91.3 / 41.4 /
+// 21.6 us), keys and values read with the same hint as well (nt 54.9 us, none 93.9 in the second).  Per
 // attended token that is the algorithmic 512 bytes (two cache lines of K, two of V) instead of
 // the page's 8 KiB, and sixteen times fewer matrix tiles.  Logits, softmax and merge are the
 // code of the page kernel.
@@ -130,21 +136,20 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_kernel(
 
 struct tile_src {
   const uint4 *k;           // key row of tile row n (lane % 16), chunk c (lane / 16): + 4 j
-  const uint16_t *v[4];     // value rows of tile rows 4c .. 4c+3 at channel n: + 16 jn
+  const uint4 *v[4];        // value rows of tile rows 4c .. 4c+3, channels 8n .. 8n+7
 };
 
-// Rows past the end of the list repeat its last entry: their loads stay inside attended data, their
-// logits are masked and their probabilities are exactly zero.
+// Rows past the end of the list, and tiles past it, repeat its last entry: their loads stay inside attended data (and
+// touch few lines), their logits are masked and their probabilities are exactly zero.
 __device__ inline tile_src tile_source(const uint4 *__restrict__ pool, const uint32_t *tok, int first, int count, int lane) {
   tile_src s;
   const int n = lane & 15, c = lane >> 4;
-  const int last = count - 1 - first;                    // >= 0: the tile exists
-  const uint32_t e = tok[first + min(n, last)];          // slot * 16 + token
+  const uint32_t e = tok[min(first + n, count - 1)];     // slot * 16 + token
   s.k = pool + (size_t)(e >> 4) * SPIN_SLOT_U4 + (e & 15u) * 16 + c;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const uint32_t ev = tok[first + min(4 * c + i, last)];
-    s.v[i] = (const uint16_t *)(pool + (size_t)(ev >> 4) * SPIN_SLOT_U4 + SPIN_KTILE_U4) + (ev & 15u) * SPIN_HEAD_DIM + n;
+    const uint32_t ev = tok[min(first + 4 * c + i, count - 1)];
+    s.v[i] = pool + (size_t)(ev >> 4) * SPIN_SLOT_U4 + SPIN_KTILE_U4 + (ev & 15u) * 16 + n;
   }
   return s;
 }
@@ -152,19 +157,54 @@ __device__ inline tile_src tile_source(const uint4 *__restrict__ pool, const uin
 __device__ inline void load_tile(page_regs &r, const tile_src &s) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) r.k[j] = spin_nt_load(s.k + 4 * j);
-  // operand layout of P V: r.v[jv] = {rows 4c,4c+1 | rows 4c+2,4c+3} for channel block 2jv, then 2jv+1.
-  // Each 16-bit load lands in its half of an operand register, so nothing waits for the data
-  // before the tile is consumed.
-  typedef unsigned short us8 __attribute__((ext_vector_type(8)));
+#pragma unroll
+  for (int i = 0; i < 4; ++i) r.v[i] = *s.v[i];
+}
+
+// The value rows 4c .. 4c+3 a lane holds, as the operands of P V: r.v[jv] = {rows 4c,4c+1 | rows 4c+2,4c+3} of channel
+// 8n + 2jv, then of 8n + 2jv+1 (channel block jn has channels 8n + jn here, decode_finish<.., true>).
+__device__ __forceinline__ void transpose_values(page_regs &r) {
+  const uint32_t w[4][4] = {{r.v[0].x, r.v[0].y, r.v[0].z, r.v[0].w}, {r.v[1].x, r.v[1].y, r.v[1].z, r.v[1].w},
+                            {r.v[2].x, r.v[2].y, r.v[2].z, r.v[2].w}, {r.v[3].x, r.v[3].y, r.v[3].z, r.v[3].w}};
 #pragma unroll
   for (int jv = 0; jv < 4; ++jv) {
-    us8 w;
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) w[4 * blk + i] = s.v[i][16 * (2 * jv + blk)];
-    r.v[jv] = __builtin_bit_cast(uint4, w);
+    auto lows = [&](int a, int b) { return (w[a][jv] & 0xffffu) | (w[b][jv] << 16); };
+    auto highs = [&](int a, int b) { return (w[a][jv] >> 16) | (w[b][jv] & 0xffff0000u); };
+    r.v[jv] = make_uint4(lows(0, 1), lows(2, 3), highs(0, 1), highs(2, 3));
   }
+}
+
+// Attends the `total` >= 1 tokens of a list through a ring of D register buffers, as attend_lane_pages does pages: the
+// loop has no branch around a load, so that it waits for exactly the tile it is about to read.
+template <int D>
+__device__ __forceinline__ void attend_token_tiles(softmax_state &st, const uint4 *__restrict__ pool, const uint32_t *tok,
+                                                   int total, int lane, int c, const spin_bf16x8 (&qf)[4],
+                                                   float scale_log2e) {
+  page_regs r[D];
+  const int ntiles = (total + 15) >> 4;
+  auto load = [&](int d, int k) {
+    load_tile(r[d], tile_source(pool, tok, 16 * k, total, lane));
+    __builtin_amdgcn_sched_barrier(0);   // asked for in the order in which the loop asks again
+  };
+  auto attend = [&](int d, int k) {
+    const int left = total - 16 * k;
+    const spin_f32x4 s = tile_logits(r[d], qf);
+    transpose_values(r[d]);
+    tile_attend(st, s, r[d], left >= 16 ? 0xffffu : ((1u << left) - 1u), c, scale_log2e);
+  };
+#pragma unroll
+  for (int d = 0; d < D; ++d) load(d, d);
+  int k = 0;
+  for (; k + D <= ntiles; k += D) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      attend(d, k + d);
+      load(d, k + d + D);
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < D - 1; ++d)
+    if (k + d < ntiles) attend(d, k + d);
 }
 
 template <int WAVES>
@@ -175,13 +215,13 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_tokens_kernel(
     const int32_t *__restrict__ skip, float scale_log2e, float *part_ml, float *part_acc, int32_t *tickets,
     uint16_t *__restrict__ out, float *__restrict__ lse, int32_t *status) {
   extern __shared__ __align__(16) float smem[];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // the token lists live behind the merge buffers of decode_finish
-  uint32_t *tok = (uint32_t *)(smem + WAVES * G * (SPIN_HEAD_DIM + 2)) + (threadIdx.x >> 6) * TOK_LIST;
+  uint32_t *tok = (uint32_t *)(smem + WAVES * G * (SPIN_HEAD_DIM + 2)) + wave * TOK_LIST;
 
   const int row = blockIdx.x / nsplit;
   const int split = blockIdx.x - row * nsplit;
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
   const int n = lane & 15, c = lane >> 4;
   const int b = row / Hkv;
   const int h = row - b * Hkv;
@@ -191,39 +231,31 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_tokens_kernel(
   int np = npages[row];
   np = np < 0 ? 0 : (np > page_stride ? page_stride : np);
 
+  // this wavefront's pages: first + i * stride, i < nw; the entries of the first 64 are asked for ahead of all else
+  int p = first + lane * stride;
+  int next_slot = rslots[min(p, page_stride - 1)];
+  unsigned next_mask = rmask[min(p, page_stride - 1)];
   spin_bf16x8 qf[4];
-  {
-    const uint4 *qrow = (const uint4 *)(q + ((size_t)(b * Hq + h * G + (n < G ? n : 0))) * SPIN_HEAD_DIM);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint4 v = qrow[j * 4 + c];
-      if (n >= G) v = make_uint4(0, 0, 0, 0);
-      qf[j] = __builtin_bit_cast(spin_bf16x8, v);
-    }
-  }
+  load_queries(qf, q, b, h, G, Hq, n, c);
   softmax_state st;
-  st.m = NEG_INF;
-  st.l = 0.f;
-#pragma unroll
-  for (int i = 0; i < 8; ++i) st.acc[i] = (spin_f32x4){0.f, 0.f, 0.f, 0.f};
+  softmax_reset(st);
 
-  const int nw_max = (page_stride - first + stride - 1) / stride;
-  for (int base = 0; base < nw_max; base += 64) {
+  const int nw = np > first ? (np - first + stride - 1) / stride : 0;
+  for (int base = 0; base < nw; base += 64) {
     int myslot = 0;
     unsigned mymask = 0;
-    const int p = first + (base + lane) * stride;
-    if (p < page_stride) {
-      myslot = rslots[p];
-      mymask = rmask[p];
+    if (base + lane < nw) {
+      if (next_slot < 0 || (int64_t)next_slot >= pool_slots) {
+        spin_raise(status, SPIN_ERR_SLOT_RANGE);
+      } else {
+        myslot = next_slot;
+        mymask = next_mask;
+      }
     }
-    const int nw = np > first ? (np - first + stride - 1) / stride : 0;
-    if (base >= nw) break;
-    const int cnt = (nw - base) < 64 ? (nw - base) : 64;
-    if (lane >= cnt) mymask = 0;
-    else if (myslot < 0 || (int64_t)myslot >= pool_slots) {
-      spin_raise(status, SPIN_ERR_SLOT_RANGE);
-      myslot = 0;
-      mymask = 0;
+    p += 64 * stride;
+    if (base + 64 < nw) {
+      next_slot = rslots[min(p, page_stride - 1)];
+      next_mask = rmask[min(p, page_stride - 1)];
     }
     // token list of this batch of pages: page order, then token order
     const int mine = __popc(mymask);
@@ -239,24 +271,11 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_tokens_kernel(
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the wavefront reads its own list: program order
-    // two register buffers: the next tile's loads are issued before the current one is consumed
-    page_regs r[2];
-    const int ntiles = (total + 15) >> 4;
-    if (ntiles > 0) load_tile(r[0], tile_source(pool, tok, 0, total, lane));
-    for (int k = 0; k < ntiles; k += 2) {
-      if (k + 1 < ntiles) load_tile(r[1], tile_source(pool, tok, 16 * (k + 1), total, lane));
-      const int left0 = total - 16 * k;
-      tile_attend(st, tile_logits(r[0], qf), r[0], left0 >= 16 ? 0xffffu : ((1u << left0) - 1u), c, scale_log2e);
-      if (k + 2 < ntiles) load_tile(r[0], tile_source(pool, tok, 16 * (k + 2), total, lane));
-      if (k + 1 < ntiles) {
-        const int left1 = total - 16 * (k + 1);
-        tile_attend(st, tile_logits(r[1], qf), r[1], left1 >= 16 ? 0xffffu : ((1u << left1) - 1u), c, scale_log2e);
-      }
-    }
+    if (total > 0) attend_token_tiles<2>(st, pool, tok, total, lane, c, qf, scale_log2e);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // before the next batch overwrites the list
   }
   __syncthreads();   // the merge buffers are separate from the lists, but keep the phases apart
-  decode_finish<WAVES>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, pstride, part_ml, part_acc, tickets, out,
+  decode_finish<WAVES, false, true>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, pstride, part_ml, part_acc, tickets, out,
                        lse);
 }
 

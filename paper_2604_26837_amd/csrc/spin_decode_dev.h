@@ -159,8 +159,9 @@ __device__ inline void write_out(uint16_t *__restrict__ out, float *__restrict__
 // launch on the same stream to start from.
 // to_partial: the merged result of the row is stored there as well, unnormalised, instead of being
 // written to `out` (the first of two attention passes over one page list).
+// LANE_ROWS: a lane's accumulators of channel block jn are of channel 8n + jn, not 16 jn + n.
 // Returns true in the workgroup that wrote the row's output.
-template <int WAVES, bool ONLY_PARTIAL = false>
+template <int WAVES, bool ONLY_PARTIAL = false, bool LANE_ROWS = false>
 __device__ __forceinline__ bool decode_finish(softmax_state &st, int row, int split, int b, int h, int lane, int wave,
                                               int n, int c, int G, int Hq, int nsplit, int pstride,
                                               float *part_ml, float *part_acc, int32_t *tickets,
@@ -182,7 +183,8 @@ __device__ __forceinline__ bool decode_finish(softmax_state &st, int row, int sp
     const int head = 4 * c + i;
     if (head < G) {
 #pragma unroll
-      for (int jn = 0; jn < 8; ++jn) s_acc[(wave * G + head) * SPIN_HEAD_DIM + 16 * jn + n] = st.acc[jn][i];
+      for (int jn = 0; jn < 8; ++jn)
+        s_acc[(wave * G + head) * SPIN_HEAD_DIM + (LANE_ROWS ? 8 * n + jn : 16 * jn + n)] = st.acc[jn][i];
     }
   }
   if (c == 0 && n < G) {
