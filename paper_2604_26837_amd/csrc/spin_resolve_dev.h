@@ -277,8 +277,7 @@ __device__ __forceinline__ void resolve_row(
                         leaf_entries, status);
     for (int k = tid; k < extraB; k += RES_BLOCK)
       emit_page<LOOKUP>(o, sel_below_b * m + ((A >= 0 && A <= B) ? extraA : 0) + k, page_stride, b0 + k,
-                page_mask(b0 + k, N), rdir, leaf_pool, leaf_chunks, dir_stride,
-                        leaf_entries, status);
+                        page_mask(b0 + k, N), rdir, leaf_pool, leaf_chunks, dir_stride, leaf_entries, status);
     // total: only the context's last partition can be short
     int total = ns * m + extraA + extraB;
     if (ns > 0) {
