@@ -152,6 +152,8 @@ __device__ inline uint4 spin_nt_load(const uint4 *p) {
 // beyond the buffer reads zeros and moves nothing, so a load that some lanes or some passes of a loop do without needs
 // no branch.  That is what software pipelines are written with here: where loads under way are joined by a path without
 // them, the compiler has to assume the path with the fewest, and waits for the ones just issued along with those it needs.
+// Only lane_offset is sure to be checked against the buffer: `offset` reaches the instruction as a scalar that the check
+// may leave out, so it must not carry a lane from inside the buffer past its end.
 __device__ inline __amdgpu_buffer_rsrc_t spin_buffer(const void *p, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00027000);
 }

@@ -65,8 +65,9 @@ __device__ __forceinline__ sketch_row sketch_row_of(const int32_t *__restrict__ 
 // of it is the second operand of an instruction whose columns are those 16 tokens of the two tiles.  Rows of heads that
 // the group does not have start from -inf instead of zero, so that the maximum needs no test per head; over the lane
 // quarters it is taken of both halves at once, after which quarters 0 and 2 store 32 neighbouring scores.
-// A wavefront asks for its 16 tiles at once (ONE), no load and no store is behind a branch (see spin_buffer).  MAXIMA:
-// tm.at is there (asked for at run time, it slowed the loop).
+// A wavefront asks for its 16 tiles at once (ONE), no load and no store is behind a branch (see spin_buffer); tiles past
+// the last are beyond the buffer by the lane's own offset.  MAXIMA: tm.at is there (asked for at run time, it slowed the
+// loop).
 // 64 rows of 65536 tokens, groups of 8: 33.3 -> 25.4 us; 16 rows of 16000, groups of 16: 10.3 -> 3.5; 32 rows of 30000,
 // groups of 5: 12.4 -> 6.2; against 8-byte loads behind branches, two exchanges through LDS per tile and one tile's
 // 16 scores per store.
@@ -103,7 +104,7 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
   uint4 ld[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    ld[u] = spin_buffer_load(in, at_in, 2 * u * 512);
+    ld[u] = spin_buffer_load(in, at_in + 2 * u * 512, 0);
     __builtin_amdgcn_sched_barrier(0);
   }
   // A operand: row n = head, k = sketched channels 4c..4c+3
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
       const uint2 lo = make_uint2(ld[u].x, ld[u].y), hi = make_uint2(ld[u].z, ld[u].w);
       const spin_f32x4 s0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qf, __builtin_bit_cast(spin_s16x4, lo), start, 0, 0, 0);
       const spin_f32x4 s1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qf, __builtin_bit_cast(spin_s16x4, hi), start, 0, 0, 0);
-      if (!ONE) ld[u] = spin_buffer_load(in, at_in, (ROUND + 2 * u) * 512);
+      if (!ONE) ld[u] = spin_buffer_load(in, at_in + (ROUND + 2 * u) * 512, 0);
       const float m0 = fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3]));
       const float m1 = fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3]));
       float m = spin_max_xor16(spin_max_xor32(m0, m1));
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch4_kernel(
   for (int u = 0; u < U; ++u)
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      ld[u][i] = spin_buffer_load(in, at_in, (4 * u + 2 * i) * 512);
+      ld[u][i] = spin_buffer_load(in, at_in + (4 * u + 2 * i) * 512, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   spin_s16x4 qa[4];
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch4_kernel(
         const uint2 lo = make_uint2(ld[u][i].x, ld[u][i].y), hi = make_uint2(ld[u][i].z, ld[u][i].w);
         s = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qa[2 * i], __builtin_bit_cast(spin_s16x4, lo), s, 0, 0, 0);
         s = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(qa[2 * i + 1], __builtin_bit_cast(spin_s16x4, hi), s, 0, 0, 0);
-        if (!ONE) ld[u][i] = spin_buffer_load(in, at_in, (ROUND + 4 * u + 2 * i) * 512);
+        if (!ONE) ld[u][i] = spin_buffer_load(in, at_in + (ROUND + 4 * u + 2 * i) * 512, 0);
       }
       float mx = -__builtin_inff();               // heads 0..3 of the lane's token
 #pragma unroll
