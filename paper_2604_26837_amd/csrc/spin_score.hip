@@ -16,6 +16,8 @@
 // row's values for four heads and the maximum over the group's heads needs no
 // exchange for groups of up to four heads (two otherwise).  Summary tiles are
 // stored chunk-major so each load is a contiguous wavefront transaction.
+#include <algorithm>
+
 #include "spin_score_dev.h"
 
 #define SCORE_WAVES 4
@@ -74,10 +76,9 @@ __device__ __forceinline__ sketch_row sketch_row_of(const int32_t *__restrict__ 
 template <bool MAXIMA, bool ONE>
 __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
     const uint16_t *__restrict__ q, const uint4 *__restrict__ summ, const int32_t *__restrict__ chan,
-    const int32_t *__restrict__ part_offsets, int Hq, int Hkv, int G, int tiles_per_wg, int wgs_per_row,
+    const int32_t *__restrict__ part_offsets, int Hkv, int G, int tiles_per_wg, int b0, int h0,
     float *__restrict__ scores, tile_maxima tm) {
-  const int row = blockIdx.x / wgs_per_row, chunk = blockIdx.x - row * wgs_per_row;
-  const int b = row / Hkv, h = row - b * Hkv;
+  const int chunk = blockIdx.x, b = b0 + blockIdx.z, h = h0 + blockIdx.y, row = b * Hkv + h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, c = lane >> 4;
   const sketch_row sr = sketch_row_of(chan, part_offsets, b, h, c);
@@ -88,7 +89,7 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
   const size_t base = (size_t)Hkv * sr.off + (size_t)h * sr.PP;
   constexpr int U = 8;                            // pairs of tiles per wavefront and round
   constexpr int ROUND = SCORE_WAVES * 2 * U;
-  const uint16_t *qrow = q + ((size_t)(b * Hq + h * G + min(n, G - 1))) * SPIN_HEAD_DIM;
+  const uint16_t *qrow = q + ((size_t)(row * G + min(n, G - 1))) * SPIN_HEAD_DIM;
   uint32_t e[4];                                  // asked for ahead of the tiles
 #pragma unroll
   for (int i = 0; i < 4; ++i) e[i] = qrow[sr.ch[i]];
@@ -153,10 +154,9 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
 template <bool MAXIMA, bool ONE>
 __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch4_kernel(
     const uint16_t *__restrict__ q, const uint4 *__restrict__ summ, const int32_t *__restrict__ chan,
-    const int32_t *__restrict__ part_offsets, int Hq, int Hkv, int G, int tiles_per_wg, int wgs_per_row,
+    const int32_t *__restrict__ part_offsets, int Hkv, int G, int tiles_per_wg, int b0, int h0,
     float *__restrict__ scores, tile_maxima tm) {
-  const int row = blockIdx.x / wgs_per_row, chunk = blockIdx.x - row * wgs_per_row;
-  const int b = row / Hkv, h = row - b * Hkv;
+  const int chunk = blockIdx.x, b = b0 + blockIdx.z, h = h0 + blockIdx.y, row = b * Hkv + h;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, c = lane >> 4;
   const sketch_row sr = sketch_row_of(chan, part_offsets, b, h, c);
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch4_kernel(
   constexpr int ROUND = SCORE_WAVES * 4 * U;
 
   // first operands: lane (r, c) supplies row r = 4j + g, channels 4c .. 4c+3; asked for ahead of the tiles
-  const uint16_t *qrow = q + ((size_t)(b * Hq + h * G + min(n & 3, G - 1))) * SPIN_HEAD_DIM;
+  const uint16_t *qrow = q + ((size_t)(row * G + min(n & 3, G - 1))) * SPIN_HEAD_DIM;
   uint32_t e[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) e[i] = qrow[sr.ch[i]];
@@ -281,21 +281,32 @@ int spin_score_impl(spin_ctx *ctx, int32_t batch, const void *q, const void *sum
     // 26.4 / 25.6 / 26.9 / 26.4 / 28.2 us on 64 rows of 65536 tokens)
     const bool four = ctx->group <= 4 && (c.score_tiles_per_wg % 4) == 0;
     const int tiles_per_wg = c.score_tiles_per_wg ? c.score_tiles_per_wg : 64, max_tiles = max_pp / 16;
-    const int wgs = (max_tiles + tiles_per_wg - 1) / tiles_per_wg;
-#define SPIN_SKETCH_ARGS                                                                                         \
-  dim3((unsigned)rows * wgs), dim3(SCORE_WAVES * 64), 0, st, (const uint16_t *)q, (const uint4 *)summaries, chan_idx, \
-      part_offsets, c.num_q_heads, c.num_kv_heads, ctx->group, tiles_per_wg, wgs, scores, tm
+    // The grid is as long as the context's longest row, so that most workgroups of a context sized for more than is
+    // running are empty.  They cost the time to start them, which a grid of three dimensions halves (no divisions), and
+    // an odd number of them per row keeps the rows' first workgroups, the only ones with work then, from all going to
+    // the same of the 8 dies.  1024 rows of 2000 tokens in contexts for 32768 / 36000: 94 / 22 -> 14 / 15 us; 256 rows of
+    // 4096 for 131072 / 1048576: 27 / 106 -> 13.5 / 86; 8 rows of 4096 and 64 of 65536 in contexts of their length 3.9 / 24.5
+    // -> 4.0 / 24.2.
+    const int wgs = ((max_tiles + tiles_per_wg - 1) / tiles_per_wg) | 1;
+    constexpr int MOST = 65535;                   // of the grid's second and third dimension
+#define SPIN_SKETCH_LAUNCH1(KERNEL)                                                                              \
+  for (int b0 = 0; b0 < batch; b0 += MOST)                                                                       \
+    for (int h0 = 0; h0 < c.num_kv_heads; h0 += MOST)                                                            \
+      spin_launch(ctx, SPIN_K_SCORE, KERNEL,                                                                     \
+                  dim3((unsigned)wgs, (unsigned)std::min(c.num_kv_heads - h0, MOST), (unsigned)std::min(batch - b0, MOST)), \
+                  dim3(SCORE_WAVES * 64), 0, st, (const uint16_t *)q, (const uint4 *)summaries, chan_idx, part_offsets, \
+                  c.num_kv_heads, ctx->group, tiles_per_wg, b0, h0, scores, tm)
 #define SPIN_SKETCH_LAUNCH(KERNEL)                                                            \
   do {                                                                                        \
-    if (maxima && tiles_per_wg <= 64) spin_launch(ctx, SPIN_K_SCORE, KERNEL<true, true>, SPIN_SKETCH_ARGS); \
-    else if (maxima) spin_launch(ctx, SPIN_K_SCORE, KERNEL<true, false>, SPIN_SKETCH_ARGS);   \
-    else if (tiles_per_wg <= 64) spin_launch(ctx, SPIN_K_SCORE, KERNEL<false, true>, SPIN_SKETCH_ARGS); \
-    else spin_launch(ctx, SPIN_K_SCORE, KERNEL<false, false>, SPIN_SKETCH_ARGS);              \
+    if (maxima && tiles_per_wg <= 64) SPIN_SKETCH_LAUNCH1((KERNEL<true, true>));              \
+    else if (maxima) SPIN_SKETCH_LAUNCH1((KERNEL<true, false>));                              \
+    else if (tiles_per_wg <= 64) SPIN_SKETCH_LAUNCH1((KERNEL<false, true>));                  \
+    else SPIN_SKETCH_LAUNCH1((KERNEL<false, false>));                                         \
   } while (0)
     if (four) SPIN_SKETCH_LAUNCH(spin_score_sketch4_kernel);
     else SPIN_SKETCH_LAUNCH(spin_score_sketch_kernel);
 #undef SPIN_SKETCH_LAUNCH
-#undef SPIN_SKETCH_ARGS
+#undef SPIN_SKETCH_LAUNCH1
   }
   return spin_launch_status();
 }

@@ -55,3 +55,27 @@ def test_scores_and_maxima(group, tiles_per_wg):
                 r = b * kv + h
                 assert np.array_equal(sel[r, :int(nsel[r])].cpu().numpy(), want)
     assert (got[total:] == 7.5).all()
+
+
+@pytest.mark.parametrize("batch,kv", [(65537, 1), (1, 65537), (70, 1000)])
+def test_more_requests_or_heads_than_a_grid_dimension_holds(batch, kv):
+    sp = binding.Spin(max_batch=batch, num_q_heads=kv, num_kv_heads=kv, partition_tokens=1, score_kind=synth.SCORE_SKETCH,
+                      topk=4, sink_pages=0, recent_pages=0, max_context=32)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(batch)
+    # one tile per row; whole numbers, whose sums are exact in any order
+    summ = torch.randint(-8, 9, (batch, kv, 4, 16, 4), generator=gen, device=DEV).to(torch.bfloat16)
+    q = torch.randint(-8, 9, (batch, kv, 128), generator=gen, device=DEV).to(torch.bfloat16)
+    chan = torch.randint(0, 128, (kv, 16), generator=gen, device=DEV, dtype=torch.int32)
+    off = torch.arange(0, 16 * batch + 1, 16, dtype=torch.int32, device=DEV)
+    seq = torch.full((batch,), 16, dtype=torch.int32, device=DEV)
+    scores = torch.full((batch * kv * 16,), 7.5, device=DEV)
+    ws = sp.new_workspace(DEV)
+    sp.score_partitions(batch, q, summ.view(-1).view(torch.uint8), chan, off, seq, scores, ws)
+    torch.cuda.synchronize()
+    taken = torch.gather(q.float(), 2, chan.long().expand(batch, kv, 16))
+    want = torch.zeros((batch, kv, 16), device=DEV)
+    for quad in range(4):
+        for i in range(4):
+            want += taken[:, :, 4 * quad + i, None] * summ[:, :, quad, :, i].float()
+    assert torch.equal(scores.view(batch, kv, 16), want)
