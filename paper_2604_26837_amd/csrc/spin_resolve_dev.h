@@ -33,10 +33,11 @@ __device__ inline void res_put(const res_out &o, int pos, int32_t slot, int32_t 
 #define RES_DIR_LDS 256
 #define SEL_HELD 2304          // a top 2048 with 256 forced ones; with these the launch by tile maxima stays under 64 KiB
 
-// What the launch that selects a row has of it in LDS when it goes on to stage 3: the selection (where no longer than
+// What the launch that selects a row has of it in LDS when it goes on to stage 3: the selection (HELD: no longer than
 // SEL_HELD) and the directory entries (where at most RES_DIR_LDS).
+template <bool HELD>
 struct held_row {
-  int32_t sel[SEL_HELD];
+  int32_t sel[HELD ? SEL_HELD : 1];
   int32_t dir[RES_DIR_LDS];
 };
 
@@ -94,7 +95,7 @@ __device__ __forceinline__ void resolve_row(
     int sink_pages, int recent_pages, int sel_stride, int page_stride, int dir_stride, int leaf_entries,
     int32_t *__restrict__ slots, int32_t *__restrict__ page_ids, uint16_t *__restrict__ valid_mask,
     int32_t *__restrict__ npages, int32_t *status, spin_var var, const spin_var_span *known = nullptr,
-    held_row *held = nullptr) {
+    held_row<HELD_SEL> *held = nullptr) {
   constexpr int RES_WAVES = RES_BLOCK / 64;
   __shared__ int s_wave[RES_WAVES];
   __shared__ int s_flagA, s_flagB, s_cntB;

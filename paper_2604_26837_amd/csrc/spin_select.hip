@@ -189,8 +189,8 @@ __global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
     spin_resolve_args ra, int page_stride, int dir_stride, int leaf_entries, int32_t *status) {
   constexpr int CAP = 4096;
   __shared__ tiles_row_lds<BLOCK, CAP> s;
-  __shared__ int32_t held_words[RESOLVE ? sizeof(held_row) / sizeof(int32_t) : 1];
-  held_row &s_held = *(held_row *)held_words;
+  __shared__ int32_t held_words[RESOLVE ? sizeof(held_row<HELD>) / sizeof(int32_t) : 1];
+  held_row<HELD> &s_held = *(held_row<HELD> *)held_words;
   const int row = blockIdx.x;
   [[maybe_unused]] int32_t mydir = 0;
   // (with 32 maxima per thread there is no register to hold it in)

@@ -16,7 +16,7 @@ __global__ __launch_bounds__(BLOCK) void spin_select_resolve_kernel(
     int32_t *__restrict__ slots, int32_t *__restrict__ page_ids, uint16_t *__restrict__ valid_mask,
     int32_t *__restrict__ npages, int32_t *status, spin_var var) {
   __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
-  __shared__ held_row s_held;
+  __shared__ held_row<HELD> s_held;
   const int row = blockIdx.x;
   int32_t mydir;
   const sel_row<HELD> rsel = {sel + (size_t)row * sel_stride, sel_stride, (spin_lds_i32 *)s_held.sel};
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(512) void spin_select_resolve_forced_kernel(
     return;
   }
   __shared__ elements_lds<512, reg_row_cap<512, KPT>()> s;
-  __shared__ held_row s_held;
+  __shared__ held_row<HELD> s_held;
   const int row = blockIdx.x;
   int32_t mydir;
   const sel_row<HELD> rsel = {sel + (size_t)row * sel_stride, sel_stride, (spin_lds_i32 *)s_held.sel};

@@ -13,16 +13,21 @@ from paper_2604_26837_amd import build
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
-@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
-def test_sketch_kernels_pass_no_scalar_offset(tmp_path):
-    out = str(tmp_path / "score.asm")
+def device_assembly(source, tmp_path):
+    """The assembly of one of the library's sources, compiled as the library is."""
+    out = str(tmp_path / (source + ".asm"))
     cmd = [HIPCC, *(f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")), "-S", "--offload-device-only",
            "-I", os.path.join(build.ROOT, "include"), "-I", os.path.join(build.PKG_DIR, "csrc"),
-           os.path.join(build.PKG_DIR, "csrc", "spin_score.hip"), "-o", out]
+           os.path.join(build.PKG_DIR, "csrc", source), "-o", out]
     res = subprocess.run(cmd, capture_output=True, text=True, timeout=600)
     assert res.returncode == 0, res.stderr[-3000:]
+    return out
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not installed")
+def test_sketch_kernels_pass_no_scalar_offset(tmp_path):
     kernel, seen = None, {}
-    with open(out) as f:
+    with open(device_assembly("spin_score.hip", tmp_path)) as f:
         for line in f:
             label = re.match(r"(_Z\w*spin_score_sketch\w*):", line)
             if label:
