@@ -193,14 +193,11 @@ extern "C" int spin_select_resolve_forced(spin_ctx *ctx, int32_t batch, const fl
       c.num_kv_heads, c.partition_tokens, c.topk, c.topk_includes_forced, c.sink_pages, c.recent_pages,       \
       ctx->sel_stride, sel, nsel, dir, leaf_pool, leaf_chunks, ctx->page_stride, ctx->dir_stride,             \
       c.leaf_entries, slots, page_ids, valid_mask, npages, (int32_t *)workspace, fa
-  const bool held = ctx->sel_stride <= SEL_HELD;   // selections up to this long are handed over in LDS
-#define SPIN_SRF_LAUNCH(KPT)                                                                                    \
-  do {                                                                                                          \
-    if (held) spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_forced_kernel<KPT, true>, SPIN_SRF_ARGS);     \
-    else spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_forced_kernel<KPT, false>, SPIN_SRF_ARGS);         \
-  } while (0)
-  if (ctx->max_parts <= 2048) SPIN_SRF_LAUNCH(4);
-  else SPIN_SRF_LAUNCH(8);
+  // selections up to SEL_HELD long, which all of at most 2048 partitions are, are handed over in LDS
+#define SPIN_SRF_LAUNCH(KPT, HELD) spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_forced_kernel<KPT, HELD>, SPIN_SRF_ARGS)
+  if (ctx->max_parts <= 2048) SPIN_SRF_LAUNCH(4, true);
+  else if (ctx->sel_stride <= SEL_HELD) SPIN_SRF_LAUNCH(8, true);
+  else SPIN_SRF_LAUNCH(8, false);
 #undef SPIN_SRF_LAUNCH
 #undef SPIN_SRF_ARGS
   return spin_launch_status();
@@ -231,17 +228,19 @@ static int select_resolve_impl(spin_ctx *ctx, int32_t batch, const float *scores
       c.topk_includes_forced, c.sink_pages, c.recent_pages, ctx->sel_stride, sel, nsel, dir, leaf_pool,       \
       leaf_chunks, ctx->page_stride, ctx->dir_stride, c.leaf_entries, slots, page_ids, valid_mask, npages,    \
       (int32_t *)workspace, ctx->var
-  const bool held = ctx->sel_stride <= SEL_HELD;
+#define SPIN_SR_LAUNCH1(BLOCK, KPT, HELD)                                                                       \
+  spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<BLOCK, KPT, HELD>, dim3((unsigned)rows), dim3(BLOCK), SPIN_SR_ARGS)
 #define SPIN_SR_LAUNCH(BLOCK, KPT)                                                                              \
   do {                                                                                                          \
-    if (held) spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<BLOCK, KPT, true>, dim3((unsigned)rows), dim3(BLOCK), SPIN_SR_ARGS); \
-    else spin_launch(ctx, SPIN_K_SELECT, spin_select_resolve_kernel<BLOCK, KPT, false>, dim3((unsigned)rows), dim3(BLOCK), SPIN_SR_ARGS);     \
+    if (ctx->sel_stride <= SEL_HELD) SPIN_SR_LAUNCH1(BLOCK, KPT, true);                                         \
+    else SPIN_SR_LAUNCH1(BLOCK, KPT, false);                                                                    \
   } while (0)
-  if (ctx->max_parts <= 2048) SPIN_SR_LAUNCH(512, 4);
+  if (ctx->max_parts <= 2048) SPIN_SR_LAUNCH1(512, 4, true);   // no selection of so few partitions is longer
   else if (ctx->max_parts <= 4096) SPIN_SR_LAUNCH(512, 8);
   else if (ctx->max_parts <= 8192) SPIN_SR_LAUNCH(512, 16);   // against 1024 x 8 and 1024 x 16, stages 2+3 of 8 rows: 9.0 / 10.4 / 11.8 us
   else SPIN_SR_LAUNCH(1024, 16);
 #undef SPIN_SR_LAUNCH
+#undef SPIN_SR_LAUNCH1
 #undef SPIN_SR_ARGS
   return spin_launch_status();
 }
