@@ -171,11 +171,6 @@ __device__ inline void spin_buffer_store(__amdgpu_buffer_rsrc_t buf, uint32_t la
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), buf, (int)lane_offset, 0, 0);
 }
 
-typedef __attribute__((ext_vector_type(2))) unsigned int spin_u32x2;
-__device__ inline uint2 spin_nt_load2(const uint2 *p) {
-  return __builtin_bit_cast(uint2, __builtin_nontemporal_load((const spin_u32x2 *)p));
-}
-
 // fp32 -> bf16 bits, round to nearest even
 __device__ inline uint16_t spin_f32_to_bf16(float f) {
   uint32_t u = __float_as_uint(f);
