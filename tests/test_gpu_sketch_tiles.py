@@ -1,6 +1,7 @@
 """Stage 1 of token partitions: tile counts around one round of a workgroup (64 tiles), tiles per workgroup that leave
 half a pair or several rounds, every kind of group.  The scores against sums in 64 bits to the order bound of 16
-products in 32 bits; nothing is stored past a row's last tile.  The tiles' maxima are those of the stored scores."""
+products in 32 bits; nothing is stored past a row's last tile.  Where they are asked for, the tiles' maxima are exactly
+those of the stored scores, and a selection that rules tiles out by them is the right one."""
 import numpy as np
 import pytest
 import torch
@@ -11,15 +12,16 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
+@pytest.mark.parametrize("maxima", [False, True])
 @pytest.mark.parametrize("tiles_per_wg", [0, 5, 36, 128])
 @pytest.mark.parametrize("group", [1, 3, 4, 5, 8, 16])
-def test_scores_and_maxima(group, tiles_per_wg):
+def test_scores_and_maxima(group, tiles_per_wg, maxima):
     from gpu_harness import unpack_summary_rows
     kv, lens = 2, (1, 16 * 63, 16 * 64 + 3, 16 * 193 + 1)
-    maxima = tiles_per_wg == 0                            # (rows long enough for stage 2 to go by them)
+    topk = 20 if tiles_per_wg else 200                    # fewer than the longest rows have tiles, and more
     sp = binding.Spin(max_batch=len(lens), num_q_heads=kv * group, num_kv_heads=kv, partition_tokens=1,
-                      score_kind=synth.SCORE_SKETCH, topk=200, sink_pages=0, recent_pages=0, score_tiles_per_wg=tiles_per_wg,
-                      max_context=16400 if maxima else max(lens))
+                      score_kind=synth.SCORE_SKETCH, topk=topk, sink_pages=0, recent_pages=0, score_tiles_per_wg=tiles_per_wg,
+                      max_context=16400 if maxima else max(lens))   # (long enough for stage 2 to go by them)
     off = tables.part_offsets(lens, 1)
     total = int(off[-1]) * kv
     gen = torch.Generator(device=DEV)
@@ -41,6 +43,8 @@ def test_scores_and_maxima(group, tiles_per_wg):
     assert sp.poll_status(ws) == 0
     rows = unpack_summary_rows(summ.view(torch.uint8), 16, 4).astype(np.uint32) << 16
     rows = rows.view(np.float32).astype(np.float64)       # [tokens][16]
+    words = ws.cpu().numpy()
+    words = words[:words.nbytes // 4 * 4].view(np.float32)
     qf, ch, got = q.double().cpu().numpy(), chan.cpu().numpy(), scores.cpu().numpy()
     for b in range(len(lens)):
         for h in range(kv):
@@ -51,9 +55,11 @@ def test_scores_and_maxima(group, tiles_per_wg):
             bound = 16 * 2.0 ** -24 * (np.abs(rows[base:base + n]) @ np.abs(heads).T).max(axis=1)
             assert (np.abs(got[base:base + n] - terms.max(axis=1)) <= bound).all()
             if maxima:                                    # the selection is the k largest of the scores, ties lowest first
-                want = np.sort(np.lexsort((np.arange(lens[b]), -got[base:base + lens[b]].astype(np.float64)))[:200])
+                want = np.sort(np.lexsort((np.arange(lens[b]), -got[base:base + lens[b]].astype(np.float64)))[:topk])
                 r = b * kv + h
                 assert np.array_equal(sel[r, :int(nsel[r])].cpu().numpy(), want)
+                tops = got[base:base + n].reshape(-1, 16).max(axis=1)      # a row's stand together in the workspace
+                assert any(np.array_equal(words[i:i + len(tops)], tops) for i in np.flatnonzero(words == tops[0]))
     assert (got[total:] == 7.5).all()
 
 
