@@ -280,7 +280,8 @@ int spin_score_impl(spin_ctx *ctx, int32_t batch, const void *q, const void *sum
     // groups of up to four heads: the four-tile kernel, 64 tiles per workgroup, one round (32 / 64 / 128 / 256 / 512:
     // 26.4 / 25.6 / 26.9 / 26.4 / 28.2 us on 64 rows of 65536 tokens)
     const bool four = ctx->group <= 4 && (c.score_tiles_per_wg % 4) == 0;
-    const int tiles_per_wg = c.score_tiles_per_wg ? c.score_tiles_per_wg : 64, max_tiles = max_pp / 16;
+    // (a workgroup addresses its tiles in 32 bits: half a GiB of them at most)
+    const int tiles_per_wg = c.score_tiles_per_wg ? std::min(c.score_tiles_per_wg, 1 << 20) : 64, max_tiles = max_pp / 16;
     // The grid is as long as the context's longest row, so that most workgroups of a context sized for more than is
     // running are empty.  They cost the time to start them, which a grid of three dimensions halves (no divisions), and
     // an odd number of them per row keeps the rows' first workgroups, the only ones with work then, from all going to

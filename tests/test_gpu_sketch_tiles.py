@@ -85,3 +85,25 @@ def test_more_requests_or_heads_than_a_grid_dimension_holds(batch, kv):
         for i in range(4):
             want += taken[:, :, 4 * quad + i, None] * summ[:, :, quad, :, i].float()
     assert torch.equal(scores.view(batch, kv, 16), want)
+
+
+def test_tiles_of_a_workgroup_beyond_4_gib():
+    """One row of 4 GiB and three tiles, all of them asked to be one workgroup's."""
+    tiles = (1 << 23) + 3
+    sp = binding.Spin(max_batch=1, num_q_heads=1, num_kv_heads=1, partition_tokens=1, score_kind=synth.SCORE_SKETCH, topk=4,
+                      sink_pages=0, recent_pages=0, max_context=16 * tiles, score_tiles_per_wg=tiles + 1)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    summ = torch.randint(-8, 9, (tiles, 4, 16, 4), generator=gen, device=DEV, dtype=torch.int8).to(torch.bfloat16)
+    q = torch.randint(-8, 9, (1, 1, 128), generator=gen, device=DEV).to(torch.bfloat16)
+    chan = torch.randperm(128, generator=gen, device=DEV)[:16].to(torch.int32).view(1, 16)
+    off = torch.tensor([0, 16 * tiles], dtype=torch.int32, device=DEV)
+    seq = torch.tensor([16 * tiles], dtype=torch.int32, device=DEV)
+    scores = torch.full((tiles * 16,), 7.5, device=DEV)
+    sp.score_partitions(1, q, summ.view(-1).view(torch.uint8), chan, off, seq, scores, sp.new_workspace(DEV))
+    torch.cuda.synchronize()
+    want = torch.zeros((tiles, 16), device=DEV)
+    for quad in range(4):
+        for i in range(4):
+            want += q[0, 0, chan[0, 4 * quad + i]].float() * summ[:, quad, :, i].float()
+    assert torch.equal(scores.view(tiles, 16), want)
