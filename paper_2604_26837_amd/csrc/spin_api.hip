@@ -84,9 +84,7 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
     return SPIN_ERR_INVALID;
   }
   x->waves = c->decode_waves ? c->decode_waves : 8;
-  // partitions smaller than a page: most pages are fetched in part (a few KiB), so a wavefront
-  // keeps two pages in flight instead of one (measured: 53 -> 42 us on 64 rows x 65536 tokens)
-  x->depth = c->decode_depth ? c->decode_depth : (tp < 16 ? 3 : 2);
+  x->depth = c->decode_depth ? c->decode_depth : 2;   // (partitions smaller than a page: the gathered tiles have two of their own)
   int32_t splits = c->decode_splits;
   if (splits == 0) {
     // about one 8-wave workgroup on each of the 256 compute units, all resident
