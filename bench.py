@@ -3,7 +3,7 @@
 
 One "step" = one pass of the whole path (score -> select -> resolve -> attend)
 for one layer over one batch of synthetic input, resident in HBM.  Prints ONE
-JSON line.  `roofline` is about the attention kernel: the bytes its launch moves (512 B per token it
+JSON line.  `roofline` is about the launch that attends: the bytes of K and V it moves (512 B per token it
 attends) over its mean duration, taken from HIP events on the launch stream, against 8 TB/s.
 """
 from __future__ import annotations
@@ -607,8 +607,8 @@ def main():
     def run_four(i):
         layer.step(qsets[i % len(qsets)], summ_copies[i % len(summ_copies)])
 
-    # the step as timed: three launches whatever the row length (score, select+resolve, attention; for long
-    # rows stages 1-3 are one call), same results bit for bit; the four separate calls are timed beside it
+    # the step as timed: two launches (score; select+resolve+attention) or three (score, select+resolve, attention; for
+    # long rows stages 1-3 are one call); the four separate calls are timed beside it
     def run_fused(i):
         layer.step_fused(qsets[i % len(qsets)], summ_copies[i % len(summ_copies)])
 
@@ -620,8 +620,8 @@ def main():
     torch.cuda.synchronize()
     assert layer.status() == 0, "device fault during warm-up"
 
-    # --- timed region: exactly K steps of the decode step as `run` issues it (by default the three-launch form:
-    # score, select+resolve in one launch, attention; --four-calls times the four separate stage calls instead;
+    # --- timed region: exactly K steps of the decode step as `run` issues it (by default
+    # in two or three launches; --four-calls times the four separate stage calls instead;
     # `step_launches` in the output says which, and the other form is timed right after for reference)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -734,20 +734,21 @@ def main():
             run(i)
         torch.cuda.synchronize()
         us_per_step_events = (time.perf_counter() - t0) * 1e6 / args.steps
-        for name in ("score", "select_hist", "select", "resolve", "decode"):
+        for name in ("score", "select_hist", "select", "resolve", "decode", "select_decode"):
             n, mean, mn = sp.profile_read(name)
             if n:
-                label = "select+resolve" if (name == "select" and not args.four_calls) else name
+                label = "select+resolve+decode" if name == "select_decode" else "select+resolve" if (name == "select" and not args.four_calls) else name
                 kernels[label] = dict(launches=n, mean_us=round(mean, 3), min_us=round(mn, 3))
         sp.profile_enable(0)
         assert layer.status() == 0, "device fault during the event-bracketed pass"
 
-    # --- when the timed step attends the sink / recent pages beside stages 2+3: the plain three-launch step with
-    # the same event bracketing, to say what that side work costs the launch of stages 2+3 and what stage 4 takes
-    # over all pages
-    forced_split = (not args.four_calls) and sp.forced_split_supported
+    # --- when the timed step runs stages 2-4 in one launch, or attends the sink / recent pages beside stages 2+3: the
+    # plain three-launch step with the same event bracketing, to say what stages 2+3 take without the attention and
+    # what stage 4 takes over all pages
+    fused_24 = (not args.four_calls) and sp.fused_splits > 0
+    forced_split = (not args.four_calls) and not fused_24 and sp.forced_split_supported
     plain_kernels = {}
-    if forced_split and not args.no_kernel_events:
+    if (fused_24 or forced_split) and not args.no_kernel_events:
         sp.profile_enable(args.steps)
         for i in range(args.steps):
             layer.step3(qsets[i % len(qsets)], summ_copies[i % len(summ_copies)])
@@ -785,7 +786,7 @@ def main():
     kv_bytes = attended_tokens * 2 * w.head_dim * 2                    # 512 B per attended token
     page_bytes = int(layer.npages.sum().item()) * 8192                 # what page-granular gathering reads
     score_bytes = int(layer.summaries.numel())                         # summary bytes of the (padded) rows
-    dec_us = kernels.get("decode", {}).get("mean_us") or None
+    dec_us = kernels.get("select+resolve+decode" if fused_24 else "decode", {}).get("mean_us") or None
     sc_us = kernels.get("score", {}).get("mean_us") or None
     # bytes stage 4's launch itself moves: with the forced split, the sink / recent pages (whole pages: one-page
     # partitions) were attended by the launch of stages 2+3
@@ -803,12 +804,16 @@ def main():
     attended = None
     if dec_us:
         # the metric's figure: all attended K/V bytes of the step over the time spent attending them (stage 4's
-        # launch plus what the side work adds to the launch of stages 2+3)
+        # launch plus what the side work adds to the launch of stages 2+3; where stages 2-4 are one launch, what that
+        # takes beyond the launch of stages 2+3 alone: `roofline` counts the whole of it)
+        if fused_24 and plain_kernels.get("select+resolve"):
+            side_us = -plain_kernels["select+resolve"]["mean_us"]
         attended = dict(bytes=kv_bytes, us=round(dec_us + side_us, 3), gbps=round(kv_bytes / (dec_us + side_us) / 1e3, 1),
                         pct_peak=round(100 * kv_bytes / (dec_us + side_us) / 1e3 / PEAK_HBM_GBPS, 2),
                         side_bytes=side_bytes, side_us=round(side_us, 3))
         ach = dec_bytes / dec_us / 1e3                                 # GB/s
-        kernel = "spin_decode_tokens_kernel<8>" if w.partition_tokens < 16 else \
+        kpt = next(k for k in (4, 8, 16, 32) if max(w.partitions(b) for b in range(w.batch)) <= 512 * k) if fused_24 else 0
+        kernel = f"spin_select_decode_kernel<{kpt}>" if fused_24 else "spin_decode_tokens_kernel<8>" if w.partition_tokens < 16 else \
             f"spin_decode_kernel<{args.decode_waves or 8}, {args.decode_depth or 2}>"
         traffic, traffic_note = read_traffic(os.path.join(ROOT, "profiles", f"{args.workload}_stage_kernels_pmc.txt"),
                                              kernel)
@@ -866,13 +871,14 @@ def main():
         "config": {"workload": w.name, "batch": w.batch, "context": w.seq_lens[0], "q_heads": w.num_q_heads,
                    "kv_heads": w.num_kv_heads, "head_dim": w.head_dim, "page_tokens": w.page_tokens,
                    "partition_tokens": w.partition_tokens, "score": ["minmax", "sketch", "repmax"][w.score_kind],
-                   "topk_partitions": w.topk, "decode_splits": sp.decode_splits, "decode_waves": args.decode_waves or 8, "query_sets": len(qsets),
+                   "topk_partitions": w.topk, "decode_splits": sp.fused_splits if fused_24 else sp.decode_splits, "decode_waves": args.decode_waves or 8, "query_sets": len(qsets),
                    "summary_copies": len(summ_copies)},
         "attended_kv_gbps": attended["gbps"] if attended else None,
         "attended_kv_pct_peak": attended["pct_peak"] if attended else None,
         "attended_kv": attended,
         "step_launches": "four stage calls" if args.four_calls else (
             "stages 1-3 in one call (stage 1 stores its tiles' maxima for stage 2, stage 2's launch resolves), attention (3 launches)" if fused_12
+            else "score, then select+resolve+attention in one launch (2 launches)" if fused_24
             else ("score, select+resolve with the sink / recent pages attended on the side, attention over the "
                   "other pages (3 launches)" if forced_split else "score, select+resolve, attention (3 launches)")),
         "kernels_plain_three_launch_step": plain_kernels or None,

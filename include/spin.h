@@ -15,6 +15,7 @@
  *   spin_offload_pages                                         Offload's copy, slot -> host page (Table 1)
  *   spin_select_resolve                                        stages 2+3 in one launch, same results
  *   spin_select_resolve_forced, spin_sparse_decode_rest        the same, the sink / recent pages attended beside 2+3
+ *   spin_select_resolve_decode                                 stages 2-4 in one launch
  *   spin_score_select_topk                                     stages 1+2 in one call, same results
  *   spin_score_select_resolve                                  stages 1-3 in one call, same results
  *   spin_pin_partitions                                        always-attended outlier partitions (Section 4.2)
@@ -358,6 +359,19 @@ int spin_select_resolve_forced(spin_ctx *ctx, int32_t batch, const float *scores
 int spin_sparse_decode_rest(spin_ctx *ctx, int32_t batch, const void *q, const void *kv_pool,
                             int64_t pool_slots, const int32_t *slots, const uint16_t *valid_mask,
                             const int32_t *npages, void *out, float *lse, void *workspace, void *stream);
+
+/* Stages 2, 3 and 4 in one launch: every workgroup that attends a part of a row's pages selects and
+ * resolves the row for itself.  Arguments as in the stage calls; sel, nsel, slots, page_ids, valid_mask and
+ * npages are exactly theirs, out and lse are stage 4's results to its tolerance (the pages are summed in another
+ * order), identical from run to run and whatever else is in the call.  spin_fused_splits says whether a context
+ * supports it: the number of those workgroups per row, or 0, and then the call is SPIN_ERR_UNSUPPORTED before
+ * anything is launched. */
+int spin_select_resolve_decode(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
+                               const int32_t *seq_lens, int32_t *sel, int32_t *nsel, const int32_t *dir,
+                               const int32_t *leaf_pool, int64_t leaf_chunks, int32_t *slots, int32_t *page_ids,
+                               uint16_t *valid_mask, int32_t *npages, const void *q, const void *kv_pool,
+                               int64_t pool_slots, void *out, float *lse, void *workspace, void *stream);
+int32_t spin_fused_splits(const spin_ctx *ctx);
 
 /* Buffer elasticity, mechanism only (Section 5.3: buffer pages are reclaimed from
  * the tail of a request's GPU page table).  Sets the slot count of every row to

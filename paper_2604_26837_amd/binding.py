@@ -30,7 +30,7 @@ EXPORTS = [
     "spin_set_partition_tables", "spin_probe_stream_read", "spin_offload_pages", "spin_score_select_topk", "spin_score_select_resolve", "spin_pin_partitions",
     "spin_set_host_page_table", "spin_set_step", "spin_advance_step", "spin_sparse_decode_static",
     "spin_select_resolve_forced", "spin_sparse_decode_rest", "spin_split_hits_misses", "spin_sparse_decode_begin",
-    "spin_sparse_decode_finish",
+    "spin_sparse_decode_finish", "spin_select_resolve_decode", "spin_fused_splits",
 ]
 
 
@@ -68,7 +68,7 @@ def load_library() -> C.CDLL:
     lib.spin_status_string.restype = C.c_char_p
     lib.spin_workspace_bytes.argtypes = [vp]
     lib.spin_workspace_bytes.restype = C.c_size_t
-    for n in ("spin_sel_stride", "spin_page_stride", "spin_dir_stride", "spin_decode_splits"):
+    for n in ("spin_sel_stride", "spin_page_stride", "spin_dir_stride", "spin_decode_splits", "spin_fused_splits"):
         getattr(lib, n).argtypes = [vp]
         getattr(lib, n).restype = i32
     lib.spin_summary_bytes.argtypes = [vp, i64]
@@ -91,6 +91,7 @@ def load_library() -> C.CDLL:
     lib.spin_sparse_decode.argtypes = [vp, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     lib.spin_sparse_decode_static.argtypes = [vp, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     lib.spin_select_resolve_forced.argtypes = [vp, i32] + [vp] * 7 + [i64] + [vp] * 6 + [i64, vp, vp]
+    lib.spin_select_resolve_decode.argtypes = [vp, i32] + [vp] * 7 + [i64] + [vp] * 6 + [i64] + [vp] * 4
     lib.spin_split_hits_misses.argtypes = [vp, i32] + [vp] * 8
     lib.spin_sparse_decode_begin.argtypes = [vp, i32, vp, vp, i64, vp, vp, vp, vp, vp]
     lib.spin_sparse_decode_finish.argtypes = [vp, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
@@ -157,6 +158,7 @@ class Spin:
         self.page_stride = self.lib.spin_page_stride(h)
         self.dir_stride = self.lib.spin_dir_stride(h)
         self.decode_splits = self.lib.spin_decode_splits(h)
+        self.fused_splits = self.lib.spin_fused_splits(h)     # 0: select_resolve_decode does not apply
         self.workspace_bytes = self.lib.spin_workspace_bytes(h)
 
     @classmethod
@@ -200,7 +202,7 @@ class Spin:
         return self.lib.spin_summary_bytes(self.h, padded_partitions)
 
     KERNEL_IDS = dict(score=0, select=1, resolve=2, decode=3, merge=4, index=5, pack=6, gather=7, probe=8, select_hist=9, offload=10, append=11,
-                      meta=12)
+                      meta=12, select_decode=13)
 
     def profile_enable(self, capacity: int):
         self._check(self.lib.spin_profile_enable(self.h, capacity), "spin_profile_enable")
@@ -364,6 +366,12 @@ class Spin:
     def sparse_decode_rest(self, batch, q, kv_pool, slots, valid_mask, npages, out, lse, ws):
         self._check(_call.spin_sparse_decode_rest(
             self._ctx, batch, q, kv_pool, slots, valid_mask, npages, out, lse, ws), "spin_sparse_decode_rest")
+
+    def select_resolve_decode(self, batch, scores, part_offsets, seq_lens, sel, nsel, dir_, leaf_pool, slots, page_ids,
+                              valid_mask, npages, q, kv_pool, out, lse, ws):
+        self._check(_call.spin_select_resolve_decode(
+            self._ctx, batch, scores, part_offsets, seq_lens, sel, nsel, dir_, leaf_pool, slots, page_ids,
+            valid_mask, npages, q, kv_pool, out, lse, ws), "spin_select_resolve_decode")
 
     def split_hits_misses(self, batch, page_ids, valid_mask, npages, miss_pages, nmiss, mask_hits, mask_misses):
         self._check(_call.spin_split_hits_misses(

@@ -108,6 +108,24 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   }
   x->pstride = splits + (x->side_wgs > 1 ? x->side_wgs : 1);
 
+  // stages 2 to 4 in one launch, where the shape of stage 4's launch is left to the library
+  x->fused_splits = 0;
+  if (c->lru_timestamps == 0 && tp >= SPIN_PAGE_TOKENS && !c->variable_partitions && x->max_parts <= 16384 &&
+      x->sel_stride <= SPIN_SEL_HELD && !c->decode_waves && !c->decode_depth && x->max_rows <= 65535 &&
+      spin_fused_lds(x) <= SPIN_FUSED_LDS) {
+    int32_t s = c->decode_splits;
+    if (s == 0) {
+      s = 256 / x->max_rows;
+      // two pages per wavefront (1 / 2 / 4 of them, steps of 8 rows of 8192 pages, 128 attended: 24.3 / 24.3 / 25.7 us),
+      // or four where that leaves one workgroup, which has nothing to merge (2 rows of 256, 32 attended: 12.3 us; with
+      // two or four workgroups 13.2 / 12.8)
+      const int32_t two = x->page_stride / 16, cap = two <= 2 ? 1 : two;
+      if (s > cap) s = cap;
+      if (s < 1) s = 1;
+    }
+    x->fused_splits = s > 64 ? 64 : s;
+  }
+
   size_t off = SPIN_WS_HEADER;
   x->ws_ticket_off = off;                       // one arrival counter per row, zero between launches
   off += (size_t)x->max_rows * sizeof(int32_t);
@@ -126,11 +144,12 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   off = (off + 255) & ~(size_t)255;
   // workgroup partials of stage 4: one per split, plus those of the always-attended pages when the launch of
   // stages 2+3 attends them (at least one: the first of two passes over a page list leaves its result there)
+  const size_t partials = (size_t)x->max_rows * (x->pstride > x->fused_splits ? x->pstride : x->fused_splits) * group;
   x->ws_ml_off = off;
-  off += (size_t)x->max_rows * x->pstride * group * 2 * sizeof(float);
+  off += partials * 2 * sizeof(float);
   off = (off + 255) & ~(size_t)255;
   x->ws_acc_off = off;
-  off += (size_t)x->max_rows * x->pstride * group * SPIN_HEAD_DIM * sizeof(float);
+  off += partials * SPIN_HEAD_DIM * sizeof(float);
   x->ws_bytes = (off + 255) & ~(size_t)255;
   // set-up for spin_sparse_decode_static on the device that is current now: its first call then asks the
   // runtime for nothing (a caller may be capturing by then).  Best effort: a context may be created with no

@@ -14,7 +14,11 @@
 #define SPIN_KTILE_U4 256     // 4096-byte K tile in 16-byte units
 #define SPIN_WS_HEADER 256    // bytes reserved in front of the workspace (status word)
 
-#define SPIN_KERNEL_IDS 13
+#define SPIN_SEL_HELD 2304    // longest selection handed over in LDS: a top 2048 with 256 forced ones; with these the launch by
+                              // tile maxima stays under 64 KiB
+#define SPIN_FUSED_LDS (96 * 1024)   // dynamic LDS the launch that runs stages 2 to 4 may use beside some 25 KiB of its own
+
+#define SPIN_KERNEL_IDS 14
 
 // Variable-length partitions (Section 5.2: the Meta-partition table holds each
 // partition's token count, the Partition Offset table where its page list
@@ -41,6 +45,7 @@ struct spin_ctx {
   int32_t splits;
   int32_t side_wgs;       // workgroups per row that attend the always-attended pages beside stages 2+3 (0: not supported)
   int32_t pstride;        // stage 4's partials per row in the workspace: one per split, then one per such workgroup
+  int32_t fused_splits;   // workgroups per row of the launch that runs stages 2 to 4 (0: not supported)
   int32_t waves;          // wavefronts per decode workgroup
   int32_t depth;          // page buffers per decode wavefront
   int32_t kd;             // contraction length of one summary row
@@ -79,6 +84,11 @@ typedef __attribute__((ext_vector_type(4))) short spin_s16x4;
 // attention over a row's always-attended pages beside stages 2+3, the rest in stage 4: all-resident mode,
 // uniform partitions of whole pages, rows short enough for the 512-thread selection
 static inline bool spin_forced_split_supported(const spin_ctx *ctx) { return ctx->side_wgs > 0; }
+
+// dynamic LDS of the launch that runs stages 2 to 4: stage 4's merge buffers (8 wavefronts) and the row's page list
+static inline size_t spin_fused_lds(const spin_ctx *ctx) {
+  return (size_t)8 * ctx->group * (SPIN_HEAD_DIM + 2) * sizeof(float) + (size_t)ctx->page_stride * 6;
+}
 
 static inline int spin_launch_status() {
   return hipGetLastError() == hipSuccess ? SPIN_OK : SPIN_ERR_HIP;
@@ -124,6 +134,7 @@ static inline void spin_launch(spin_ctx *ctx, int kid, K kernel, dim3 grid, dim3
 
 // words known to lie in LDS, which a pointer to ordinary memory does not say of itself
 typedef __attribute__((address_space(3))) int32_t spin_lds_i32;
+typedef __attribute__((address_space(3))) uint16_t spin_lds_u16;
 
 // first device-detected fault wins; later ones are dropped
 __device__ inline void spin_raise(int32_t *status, int32_t err) { atomicCAS(status, 0, err); }

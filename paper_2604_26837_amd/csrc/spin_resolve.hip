@@ -18,8 +18,8 @@ __global__ __launch_bounds__(RES_BLOCK) void spin_resolve_kernel(
     int32_t *__restrict__ npages, int32_t *status, spin_var var) {
   const int row = blockIdx.x;
   resolve_row<RES_BLOCK>(row, nsel[row], sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages, recent_pages,
-                         sel_stride, page_stride, dir_stride, leaf_entries, slots, page_ids, valid_mask, npages, status,
-                         var);
+                         sel_stride, page_stride, dir_stride, leaf_entries,
+                         res_row_out(slots, page_ids, valid_mask, npages, row, page_stride), status, var);
 }
 
 // ---------------------------------------------------------------------------
@@ -78,8 +78,8 @@ __device__ inline int lru_input(int row, const int32_t *__restrict__ sel, const 
     return nsel[row];
   }
   resolve_row<LRU_BLOCK, false>(row, nsel[row], sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, ex.tp, ex.sink_pages,
-                                ex.recent_pages, sel_stride, page_stride, dir_stride, leaf_entries, slots, page_ids,
-                                valid_mask, npages, status, ex.var);
+                                ex.recent_pages, sel_stride, page_stride, dir_stride, leaf_entries,
+                                res_row_out(slots, page_ids, valid_mask, npages, row, page_stride), status, ex.var);
   __syncthreads();   // the list was written by this workgroup: visible to all its threads from here
   list = page_ids + (size_t)row * page_stride;
   return npages[row];

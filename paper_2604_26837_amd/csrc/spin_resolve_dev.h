@@ -19,19 +19,27 @@ __device__ inline uint32_t page_mask(int page, int N) {
   return (1u << n) - 1u;
 }
 
+// where a row's page list goes
 struct res_out {
   int32_t *slots, *page_ids;
   uint16_t *mask;
+  int32_t *npages;
+  __device__ __forceinline__ void put(int pos, int32_t slot, int32_t page, uint32_t m) const {
+    slots[pos] = slot;
+    page_ids[pos] = page;
+    mask[pos] = (uint16_t)m;
+  }
+  __device__ __forceinline__ void count(int total) const { *npages = total; }
 };
-
-__device__ inline void res_put(const res_out &o, int pos, int32_t slot, int32_t page, uint32_t mask) {
-  o.slots[pos] = slot;
-  o.page_ids[pos] = page;
-  o.mask[pos] = (uint16_t)mask;
+__device__ __forceinline__ res_out res_row_out(int32_t *__restrict__ slots, int32_t *__restrict__ page_ids,
+                                               uint16_t *__restrict__ valid_mask, int32_t *__restrict__ npages, int row,
+                                               int page_stride) {
+  const size_t at = (size_t)row * page_stride;
+  return res_out{slots + at, page_ids + at, valid_mask + at, npages + row};
 }
 
 #define RES_DIR_LDS 256
-#define SEL_HELD 2304          // a top 2048 with 256 forced ones; with these the launch by tile maxima stays under 64 KiB
+#define SEL_HELD SPIN_SEL_HELD
 
 // What the launch that selects a row has of it in LDS when it goes on to stage 3: the selection (HELD: no longer than
 // SEL_HELD) and the directory entries (where at most RES_DIR_LDS).
@@ -54,8 +62,8 @@ struct row_dir {
 };
 
 // LOOKUP = false: only the page list and the masks are wanted (budget mode decides the slots)
-template <bool LOOKUP>
-__device__ __forceinline__ void emit_page(const res_out &o, int pos, int page_stride, int page, uint32_t mask,
+template <bool LOOKUP, typename OUT>
+__device__ __forceinline__ void emit_page(const OUT &o, int pos, int page_stride, int page, uint32_t mask,
                                           const row_dir &dir, const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks,
                                           int dir_stride, int leaf_entries, int32_t *status) {
   if (pos < 0 || pos >= page_stride) return;
@@ -73,28 +81,28 @@ __device__ __forceinline__ void emit_page(const res_out &o, int pos, int page_st
       mask = 0;
     }
   }
-  res_put(o, pos, slot, page, mask);
+  o.put(pos, slot, page, mask);
 }
 
 // A selection entry outside the row: its output position holds no page (nothing of a previous
 // step stays there for stage 4 to attend) and the fault is reported.
-__device__ inline void emit_invalid(const res_out &o, int pos, int page_stride, int32_t *status) {
+template <typename OUT>
+__device__ inline void emit_invalid(const OUT &o, int pos, int page_stride, int32_t *status) {
   spin_raise(status, SPIN_ERR_INVALID);
   if (pos < 0 || pos >= page_stride) return;
-  res_put(o, pos, -1, -1, 0);
+  o.put(pos, -1, -1, 0);
 }
 
 // Resolves one row with the calling workgroup of RES_BLOCK threads; `ns` = the
 // row's selection count.  `known`: the row's windows, where the caller has them
 // (variable-length partitions).  HELD_DIR, HELD_SEL: the calling launch has staged the row's directory, or its selection,
-// in `held`.
-template <int RES_BLOCK, bool LOOKUP = true, bool HELD_DIR = false, bool HELD_SEL = false>
-__device__ __forceinline__ void resolve_row(
+// in `held`.  Returns the length of the page list.
+template <int RES_BLOCK, bool LOOKUP = true, bool HELD_DIR = false, bool HELD_SEL = false, typename OUT>
+__device__ __forceinline__ int resolve_row(
     int row, int ns, const int32_t *__restrict__ sel, const int32_t *__restrict__ seq_lens,
     const int32_t *dir, const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks, int Hkv, int tp,
-    int sink_pages, int recent_pages, int sel_stride, int page_stride, int dir_stride, int leaf_entries,
-    int32_t *__restrict__ slots, int32_t *__restrict__ page_ids, uint16_t *__restrict__ valid_mask,
-    int32_t *__restrict__ npages, int32_t *status, spin_var var, const spin_var_span *known = nullptr,
+    int sink_pages, int recent_pages, int sel_stride, int page_stride, int dir_stride, int leaf_entries, const OUT &o,
+    int32_t *status, spin_var var, const spin_var_span *known = nullptr,
     held_row<HELD_SEL> *held = nullptr) {
   constexpr int RES_WAVES = RES_BLOCK / 64;
   __shared__ int s_wave[RES_WAVES];
@@ -118,9 +126,6 @@ __device__ __forceinline__ void resolve_row(
     if (HELD_SEL) return lsel[i];
     return rsel[i];
   };
-  res_out o = {slots + (size_t)row * page_stride, page_ids + (size_t)row * page_stride,
-               valid_mask + (size_t)row * page_stride};
-
   if (!HELD_DIR && dir_in_lds) __syncthreads();
 
   if (var.count) {
@@ -206,8 +211,9 @@ __device__ __forceinline__ void resolve_row(
     for (int k = tid; k < extraB; k += RES_BLOCK)
       put(s_sumB + ((A >= 0 && A <= B) ? extraA : 0) + k, pb, w.recent_begin - pb.first + k);
     const int total = min(carry + extraA + extraB, page_stride);
-    for (int i = total + tid; i < page_stride; i += RES_BLOCK) res_put(o, i, -1, -1, 0);
-    if (tid == 0) npages[row] = total;
+    for (int i = total + tid; i < page_stride; i += RES_BLOCK) o.put(i, -1, -1, 0);
+    if (tid == 0) o.count(total);
+    return total;
   } else if (tp == 16) {
     // partition == page: the selection is the page list.  The entry is loaded
     // before the row's counts are known (the buffer is sel_stride wide), so the
@@ -225,8 +231,9 @@ __device__ __forceinline__ void resolve_row(
       if (i0 + RES_BLOCK >= ns) break;
     }
     const int total = min(ns, page_stride);
-    for (int i = total + tid; i < page_stride; i += RES_BLOCK) res_put(o, i, -1, -1, 0);
-    if (tid == 0) npages[row] = total;
+    for (int i = total + tid; i < page_stride; i += RES_BLOCK) o.put(i, -1, -1, 0);
+    if (tid == 0) o.count(total);
+    return total;
   } else if (tp > 16) {
     const int m = tp >> 4;
     int sink_end = min(sink_pages, pages);
@@ -286,8 +293,9 @@ __device__ __forceinline__ void resolve_row(
       total -= max((last + 1) * m - pages, 0);
     }
     total = min(total, page_stride);
-    for (int i = total + tid; i < page_stride; i += RES_BLOCK) res_put(o, i, -1, -1, 0);
-    if (tid == 0) npages[row] = total;
+    for (int i = total + tid; i < page_stride; i += RES_BLOCK) o.put(i, -1, -1, 0);
+    if (tid == 0) o.count(total);
+    return total;
   } else {
     const int ppp = 16 / tp;   // partitions per page: a power of two
     const int ppp_log = 31 - __clz(ppp);
@@ -317,8 +325,9 @@ __device__ __forceinline__ void resolve_row(
       carry += tot;
     }
     const int total = min(carry, page_stride);
-    for (int i = total + tid; i < page_stride; i += RES_BLOCK) res_put(o, i, -1, -1, 0);
-    if (tid == 0) npages[row] = total;
+    for (int i = total + tid; i < page_stride; i += RES_BLOCK) o.put(i, -1, -1, 0);
+    if (tid == 0) o.count(total);
+    return total;
   }
 }
 

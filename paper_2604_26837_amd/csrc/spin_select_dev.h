@@ -52,6 +52,8 @@ struct sel_row {
       else out[pos] = id;
     }
   }
+  __device__ __forceinline__ void pad(int pos) const { out[pos] = -1; }
+  __device__ __forceinline__ void count(int32_t *__restrict__ nsel, int row, int take) const { nsel[row] = take; }
 };
 
 // ---------------------------------------------------------------------------
@@ -156,7 +158,7 @@ __device__ __forceinline__ void block_kth(const uint32_t (&key)[KPT], typename k
         const uint32_t o = top - ((key[j] >> lo) & dmask);
         if (((valid >> j) & 1u) && o < 8u) acc += 1ull << (8u * o);
       }
-      // 16 bits each, of which a wavefront's sum needs 11
+      // 16 bits each, of which a wavefront's sum needs 12
       static_assert(!MANY || KPT <= 255, "a thread's count fits a byte, a wavefront's 16 bits");
       uint32_t part[4] = {(uint32_t)acc & 0x00ff00ffu, (uint32_t)(acc >> 8) & 0x00ff00ffu,
                           (uint32_t)(acc >> 32) & 0x00ff00ffu, (uint32_t)(acc >> 40) & 0x00ff00ffu};
@@ -361,7 +363,7 @@ __device__ __forceinline__ void select_elements(const float (&f)[KPT], typename 
   uint32_t key[KPT];
 #pragma unroll
   for (int k = 0; k < KPT; ++k) key[k] = score_key(f[k]);
-  block_kth<BLOCK, KPT, KPT == 16>(key, valid, kprime, 0, s.kth, T, need_eq, total >= 4096);
+  block_kth<BLOCK, KPT, KPT == 16 || KPT == 32>(key, valid, kprime, 0, s.kth, T, need_eq, total >= 4096);
   M gt = 0, eq = 0;
 #pragma unroll
   for (int k = 0; k < KPT; ++k) {
@@ -386,8 +388,8 @@ __device__ __forceinline__ void emit_forced(const sel_plan &pl, const ROW &rsel,
   for (int i = tid; i < min(pl.nf_lo, rsel.stride); i += BLOCK) rsel.put(i, i);
   const int at = pl.nf_lo + pl.kprime;
   for (int i = tid; i < pl.P - pl.first_hi && at + i < rsel.stride; i += BLOCK) rsel.put(at + i, pl.first_hi + i);
-  for (int i = pl.take + tid; i < rsel.stride; i += BLOCK) rsel.out[i] = -1;
-  if (tid == 0) nsel[row] = pl.take;
+  for (int i = pl.take + tid; i < rsel.stride; i += BLOCK) rsel.pad(i);
+  if (tid == 0) rsel.count(nsel, row, pl.take);
 }
 
 // The windows of a row of at most BLOCK * KPT variable-length partitions, and its forced prefix and suffix

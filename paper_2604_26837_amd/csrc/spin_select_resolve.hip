@@ -69,18 +69,6 @@ __device__ inline void forced_lookup(bool active, int j, int nlo, int recent_beg
   }
 }
 
-struct forced_span {
-  int nlo, nhi, recent_begin;
-};
-// the same rule as stages 2 and 3: a context no longer than the two windows is attended whole
-__device__ inline forced_span forced_pages_of(int N, int sink_pages, int recent_pages) {
-  const int pages = (N + 15) >> 4;
-  int sink_end = min(sink_pages, pages);
-  int recent_begin = max(pages - recent_pages, 0);
-  if (sink_end >= recent_begin) { sink_end = pages; recent_begin = pages; }
-  return forced_span{sink_end, pages - recent_begin, recent_begin};
-}
-
 template <int WAVES>
 __device__ __forceinline__ void attend_forced_row(
     int row, int side, int nside, const uint16_t *__restrict__ q, const uint4 *__restrict__ pool, int64_t pool_slots,

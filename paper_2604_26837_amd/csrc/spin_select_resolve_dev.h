@@ -3,6 +3,19 @@
 #include "spin_resolve_dev.h"
 #include "spin_select_dev.h"
 
+// A row's always-attended pages: its first nlo, and nhi from recent_begin on.
+struct forced_span {
+  int nlo, nhi, recent_begin;
+};
+// the same rule as stages 2 and 3: a context no longer than the two windows is attended whole
+__device__ inline forced_span forced_pages_of(int N, int sink_pages, int recent_pages) {
+  const int pages = (N + 15) >> 4;
+  int sink_end = min(sink_pages, pages);
+  int recent_begin = max(pages - recent_pages, 0);
+  if (sink_end >= recent_begin) { sink_end = pages; recent_begin = pages; }
+  return forced_span{sink_end, pages - recent_begin, recent_begin};
+}
+
 // The calling thread's entry of the row's directory, asked for before stage 2, whose chain hides it.  Without a
 // branch, so that nothing else waits for it.
 __device__ __forceinline__ int32_t row_dir_entry(const int32_t *__restrict__ dir, int dir_stride, int row) {
@@ -29,6 +42,7 @@ __device__ __forceinline__ void resolve_selected(
   if (HELD)
     for (int i = tid; i < take; i += BLOCK) rsel.out[i] = rsel.lds[i];
   resolve_row<BLOCK, true, true, HELD>(row, take, sel, seq_lens, dir, leaf_pool, leaf_chunks, Hkv, tp, sink_pages,
-                                       recent_pages, rsel.stride, page_stride, dir_stride, leaf_entries, slots, page_ids,
-                                       valid_mask, npages, status, var, known, &held);
+                                       recent_pages, rsel.stride, page_stride, dir_stride, leaf_entries,
+                                       res_row_out(slots, page_ids, valid_mask, npages, row, page_stride), status, var, known,
+                                       &held);
 }

@@ -143,10 +143,23 @@ class LayerState:
         sp.sparse_decode_rest(w.batch, q, self.kv_pool, self.slots, self.valid_mask, self.npages, self.out, self.lse,
                               self.ws)
 
+    def step2(self, q: torch.Tensor, summaries: Optional[torch.Tensor] = None):
+        """The step in two launches: stage 1, then stages 2-4, the sink / recent pages asked for ahead of the
+        selection."""
+        sp, w = self.spin, self.w
+        summ = self.summaries if summaries is None else summaries
+        sp.score_partitions(w.batch, q, summ, self.chan, self.part_offsets, self.seq_lens, self.scores, self.ws)
+        sp.select_resolve_decode(w.batch, self.scores, self.part_offsets, self.seq_lens, self.sel, self.nsel, self.dir,
+                                 self.leaf_pool, self.slots, self.page_ids, self.valid_mask, self.npages, q,
+                                 self.kv_pool, self.out, self.lse, self.ws)
+
     def step_fused(self, q: torch.Tensor, summaries: Optional[torch.Tensor] = None):
-        """The step in three launches (what ``bench.py`` times): stages 1-3 in two, with the sink / recent pages
-        attended beside stages 2+3 where that applies, then attention."""
-        if self.spin.forced_split_supported and self.layouts_none:
+        """The step in as few launches as the context allows (what ``bench.py`` times): stage 1, then stages 2-4 in
+        one; or stages 1-3 in two, with the sink / recent pages attended beside stages 2+3 where that applies, then
+        attention."""
+        if self.spin.fused_splits and self.layouts_none:
+            self.step2(q, summaries)
+        elif self.spin.forced_split_supported and self.layouts_none:
             self.step3f(q, summaries)
         else:
             self.step123(q, summaries)

@@ -1,0 +1,144 @@
+"""Stages 2 to 4 in one launch: the page lists have the bits of the separate stage calls, the attention is theirs to the
+tolerance of a bf16 output of two summation orders, whatever the number of workgroups per row."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_26837_amd import binding, runner, synth
+
+LISTS = ("sel", "nsel", "slots", "page_ids", "valid_mask", "npages")
+
+
+def _workload(lens, part=16, topk=40, incl=True, sink=2, recent=5, heads=8, kv=2, leaf=512, score=synth.SCORE_MINMAX):
+    return synth.Workload(name="fused", seq_lens=lens, num_q_heads=heads, num_kv_heads=kv, partition_tokens=part,
+                          score_kind=score, reps_per_partition=1, topk=topk, topk_includes_forced=incl, sink_pages=sink,
+                          recent_pages=recent, planted_frac=0.0, leaf_entries=leaf, seed=part * 1009 + topk)
+
+
+def _same_as_stage_calls(layer, q):
+    def run(step):
+        for n in LISTS:
+            getattr(layer, n).fill_(77)
+        layer.out.fill_(3.0)
+        layer.lse.fill_(3.0)
+        step(q)
+        torch.cuda.synchronize()
+        assert layer.status() == 0
+        return {n: getattr(layer, n).clone() for n in LISTS + ("out", "lse")}
+
+    want, got, again = run(layer.step), run(layer.step2), run(layer.step2)
+    for n in LISTS:
+        assert torch.equal(want[n], got[n]), n
+    for n in LISTS + ("out", "lse"):                                  # (the second: the row tickets are left cleared)
+        assert torch.equal(got[n].view(torch.uint8), again[n].view(torch.uint8)), n
+    # probabilities are rounded to bf16 (2^-9) before they meet the values, the output once more; lse sums them
+    # unrounded: a few hundred roundings of 2^-24, exp2's last bit
+    assert (got["out"].float() - want["out"].float()).abs().max() <= 2 ** -6 * want["out"].float().abs().max()
+    assert torch.nan_to_num(got["lse"] - want["lse"], nan=0.0).abs().max() <= 4e-5
+    assert torch.equal(got["lse"].isinf(), want["lse"].isinf())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
+    dict(lens=(1, 16, 17, 100, 112, 113, 4096)),                      # rows as short as the windows, and shorter
+    dict(lens=(32768, 32753, 20001), topk=33),                        # 2048 partitions: 4 per thread
+    dict(lens=(32769, 65536), topk=128, sink=4, recent=8),            # 8
+    dict(lens=(65537, 131072, 3000), topk=128, sink=0, recent=1),     # 16
+    dict(lens=(131073, 262144, 50000), topk=200, sink=0, recent=0),   # 32
+    dict(lens=(6001, 9000), topk=6, part=128, incl=False, recent=68),           # blocks, windows that cut them
+    dict(lens=(6001, 9000, 30), topk=3, part=48, incl=False, sink=7, recent=10),
+    dict(lens=(20000, 1234), topk=2304),                              # the longest selection held in LDS, or nearly all pages
+    dict(lens=(40000,), topk=700, kv=1, sink=300, recent=400),        # more windows than wavefronts have lanes to ask ahead
+    dict(lens=(3000, 5000), heads=32, kv=2, topk=60),                 # 16 heads to a group
+    dict(lens=(3000, 5000), heads=10, kv=2, topk=60),                 # 5
+    dict(lens=(64 * 16 + 1, 300 * 16), leaf=1, topk=30),              # directories of more than 64 and 256 entries
+    dict(lens=(20000,), leaf=6, topk=30),
+])
+@pytest.mark.parametrize("splits", [0, 1, 3])
+def test_equals_the_stage_calls(kw, splits):
+    layer, _ = runner.build_device_layer(_workload(**kw), decode_splits=splits)
+    assert layer.spin.fused_splits >= 1
+    _same_as_stage_calls(layer, layer.q0)
+
+
+@pytest.mark.gpu
+def test_scores_that_tie_or_are_not_finite():
+    layer, _ = runner.build_device_layer(_workload((30000, 8000), topk=64))
+    sp, w = layer.spin, layer.w
+    for fill in ("ties", "inf", "nan", "spread"):
+        gen = torch.Generator(device="cuda:0")
+        gen.manual_seed(5)
+        layer.scores.normal_(generator=gen)
+        pick = torch.rand(layer.scores.shape, generator=gen, device="cuda:0")
+        if fill == "ties":
+            layer.scores.copy_((layer.scores * 2).round())
+        elif fill == "inf":
+            layer.scores[pick < 0.01] = float("inf")
+            layer.scores[pick > 0.5] = float("-inf")
+        elif fill == "nan":
+            layer.scores[pick < 0.999] = float("nan")                 # fewer numbers than are wanted
+        else:
+            layer.scores.mul_(torch.exp2(pick * 200 - 100))
+        sp.select_topk(w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.ws)
+        want = layer.sel.clone()
+        layer.sel.fill_(7)
+        sp.select_resolve_decode(w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel,
+                                 layer.dir, layer.leaf_pool, layer.slots, layer.page_ids, layer.valid_mask, layer.npages,
+                                 layer.q0, layer.kv_pool, layer.out, layer.lse, layer.ws)
+        assert torch.equal(want, layer.sel), fill
+    assert layer.status() == 0
+
+
+@pytest.mark.gpu
+def test_pages_that_are_missing_or_outside_the_pool():
+    for slot, code, note in ((-1, -6, "not resident"), (1 << 30, -7, "outside the pool")):
+        layer, _ = runner.build_device_layer(_workload((5000, 3000), topk=30, sink=0, recent=0))
+        layer.step(layer.q0)
+        chosen = int(layer.page_ids[1, 7])                            # row 1: request 0, head 1
+        chunk = int(layer.dir[1, chosen // layer.w.leaf_entries])
+        layer.leaf_pool[chunk, chosen % layer.w.leaf_entries] = slot
+        layer.step(layer.q0)
+        want = {n: getattr(layer, n).clone() for n in LISTS + ("out",)}
+        assert layer.status() == code
+        layer.spin.workspace_init(layer.ws)
+        layer.step2(layer.q0)
+        assert layer.status() == code, note
+        for n in LISTS:
+            assert torch.equal(want[n], getattr(layer, n)), (note, n)
+        assert (layer.out.float() - want["out"].float()).abs().max() <= 2 ** -6 * want["out"].float().abs().max()
+
+
+@pytest.mark.gpu
+def test_replays_of_a_graph():
+    layer, _ = runner.build_device_layer(_workload((9001, 4000), topk=64))
+    q = layer.q0.clone()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        layer.step2(q)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        layer.step2(q)
+    for seed in range(4):
+        q.copy_(synth.make_queries_on_device(layer.w, seed, "cuda:0"))
+        layer.step2(q)
+        want = layer.out.clone()
+        layer.out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(layer.out, want)
+
+
+def test_contexts_that_it_does_not_take():
+    base = dict(max_batch=2, num_q_heads=8, num_kv_heads=2, topk=8, max_context=4096)
+    assert binding.Spin(**base).fused_splits == 1
+    assert binding.Spin(**dict(base, max_batch=1, topk=128, max_context=131072, num_kv_heads=8)).fused_splits == 8
+    for other in (dict(partition_tokens=8), dict(lru_timestamps=8), dict(variable_partitions=1), dict(decode_waves=4),
+                  dict(decode_depth=3), dict(max_context=262145), dict(topk=2305, max_context=65536)):
+        sp = binding.Spin(**dict(base, **other))
+        assert sp.fused_splits == 0, other
+        fake = 4096   # never dereferenced: the call returns before anything is launched
+        import ctypes as C
+        assert sp.lib.spin_select_resolve_decode(sp.h, 1, fake, fake, fake, fake, fake, fake, fake, C.c_int64(1), fake, fake,
+                                                 fake, fake, fake, fake, C.c_int64(1), fake, fake, fake, None) == -2
