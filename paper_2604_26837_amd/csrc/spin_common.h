@@ -87,7 +87,7 @@ static inline bool spin_forced_split_supported(const spin_ctx *ctx) { return ctx
 
 // dynamic LDS of the launch that runs stages 2 to 4: stage 4's merge buffers (8 wavefronts) and the row's page list
 static inline size_t spin_fused_lds(const spin_ctx *ctx) {
-  return (size_t)8 * ctx->group * (SPIN_HEAD_DIM + 2) * sizeof(float) + (size_t)ctx->page_stride * 6;
+  return (size_t)8 * ctx->group * (SPIN_HEAD_DIM + 2) * sizeof(float) + (size_t)ctx->page_stride * 8;
 }
 
 static inline int spin_launch_status() {
@@ -152,6 +152,9 @@ __device__ inline float2 spin_dev_load2(const float *p) {
   return __builtin_bit_cast(float2, __hip_atomic_load((const unsigned long long *)p, __ATOMIC_RELAXED,
                                                       __HIP_MEMORY_SCOPE_AGENT));
 }
+
+// four words at an address that is a multiple of 4
+typedef int32_t spin_i32x4_at4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // 16-byte load marked non-temporal (streamed once, not worth keeping in cache)
 typedef __attribute__((ext_vector_type(4))) unsigned int spin_u32x4;
@@ -248,6 +251,7 @@ __device__ inline spin_var_span spin_var_span_of(const spin_var &v, size_t base,
 #define SPIN_DPP_XOR2 0x4E        /* quad_perm [2,3,0,1] */
 #define SPIN_DPP_HALF_MIRROR 0x141
 #define SPIN_DPP_MIRROR 0x140
+#define SPIN_DPP_ROR8 0x128       /* row_ror:8 */
 template <int CTRL>
 __device__ inline float spin_dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));

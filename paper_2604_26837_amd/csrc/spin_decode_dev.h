@@ -87,26 +87,26 @@ __device__ __forceinline__ void tile_attend(softmax_state &st, const spin_f32x4 
 }
 
 // Attends `cnt` (<= 64) pages whose slot and mask are held one per lane (lane i: the i-th page; a slot inside the pool
-// in every lane), in lane order, through a ring of DEPTH register buffers.  A tile's registers are loaded again as soon
+// in every lane), in lane order from page `from` on, through a ring of DEPTH register buffers.  A tile's registers are loaded again as soon
 // as it has been consumed, and what lies past the end is loaded as an empty page, so that the loop is straight-line
 // code that waits for exactly the tile it is about to read (see spin_buffer).  `asked` runs once the first DEPTH pages
 // have been asked for.
 template <int DEPTH, typename ASKED>
 __device__ __forceinline__ void attend_lane_pages(softmax_state &st, const uint4 *__restrict__ pool, int myslot,
-                                                  unsigned mymask, int cnt, int lane, int c,
+                                                  unsigned mymask, int from, int cnt, int lane, int c,
                                                   const spin_bf16x8 (&qf)[4], float scale_log2e, ASKED asked) {
   page_regs r[DEPTH];
   auto slot_of = [&](int i) { return __builtin_amdgcn_readlane(myslot, i < cnt ? i : 0); };
   auto mask_of = [&](int i) { return (unsigned)__builtin_amdgcn_readlane((int)mymask, i & 63) & (i < cnt ? 0xffffu : 0u); };
 #pragma unroll
   for (int d = 0; d < DEPTH; ++d) {
-    load_k_tile(r[d], pool, slot_of(d), lane, mask_of(d));
+    load_k_tile(r[d], pool, slot_of(from + d), lane, mask_of(from + d));
     __builtin_amdgcn_sched_barrier(0);   // asked for in the order in which the loop asks again
-    load_v_tile(r[d], pool, slot_of(d), lane, mask_of(d));
+    load_v_tile(r[d], pool, slot_of(from + d), lane, mask_of(from + d));
     __builtin_amdgcn_sched_barrier(0);
   }
   asked();
-  int i = 0;
+  int i = from;
   for (; i + DEPTH <= cnt; i += DEPTH) {
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) {
@@ -126,7 +126,7 @@ template <int DEPTH>
 __device__ __forceinline__ void attend_lane_pages(softmax_state &st, const uint4 *__restrict__ pool, int myslot,
                                                   unsigned mymask, int cnt, int lane, int c,
                                                   const spin_bf16x8 (&qf)[4], float scale_log2e) {
-  attend_lane_pages<DEPTH>(st, pool, myslot, mymask, cnt, lane, c, qf, scale_log2e, [] {});
+  attend_lane_pages<DEPTH>(st, pool, myslot, mymask, 0, cnt, lane, c, qf, scale_log2e, [] {});
 }
 
 // the group's queries as the second matrix operand of the logit tile: column n = head, k = channels 32j+8c..+8

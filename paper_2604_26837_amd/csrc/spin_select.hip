@@ -145,7 +145,7 @@ __global__ __launch_bounds__(BLOCK) void spin_select_reg_kernel(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
     int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, spin_var var) {
-  __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
+  __shared__ reg_row_lds<BLOCK> s;
   spin_var_span span;
   (void)select_reg_row<BLOCK, KPT>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
                                    recent_pages, sel_row<false>{sel + (size_t)blockIdx.x * sel_stride, sel_stride, nullptr},

@@ -60,21 +60,83 @@ struct spin_step_args {
   float *lse, *part_ml, *part_acc;
   int32_t *tickets, *status;
   int tp, topk, includes_forced, sink_pages, recent_pages, sel_stride, page_stride, leaf_entries;
+  int leaf_log;                       // log2 of leaf_entries, or -1
   float scale_log2e;
 };
 
-// grid: splits x KV heads x requests
-template <int KPT>
+// The first of this wavefront's always-attended pages, number `first` of the row's: its leaf entry's index and whether there
+// is one.  lane_dir: the row's directory, one entry per lane.
+struct asked_page {
+  int page;
+  size_t leaf;
+  bool there;
+};
+__device__ __forceinline__ asked_page page_ahead(bool mine, int first, const forced_span &fs, int32_t lane_dir, int dir_stride,
+                                                 int64_t leaf_chunks, int leaf_entries, int leaf_log) {
+  asked_page p;
+  p.page = first < fs.nlo ? first : fs.recent_begin + (first - fs.nlo);
+  const int ci = !mine ? 0 : (leaf_log >= 0 ? p.page >> leaf_log : p.page / leaf_entries);
+  const int32_t chunk = __builtin_amdgcn_readlane(lane_dir, ci < dir_stride ? ci : 0);
+  p.there = mine && ci < dir_stride && chunk >= 0 && (int64_t)chunk < leaf_chunks;
+  p.leaf = p.there ? (size_t)chunk * leaf_entries + (p.page - ci * leaf_entries) : 0;
+  return p;
+}
+
+// The selection of a row of partitions of one page, KPT of them per thread: the chosen pages in order to l_page, and with
+// `with_leaf` their leaf entries, which came with the scores, to l_slot (a thread's pages are quads of one leaf).
+template <int BLOCK, int KPT, typename ASK>
+__device__ __forceinline__ void select_pages(const __amdgpu_buffer_rsrc_t scores, const sel_plan &pl, bool with_leaf,
+                                             int32_t lane_dir, int dir_stride, const spin_step_args &a, spin_lds_i32 *l_page,
+                                             spin_lds_i32 *l_slot, reg_row_lds<BLOCK> &s, ASK ask_ahead) {
+  typedef typename key_bits<KPT>::type M;
+  constexpr int Q = KPT <= 8 ? KPT / 4 : 1;
+  const int c0 = threadIdx.x * KPT;
+  float f[KPT];
+#pragma unroll
+  for (int k4 = 0; k4 < KPT; k4 += 4) {
+    const float4 v = __builtin_bit_cast(float4, spin_buffer_load_kept(scores, (uint32_t)(c0 + k4) * sizeof(float)));
+    f[k4] = v.x; f[k4 + 1] = v.y; f[k4 + 2] = v.z; f[k4 + 3] = v.w;
+  }
+  spin_i32x4_at4 leaf[Q];
+  [[maybe_unused]] bool there[Q];
+  if constexpr (KPT <= 8) {
+    if (with_leaf) {
+#pragma unroll
+      for (int j = 0; j < Q; ++j) {
+        const int p = c0 + 4 * j, ci = p >> a.leaf_log;
+        const int32_t chunk = __shfl(lane_dir, min(ci, dir_stride - 1));
+        there[j] = ci < dir_stride && chunk >= 0 && (int64_t)chunk < a.leaf_chunks;
+        leaf[j] = *(const spin_i32x4_at4 *)(a.leaf_pool + (there[j] ? ((size_t)chunk << a.leaf_log) + (p & (a.leaf_entries - 1)) : 0));
+      }
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const M cand = range_bits<KPT>(c0, pl.nf_lo, pl.first_hi);
+  const M forced = range_bits<KPT>(c0, 0, pl.P) & ~cand;
+  ask_ahead();
+  select_elements<BLOCK, KPT>(f, cand, forced, c0, pl.nf_lo, pl.first_hi, pl.kprime, s, [&](int pos, int k) {
+    if (pos >= a.page_stride) return;
+    l_page[pos] = c0 + k;
+    if constexpr (KPT <= 8)
+      if (with_leaf) l_slot[pos] = there[k / 4] ? leaf[k / 4][k & 3] : -1;
+  });
+}
+
+// grid: splits x KV heads x requests.  PAGES: partitions of one page, 2^leaf_log >= 4 entries to a leaf; the selection is
+// the page list, nothing is divided, a row takes as many scores per thread as its own length asks for, and with up to 8 a
+// page's leaf entry comes with its score.
+template <int KPT, bool PAGES>       // KPT: scores per thread of the longest row
 __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets, const int32_t *__restrict__ seq_lens,
     const int32_t *__restrict__ dir, const uint16_t *__restrict__ q, int Hkv, int nsplit, int G, int Hq, int dir_stride,
     spin_step_args a) {
   constexpr int WAVES = 8, BLOCK = 64 * WAVES;
-  __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
-  __shared__ held_row<true> s_held;
+  __shared__ reg_row_lds<BLOCK> s;
+  __shared__ int32_t held_words[PAGES ? RES_DIR_LDS : sizeof(held_row<true>) / sizeof(int32_t)];
   extern __shared__ __align__(16) float smem[];       // the merge buffers of decode_finish, then the row's page list
   spin_lds_i32 *l_slot = (spin_lds_i32 *)(smem + WAVES * G * (SPIN_HEAD_DIM + 2));
-  spin_lds_u16 *l_mask = (spin_lds_u16 *)(l_slot + a.page_stride);
+  spin_lds_i32 *l_page = l_slot + a.page_stride;      // PAGES: the pages
+  spin_lds_u16 *l_mask = (spin_lds_u16 *)l_page;      // otherwise: the masks
   const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z, row = b * Hkv + h;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 15, c = lane >> 4;
@@ -83,68 +145,128 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
   // Pages are dealt round-robin, the always-attended ones (first the sink, then the recent ones) ahead of the others:
   // page v goes to split v % nsplit, wavefront (v / nsplit) % WAVES.
   const int first = wave * nsplit + split, stride = WAVES * nsplit;
+  const int32_t *rdir = dir + (size_t)row * dir_stride;
   // the directory one entry per lane (larger ones: no page is asked for ahead)
   const bool ahead = dir_stride <= 64;
-  const int32_t lane_dir = dir[(size_t)row * dir_stride + min(lane, dir_stride - 1)];
+  const int32_t lane_dir = rdir[min(lane, dir_stride - 1)];
+  const int N = max(seq_lens[b], 0);
+  const forced_span fs = forced_pages_of(N, a.sink_pages, a.recent_pages);
+  const bool asked = ahead && first < fs.nlo + fs.nhi;
   spin_bf16x8 qf[4];
-  load_queries(qf, q, b, h, G, Hq, n, c);
-
-  int32_t mydir;
   page_regs rf;
   unsigned rf_mask = 0;
-  forced_span fs;
-  const step_sel rsel = {a.sel + (size_t)row * a.sel_stride, a.sel_stride, (spin_lds_i32 *)s_held.sel, store};
-  spin_var_span span;                // (uniform partitions)
-  const int take = select_reg_row<BLOCK, KPT>(
-      scores, part_offsets, seq_lens, Hkv, a.tp, a.topk, a.includes_forced, a.sink_pages, a.recent_pages, rsel, a.nsel, row,
-      spin_var{}, span, s, [&] {
-        mydir = row_dir_entry(dir, dir_stride, row);
-        const int N = seq_lens[b];
-        fs = forced_pages_of(N, a.sink_pages, a.recent_pages);
-        const bool mine = ahead && first < fs.nlo + fs.nhi;
-        const int page = first < fs.nlo ? first : fs.recent_begin + (first - fs.nlo), ci = mine ? page / a.leaf_entries : 0;
-        const int32_t chunk = __builtin_amdgcn_readlane(lane_dir, ci < dir_stride ? ci : 0);
-        const bool there = mine && ci < dir_stride && chunk >= 0 && (int64_t)chunk < a.leaf_chunks;
-        const int32_t slot = __builtin_amdgcn_readfirstlane(
-            a.leaf_pool[there ? (size_t)chunk * a.leaf_entries + (page - ci * a.leaf_entries) : 0]);
-        const bool ok = there && slot >= 0 && (int64_t)slot < a.pool_slots;
-        rf_mask = ok ? page_mask(page, N) : 0u;
-        load_k_tile(rf, a.pool, ok ? slot : 0, lane, rf_mask);
-        load_v_tile(rf, a.pool, ok ? slot : 0, lane, rf_mask);
-        __builtin_amdgcn_sched_barrier(0);
-      });
-  if (tid < RES_DIR_LDS) s_held.dir[tid] = mydir;
-  __syncthreads();                   // the selection and the directory are whole
-  if (store)
-    for (int i = tid; i < take; i += BLOCK) rsel.out[i] = rsel.lds[i];
-  const step_pages list = {res_row_out(a.slots, a.page_ids, a.valid_mask, a.npages, row, a.page_stride), l_slot, l_mask, store};
-  const int np = resolve_row<BLOCK, true, true, true>(row, take, a.sel, seq_lens, dir, a.leaf_pool, a.leaf_chunks, Hkv, a.tp,
-                                                      a.sink_pages, a.recent_pages, a.sel_stride, a.page_stride, dir_stride,
-                                                      a.leaf_entries, list, a.status, spin_var{}, nullptr, &s_held);
+  auto ask_ahead = [&](const asked_page &p) {
+    const int32_t slot = __builtin_amdgcn_readfirstlane(a.leaf_pool[p.leaf]);
+    const bool ok = p.there && slot >= 0 && (int64_t)slot < a.pool_slots;
+    rf_mask = ok ? page_mask(p.page, N) : 0u;
+    load_k_tile(rf, a.pool, ok ? slot : 0, lane, rf_mask);
+    load_v_tile(rf, a.pool, ok ? slot : 0, lane, rf_mask);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  int np;                                             // pages of the row's list
+  [[maybe_unused]] bool with_leaf = false;
+  if constexpr (PAGES) {
+    const int off = part_offsets[b], PP = part_offsets[b + 1] - off;
+    const int32_t mydir = rdir[min(tid, dir_stride - 1)];
+    load_queries(qf, q, b, h, G, Hq, n, c);
+    __builtin_amdgcn_sched_barrier(0);
+    // the selection's plan: partitions are pages
+    const int P = min(min((N + 15) >> 4, PP), BLOCK * KPT);
+    const sel_plan pl = plan_of(P, min(fs.nlo, P), min(fs.recent_begin, P), a.topk, a.includes_forced, a.sel_stride);
+    // zeros past the row's end
+    const __amdgpu_buffer_rsrc_t buf = spin_buffer(scores + (size_t)Hkv * off + (size_t)h * PP, (uint32_t)max(PP, 0) * sizeof(float));
+    with_leaf = ahead && P <= 8 * BLOCK;
+    auto ask = [&] {
+      ask_ahead(page_ahead(asked, first, fs, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
+      if (!with_leaf && tid < RES_DIR_LDS) held_words[tid] = mydir;
+    };
+    if (KPT == 4 || P <= 4 * BLOCK) select_pages<BLOCK, 4>(buf, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+    else if (KPT == 8 || P <= 8 * BLOCK) select_pages<BLOCK, 8>(buf, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+    else if (KPT == 16 || P <= 16 * BLOCK) select_pages<BLOCK, 16>(buf, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+    else select_pages<BLOCK, 32>(buf, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+    np = min(pl.take, a.page_stride);
+  } else {
+    load_queries(qf, q, b, h, G, Hq, n, c);
+    held_row<true> &s_held = *(held_row<true> *)held_words;
+    int32_t mydir;
+    const step_sel rsel = {a.sel + (size_t)row * a.sel_stride, a.sel_stride, (spin_lds_i32 *)s_held.sel, store};
+    spin_var_span span;                // (uniform partitions)
+    const int take = select_reg_row<BLOCK, KPT>(
+        scores, part_offsets, seq_lens, Hkv, a.tp, a.topk, a.includes_forced, a.sink_pages, a.recent_pages, rsel, a.nsel, row,
+        spin_var{}, span, s, [&] {
+          mydir = row_dir_entry(dir, dir_stride, row);
+          ask_ahead(page_ahead(asked, first, fs, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
+        });
+    if (tid < RES_DIR_LDS) s_held.dir[tid] = mydir;
+    __syncthreads();                   // the selection and the directory are whole
+    if (store)
+      for (int i = tid; i < take; i += BLOCK) rsel.out[i] = rsel.lds[i];
+    const step_pages list = {res_row_out(a.slots, a.page_ids, a.valid_mask, a.npages, row, a.page_stride), l_slot, l_mask, store};
+    np = resolve_row<BLOCK, true, true, true>(row, take, a.sel, seq_lens, dir, a.leaf_pool, a.leaf_chunks, Hkv, a.tp,
+                                              a.sink_pages, a.recent_pages, a.sel_stride, a.page_stride, dir_stride,
+                                              a.leaf_entries, list, a.status, spin_var{}, nullptr, &s_held);
+  }
   __syncthreads();
 
   // The sink pages open the list and the recent ones close it.
   softmax_state st;
   softmax_reset(st);
-  const int nf = min(fs.nlo + fs.nhi, np), all = np;
-  const int asked = ahead && first < nf ? 1 : 0;          // of this wavefront's pages
-  const int cnt = all > first ? (all - first + stride - 1) / stride : 0;
-  for (int base = asked; base == asked || base < cnt; base += 64) {
+  const int nf = min(fs.nlo + fs.nhi, np);
+  const int cnt_all = np > first ? (np - first + stride - 1) / stride : 0;
+  const res_out out = res_row_out(a.slots, a.page_ids, a.valid_mask, a.npages, row, a.page_stride);
+  for (int base = 0; base == 0 || base < cnt_all; base += 64) {
+    const int cnt = max(min(cnt_all - base, 64), 0);
     int myslot = 0;
     unsigned mymask = 0;
-    if (base + lane < cnt) {
+    [[maybe_unused]] int at = 0, page = -1, found = -1;
+    [[maybe_unused]] unsigned found_mask = 0;
+    if (lane < cnt) {
       const int v = first + (base + lane) * stride;
-      const int at = v < nf ? (v < fs.nlo ? v : max(np - fs.nhi + (v - fs.nlo), 0)) : fs.nlo + (v - nf);
-      const int32_t slot = l_slot[at];
-      if (slot >= 0 && (int64_t)slot < a.pool_slots) {
-        myslot = slot;
-        mymask = l_mask[at];
+      at = v < nf ? (v < fs.nlo ? v : max(np - fs.nhi + (v - fs.nlo), 0)) : fs.nlo + (v - nf);
+      if constexpr (PAGES) {
+        page = l_page[at];
+        if (with_leaf) {
+          found = l_slot[at];
+        } else {
+          const int ci = page >> a.leaf_log;
+          if (ci < dir_stride) {
+            const int32_t chunk = dir_stride <= RES_DIR_LDS ? ((spin_lds_i32 *)held_words)[ci] : rdir[ci];
+            if (chunk >= 0 && (int64_t)chunk < a.leaf_chunks)
+              found = a.leaf_pool[((size_t)chunk << a.leaf_log) + (page & (a.leaf_entries - 1))];
+          }
+        }
+        if (found < 0) {
+          found = -1;
+          spin_raise(a.status, SPIN_ERR_NOT_RESIDENT);
+        }
+        found_mask = found >= 0 ? page_mask(page, N) : 0u;
+      } else {
+        found = l_slot[at];
+        found_mask = l_mask[at];
+      }
+      if (found >= 0 && (int64_t)found < a.pool_slots) {
+        myslot = found;
+        mymask = found_mask;
       } else if (v >= nf) {
         spin_raise(a.status, SPIN_ERR_SLOT_RANGE);        // attends to none of it
       }
     }
-    attend_lane_pages<2>(st, a.pool, myslot, mymask, max(min(cnt - base, 64), 0), lane, c, qf, a.scale_log2e, [&] {
-      if (base == asked && asked) tile_attend(st, tile_logits(rf, qf), rf, rf_mask, c, a.scale_log2e);
+    const int from = base == 0 && asked ? 1 : 0;          // the first one was asked for already
+    attend_lane_pages<2>(st, a.pool, myslot, mymask, from, cnt, lane, c, qf, a.scale_log2e, [&] {
+      if (from && cnt > 0) tile_attend(st, tile_logits(rf, qf), rf, rf_mask, c, a.scale_log2e);
+      if constexpr (PAGES) {                              // the row's lists: its own entries from every wavefront
+        if (lane < cnt) out.put(at, found, page, found_mask);
+        if (store && base == 0) {
+          int32_t *rsel = a.sel + (size_t)row * a.sel_stride;
+          for (int i = tid; i < a.sel_stride; i += BLOCK) rsel[i] = i < np ? l_page[i] : -1;
+          for (int i = np + tid; i < a.page_stride; i += BLOCK) out.put(i, -1, -1, 0);
+          if (tid == 0) {
+            a.nsel[row] = np;
+            out.count(np);
+          }
+        }
+      }
     });
   }
   decode_finish<WAVES>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, nsplit, a.part_ml, a.part_acc, a.tickets, a.out,
@@ -165,20 +287,27 @@ extern "C" int spin_select_resolve_decode(spin_ctx *ctx, int32_t batch, const fl
   if (!workspace) return SPIN_ERR_WORKSPACE;
   const spin_config &c = ctx->cfg;
   char *ws = (char *)workspace;
+  const int leaf_log = (c.leaf_entries & (c.leaf_entries - 1)) ? -1 : 31 - __builtin_clz((unsigned)c.leaf_entries);
   const spin_step_args a = {leaf_pool, leaf_chunks, sel, nsel, slots, page_ids, valid_mask, npages, (const uint4 *)kv_pool,
                             pool_slots, (uint16_t *)out, lse, (float *)(ws + ctx->ws_ml_off),
                             (float *)(ws + ctx->ws_acc_off), (int32_t *)(ws + ctx->ws_ticket_off), (int32_t *)workspace,
                             c.partition_tokens, c.topk, c.topk_includes_forced, c.sink_pages, c.recent_pages,
-                            ctx->sel_stride, ctx->page_stride, c.leaf_entries, ctx->scale * 1.4426950408889634f};
-#define SPIN_SD_LAUNCH(KPT)                                                                                       \
-  spin_launch(ctx, SPIN_K_SELECT_DECODE, spin_select_decode_kernel<KPT>,                                          \
+                            ctx->sel_stride, ctx->page_stride, c.leaf_entries, leaf_log, ctx->scale * 1.4426950408889634f};
+#define SPIN_SD_LAUNCH1(KPT, PAGES)                                                                               \
+  spin_launch(ctx, SPIN_K_SELECT_DECODE, spin_select_decode_kernel<KPT, PAGES>,                                   \
               dim3((unsigned)ctx->fused_splits, (unsigned)c.num_kv_heads, (unsigned)batch), dim3(512), spin_fused_lds(ctx), \
               (hipStream_t)stream, scores, part_offsets, seq_lens, dir, (const uint16_t *)q, c.num_kv_heads,      \
               ctx->fused_splits, ctx->group, c.num_q_heads, ctx->dir_stride, a)
+#define SPIN_SD_LAUNCH(KPT)                                                            \
+  do {                                                                                 \
+    if (c.partition_tokens == SPIN_PAGE_TOKENS && leaf_log >= 2) SPIN_SD_LAUNCH1(KPT, true); \
+    else SPIN_SD_LAUNCH1(KPT, false);                                                  \
+  } while (0)
   if (ctx->max_parts <= 2048) SPIN_SD_LAUNCH(4);
   else if (ctx->max_parts <= 4096) SPIN_SD_LAUNCH(8);
   else if (ctx->max_parts <= 8192) SPIN_SD_LAUNCH(16);
   else SPIN_SD_LAUNCH(32);
+#undef SPIN_SD_LAUNCH1
 #undef SPIN_SD_LAUNCH
   return spin_launch_status();
 }

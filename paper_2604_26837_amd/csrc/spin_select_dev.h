@@ -265,13 +265,13 @@ __device__ inline float key_floor_score(uint32_t K, bool low_end) {
 }
 #define SPIN_KEY_MINUS_INF 0x007fffffu
 
-// LDS of select_elements: the candidates that are left, in partition order
+// the candidates that are left, in partition order
 template <int BLOCK, int CAP>
 struct elements_lds {
   kth_lds<BLOCK> kth;
   uint2 wtot[BLOCK / 64];
-  uint32_t key[CAP > 0 ? CAP : 1];
-  int32_t id[CAP > 0 ? CAP : 1];
+  uint32_t key[CAP];
+  int32_t id[CAP];
 };
 
 // The kprime best of the `total` entries of an ordered list in LDS, stored ascending at rsel[first ..].
@@ -311,74 +311,227 @@ __device__ __forceinline__ void pick_from_list(int total, int kprime, int first,
   else pick_list(std::integral_constant<int, LPT>());
 }
 
-// Picks the kprime best of the candidates a workgroup holds in registers (KPT scores per thread, bit k of `cand`:
-// f[k] is a candidate; thread, then k is ascending partition order; id(k) names its partition) and stores their
-// ids at rsel[first ..], ascending.  `bound`: a key that at least kprime of the candidates reach (0: none known).
-// What the one compute unit of a row spends its time on is instructions per score (at 1024 threads one
-// instruction on every thread's score takes the unit 6.7 ns), so a score is only compared as a float with the
-// bound (key order is float order) and the few that pass form a list in LDS, on which the exact search runs with
-// one to CAP / BLOCK keys per thread.  A row with more than CAP of them (every row where CAP is 0: few scores per
-// thread, for which the list does not pay) searches its registers.
-template <int BLOCK, int KPT, int CAP, typename ROW, typename ID>
-__device__ __forceinline__ void select_elements(const float (&f)[KPT], typename key_bits<KPT>::type cand, uint32_t bound,
-                                       int kprime, int first, const ROW &rsel,
-                                       elements_lds<BLOCK, CAP> &s, ID id) {
+// ---------------------------------------------------------------------------
+// Rows whose scores a workgroup holds in registers.
+#define TAIL_BINS 512
+#define TAIL_MEMBERS 64
+template <int BLOCK>
+struct reg_row_lds {
+  kth_lds<BLOCK> kth;
+  alignas(16) int bins[TAIL_BINS + TAIL_BINS / 2];
+  alignas(16) float lo[BLOCK / 64];
+  float top[BLOCK];
+  uint2 wtot[BLOCK / 64];
+  int listed;
+  alignas(16) uint64_t member[TAIL_MEMBERS];     // key, then the complement of the partition: the better, the greater
+};
+
+// Where bin `b` of the tail's histogram lies: four words of padding after every eight, so that tail_bin_of_rank's lanes,
+// which read eight each, meet in no bank.
+__device__ __forceinline__ int tail_word(int b) { return b + ((b >> 3) << 2); }
+
+// As digit_of_rank, of TAIL_BINS bins: lane l has the eight from TAIL_BINS - 1 - 8 l down.
+__device__ __forceinline__ int tail_bin_of_rank(const int *bins, int &rank, int &in_bin) {
+  const int block = 63 - (threadIdx.x & 63);
+  const int4 u = *(const int4 *)(bins + block * 12), v = *(const int4 *)(bins + block * 12 + 4);
+  const int upper = (v.x + v.y) + (v.z + v.w), local = ((u.x + u.y) + (u.z + u.w)) + upper;
+  const int inc = spin_wave_inclusive_scan(local);
+  const unsigned long long found = __ballot(inc >= rank);   // the first of them has it
+  if (!found) return -1;
+  int r = rank - (inc - local);
+  const bool below = r > upper;                             // in the lower four of the lane's
+  r -= below ? upper : 0;
+  const int4 q = below ? u : v;
+  int e = below ? 3 : 7, n = q.w;
+  if (r > n) {
+    r -= n; n = q.z; --e;
+    if (r > n) {
+      r -= n; n = q.y; --e;
+      if (r > n) { r -= n; n = q.x; --e; }
+    }
+  }
+  const int src = __ffsll((long long)found) - 1;
+  rank = __builtin_amdgcn_readlane(r, src);
+  in_bin = __builtin_amdgcn_readlane(n, src);
+  return __builtin_amdgcn_readlane(block * 8 + e, src);
+}
+
+// Picks the kprime best of the candidates a workgroup holds in registers: thread t has the scores f[k] of partitions
+// c0 + k, c0 = t * KPT, and the candidates are [nf_lo, first_hi).  put(pos, k) is called for those and the `forced` ones
+// (bit k: of the calling thread's), pos = 0, 1 .. in ascending partition order.
+// Latency bounds this (the row's one compute unit waits for memory, LDS and barriers in turn, and an instruction of all
+// eight wavefronts takes it 8 cycles), so the chain is short: one histogram of the row's upper tail in equal steps of
+// score, an exact ranking of the few scores in the step that holds the threshold, one prefix sum; three barriers.
+// Both ends of the tail are places in the row's order, so that the steps lie where the scores do, however these are
+// spread.  The lower one is the least of the maxima of groups of scores (of four threads down to a quarter of a
+// thread's): with at least kprime groups that hold candidates, at least kprime scores reach it.  The upper one is the
+// least of the maxima of 2, 8 or 64 interleaved parts of the row, which some 3, 20 or 300 scores exceed; those share the
+// last step.
+// A step is a monotone function of the score (subtraction, product with a positive scale and truncation are), so the
+// order is the scores' own.
+// Rows for which that does not work (more than 64 scores in the threshold's step: ties) take block_kth, over all of the
+// row or over that step.
+// Against one radix digit of 8 bits per barrier (and, with 16 scores per thread and more, a bound from a search among the
+// threads' maxima and a list in LDS first), stages 2+3 of normal scores, us: 128 rows of 2048, k 128 5.9 -> 5.8; 32 of 4096
+// 7.0 -> 6.4; 64 of 8192 8.0 -> 6.6, 8 of them with k 1024 9.6 -> 7.9; 256 ragged ones of up to 16384 10.7 -> 8.5, 32 of 16384
+// with k 1500 13.3 -> 10.2.  Slower where many scores tie at the threshold (128 rows of 2048 with steps of a quarter of their
+// deviation 6.7 -> 8.4, 64 of 8192 9.3 -> 10.8) or more outliers than there are parts are a million times the others
+// (256 of 16384 10.8 -> 16.2).
+template <int BLOCK, int KPT, typename PUT>
+__device__ __forceinline__ void select_elements(float (&f)[KPT], typename key_bits<KPT>::type cand,
+                                                typename key_bits<KPT>::type forced, int c0, int nf_lo, int first_hi,
+                                                int kprime, reg_row_lds<BLOCK> &s, PUT put) {
   typedef typename key_bits<KPT>::type M;
-  [[maybe_unused]] constexpr int NW = BLOCK / 64;
-  [[maybe_unused]] const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int total = 0;                                 // candidates left (counted where there is a list)
-  M valid = cand;
-  if (bound > SPIN_KEY_MINUS_INF) {            // (at -inf NaN scores, which rank there, would fail the comparison)
-    const float bf = key_floor_score(bound, true);
-    M above = 0;
+  constexpr int NW = BLOCK / 64, KLOG = KPT == 4 ? 2 : KPT == 8 ? 3 : KPT == 16 ? 4 : KPT == 32 ? 5 : 6;
+  static_assert(KPT == 1 << KLOG, "a power of two");
+  constexpr M full = KPT == (int)(8 * sizeof(M)) ? ~(M)0 : ((M)1 << (KPT & (int)(8 * sizeof(M) - 1))) - 1;
+  const float inf = __builtin_inff();
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int i = tid; i < TAIL_BINS + TAIL_BINS / 2; i += BLOCK) s.bins[i] = 0;
+  if (tid < TAIL_MEMBERS) s.member[tid] = 0;
+  if (tid == 0) s.listed = 0;
+  // groups of KPT * 2^g partitions that hold a candidate: at least kprime of them (g < -2: there are not)
+  int g = 2;
+  while (g >= -2 && ((first_hi - 1) >> (KLOG + g)) - (nf_lo >> (KLOG + g)) + 1 < kprime) --g;
 #pragma unroll
-    for (int k = 0; k < KPT; ++k) above |= f[k] >= bf ? (M)1 << k : (M)0;
-    valid &= above;
+  for (int k = 0; k < KPT; ++k) f[k] = fmaxf(f[k], -inf);        // NaN ranks as -inf
+  if (!__all(cand == full)) {
+#pragma unroll
+    for (int k = 0; k < KPT; ++k) f[k] = (cand >> k) & 1u ? f[k] : -inf;
   }
-  uint32_t T;
-  unsigned need_eq;
-  if constexpr (CAP > 0) {
-    // ordered list of the candidates left
-    const int mine = popc_bits(valid);
-    const int inc = spin_wave_inclusive_scan(mine);
-    if (lane == 63) s.wtot[wave].x = (unsigned)inc;
-    __syncthreads();
-    const int before = spin_waves_before<NW>((int)s.wtot[lane % NW].x, wave, total) + inc - mine;
-    if (total <= CAP) {                          // block-uniform
-      if (valid) {
-        int pos = before;
+  float part[4];
 #pragma unroll
-        for (int k = 0; k < KPT; ++k)
-          if ((valid >> k) & 1u) {
-            s.key[pos] = score_key(f[k]);
-            s.id[pos] = id(k);
-            ++pos;
-          }
+  for (int i = 0; i < 4; ++i) {
+    part[i] = f[i * (KPT / 4)];
+#pragma unroll
+    for (int k = 1; k < KPT / 4; ++k) part[i] = fmaxf(part[i], f[i * (KPT / 4) + k]);
+  }
+  float lo, top = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+  // (groups of -inf do not count: either they hold no candidate, or the tail may be too short, which the search tells)
+  auto counts = [&](float v) { return v == -inf ? inf : v; };
+  if (g >= 0) {
+    lo = top;
+    if (g >= 1) lo = fmaxf(lo, spin_dpp<SPIN_DPP_XOR1>(lo));
+    if (g == 2) lo = fmaxf(lo, spin_dpp<SPIN_DPP_XOR2>(lo));
+    lo = counts(lo);
+  } else if (g == -1) {
+    lo = fminf(counts(fmaxf(part[0], part[1])), counts(fmaxf(part[2], part[3])));
+  } else if (g == -2 || KPT == 4) {
+    lo = fminf(fminf(counts(part[0]), counts(part[1])), fminf(counts(part[2]), counts(part[3])));
+  } else {
+    lo = inf;
+#pragma unroll
+    for (int k = 0; k < KPT; ++k) lo = fminf(lo, counts(f[k]));
+  }
+  lo = -spin_wave_max(-lo);
+  s.top[tid] = top;
+  if (lane == 0) s.lo[wave] = lo;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NW; i += 4) {
+    const float4 l = *(const float4 *)(s.lo + i);
+    lo = i ? fminf(lo, l.x) : l.x;
+    lo = fminf(fminf(lo, l.y), fminf(l.z, l.w));
+  }
+#pragma unroll
+  for (int i = 0; i < NW; ++i) top = fmaxf(top, s.top[i * 64 + lane]);
+  if (kprime < 512) {                            // 64 interleaved parts of the row, or these merged to 8 or 2
+    top = spin_max_xor32(spin_max_xor16(fmaxf(top, spin_dpp<SPIN_DPP_ROR8>(top))));
+    if (kprime < 64) {
+      top = fmaxf(top, spin_dpp<SPIN_DPP_XOR1>(top));
+      top = fmaxf(top, spin_dpp<SPIN_DPP_XOR2>(top));
+    }
+    top = counts(top);
+    top = fminf(top, spin_dpp<SPIN_DPP_XOR1>(top));
+    top = fminf(top, spin_dpp<SPIN_DPP_XOR2>(top));
+    top = fminf(top, spin_dpp<SPIN_DPP_HALF_MIRROR>(top));
+  } else {
+    top = -spin_wave_max(-counts(top));
+  }
+  lo = spin_readlane(lo, 0);
+  const float spread = spin_readlane(top, 0) - lo;
+  // (no group that counts: lo = inf; below 2^-100 the scale might overflow)
+  const bool usable = kprime > 0 && spread > 0x1p-100f && spread < inf;
+  const float scale = (float)(TAIL_BINS - 1) * __builtin_amdgcn_rcpf(spread);
+  int bin = -1, need = kprime, in_bin = 0;
+  int b[KPT];
+  M sure = forced, member = kprime > 0 ? cand : 0;
+  if (usable) {
+#pragma unroll
+    for (int k = 0; k < KPT; ++k) {
+      b[k] = -1;
+      if (f[k] >= lo) {
+        b[k] = (int)fminf((f[k] - lo) * scale, (float)(TAIL_BINS - 1));
+        atomicAdd(&s.bins[tail_word(b[k])], 1);
       }
-      __syncthreads();
-      pick_from_list<BLOCK, CAP>(total, kprime, first, rsel, s);
-      return;
+    }
+    __syncthreads();
+    bin = tail_bin_of_rank(s.bins, need, in_bin);
+    if (bin >= 0) {
+      member = 0;
+#pragma unroll
+      for (int k = 0; k < KPT; ++k) {
+        sure |= b[k] > bin ? (M)1 << k : (M)0;
+        member |= b[k] == bin ? (M)1 << k : (M)0;
+      }
     }
   }
-  uint32_t key[KPT];
+  int pos;
+  if (kprime > 0 && (bin < 0 || (in_bin > TAIL_MEMBERS && in_bin != need))) {   // uniform
+    uint32_t key[KPT], T;
+    unsigned need_eq;
 #pragma unroll
-  for (int k = 0; k < KPT; ++k) key[k] = score_key(f[k]);
-  block_kth<BLOCK, KPT, KPT == 16 || KPT == 32>(key, valid, kprime, 0, s.kth, T, need_eq, total >= 4096);
-  M gt = 0, eq = 0;
+    for (int k = 0; k < KPT; ++k) key[k] = score_key(f[k]);
+    block_kth<BLOCK, KPT, KPT == 16 || KPT == 32>(key, member, need, 0, s.kth, T, need_eq, first_hi - nf_lo >= 4096);
+    M gt = 0, eq = 0;
 #pragma unroll
-  for (int k = 0; k < KPT; ++k) {
-    gt |= key[k] > T ? (M)1 << k : (M)0;
-    eq |= key[k] == T ? (M)1 << k : (M)0;
-  }
-  int pos, picked, eq_picked;
-  const M pick = ordered_picks<BLOCK>((M)(gt & valid), (M)(eq & valid), need_eq, s.wtot, pos, picked, eq_picked);
-  pos += first;
-#pragma unroll
-  for (int k = 0; k < KPT; ++k)
-    if ((pick >> k) & 1u) {
-      rsel.put(pos, id(k));
-      ++pos;
+    for (int k = 0; k < KPT; ++k) {
+      gt |= key[k] > T ? (M)1 << k : (M)0;
+      eq |= key[k] == T ? (M)1 << k : (M)0;
     }
+    int picked, eq_picked;
+    sure = ordered_picks<BLOCK>((M)(sure | (gt & member)), (M)(eq & member), need_eq, s.wtot, pos, picked, eq_picked);
+  } else {
+    const bool all = in_bin == need;
+    if (all) {
+      sure |= member;
+    } else if (member) {
+#pragma unroll
+      for (int k = 0; k < KPT; ++k)
+        if ((member >> k) & 1u) s.member[atomicAdd(&s.listed, 1)] = ((uint64_t)score_key(f[k]) << 32) | (uint32_t)~(c0 + k);
+    }
+    const int mine = popc_bits(sure), inc = spin_wave_inclusive_scan(mine);
+    if (lane == 63) s.wtot[wave].x = (uint32_t)inc;
+    __syncthreads();
+    int total;
+    pos = spin_waves_before<NW>((int)s.wtot[lane % NW].x, wave, total) + inc - mine;
+    if (!all) {                                  // the `need` best of the bin's scores, lower partitions first among equals
+      const uint64_t me = s.member[lane];
+      int better = 0;
+      for (int j = 0; j < in_bin; j += 8) {      // (zeros past the last: no score's key is)
+        uint64_t other[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) other[i] = s.member[j + i];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) better += other[i] > me;
+      }
+      for (unsigned long long m = __ballot(lane < in_bin && better < need); m; m &= m - 1) {
+        const int d = ~__builtin_amdgcn_readlane((int)(uint32_t)me, __ffsll((long long)m) - 1) - c0;
+        pos += d < 0;
+        sure |= d >= 0 && d < KPT ? (M)1 << (d & (KPT - 1)) : (M)0;
+      }
+    }
+  }
+  if constexpr (KPT <= 8) {
+#pragma unroll
+    for (int k = 0; k < KPT; ++k)
+      if ((sure >> k) & 1u) {
+        put(pos, k);
+        ++pos;
+      }
+  } else {                                       // few of a thread's many
+    for (; sure; sure &= sure - 1, ++pos) put(pos, ffs_bits(sure) - 1);
+  }
 }
 
 // forced partitions (a prefix and a suffix of the row) around the kprime candidates, and the padding
@@ -464,25 +617,16 @@ __device__ __forceinline__ spin_var_span block_var_span(const spin_var &var, siz
 
 // Register-resident variant for rows of at most BLOCK * KPT partitions: every
 // thread keeps KPT consecutive scores in registers, so they are read once.
-// With 16 or more of them per thread most are ruled out first: the k'-th largest of the threads' largest keys
-// is a lower bound of the threshold (k' threads hold a key at least that large).
-// Latency bounds this kernel: dependent loads, a barrier per digit, and the instructions per score on the row's
-// one compute unit.  Stages 2+3, top 128, before (every score in every histogram) and after: 8 rows of 8192
-// 14.7 -> 9.4 us, 8 rows of 16384 16.2 -> 11.5, 256 ragged rows of up to 16384 17.4 -> 13.4.
 // Returns the number of selected partitions (and, with variable-length partitions, the row's windows in `span`).
-template <int BLOCK, int KPT>
-constexpr int reg_row_cap() { return KPT >= 16 ? 2 * BLOCK : 0; }
-
 // `meanwhile` issues what the caller wants under way beside the scores.
 template <int BLOCK, int KPT, typename ROW, typename MEANWHILE>
 __device__ __forceinline__ int select_reg_row(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
     int recent_pages, const ROW &rsel, int32_t *__restrict__ nsel, int row, spin_var var,
-    spin_var_span &span, elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> &s,
+    spin_var_span &span, reg_row_lds<BLOCK> &s,
     MEANWHILE meanwhile) {
   typedef typename key_bits<KPT>::type M;
-  constexpr int CAP = reg_row_cap<BLOCK, KPT>();
   const int b = row / Hkv, h = row - b * Hkv;
   const int N = seq_lens[b];
   const int off_b = part_offsets[b];
@@ -517,24 +661,12 @@ __device__ __forceinline__ int select_reg_row(
     pl.kprime = min(pl.kprime, pl.first_hi - pl.nf_lo);
     pl.take = min(pl.nf_lo + pl.kprime + pl.P - pl.first_hi, sel_stride);
   }
-  emit_forced<BLOCK>(pl, rsel, nsel, row);   // under way while the scores are still coming
-  if (pl.kprime > 0) {
-    const M cand = range_bits<KPT>(c0, pl.nf_lo, pl.first_hi);
-    uint32_t bound = 0;
-    if (KPT >= 16) {
-      const int holders = (pl.first_hi - 1) / KPT - pl.nf_lo / KPT + 1;   // threads that hold a candidate
-      if (holders >= pl.kprime + (pl.kprime >> 1)) {                      // block-uniform
-        float mx = -__builtin_inff();                                     // NaN scores rank as -inf: dropped
-#pragma unroll
-        for (int k = 0; k < KPT; ++k) mx = fmaxf(mx, ((cand >> k) & 1u) ? f[k] : mx);
-        const uint32_t top[1] = {score_key(mx)};
-        unsigned at_bound;
-        block_kth<BLOCK, 1>(top, cand ? 1u : 0u, pl.kprime, pl.kprime >> 2, s.kth, bound, at_bound);
-      }
-    }
-    select_elements<BLOCK, KPT, CAP>(f, cand, bound, pl.kprime, pl.nf_lo, rsel, s,
-                                     [&](int k) { return c0 + k; });
-  }
+  for (int i = pl.take + (int)threadIdx.x; i < sel_stride; i += BLOCK) rsel.pad(i);
+  if (threadIdx.x == 0) rsel.count(nsel, row, pl.take);
+  const M cand = range_bits<KPT>(c0, pl.nf_lo, pl.first_hi);
+  const M forced = range_bits<KPT>(c0, 0, pl.P) & ~cand;
+  select_elements<BLOCK, KPT>(f, cand, forced, c0, pl.nf_lo, pl.first_hi, pl.kprime, s,
+                              [&](int pos, int k) { rsel.put(pos, c0 + k); });
   return pl.take;
 }
 

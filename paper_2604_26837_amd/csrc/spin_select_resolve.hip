@@ -15,7 +15,7 @@ __global__ __launch_bounds__(BLOCK) void spin_select_resolve_kernel(
     const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks, int page_stride, int dir_stride, int leaf_entries,
     int32_t *__restrict__ slots, int32_t *__restrict__ page_ids, uint16_t *__restrict__ valid_mask,
     int32_t *__restrict__ npages, int32_t *status, spin_var var) {
-  __shared__ elements_lds<BLOCK, reg_row_cap<BLOCK, KPT>()> s;
+  __shared__ reg_row_lds<BLOCK> s;
   __shared__ held_row<HELD> s_held;
   const int row = blockIdx.x;
   int32_t mydir;
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(512) void spin_select_resolve_forced_kernel(
                          fa.scale_log2e, fa.part_ml, fa.part_acc, fa.skip);
     return;
   }
-  __shared__ elements_lds<512, reg_row_cap<512, KPT>()> s;
+  __shared__ reg_row_lds<512> s;
   __shared__ held_row<HELD> s_held;
   const int row = blockIdx.x;
   int32_t mydir;
