@@ -812,8 +812,13 @@ def main():
                         pct_peak=round(100 * kv_bytes / (dec_us + side_us) / 1e3 / PEAK_HBM_GBPS, 2),
                         side_bytes=side_bytes, side_us=round(side_us, 3))
         ach = dec_bytes / dec_us / 1e3                                 # GB/s
-        kpt = next(k for k in (4, 8, 16, 32) if max(w.partitions(b) for b in range(w.batch)) <= 512 * k) if fused_24 else 0
-        kernel = f"spin_select_decode_kernel<{kpt}>" if fused_24 else "spin_decode_tokens_kernel<8>" if w.partition_tokens < 16 else \
+        parts = max(w.partitions(b) for b in range(w.batch))
+        # the fused launch's instantiation: scores (beyond 16384 partitions tile maxima) per thread, one-page partitions, tiles
+        tiles = parts > 16384
+        per_thread = next((k for k in (4, 8, 16, 32) if parts <= 512 * k), 8 if parts <= 65536 else 16)
+        kernel = f"spin_select_decode_tokens_kernel<{per_thread}, {str(tiles).lower()}>" if fused_24 and w.partition_tokens < 16 else \
+            f"spin_select_decode_kernel<{per_thread}, {str(w.partition_tokens == 16).lower()}, {str(tiles).lower()}>" if fused_24 else \
+            "spin_decode_tokens_kernel<8>" if w.partition_tokens < 16 else \
             f"spin_decode_kernel<{args.decode_waves or 8}, {args.decode_depth or 2}>"
         traffic, traffic_note = read_traffic(os.path.join(ROOT, "profiles", f"{args.workload}_stage_kernels_pmc.txt"),
                                              kernel)

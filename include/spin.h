@@ -15,7 +15,7 @@
  *   spin_offload_pages                                         Offload's copy, slot -> host page (Table 1)
  *   spin_select_resolve                                        stages 2+3 in one launch, same results
  *   spin_select_resolve_forced, spin_sparse_decode_rest        the same, the sink / recent pages attended beside 2+3
- *   spin_select_resolve_decode                                 stages 2-4 in one launch
+ *   spin_select_resolve_decode, spin_decode_step               stages 2-4 in one launch, stages 1-4 in one call
  *   spin_score_select_topk                                     stages 1+2 in one call, same results
  *   spin_score_select_resolve                                  stages 1-3 in one call, same results
  *   spin_pin_partitions                                        always-attended outlier partitions (Section 4.2)
@@ -372,6 +372,13 @@ int spin_select_resolve_decode(spin_ctx *ctx, int32_t batch, const float *scores
                                uint16_t *valid_mask, int32_t *npages, const void *q, const void *kv_pool,
                                int64_t pool_slots, void *out, float *lse, void *workspace, void *stream);
 int32_t spin_fused_splits(const spin_ctx *ctx);
+/* spin_score_partitions and the above in one call (two launches; rows of more than 16384 partitions are selected from
+ * the maxima that stage 1 takes of its tiles).  Same results, same conditions. */
+int spin_decode_step(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries, const int32_t *chan_idx,
+                     const int32_t *part_offsets, const int32_t *seq_lens, float *scores, int32_t *sel, int32_t *nsel,
+                     const int32_t *dir, const int32_t *leaf_pool, int64_t leaf_chunks, int32_t *slots, int32_t *page_ids,
+                     uint16_t *valid_mask, int32_t *npages, const void *kv_pool, int64_t pool_slots, void *out, float *lse,
+                     void *workspace, void *stream);
 
 /* Buffer elasticity, mechanism only (Section 5.3: buffer pages are reclaimed from
  * the tail of a request's GPU page table).  Sets the slot count of every row to

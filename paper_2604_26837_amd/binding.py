@@ -30,7 +30,7 @@ EXPORTS = [
     "spin_set_partition_tables", "spin_probe_stream_read", "spin_offload_pages", "spin_score_select_topk", "spin_score_select_resolve", "spin_pin_partitions",
     "spin_set_host_page_table", "spin_set_step", "spin_advance_step", "spin_sparse_decode_static",
     "spin_select_resolve_forced", "spin_sparse_decode_rest", "spin_split_hits_misses", "spin_sparse_decode_begin",
-    "spin_sparse_decode_finish", "spin_select_resolve_decode", "spin_fused_splits",
+    "spin_sparse_decode_finish", "spin_select_resolve_decode", "spin_fused_splits", "spin_decode_step",
 ]
 
 
@@ -91,6 +91,7 @@ def load_library() -> C.CDLL:
     lib.spin_sparse_decode.argtypes = [vp, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     lib.spin_sparse_decode_static.argtypes = [vp, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     lib.spin_select_resolve_forced.argtypes = [vp, i32] + [vp] * 7 + [i64] + [vp] * 6 + [i64, vp, vp]
+    lib.spin_decode_step.argtypes = [vp, i32] + [vp] * 9 + [i64] + [vp] * 5 + [i64] + [vp] * 4
     lib.spin_select_resolve_decode.argtypes = [vp, i32] + [vp] * 7 + [i64] + [vp] * 6 + [i64] + [vp] * 4
     lib.spin_split_hits_misses.argtypes = [vp, i32] + [vp] * 8
     lib.spin_sparse_decode_begin.argtypes = [vp, i32, vp, vp, i64, vp, vp, vp, vp, vp]
@@ -372,6 +373,12 @@ class Spin:
         self._check(_call.spin_select_resolve_decode(
             self._ctx, batch, scores, part_offsets, seq_lens, sel, nsel, dir_, leaf_pool, slots, page_ids,
             valid_mask, npages, q, kv_pool, out, lse, ws), "spin_select_resolve_decode")
+
+    def decode_step(self, batch, q, summaries, chan, part_offsets, seq_lens, scores, sel, nsel, dir_, leaf_pool, slots,
+                    page_ids, valid_mask, npages, kv_pool, out, lse, ws):
+        self._check(_call.spin_decode_step(
+            self._ctx, batch, q, summaries, chan, part_offsets, seq_lens, scores, sel, nsel, dir_, leaf_pool, slots,
+            page_ids, valid_mask, npages, kv_pool, out, lse, ws), "spin_decode_step")
 
     def split_hits_misses(self, batch, page_ids, valid_mask, npages, miss_pages, nmiss, mask_hits, mask_misses):
         self._check(_call.spin_split_hits_misses(

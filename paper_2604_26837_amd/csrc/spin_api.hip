@@ -108,18 +108,26 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   }
   x->pstride = splits + (x->side_wgs > 1 ? x->side_wgs : 1);
 
+  // rows beyond 16384 partitions go by the maxima of their score tiles
+  x->tile_log = x->rows_per_part == 4 ? 2 : x->rows_per_part == 2 ? 3 : 4;
+  if (x->max_parts > 16384 && x->max_parts <= 131072 && !c->variable_partitions)
+    x->max_stride = ((cdiv32(x->max_parts, 16) * 16 >> x->tile_log) + 3) & ~3;
+
   // stages 2 to 4 in one launch, where the shape of stage 4's launch is left to the library
   x->fused_splits = 0;
-  if (c->lru_timestamps == 0 && tp >= SPIN_PAGE_TOKENS && !c->variable_partitions && x->max_parts <= 16384 &&
-      x->sel_stride <= SPIN_SEL_HELD && !c->decode_waves && !c->decode_depth && x->max_rows <= 65535 &&
-      spin_fused_lds(x) <= SPIN_FUSED_LDS) {
+  if (c->lru_timestamps == 0 && !c->variable_partitions &&
+      (x->max_parts <= 16384 || (x->max_stride && x->max_stride <= 8192)) && x->sel_stride <= SPIN_SEL_HELD &&
+      !c->decode_waves && !c->decode_depth && x->max_rows <= 65535 && spin_fused_lds(x) <= SPIN_FUSED_LDS) {
     int32_t s = c->decode_splits;
     if (s == 0) {
       s = 256 / x->max_rows;
       // two pages per wavefront (1 / 2 / 4 of them, steps of 8 rows of 8192 pages, 128 attended: 24.3 / 24.3 / 25.7 us),
       // or four where that leaves one workgroup, which has nothing to merge (2 rows of 256, 32 attended: 12.3 us; with
       // two or four workgroups 13.2 / 12.8)
-      const int32_t two = x->page_stride / 16, cap = two <= 2 ? 1 : two;
+      // Partitions smaller than a page: one tile of 16 tokens per wavefront (one / two of them, steps of 8 rows of 65536
+      // tokens, 1024 attended: 24.4 / 25.4 us; 32 rows of 9001, 400 attended: 19.0 / 20.6).
+      const int32_t share = tp < SPIN_PAGE_TOKENS ? (x->sel_stride * tp + 15) / 16 / 8 : x->page_stride / 16;
+      const int32_t cap = share <= 2 ? 1 : share;
       if (s > cap) s = cap;
       if (s < 1) s = 1;
     }
@@ -132,9 +140,7 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   off = (off + 255) & ~(size_t)255;
   x->ws_zero_bytes = off;
   // stage 2 of rows beyond 16384 partitions: the maxima of the rows' score tiles
-  x->tile_log = x->rows_per_part == 4 ? 2 : x->rows_per_part == 2 ? 3 : 4;
-  if (x->max_parts > 16384 && x->max_parts <= 131072 && !c->variable_partitions) {
-    x->max_stride = ((cdiv32(x->max_parts, 16) * 16 >> x->tile_log) + 3) & ~3;
+  if (x->max_stride) {
     x->ws_max_off = off;
     off += (size_t)x->max_rows * x->max_stride * sizeof(float);
     off = (off + 255) & ~(size_t)255;

@@ -18,6 +18,9 @@
                               // tile maxima stays under 64 KiB
 #define SPIN_FUSED_LDS (96 * 1024)   // dynamic LDS the launch that runs stages 2 to 4 may use beside some 25 KiB of its own
 
+#define SPIN_TILES_LDS (54 * 1024)           // scratch of the selection by tile maxima in that launch
+#define SPIN_STEP_TOKENS_LDS (8 * 1024)      // token lists of its 8 wavefronts
+
 #define SPIN_KERNEL_IDS 14
 
 // Variable-length partitions (Section 5.2: the Meta-partition table holds each
@@ -85,9 +88,16 @@ typedef __attribute__((ext_vector_type(4))) short spin_s16x4;
 // uniform partitions of whole pages, rows short enough for the 512-thread selection
 static inline bool spin_forced_split_supported(const spin_ctx *ctx) { return ctx->side_wgs > 0; }
 
-// dynamic LDS of the launch that runs stages 2 to 4: stage 4's merge buffers (8 wavefronts) and the row's page list
+// Dynamic LDS of the launch that runs stages 2 to 4: stage 4's merge buffers (8 wavefronts), which where rows go by their
+// tiles' maxima take the place of the selection's scratch; behind them the row's page list, or (partitions smaller than a
+// page) the wavefronts' token lists and the row's selection.
+static inline size_t spin_fused_front(const spin_ctx *ctx) {
+  const size_t merge = (size_t)8 * ctx->group * (SPIN_HEAD_DIM + 2) * sizeof(float);
+  return ctx->max_parts > 16384 && merge < SPIN_TILES_LDS ? SPIN_TILES_LDS : merge;
+}
 static inline size_t spin_fused_lds(const spin_ctx *ctx) {
-  return (size_t)8 * ctx->group * (SPIN_HEAD_DIM + 2) * sizeof(float) + (size_t)ctx->page_stride * 8;
+  return spin_fused_front(ctx) +
+         (ctx->k_token_major ? SPIN_STEP_TOKENS_LDS + (size_t)ctx->sel_stride * 4 : (size_t)ctx->page_stride * 8);
 }
 
 static inline int spin_launch_status() {
@@ -113,6 +123,8 @@ struct spin_resolve_args {
 // Looks the device address of the library's own scratch array up for the current device (kept per device
 // from then on), so that spin_sparse_decode_static need not do it on its first call.
 int spin_static_scratch_prepare(void);
+// launches the kernel that takes a maximum per score tile (rows <= 65535)
+void spin_take_maxima(spin_ctx *ctx, int rows, const float *scores, const int32_t *part_offsets, float *maxima, void *stream);
 int spin_select_impl(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
                      const int32_t *seq_lens, int32_t *sel, int32_t *nsel, void *workspace, void *stream,
                      bool maxima_ready, const spin_resolve_args *res);

@@ -13,125 +13,6 @@
 
 #define SEL_BLOCK 512
 
-// exclusive prefix sum of one int per thread over the workgroup, plus the total
-template <int BLOCK>
-__device__ inline int block_exclusive_scan(int v, int *s_wave, int &total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int inc = spin_wave_inclusive_scan(v);
-  __syncthreads();  // s_wave may still be read from a previous scan
-  if (lane == 63) s_wave[wave] = inc;
-  __syncthreads();
-  int off = 0, tot = 0;
-#pragma unroll
-  for (int w = 0; w < BLOCK / 64; ++w) {
-    const int x = s_wave[w];
-    if (w < wave) off += x;
-    tot += x;
-  }
-  total = tot;
-  return off + inc - v;
-}
-
-// Rows of any length: every pass re-reads the row's scores.
-template <int BLOCK>
-__device__ inline void select_generic_row(
-    const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
-    const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
-    int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, int row) {
-  __shared__ int s_hist[256];
-  __shared__ int s_wave[BLOCK / 64];
-  __shared__ int s_digit, s_remaining;
-
-  const int b = row / Hkv, h = row - b * Hkv;
-  const int N = seq_lens[b];
-  const int PP = part_offsets[b + 1] - part_offsets[b];
-  const float *rs = scores + (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
-  int32_t *rsel = sel + (size_t)row * sel_stride;
-  const int tid = threadIdx.x;
-  int P = N > 0 ? (N + tp - 1) / tp : 0;
-  if (P > PP) P = PP;
-
-  // forced partitions: a prefix [0, nf_lo) and a suffix [first_hi, P)
-  const int pages = (N + 15) >> 4;
-  int sink_end = min(sink_pages, pages);
-  int recent_begin = max(pages - recent_pages, 0);
-  if (sink_end >= recent_begin) { sink_end = pages; recent_begin = pages; }
-  int nf_lo = (N <= sink_end * 16) ? P : (sink_end * 16) / tp;
-  int first_hi = min((recent_begin * 16 + tp - 1) / tp, P);
-  if (first_hi <= nf_lo) { nf_lo = P; first_hi = P; }
-  const int nforced = nf_lo + (P - first_hi);
-  const int ncand = P - nforced;
-  int kprime = includes_forced ? max(topk - nforced, 0) : topk;
-  kprime = min(kprime, ncand);
-  int take = nforced + kprime;
-  if (take > sel_stride) {   // cannot happen for strides from spin_sel_stride(); keep stores in range
-    kprime = max(sel_stride - nforced, 0);
-    take = min(nforced + kprime, sel_stride);
-  }
-
-  // contiguous chunk of partitions per thread
-  int chunk = (P + BLOCK - 1) / BLOCK;
-  chunk = (chunk + 3) & ~3;
-  const int c0 = min(tid * chunk, P), c1 = min(c0 + chunk, P);
-
-  // ---- radix select of the kprime-th largest candidate key ----
-  uint32_t prefix = 0;
-  int remaining = kprime;   // rank (1-based) of the wanted key among keys matching the prefix
-  if (kprime > 0) {
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      if (tid < 256) s_hist[tid] = 0;
-      __syncthreads();
-      for (int p = c0; p < c1; ++p) {
-        if (p < nf_lo || p >= first_hi) continue;
-        const uint32_t k = score_key(rs[p]);
-        if (shift == 24 || (k >> (shift + 8)) == prefix) atomicAdd(&s_hist[(k >> shift) & 255u], 1);
-      }
-      __syncthreads();
-      // suffix sums over digits: thread t looks at digit 255 - t
-      int cnt = tid < 256 ? s_hist[255 - tid] : 0, total;
-      const int excl = block_exclusive_scan<BLOCK>(cnt, s_wave, total);
-      if (tid < 256 && excl < remaining && excl + cnt >= remaining) {
-        s_digit = 255 - tid;
-        s_remaining = remaining - excl;
-      }
-      __syncthreads();
-      prefix = (prefix << 8) | (uint32_t)s_digit;
-      remaining = s_remaining;
-      __syncthreads();
-    }
-  }
-  const uint32_t T = prefix;
-  const int need_eq = kprime > 0 ? remaining : 0;   // how many candidates with key == T to take
-
-  // ---- index-ordered compaction ----
-  int my_gt = 0, my_eq = 0;
-  for (int p = c0; p < c1; ++p) {
-    if (p < nf_lo || p >= first_hi) { ++my_gt; continue; }
-    if (kprime == 0) continue;
-    const uint32_t k = score_key(rs[p]);
-    my_gt += k > T;
-    my_eq += k == T;
-  }
-  int total_eq, total_sel;
-  const int eq_before = block_exclusive_scan<BLOCK>(my_eq, s_wave, total_eq);
-  int eq_quota = min(max(need_eq - eq_before, 0), my_eq);
-  const int pos0 = block_exclusive_scan<BLOCK>(my_gt + eq_quota, s_wave, total_sel);
-  int pos = pos0;
-  for (int p = c0; p < c1; ++p) {
-    bool pick;
-    if (p < nf_lo || p >= first_hi) pick = true;
-    else if (kprime == 0) pick = false;
-    else {
-      const uint32_t k = score_key(rs[p]);
-      pick = k > T;
-      if (k == T && eq_quota > 0) { pick = true; --eq_quota; }
-    }
-    if (pick && pos < sel_stride) rsel[pos++] = p;
-  }
-  for (int i = take + tid; i < sel_stride; i += BLOCK) rsel[i] = -1;
-  if (tid == 0) nsel[row] = min(total_sel, sel_stride);
-}
-
 __global__ __launch_bounds__(SEL_BLOCK) void spin_select_kernel(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
@@ -177,7 +58,9 @@ __global__ __launch_bounds__(256) void spin_tile_max_kernel(const float *__restr
 // One workgroup per row.  MPT: maxima per thread.  RESOLVE: the workgroup goes on to stage 3 for its row (same device
 // function as the stage call).
 // Latency bounds it: a dependent load each for maxima, scores and leaf entries, about 14 barriers, and whatever every
-// wavefront does for itself.  With a chip-wide histogram of the leading 12 key bits in its place one compute unit
+// wavefront does for itself.  Tiles and listed candidates are chosen by select_elements (8 rows of 62500 and 64 of 65536:
+// as fast as by radix digits here, but it reads no tile too many: 1024 tiles and a slack were two rounds of loads, not
+// one, where 512 threads fetch them).  With a chip-wide histogram of the leading 12 key bits in its place one compute unit
 // walked the row's scores, and rows with many scores in the threshold's bin were searched whole: stages 2+3, 8 rows
 // of 62500, k' = 244: 28.8 -> 12.7 us; 64 rows of 65536, k' = 1024: 22.8 -> 20.0; and stage 1, which counted the
 // histogram in LDS, 42.7 -> 39.5 us on 8 rows of 62500.
@@ -195,31 +78,21 @@ __global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
   [[maybe_unused]] int32_t mydir = 0;
   // (with 32 maxima per thread there is no register to hold it in)
   if (RESOLVE && MPT < 32) mydir = row_dir_entry(ra.dir, dir_stride, row);
-  float4 mine[MPT / 4];
-  load_tile_maxima<MPT>(mine, maxima + (size_t)row * max_stride, max_stride);
-  const int b = row / Hkv, h = row - b * Hkv;
-  const int PP = part_offsets[b + 1] - part_offsets[b];
-  const float *rs = scores + (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
-  const sel_plan pl = select_plan(seq_lens[b], PP, tp, topk, includes_forced, sink_pages, recent_pages, sel_stride);
   const sel_row<HELD> rsel = {sel + (size_t)row * sel_stride, sel_stride, (spin_lds_i32 *)s_held.sel};
-  // (a row that is longer than the context's longest one has no maxima for all its tiles)
-  const bool no_maxima = pl.kprime > 0 && ((pl.P >> gs_log) > min(max_stride, BLOCK * MPT) || pl.P > ROW_PARTS);
-  if (!no_maxima) {
-    emit_forced<BLOCK>(pl, rsel, nsel, row);
-    if (pl.kprime > 0) select_by_tile_maxima<BLOCK, MPT, CAP>(rs, mine, gs_log, pl, rsel, s);
-  } else {
-    select_generic_row<BLOCK>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages,
-                              recent_pages, sel_stride, sel, nsel, row);
-    __syncthreads();
-    if (HELD)
-      for (int i = threadIdx.x; i < pl.take; i += BLOCK) rsel.lds[i] = rsel.out[i];
-  }
+  const int take = select_tiles_row<BLOCK, MPT, CAP, HELD>(scores, maxima, max_stride, gs_log, part_offsets, seq_lens, Hkv, tp, topk,
+                                                           includes_forced, sink_pages, recent_pages, sel, rsel, nsel, row, s);
   if (RESOLVE) {
     if (MPT >= 32) mydir = row_dir_entry(ra.dir, dir_stride, row);
-    resolve_selected<BLOCK>(s_held, rsel, mydir, row, pl.take, sel, seq_lens, ra.dir, ra.leaf_pool, ra.leaf_chunks, Hkv,
+    resolve_selected<BLOCK>(s_held, rsel, mydir, row, take, sel, seq_lens, ra.dir, ra.leaf_pool, ra.leaf_chunks, Hkv,
                             tp, sink_pages, recent_pages, page_stride, dir_stride, leaf_entries, ra.slots, ra.page_ids,
                             ra.valid_mask, ra.npages, status, spin_var{}, nullptr);
   }
+}
+
+void spin_take_maxima(spin_ctx *ctx, int rows, const float *scores, const int32_t *part_offsets, float *maxima, void *stream) {
+  spin_launch(ctx, SPIN_K_SELECT_HIST, spin_tile_max_kernel,
+              dim3((unsigned)((ctx->max_parts + 1023) / 1024), (unsigned)rows), dim3(256), 0, (hipStream_t)stream,
+              scores, part_offsets, ctx->cfg.num_kv_heads, ctx->tile_log, maxima, ctx->max_stride);
 }
 
 int spin_select_impl(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
@@ -237,10 +110,7 @@ int spin_select_impl(spin_ctx *ctx, int32_t batch, const float *scores, const in
   if (by_maxima) {
     float *maxima = (float *)((char *)workspace + ctx->ws_max_off);
     const int stride = ctx->max_stride, gs_log = ctx->tile_log;
-    if (!maxima_ready)
-      spin_launch(ctx, SPIN_K_SELECT_HIST, spin_tile_max_kernel,
-                  dim3((unsigned)((ctx->max_parts + 1023) / 1024), (unsigned)rows), dim3(256), 0, (hipStream_t)stream,
-                  scores, part_offsets, c.num_kv_heads, gs_log, maxima, stride);
+    if (!maxima_ready) spin_take_maxima(ctx, rows, scores, part_offsets, maxima, stream);
 #define SPIN_TILES_LAUNCH1(BLOCK, MPT, RESOLVE, HELD, ARGS)                                                    \
   spin_launch(ctx, SPIN_K_SELECT, spin_select_tiles_kernel<BLOCK, MPT, RESOLVE, HELD>, dim3((unsigned)rows),   \
               dim3(BLOCK), 0, (hipStream_t)stream, scores, (const float *)maxima, stride, gs_log,              \

@@ -1,5 +1,5 @@
 // Stages 2, 3 and 4 in one launch (all-resident mode, uniform partitions of whole pages, rows that fit a workgroup's
-// registers).
+// registers or go by their tiles' maxima).
 //
 // A launch that depends on the one before it starts 2 to 3 us after that one's last wavefront has its result, and the
 // page list goes out to memory and back in between.  Here every workgroup of a row, one per split of stage 4, selects
@@ -8,12 +8,12 @@
 // scores and its leaf entries, on compute units that would have waited.  Whole steps, us, against the launch of stages
 // 2+3 followed by that of stage 4: 128 rows of 2048 pages, 128 attended 52.6 -> 50.2; 24 rows of 512, 64 attended 23.0 ->
 // 20.8; 8 rows of 8192 28.0 -> 24.7; 256 ragged rows of up to 16384 139.5 -> 137.6; 32 rows of 1024 blocks 31.5 -> 30.1;
-// 512 rows of 500 and 1000 83.9 -> 72.4 and 143.5 -> 132.9 (also where the rows are more than the compute units, then).
+// 512 rows of 500 and 1000 83.9 -> 72.4 and 143.5 -> 132.9 (also where the rows are more than the compute units, then);
+// 8 rows of 62500, 256 attended 61.8 -> 58.3.
 //
 // The row's always-attended pages are known before its scores are: each wavefront asks for the first of its own ahead of
 // the selection and attends it when the first selected ones are under way.
-#include "spin_decode_dev.h"
-#include "spin_select_resolve_dev.h"
+#include "spin_step_dev.h"
 
 // the selection goes to LDS; memory has it from the row's first workgroup
 struct step_sel {
@@ -48,35 +48,20 @@ struct step_pages {
   }
 };
 
-struct spin_step_args {
-  const int32_t *leaf_pool;
-  int64_t leaf_chunks;
-  int32_t *sel, *nsel, *slots, *page_ids;
-  uint16_t *valid_mask;
-  int32_t *npages;
-  const uint4 *pool;
-  int64_t pool_slots;
-  uint16_t *out;
-  float *lse, *part_ml, *part_acc;
-  int32_t *tickets, *status;
-  int tp, topk, includes_forced, sink_pages, recent_pages, sel_stride, page_stride, leaf_entries;
-  int leaf_log;                       // log2 of leaf_entries, or -1
-  float scale_log2e;
-};
-
 // The first of this wavefront's always-attended pages, number `first` of the row's: its leaf entry's index and whether there
-// is one.  lane_dir: the row's directory, one entry per lane.
+// is one.  rdir: the row's directory; NULL: lane_dir holds it, one entry per lane.
 struct asked_page {
   int page;
   size_t leaf;
   bool there;
 };
-__device__ __forceinline__ asked_page page_ahead(bool mine, int first, const forced_span &fs, int32_t lane_dir, int dir_stride,
-                                                 int64_t leaf_chunks, int leaf_entries, int leaf_log) {
+__device__ __forceinline__ asked_page page_ahead(bool mine, int first, const forced_span &fs, const int32_t *__restrict__ rdir,
+                                                 int32_t lane_dir, int dir_stride, int64_t leaf_chunks, int leaf_entries,
+                                                 int leaf_log) {
   asked_page p;
   p.page = first < fs.nlo ? first : fs.recent_begin + (first - fs.nlo);
   const int ci = !mine ? 0 : (leaf_log >= 0 ? p.page >> leaf_log : p.page / leaf_entries);
-  const int32_t chunk = __builtin_amdgcn_readlane(lane_dir, ci < dir_stride ? ci : 0);
+  const int32_t chunk = rdir ? rdir[ci < dir_stride ? ci : 0] : __builtin_amdgcn_readlane(lane_dir, ci < dir_stride ? ci : 0);
   p.there = mine && ci < dir_stride && chunk >= 0 && (int64_t)chunk < leaf_chunks;
   p.leaf = p.there ? (size_t)chunk * leaf_entries + (p.page - ci * leaf_entries) : 0;
   return p;
@@ -125,16 +110,18 @@ __device__ __forceinline__ void select_pages(const __amdgpu_buffer_rsrc_t scores
 // grid: splits x KV heads x requests.  PAGES: partitions of one page, 2^leaf_log >= 4 entries to a leaf; the selection is
 // the page list, nothing is divided, a row takes as many scores per thread as its own length asks for, and with up to 8 a
 // page's leaf entry comes with its score.
-template <int KPT, bool PAGES>       // KPT: scores per thread of the longest row
+// TILES: rows beyond a workgroup's registers, selected from their tiles' maxima, KPT of them per thread; otherwise KPT is the
+// scores per thread of the longest row.
+template <int KPT, bool PAGES, bool TILES>
 __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets, const int32_t *__restrict__ seq_lens,
     const int32_t *__restrict__ dir, const uint16_t *__restrict__ q, int Hkv, int nsplit, int G, int Hq, int dir_stride,
     spin_step_args a) {
   constexpr int WAVES = 8, BLOCK = 64 * WAVES;
-  __shared__ reg_row_lds<BLOCK> s;
+  __shared__ typename std::conditional<TILES, int, reg_row_lds<BLOCK>>::type s;
   __shared__ int32_t held_words[PAGES ? RES_DIR_LDS : sizeof(held_row<true>) / sizeof(int32_t)];
   extern __shared__ __align__(16) float smem[];       // the merge buffers of decode_finish, then the row's page list
-  spin_lds_i32 *l_slot = (spin_lds_i32 *)(smem + WAVES * G * (SPIN_HEAD_DIM + 2));
+  spin_lds_i32 *l_slot = (spin_lds_i32 *)(smem + a.lists_at);
   spin_lds_i32 *l_page = l_slot + a.page_stride;      // PAGES: the pages
   spin_lds_u16 *l_mask = (spin_lds_u16 *)l_page;      // otherwise: the masks
   const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z, row = b * Hkv + h;
@@ -146,8 +133,9 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
   // page v goes to split v % nsplit, wavefront (v / nsplit) % WAVES.
   const int first = wave * nsplit + split, stride = WAVES * nsplit;
   const int32_t *rdir = dir + (size_t)row * dir_stride;
-  // the directory one entry per lane (larger ones: no page is asked for ahead)
-  const bool ahead = dir_stride <= 64;
+  // the directory one entry per lane (larger ones: no page is asked for ahead, but by TILES, whose chain is long enough for
+  // the trip to the entry as well)
+  const bool ahead = TILES || dir_stride <= 64;
   const int32_t lane_dir = rdir[min(lane, dir_stride - 1)];
   const int N = max(seq_lens[b], 0);
   const forced_span fs = forced_pages_of(N, a.sink_pages, a.recent_pages);
@@ -171,33 +159,49 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     const int32_t mydir = rdir[min(tid, dir_stride - 1)];
     load_queries(qf, q, b, h, G, Hq, n, c);
     __builtin_amdgcn_sched_barrier(0);
-    // the selection's plan: partitions are pages
-    const int P = min(min((N + 15) >> 4, PP), BLOCK * KPT);
-    const sel_plan pl = plan_of(P, min(fs.nlo, P), min(fs.recent_begin, P), a.topk, a.includes_forced, a.sel_stride);
-    // zeros past the row's end
-    const __amdgpu_buffer_rsrc_t buf = spin_buffer(scores + (size_t)Hkv * off + (size_t)h * PP, (uint32_t)max(PP, 0) * sizeof(float));
-    with_leaf = ahead && P <= 8 * BLOCK;
     auto ask = [&] {
-      ask_ahead(page_ahead(asked, first, fs, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
+      ask_ahead(page_ahead(asked, first, fs, TILES ? rdir : nullptr, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
       if (!with_leaf && tid < RES_DIR_LDS) held_words[tid] = mydir;
     };
-    if (KPT == 4 || P <= 4 * BLOCK) select_pages<BLOCK, 4>(buf, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
-    else if (KPT == 8 || P <= 8 * BLOCK) select_pages<BLOCK, 8>(buf, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
-    else if (KPT == 16 || P <= 16 * BLOCK) select_pages<BLOCK, 16>(buf, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
-    else select_pages<BLOCK, 32>(buf, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
-    np = min(pl.take, a.page_stride);
+    if constexpr (TILES) {
+      ask();
+      const lds_sel rsel = {min(a.sel_stride, a.page_stride), l_page};
+      np = select_tiles_row<BLOCK, KPT, STEP_CAP, true>(scores, a.maxima, a.max_stride, a.gs_log, part_offsets, seq_lens, Hkv,
+                                                        SPIN_PAGE_TOKENS, a.topk, a.includes_forced, a.sink_pages,
+                                                        a.recent_pages, a.sel, rsel, a.nsel, row, *(step_tiles_lds *)smem);
+    } else {
+      // the selection's plan: partitions are pages
+      const int P = min(min((N + 15) >> 4, PP), BLOCK * KPT);
+      const sel_plan pl = plan_of(P, min(fs.nlo, P), min(fs.recent_begin, P), a.topk, a.includes_forced, a.sel_stride);
+      // zeros past the row's end
+      const __amdgpu_buffer_rsrc_t buf = spin_buffer(scores + (size_t)Hkv * off + (size_t)h * PP, (uint32_t)max(PP, 0) * sizeof(float));
+      with_leaf = ahead && P <= 8 * BLOCK;
+      if (KPT == 4 || P <= 4 * BLOCK) select_pages<BLOCK, 4>(buf, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+      else if (KPT == 8 || P <= 8 * BLOCK) select_pages<BLOCK, 8>(buf, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+      else if (KPT == 16 || P <= 16 * BLOCK) select_pages<BLOCK, 16>(buf, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+      else select_pages<BLOCK, 32>(buf, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+      np = min(pl.take, a.page_stride);
+    }
   } else {
     load_queries(qf, q, b, h, G, Hq, n, c);
     held_row<true> &s_held = *(held_row<true> *)held_words;
     int32_t mydir;
     const step_sel rsel = {a.sel + (size_t)row * a.sel_stride, a.sel_stride, (spin_lds_i32 *)s_held.sel, store};
-    spin_var_span span;                // (uniform partitions)
-    const int take = select_reg_row<BLOCK, KPT>(
-        scores, part_offsets, seq_lens, Hkv, a.tp, a.topk, a.includes_forced, a.sink_pages, a.recent_pages, rsel, a.nsel, row,
-        spin_var{}, span, s, [&] {
-          mydir = row_dir_entry(dir, dir_stride, row);
-          ask_ahead(page_ahead(asked, first, fs, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
-        });
+    auto ask = [&] {
+      mydir = row_dir_entry(dir, dir_stride, row);
+      ask_ahead(page_ahead(asked, first, fs, TILES ? rdir : nullptr, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
+    };
+    int take;
+    if constexpr (TILES) {
+      ask();
+      take = select_tiles_row<BLOCK, KPT, STEP_CAP, true>(scores, a.maxima, a.max_stride, a.gs_log, part_offsets, seq_lens, Hkv,
+                                                          a.tp, a.topk, a.includes_forced, a.sink_pages, a.recent_pages,
+                                                          a.sel, rsel, a.nsel, row, *(step_tiles_lds *)smem);
+    } else {
+      spin_var_span span;              // (uniform partitions)
+      take = select_reg_row<BLOCK, KPT>(scores, part_offsets, seq_lens, Hkv, a.tp, a.topk, a.includes_forced, a.sink_pages,
+                                        a.recent_pages, rsel, a.nsel, row, spin_var{}, span, s, ask);
+    }
     if (tid < RES_DIR_LDS) s_held.dir[tid] = mydir;
     __syncthreads();                   // the selection and the directory are whole
     if (store)
@@ -273,11 +277,13 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
                        a.lse);
 }
 
-extern "C" int spin_select_resolve_decode(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
-                                          const int32_t *seq_lens, int32_t *sel, int32_t *nsel, const int32_t *dir,
-                                          const int32_t *leaf_pool, int64_t leaf_chunks, int32_t *slots, int32_t *page_ids,
-                                          uint16_t *valid_mask, int32_t *npages, const void *q, const void *kv_pool,
-                                          int64_t pool_slots, void *out, float *lse, void *workspace, void *stream) {
+// maxima_ready: stage 1 of this step has left its tiles' maxima in the workspace
+static int select_resolve_decode_impl(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
+                                      const int32_t *seq_lens, int32_t *sel, int32_t *nsel, const int32_t *dir,
+                                      const int32_t *leaf_pool, int64_t leaf_chunks, int32_t *slots, int32_t *page_ids,
+                                      uint16_t *valid_mask, int32_t *npages, const void *q, const void *kv_pool,
+                                      int64_t pool_slots, void *out, float *lse, void *workspace, void *stream,
+                                      bool maxima_ready) {
   if (!ctx || batch < 0 || batch > ctx->cfg.max_batch || leaf_chunks <= 0 || pool_slots <= 0) return SPIN_ERR_INVALID;
   if (ctx->fused_splits == 0 || ctx->var.count) return SPIN_ERR_UNSUPPORTED;
   if (batch == 0) return SPIN_OK;
@@ -288,28 +294,70 @@ extern "C" int spin_select_resolve_decode(spin_ctx *ctx, int32_t batch, const fl
   const spin_config &c = ctx->cfg;
   char *ws = (char *)workspace;
   const int leaf_log = (c.leaf_entries & (c.leaf_entries - 1)) ? -1 : 31 - __builtin_clz((unsigned)c.leaf_entries);
+  const bool tiles = ctx->max_parts > 16384;
+  float *maxima = tiles ? (float *)(ws + ctx->ws_max_off) : nullptr;
+  if (tiles && !maxima_ready) spin_take_maxima(ctx, batch * c.num_kv_heads, scores, part_offsets, maxima, stream);
   const spin_step_args a = {leaf_pool, leaf_chunks, sel, nsel, slots, page_ids, valid_mask, npages, (const uint4 *)kv_pool,
                             pool_slots, (uint16_t *)out, lse, (float *)(ws + ctx->ws_ml_off),
                             (float *)(ws + ctx->ws_acc_off), (int32_t *)(ws + ctx->ws_ticket_off), (int32_t *)workspace,
                             c.partition_tokens, c.topk, c.topk_includes_forced, c.sink_pages, c.recent_pages,
-                            ctx->sel_stride, ctx->page_stride, c.leaf_entries, leaf_log, ctx->scale * 1.4426950408889634f};
-#define SPIN_SD_LAUNCH1(KPT, PAGES)                                                                               \
-  spin_launch(ctx, SPIN_K_SELECT_DECODE, spin_select_decode_kernel<KPT, PAGES>,                                   \
+                            ctx->sel_stride, ctx->page_stride, c.leaf_entries, leaf_log,
+                            (int)(spin_fused_front(ctx) / sizeof(float)), maxima, ctx->max_stride, ctx->tile_log,
+                            ctx->scale * 1.4426950408889634f};
+  if (ctx->k_token_major) return spin_step_tokens_launch(ctx, batch, scores, part_offsets, seq_lens, dir, q, a, stream);
+#define SPIN_SD_LAUNCH1(KPT, PAGES, TILES)                                                                        \
+  spin_launch(ctx, SPIN_K_SELECT_DECODE, spin_select_decode_kernel<KPT, PAGES, TILES>,                            \
               dim3((unsigned)ctx->fused_splits, (unsigned)c.num_kv_heads, (unsigned)batch), dim3(512), spin_fused_lds(ctx), \
               (hipStream_t)stream, scores, part_offsets, seq_lens, dir, (const uint16_t *)q, c.num_kv_heads,      \
               ctx->fused_splits, ctx->group, c.num_q_heads, ctx->dir_stride, a)
-#define SPIN_SD_LAUNCH(KPT)                                                            \
-  do {                                                                                 \
-    if (c.partition_tokens == SPIN_PAGE_TOKENS && leaf_log >= 2) SPIN_SD_LAUNCH1(KPT, true); \
-    else SPIN_SD_LAUNCH1(KPT, false);                                                  \
+#define SPIN_SD_LAUNCH(KPT, TILES)                                                                \
+  do {                                                                                            \
+    if (c.partition_tokens == SPIN_PAGE_TOKENS && leaf_log >= 2) SPIN_SD_LAUNCH1(KPT, true, TILES); \
+    else SPIN_SD_LAUNCH1(KPT, false, TILES);                                                      \
   } while (0)
-  if (ctx->max_parts <= 2048) SPIN_SD_LAUNCH(4);
-  else if (ctx->max_parts <= 4096) SPIN_SD_LAUNCH(8);
-  else if (ctx->max_parts <= 8192) SPIN_SD_LAUNCH(16);
-  else SPIN_SD_LAUNCH(32);
+  if (ctx->max_parts <= 2048) SPIN_SD_LAUNCH(4, false);
+  else if (ctx->max_parts <= 4096) SPIN_SD_LAUNCH(8, false);
+  else if (ctx->max_parts <= 8192) SPIN_SD_LAUNCH(16, false);
+  else if (!tiles) SPIN_SD_LAUNCH(32, false);
+  else if (ctx->max_stride <= 4096) SPIN_SD_LAUNCH(8, true);
+  else SPIN_SD_LAUNCH(16, true);
 #undef SPIN_SD_LAUNCH1
 #undef SPIN_SD_LAUNCH
   return spin_launch_status();
+}
+
+extern "C" int spin_select_resolve_decode(spin_ctx *ctx, int32_t batch, const float *scores, const int32_t *part_offsets,
+                                          const int32_t *seq_lens, int32_t *sel, int32_t *nsel, const int32_t *dir,
+                                          const int32_t *leaf_pool, int64_t leaf_chunks, int32_t *slots, int32_t *page_ids,
+                                          uint16_t *valid_mask, int32_t *npages, const void *q, const void *kv_pool,
+                                          int64_t pool_slots, void *out, float *lse, void *workspace, void *stream) {
+  return select_resolve_decode_impl(ctx, batch, scores, part_offsets, seq_lens, sel, nsel, dir, leaf_pool, leaf_chunks,
+                                    slots, page_ids, valid_mask, npages, q, kv_pool, pool_slots, out, lse, workspace,
+                                    stream, false);
+}
+
+// Stages 1 to 4 in one call, two launches: stage 1 (for rows of more than 16384 partitions with its tiles' maxima), then
+// the above.
+extern "C" int spin_decode_step(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries, const int32_t *chan_idx,
+                                const int32_t *part_offsets, const int32_t *seq_lens, float *scores, int32_t *sel,
+                                int32_t *nsel, const int32_t *dir, const int32_t *leaf_pool, int64_t leaf_chunks,
+                                int32_t *slots, int32_t *page_ids, uint16_t *valid_mask, int32_t *npages,
+                                const void *kv_pool, int64_t pool_slots, void *out, float *lse, void *workspace,
+                                void *stream) {
+  // refuse before stage 1 is issued what the second launch would refuse
+  if (!ctx || batch < 0 || batch > ctx->cfg.max_batch || leaf_chunks <= 0 || pool_slots <= 0) return SPIN_ERR_INVALID;
+  if (ctx->fused_splits == 0 || ctx->var.count) return SPIN_ERR_UNSUPPORTED;
+  if (batch == 0) return SPIN_OK;
+  if (!sel || !nsel || !dir || !leaf_pool || !slots || !page_ids || !valid_mask || !npages || !kv_pool || !out)
+    return SPIN_ERR_INVALID;
+  if (!workspace) return SPIN_ERR_WORKSPACE;
+  const bool tiles = ctx->max_parts > 16384;
+  const int st = spin_score_impl(ctx, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, workspace, stream,
+                                 tiles ? (float *)((char *)workspace + ctx->ws_max_off) : nullptr);
+  if (st != SPIN_OK) return st;
+  return select_resolve_decode_impl(ctx, batch, scores, part_offsets, seq_lens, sel, nsel, dir, leaf_pool, leaf_chunks,
+                                    slots, page_ids, valid_mask, npages, q, kv_pool, pool_slots, out, lse, workspace,
+                                    stream, true);
 }
 
 extern "C" int32_t spin_fused_splits(const spin_ctx *c) { return c ? c->fused_splits : 0; }

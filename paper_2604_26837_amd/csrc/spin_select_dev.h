@@ -265,52 +265,6 @@ __device__ inline float key_floor_score(uint32_t K, bool low_end) {
 }
 #define SPIN_KEY_MINUS_INF 0x007fffffu
 
-// the candidates that are left, in partition order
-template <int BLOCK, int CAP>
-struct elements_lds {
-  kth_lds<BLOCK> kth;
-  uint2 wtot[BLOCK / 64];
-  uint32_t key[CAP];
-  int32_t id[CAP];
-};
-
-// The kprime best of the `total` entries of an ordered list in LDS, stored ascending at rsel[first ..].
-template <int BLOCK, int CAP, typename ROW>
-__device__ __forceinline__ void pick_from_list(int total, int kprime, int first, const ROW &rsel,
-                                      elements_lds<BLOCK, CAP> &s) {
-  const int tid = threadIdx.x;
-  auto pick_list = [&](auto entries) {
-    constexpr int E = decltype(entries)::value;  // list entries per thread
-    uint32_t T;
-    unsigned need_eq;
-    uint32_t key[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) key[j] = tid * E + j < total ? s.key[tid * E + j] : 0u;
-    const uint32_t have = range_bits<E>(tid * E, 0, total);
-    block_kth<BLOCK, E>(key, have, kprime, 0, s.kth, T, need_eq);
-    uint32_t gt = 0, eq = 0;
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      gt |= key[j] > T ? 1u << j : 0u;
-      eq |= key[j] == T ? 1u << j : 0u;
-    }
-    int pos, picked, eq_picked;
-    uint32_t pick = ordered_picks<BLOCK>(gt & have, eq & have, need_eq, s.wtot, pos, picked, eq_picked);
-    pos += first;
-#pragma unroll
-    for (int j = 0; j < E; ++j)
-      if ((pick >> j) & 1u) {
-        rsel.put(pos, s.id[tid * E + j]);
-        ++pos;
-      }
-  };
-  constexpr int LPT = CAP / BLOCK;
-  if (total <= BLOCK) pick_list(std::integral_constant<int, 1>());
-  else if (LPT > 2 && total <= 2 * BLOCK) pick_list(std::integral_constant<int, 2>());
-  else if (LPT > 4 && total <= 4 * BLOCK) pick_list(std::integral_constant<int, 4>());
-  else pick_list(std::integral_constant<int, LPT>());
-}
-
 // ---------------------------------------------------------------------------
 // Rows whose scores a workgroup holds in registers.
 #define TAIL_BINS 512
@@ -685,7 +639,12 @@ __device__ __forceinline__ int select_reg_row(
 #define ROW_BINS 4096
 #define ROW_LIST 2048
 template <int BLOCK, int CAP>
-struct tiles_lds : elements_lds<BLOCK, CAP> {
+struct tiles_lds {
+  reg_row_lds<BLOCK> row;
+  uint2 wtot[BLOCK / 64];
+  float least[BLOCK / 64];
+  alignas(16) float score[CAP];   // the candidates that are left, in partition order
+  int32_t id[CAP];
   uint16_t tile[TILE_LIST];
 };
 // LDS of select_whole_row
@@ -867,35 +826,33 @@ __device__ __forceinline__ void select_whole_row(const float *__restrict__ rs, u
 }
 
 // False (for the whole workgroup, nothing stored): more scores than the list holds.
+// `top`: the calling thread's MPT maxima, `cand` those of tiles of candidates only.
 template <int BLOCK, int MPT, int CAP, typename ROW>
-__device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs, const uint32_t (&top)[MPT],
+__device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs, float (&top)[MPT],
                                            typename key_bits<MPT>::type cand, int t_lo, int t_hi, int gs_log,
                                            const sel_plan &pl, const ROW &rsel, tiles_lds<BLOCK, CAP> &s) {
   constexpr int NW = BLOCK / 64;
-  typedef typename key_bits<MPT>::type M;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gs = 1 << gs_log, kprime = pl.kprime, m0 = tid * MPT;
-  uint32_t T0 = 0;
-  unsigned need_eq = 0;
-  if (t_hi - t_lo >= kprime) block_kth<BLOCK, MPT>(top, cand, kprime, kprime >> 3, s.kth, T0, need_eq);
   // ascending list of the tiles to read, the one that straddles either end of the candidates among them (both
   // ends in one tile: that one)
   const int has_lo = (pl.nf_lo & (gs - 1)) ? 1 : 0, has_hi = (pl.first_hi & (gs - 1)) && t_hi >= t_lo ? 1 : 0;
-  M gt = 0, eq = 0;
+  const bool bound = t_hi - t_lo >= kprime;            // uniform
+  int ntiles = has_lo + (bound ? kprime : max(t_hi - t_lo, 0));
+  float least = __builtin_inff();
+  if (bound) {
+    select_elements<BLOCK, MPT>(top, cand, 0, m0, t_lo, t_hi, kprime, s.row, [&](int pos, int k) {
+      if (has_lo + pos < TILE_LIST) s.tile[has_lo + pos] = (uint16_t)(m0 + k);
+      float f = top[0];                                // (k is no constant where a thread has many)
 #pragma unroll
-  for (int j = 0; j < MPT; ++j) {
-    gt |= top[j] > T0 ? (M)1 << j : (M)0;
-    eq |= top[j] == T0 ? (M)1 << j : (M)0;
-  }
-  int pos, ntiles, eq_tiles;
-  M pick = ordered_picks<BLOCK>((M)(gt & cand), (M)(eq & cand), need_eq, s.wtot, pos, ntiles, eq_tiles);
-  ntiles += has_lo;
-  pos += has_lo;
-  while (pick) {
-    const int j = ffs_bits(pick) - 1;
-    pick &= pick - 1;
-    if (pos < TILE_LIST) s.tile[pos] = (uint16_t)(m0 + j);
-    ++pos;
+      for (int j = 1; j < MPT; ++j) f = k == j ? top[j] : f;
+      least = fminf(least, f);
+    });
+    least = -spin_wave_max(-least);
+    if (lane == 0) s.least[wave] = least;
+  } else {
+    for (int t = t_lo + tid; t < t_hi; t += BLOCK)
+      if (has_lo + t - t_lo < TILE_LIST) s.tile[has_lo + t - t_lo] = (uint16_t)t;
   }
   if (tid == 0) {
     if (has_lo) s.tile[0] = (uint16_t)(t_lo - 1);
@@ -903,8 +860,8 @@ __device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs
   }
   ntiles = min(ntiles + has_hi, TILE_LIST);
   __syncthreads();
-  const bool all = T0 <= SPIN_KEY_MINUS_INF;           // (NaN scores rank at -inf and would fail the comparison)
-  const float bf = key_floor_score(T0, true);
+  const float bf = bound ? -spin_wave_max(-s.least[lane % NW]) : -__builtin_inff();
+  const bool all = bf == -__builtin_inff();            // (NaN scores rank at -inf and would fail the comparison)
   const int q_log = gs_log - 2, nquads = ntiles << q_log;
   // Four scores (a quad) per lane and load, neighbouring lanes neighbouring quads: a wavefront's load touches as few
   // lines as there are, which matters because the one compute unit that fetches k' scattered lines is bound by them
@@ -967,7 +924,7 @@ __device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if ((keep[j] >> e) & 1u) {
-            s.key[to] = score_key(f[e]);
+            s.score[to] = f[e];
             s.id[to] = p[j] + e;
             ++to;
           }
@@ -978,9 +935,23 @@ __device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs
   // loads per lane: a quad that is not there costs as many instructions as one that is
   if (nquads <= BLOCK * 3) gather(std::integral_constant<int, 3>());
   else if (nquads <= BLOCK * 5) gather(std::integral_constant<int, 5>());
-  else gather(std::integral_constant<int, 8>());
+  else gather(std::integral_constant<int, 9>());
   if (total > CAP) return false;
-  pick_from_list<BLOCK, CAP>(total, kprime, pl.nf_lo, rsel, s);
+  auto pick = [&](auto entries) {
+    constexpr int E = decltype(entries)::value;        // list entries per thread
+    const int c0 = tid * E;
+    float f[E];
+#pragma unroll
+    for (int j = 0; j < E; j += 4) {                   // (what lies past the list's end is masked)
+      const float4 v = *(const float4 *)(s.score + c0 + j);
+      f[j] = v.x; f[j + 1] = v.y; f[j + 2] = v.z; f[j + 3] = v.w;
+    }
+    select_elements<BLOCK, E>(f, range_bits<E>(c0, 0, total), 0, c0, 0, total, kprime, s.row,
+                              [&](int pos, int k) { rsel.put(pl.nf_lo + pos, s.id[c0 + k]); });
+  };
+  static_assert(CAP / BLOCK == 4 || CAP / BLOCK == 8, "one or two quads per thread");
+  if (CAP == 4 * BLOCK || total <= 4 * BLOCK) pick(std::integral_constant<int, 4>());
+  else pick(std::integral_constant<int, CAP / BLOCK>());
   return true;
 }
 
@@ -1004,39 +975,181 @@ __device__ __forceinline__ void select_by_tile_maxima(const float *__restrict__ 
   const int gs = 1 << gs_log, kprime = pl.kprime;
   const int t_lo = (pl.nf_lo + gs - 1) >> gs_log, t_hi = pl.first_hi >> gs_log;   // tiles of candidates only
   const int m0 = tid * MPT;
-  uint32_t top[MPT];
+  float top[MPT];
 #pragma unroll
   for (int j = 0; j < MPT / 4; ++j) {
-    top[4 * j] = score_key(maxima[j].x);
-    top[4 * j + 1] = score_key(maxima[j].y);
-    top[4 * j + 2] = score_key(maxima[j].z);
-    top[4 * j + 3] = score_key(maxima[j].w);
+    top[4 * j] = maxima[j].x; top[4 * j + 1] = maxima[j].y; top[4 * j + 2] = maxima[j].z; top[4 * j + 3] = maxima[j].w;
   }
   const M cand = range_bits<MPT>(m0, t_lo, t_hi);
   // Scores above the bound: all candidates where there is none, else a share of 1 - k'/T of the T tiles holds none, so
-  // that there are about T ln(T / (T - k')) where scores come in no order (k' with the search's slack).
-  const int T = t_hi - t_lo, most = kprime + (kprime >> 3);
+  // that there are about T ln(T / (T - k')) where scores come in no order.
+  const int T = t_hi - t_lo;
   const bool whole = pl.first_hi - pl.nf_lo > CAP &&                               // block-uniform
-      (most >= T || most + 2 > TILE_LIST ||
-       (float)T * (__builtin_amdgcn_logf((float)T) - __builtin_amdgcn_logf((float)(T - most))) > CAP * 1.4427f);
-  if (whole) {
-    uint32_t kmx = 0u, kmn = 0xffffffffu;
+      (kprime >= T || kprime + 2 > TILE_LIST ||
+       (float)T * (__builtin_amdgcn_logf((float)T) - __builtin_amdgcn_logf((float)(T - kprime))) > CAP * 1.4427f);
+  if (!whole && list_by_tile_maxima<BLOCK, MPT, CAP>(rs, top, cand, t_lo, t_hi, gs_log, pl, rsel, s)) return;
+  // from the least to the greatest of the tiles' maxima; the candidates of the tiles that straddle either end may be greater
+  uint32_t kmx = 0u, kmn = 0xffffffffu;
 #pragma unroll
-    for (int j = 0; j < MPT; ++j)
-      if ((cand >> j) & 1u) { kmx = max(kmx, top[j]); kmn = min(kmn, top[j]); }
-    kmx = spin_wave_max_u32(kmx);
-    kmn = spin_wave_min_u32(kmn);
-    if (lane == 0) { s.kth.wmax[wave] = kmx; s.kth.wmin[wave] = kmn; }
-  } else if (list_by_tile_maxima<BLOCK, MPT, CAP>(rs, top, cand, t_lo, t_hi, gs_log, pl, rsel, s)) {
-    return;
-  }
+  for (int j = 0; j < MPT; ++j)
+    if ((cand >> j) & 1u) { kmx = max(kmx, score_key(top[j])); kmn = min(kmn, score_key(top[j])); }
+  kmx = spin_wave_max_u32(kmx);
+  kmn = spin_wave_min_u32(kmn);
+  __syncthreads();                                     // (the list's scratch may still be read)
+  if (lane == 0) s.wtot[wave] = make_uint2(kmx, kmn);
   __syncthreads();
-  // from the least to the greatest of the tiles' maxima, which block_kth leaves in LDS as well; the candidates of the
-  // tiles that straddle either end may be greater
-  uint32_t kmx = spin_wave_max_u32(s.kth.wmax[lane % NW]);
-  const uint32_t kmn = spin_wave_min_u32(s.kth.wmin[lane % NW]);
+  kmx = spin_wave_max_u32(s.wtot[lane % NW].x);
+  kmn = spin_wave_min_u32(s.wtot[lane % NW].y);
   const int p = ((lane & 16 ? t_hi : t_lo - 1) << gs_log) + (lane & (gs - 1));
   kmx = max(kmx, spin_wave_max_u32(p >= pl.nf_lo && p < pl.first_hi ? score_key(rs[p]) : 0u));
   __syncthreads();
   select_whole_row<BLOCK>(rs, min(kmn, kmx), kmx + 1, pl, rsel, lds.row);
+}
+
+// exclusive prefix sum of one int per thread over the workgroup, plus the total
+template <int BLOCK>
+__device__ inline int block_exclusive_scan(int v, int *s_wave, int &total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int inc = spin_wave_inclusive_scan(v);
+  __syncthreads();  // s_wave may still be read from a previous scan
+  if (lane == 63) s_wave[wave] = inc;
+  __syncthreads();
+  int off = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < BLOCK / 64; ++w) {
+    const int x = s_wave[w];
+    if (w < wave) off += x;
+    tot += x;
+  }
+  total = tot;
+  return off + inc - v;
+}
+
+// Rows of any length: every pass re-reads the row's scores.
+template <int BLOCK>
+__device__ inline void select_generic_row(
+    const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
+    const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
+    int recent_pages, int sel_stride, int32_t *__restrict__ sel, int32_t *__restrict__ nsel, int row) {
+  __shared__ int s_hist[256];
+  __shared__ int s_wave[BLOCK / 64];
+  __shared__ int s_digit, s_remaining;
+
+  const int b = row / Hkv, h = row - b * Hkv;
+  const int N = seq_lens[b];
+  const int PP = part_offsets[b + 1] - part_offsets[b];
+  const float *rs = scores + (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
+  int32_t *rsel = sel + (size_t)row * sel_stride;
+  const int tid = threadIdx.x;
+  int P = N > 0 ? (N + tp - 1) / tp : 0;
+  if (P > PP) P = PP;
+
+  // forced partitions: a prefix [0, nf_lo) and a suffix [first_hi, P)
+  const int pages = (N + 15) >> 4;
+  int sink_end = min(sink_pages, pages);
+  int recent_begin = max(pages - recent_pages, 0);
+  if (sink_end >= recent_begin) { sink_end = pages; recent_begin = pages; }
+  int nf_lo = (N <= sink_end * 16) ? P : (sink_end * 16) / tp;
+  int first_hi = min((recent_begin * 16 + tp - 1) / tp, P);
+  if (first_hi <= nf_lo) { nf_lo = P; first_hi = P; }
+  const int nforced = nf_lo + (P - first_hi);
+  const int ncand = P - nforced;
+  int kprime = includes_forced ? max(topk - nforced, 0) : topk;
+  kprime = min(kprime, ncand);
+  int take = nforced + kprime;
+  if (take > sel_stride) {   // cannot happen for strides from spin_sel_stride(); keep stores in range
+    kprime = max(sel_stride - nforced, 0);
+    take = min(nforced + kprime, sel_stride);
+  }
+
+  // contiguous chunk of partitions per thread
+  int chunk = (P + BLOCK - 1) / BLOCK;
+  chunk = (chunk + 3) & ~3;
+  const int c0 = min(tid * chunk, P), c1 = min(c0 + chunk, P);
+
+  // ---- radix select of the kprime-th largest candidate key ----
+  uint32_t prefix = 0;
+  int remaining = kprime;   // rank (1-based) of the wanted key among keys matching the prefix
+  if (kprime > 0) {
+    for (int shift = 24; shift >= 0; shift -= 8) {
+      if (tid < 256) s_hist[tid] = 0;
+      __syncthreads();
+      for (int p = c0; p < c1; ++p) {
+        if (p < nf_lo || p >= first_hi) continue;
+        const uint32_t k = score_key(rs[p]);
+        if (shift == 24 || (k >> (shift + 8)) == prefix) atomicAdd(&s_hist[(k >> shift) & 255u], 1);
+      }
+      __syncthreads();
+      // suffix sums over digits: thread t looks at digit 255 - t
+      int cnt = tid < 256 ? s_hist[255 - tid] : 0, total;
+      const int excl = block_exclusive_scan<BLOCK>(cnt, s_wave, total);
+      if (tid < 256 && excl < remaining && excl + cnt >= remaining) {
+        s_digit = 255 - tid;
+        s_remaining = remaining - excl;
+      }
+      __syncthreads();
+      prefix = (prefix << 8) | (uint32_t)s_digit;
+      remaining = s_remaining;
+      __syncthreads();
+    }
+  }
+  const uint32_t T = prefix;
+  const int need_eq = kprime > 0 ? remaining : 0;   // how many candidates with key == T to take
+
+  // ---- index-ordered compaction ----
+  int my_gt = 0, my_eq = 0;
+  for (int p = c0; p < c1; ++p) {
+    if (p < nf_lo || p >= first_hi) { ++my_gt; continue; }
+    if (kprime == 0) continue;
+    const uint32_t k = score_key(rs[p]);
+    my_gt += k > T;
+    my_eq += k == T;
+  }
+  int total_eq, total_sel;
+  const int eq_before = block_exclusive_scan<BLOCK>(my_eq, s_wave, total_eq);
+  int eq_quota = min(max(need_eq - eq_before, 0), my_eq);
+  const int pos0 = block_exclusive_scan<BLOCK>(my_gt + eq_quota, s_wave, total_sel);
+  int pos = pos0;
+  for (int p = c0; p < c1; ++p) {
+    bool pick;
+    if (p < nf_lo || p >= first_hi) pick = true;
+    else if (kprime == 0) pick = false;
+    else {
+      const uint32_t k = score_key(rs[p]);
+      pick = k > T;
+      if (k == T && eq_quota > 0) { pick = true; --eq_quota; }
+    }
+    if (pick && pos < sel_stride) rsel[pos++] = p;
+  }
+  for (int i = take + tid; i < sel_stride; i += BLOCK) rsel[i] = -1;
+  if (tid == 0) nsel[row] = min(total_sel, sel_stride);
+}
+
+// Selects a row of at most ROW_PARTS partitions from its scores and their tiles' maxima; returns the selection's length.
+// HELD: `rsel` keeps the selection in LDS and the caller stores it.  (A row that is longer than the context's longest one
+// has no maxima for all its tiles: its selection goes through `sel` in memory.)
+template <int BLOCK, int MPT, int CAP, bool HELD, typename ROW>
+__device__ __forceinline__ int select_tiles_row(
+    const float *__restrict__ scores, const float *__restrict__ maxima, int max_stride, int gs_log,
+    const int32_t *__restrict__ part_offsets, const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk,
+    int includes_forced, int sink_pages, int recent_pages, int32_t *sel, const ROW &rsel, int32_t *__restrict__ nsel,
+    int row, tiles_row_lds<BLOCK, CAP> &s) {
+  float4 mine[MPT / 4];
+  load_tile_maxima<MPT>(mine, maxima + (size_t)row * max_stride, max_stride);
+  const int b = row / Hkv, h = row - b * Hkv;
+  const int PP = part_offsets[b + 1] - part_offsets[b];
+  const float *rs = scores + (size_t)Hkv * part_offsets[b] + (size_t)h * PP;
+  const sel_plan pl = select_plan(seq_lens[b], PP, tp, topk, includes_forced, sink_pages, recent_pages, rsel.stride);
+  const bool no_maxima = pl.kprime > 0 && ((pl.P >> gs_log) > min(max_stride, BLOCK * MPT) || pl.P > ROW_PARTS);
+  if (!no_maxima) {
+    emit_forced<BLOCK>(pl, rsel, nsel, row);
+    if (pl.kprime > 0) select_by_tile_maxima<BLOCK, MPT, CAP>(rs, mine, gs_log, pl, rsel, s);
+  } else {
+    select_generic_row<BLOCK>(scores, part_offsets, seq_lens, Hkv, tp, topk, includes_forced, sink_pages, recent_pages,
+                              rsel.stride, sel, nsel, row);
+    __syncthreads();
+    if (HELD)
+      for (int i = threadIdx.x; i < pl.take; i += BLOCK) rsel.put(i, sel[(size_t)row * rsel.stride + i]);
+  }
+  return pl.take;
 }

@@ -148,10 +148,9 @@ class LayerState:
         selection."""
         sp, w = self.spin, self.w
         summ = self.summaries if summaries is None else summaries
-        sp.score_partitions(w.batch, q, summ, self.chan, self.part_offsets, self.seq_lens, self.scores, self.ws)
-        sp.select_resolve_decode(w.batch, self.scores, self.part_offsets, self.seq_lens, self.sel, self.nsel, self.dir,
-                                 self.leaf_pool, self.slots, self.page_ids, self.valid_mask, self.npages, q,
-                                 self.kv_pool, self.out, self.lse, self.ws)
+        sp.decode_step(w.batch, q, summ, self.chan, self.part_offsets, self.seq_lens, self.scores, self.sel, self.nsel,
+                       self.dir, self.leaf_pool, self.slots, self.page_ids, self.valid_mask, self.npages, self.kv_pool,
+                       self.out, self.lse, self.ws)
 
     def step_fused(self, q: torch.Tensor, summaries: Optional[torch.Tensor] = None):
         """The step in as few launches as the context allows (what ``bench.py`` times): stage 1, then stages 2-4 in

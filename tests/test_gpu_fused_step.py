@@ -62,8 +62,52 @@ def test_equals_the_stage_calls(kw, splits):
 
 
 @pytest.mark.gpu
-def test_scores_that_tie_or_are_not_finite():
-    layer, _ = runner.build_device_layer(_workload((30000, 8000), topk=64))
+@pytest.mark.parametrize("kw", [
+    dict(lens=(1, 15, 16, 17, 33, 100, 512), topk=40),                # rows as short as the windows; 1 to 3 tiles
+    dict(lens=(2048, 2047, 700), topk=128, sink=0, recent=0),         # 4 scores per thread
+    dict(lens=(4096, 3001), topk=300),                                # 8
+    dict(lens=(8192, 5000), topk=1025, sink=1, recent=2),             # 16; more entries than threads
+    dict(lens=(16384, 16001, 9), topk=2048),                          # 32
+    dict(lens=(16385, 40000, 65536, 20), topk=1024, sink=0, recent=0),    # by the tiles' maxima: 8 per thread
+    dict(lens=(131072, 70001), topk=333),                             # 16
+    dict(lens=(17000, 20000), topk=2048, heads=32),                   # walked whole; 16 heads to a group
+    dict(lens=(9001, 30), part=2, topk=200, score=synth.SCORE_MINMAX),
+    dict(lens=(9001, 29), part=4, topk=99, score=synth.SCORE_MINMAX, incl=False, heads=10),
+    dict(lens=(9001, 27), part=8, topk=70, score=synth.SCORE_MINMAX, leaf=3),
+    dict(lens=(300000, 140001), part=8, topk=50, score=synth.SCORE_MINMAX),
+    dict(lens=(300 * 16, 999), leaf=1, topk=100),                     # a directory of more than 256 entries
+])
+@pytest.mark.parametrize("splits", [0, 1, 3])
+def test_partitions_smaller_than_a_page(kw, splits):
+    layer, _ = runner.build_device_layer(_workload(**dict(dict(part=1, score=synth.SCORE_SKETCH), **kw)), decode_splits=splits)
+    assert layer.spin.fused_splits >= 1
+    _same_as_stage_calls(layer, layer.q0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
+    dict(lens=(262145, 400000, 5, 70000), topk=128),                  # 8 maxima per thread
+    dict(lens=(1048576, 1100001), topk=256, sink=4, recent=8, kv=1, heads=4),    # 16
+    dict(lens=(300000,), topk=2000, sink=100, recent=200),            # walked whole; windows of more than a page a wavefront
+    dict(lens=(300000, 280001), topk=64, leaf=6),                     # leaves that are no power of two
+    dict(lens=(600001, 30000), part=32, topk=30, incl=False, sink=3, recent=9),
+])
+@pytest.mark.parametrize("splits", [0, 1, 3])
+def test_rows_beyond_the_registers(kw, splits):
+    layer, _ = runner.build_device_layer(_workload(**kw), decode_splits=splits)
+    assert layer.spin.fused_splits >= 1
+    _same_as_stage_calls(layer, layer.q0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
+    dict(lens=(30000, 8000), topk=64),
+    dict(lens=(30000, 8000), topk=500, part=1, score=synth.SCORE_SKETCH),
+    dict(lens=(9000, 8000), topk=300, part=1, score=synth.SCORE_SKETCH),
+    dict(lens=(300000, 8000), topk=64),
+])
+def test_scores_that_tie_or_are_not_finite(kw):
+    layer, _ = runner.build_device_layer(_workload(**kw))
     sp, w = layer.spin, layer.w
     for fill in ("ties", "inf", "nan", "spread"):
         gen = torch.Generator(device="cuda:0")
@@ -90,9 +134,10 @@ def test_scores_that_tie_or_are_not_finite():
 
 
 @pytest.mark.gpu
-def test_pages_that_are_missing_or_outside_the_pool():
+@pytest.mark.parametrize("kw", [dict(), dict(part=1, score=synth.SCORE_SKETCH, topk=90), dict(part=4, topk=60)])
+def test_pages_that_are_missing_or_outside_the_pool(kw):
     for slot, code, note in ((-1, -6, "not resident"), (1 << 30, -7, "outside the pool")):
-        layer, _ = runner.build_device_layer(_workload((5000, 3000), topk=30, sink=0, recent=0))
+        layer, _ = runner.build_device_layer(_workload((5000, 3000), **dict(dict(topk=30, sink=0, recent=0), **kw)))
         layer.step(layer.q0)
         chosen = int(layer.page_ids[1, 7])                            # row 1: request 0, head 1
         chunk = int(layer.dir[1, chosen // layer.w.leaf_entries])
@@ -109,8 +154,9 @@ def test_pages_that_are_missing_or_outside_the_pool():
 
 
 @pytest.mark.gpu
-def test_replays_of_a_graph():
-    layer, _ = runner.build_device_layer(_workload((9001, 4000), topk=64))
+@pytest.mark.parametrize("kw", [dict(lens=(9001, 4000)), dict(lens=(20001, 4000), part=1, score=synth.SCORE_SKETCH)])
+def test_replays_of_a_graph(kw):
+    layer, _ = runner.build_device_layer(_workload(topk=64, **kw))
     q = layer.q0.clone()
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
@@ -134,8 +180,12 @@ def test_contexts_that_it_does_not_take():
     base = dict(max_batch=2, num_q_heads=8, num_kv_heads=2, topk=8, max_context=4096)
     assert binding.Spin(**base).fused_splits == 1
     assert binding.Spin(**dict(base, max_batch=1, topk=128, max_context=131072, num_kv_heads=8)).fused_splits == 8
-    for other in (dict(partition_tokens=8), dict(lru_timestamps=8), dict(variable_partitions=1), dict(decode_waves=4),
-                  dict(decode_depth=3), dict(max_context=262145), dict(topk=2305, max_context=65536)):
+    assert binding.Spin(**dict(base, partition_tokens=8)).fused_splits == 1
+    assert binding.Spin(**dict(base, partition_tokens=1, topk=1024, max_context=65536, max_batch=32)).fused_splits == 4
+    assert binding.Spin(**dict(base, topk=256, max_context=2097152)).fused_splits == 16
+    for other in (dict(lru_timestamps=8), dict(variable_partitions=1), dict(decode_waves=4), dict(decode_depth=3),
+                  dict(max_context=2097153), dict(partition_tokens=1, max_context=131073),
+                  dict(topk=2305, max_context=65536)):
         sp = binding.Spin(**dict(base, **other))
         assert sp.fused_splits == 0, other
         fake = 4096   # never dereferenced: the call returns before anything is launched
