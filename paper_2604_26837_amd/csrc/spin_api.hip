@@ -115,7 +115,7 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
 
   // stages 2 to 4 in one launch, where the shape of stage 4's launch is left to the library
   x->fused_splits = 0;
-  if (c->lru_timestamps == 0 && !c->variable_partitions &&
+  if (c->lru_timestamps == 0 &&
       (x->max_parts <= 16384 || (x->max_stride && x->max_stride <= 8192)) && x->sel_stride <= SPIN_SEL_HELD &&
       !c->decode_waves && !c->decode_depth && x->max_rows <= 65535 && spin_fused_lds(x) <= SPIN_FUSED_LDS) {
     int32_t s = c->decode_splits;

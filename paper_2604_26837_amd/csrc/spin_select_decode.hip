@@ -1,4 +1,4 @@
-// Stages 2, 3 and 4 in one launch (all-resident mode, uniform partitions of whole pages, rows that fit a workgroup's
+// Stages 2, 3 and 4 in one launch (all-resident mode, partitions of whole pages, rows that fit a workgroup's
 // registers or go by their tiles' maxima).
 //
 // A launch that depends on the one before it starts 2 to 3 us after that one's last wavefront has its result, and the
@@ -9,7 +9,8 @@
 // 2+3 followed by that of stage 4: 128 rows of 2048 pages, 128 attended 52.6 -> 50.2; 24 rows of 512, 64 attended 23.0 ->
 // 20.8; 8 rows of 8192 28.0 -> 24.7; 256 ragged rows of up to 16384 139.5 -> 137.6; 32 rows of 1024 blocks 31.5 -> 30.1;
 // 512 rows of 500 and 1000 83.9 -> 72.4 and 143.5 -> 132.9 (also where the rows are more than the compute units, then);
-// 8 rows of 62500, 256 attended 61.8 -> 58.3.
+// 8 rows of 62500, 256 attended 61.8 -> 58.3; 32 rows of 250 clusters, 32 of them attended 24.6 -> 23.1, and 22.7 with the
+// windows' tables read four entries at a time, without branches.
 //
 // The row's always-attended pages are known before its scores are: each wavefront asks for the first of its own ahead of
 // the selection and attends it when the first selected ones are under way.
@@ -112,7 +113,8 @@ __device__ __forceinline__ void select_pages(const __amdgpu_buffer_rsrc_t scores
 // page's leaf entry comes with its score.
 // TILES: rows beyond a workgroup's registers, selected from their tiles' maxima, KPT of them per thread; otherwise KPT is the
 // scores per thread of the longest row.
-template <int KPT, bool PAGES, bool TILES>
+// VAR: variable-length partitions.  Which pages their windows cover is known from the tables only: none is asked for ahead.
+template <int KPT, bool PAGES, bool TILES, bool VAR>
 __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets, const int32_t *__restrict__ seq_lens,
     const int32_t *__restrict__ dir, const uint16_t *__restrict__ q, int Hkv, int nsplit, int G, int Hq, int dir_stride,
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
   const bool ahead = TILES || dir_stride <= 64;
   const int32_t lane_dir = rdir[min(lane, dir_stride - 1)];
   const int N = max(seq_lens[b], 0);
-  const forced_span fs = forced_pages_of(N, a.sink_pages, a.recent_pages);
+  const forced_span fs = VAR ? forced_span{0, 0, 0} : forced_pages_of(N, a.sink_pages, a.recent_pages);
   const bool asked = ahead && first < fs.nlo + fs.nhi;
   spin_bf16x8 qf[4];
   page_regs rf;
@@ -189,18 +191,18 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     const step_sel rsel = {a.sel + (size_t)row * a.sel_stride, a.sel_stride, (spin_lds_i32 *)s_held.sel, store};
     auto ask = [&] {
       mydir = row_dir_entry(dir, dir_stride, row);
-      ask_ahead(page_ahead(asked, first, fs, TILES ? rdir : nullptr, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
+      if constexpr (!VAR) ask_ahead(page_ahead(asked, first, fs, TILES ? rdir : nullptr, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
     };
     int take;
+    spin_var_span span;
     if constexpr (TILES) {
       ask();
       take = select_tiles_row<BLOCK, KPT, STEP_CAP, true>(scores, a.maxima, a.max_stride, a.gs_log, part_offsets, seq_lens, Hkv,
                                                           a.tp, a.topk, a.includes_forced, a.sink_pages, a.recent_pages,
                                                           a.sel, rsel, a.nsel, row, *(step_tiles_lds *)smem);
     } else {
-      spin_var_span span;              // (uniform partitions)
       take = select_reg_row<BLOCK, KPT>(scores, part_offsets, seq_lens, Hkv, a.tp, a.topk, a.includes_forced, a.sink_pages,
-                                        a.recent_pages, rsel, a.nsel, row, spin_var{}, span, s, ask);
+                                        a.recent_pages, rsel, a.nsel, row, VAR ? a.var : spin_var{}, span, s, ask);
     }
     if (tid < RES_DIR_LDS) s_held.dir[tid] = mydir;
     __syncthreads();                   // the selection and the directory are whole
@@ -209,7 +211,7 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     const step_pages list = {res_row_out(a.slots, a.page_ids, a.valid_mask, a.npages, row, a.page_stride), l_slot, l_mask, store};
     np = resolve_row<BLOCK, true, true, true>(row, take, a.sel, seq_lens, dir, a.leaf_pool, a.leaf_chunks, Hkv, a.tp,
                                               a.sink_pages, a.recent_pages, a.sel_stride, a.page_stride, dir_stride,
-                                              a.leaf_entries, list, a.status, spin_var{}, nullptr, &s_held);
+                                              a.leaf_entries, list, a.status, VAR ? a.var : spin_var{}, VAR ? &span : nullptr, &s_held);
   }
   __syncthreads();
 
@@ -285,7 +287,7 @@ static int select_resolve_decode_impl(spin_ctx *ctx, int32_t batch, const float 
                                       int64_t pool_slots, void *out, float *lse, void *workspace, void *stream,
                                       bool maxima_ready) {
   if (!ctx || batch < 0 || batch > ctx->cfg.max_batch || leaf_chunks <= 0 || pool_slots <= 0) return SPIN_ERR_INVALID;
-  if (ctx->fused_splits == 0 || ctx->var.count) return SPIN_ERR_UNSUPPORTED;
+  if (ctx->fused_splits == 0) return SPIN_ERR_UNSUPPORTED;
   if (batch == 0) return SPIN_OK;
   if (!scores || !part_offsets || !seq_lens || !sel || !nsel || !dir || !leaf_pool || !slots || !page_ids ||
       !valid_mask || !npages || !q || !kv_pool || !out)
@@ -302,18 +304,19 @@ static int select_resolve_decode_impl(spin_ctx *ctx, int32_t batch, const float 
                             (float *)(ws + ctx->ws_acc_off), (int32_t *)(ws + ctx->ws_ticket_off), (int32_t *)workspace,
                             c.partition_tokens, c.topk, c.topk_includes_forced, c.sink_pages, c.recent_pages,
                             ctx->sel_stride, ctx->page_stride, c.leaf_entries, leaf_log,
-                            (int)(spin_fused_front(ctx) / sizeof(float)), maxima, ctx->max_stride, ctx->tile_log,
+                            (int)(spin_fused_front(ctx) / sizeof(float)), maxima, ctx->max_stride, ctx->tile_log, ctx->var,
                             ctx->scale * 1.4426950408889634f};
   if (ctx->k_token_major) return spin_step_tokens_launch(ctx, batch, scores, part_offsets, seq_lens, dir, q, a, stream);
-#define SPIN_SD_LAUNCH1(KPT, PAGES, TILES)                                                                        \
-  spin_launch(ctx, SPIN_K_SELECT_DECODE, spin_select_decode_kernel<KPT, PAGES, TILES>,                            \
+#define SPIN_SD_LAUNCH1(KPT, PAGES, TILES, VAR)                                                                        \
+  spin_launch(ctx, SPIN_K_SELECT_DECODE, spin_select_decode_kernel<KPT, PAGES, TILES, VAR>,                            \
               dim3((unsigned)ctx->fused_splits, (unsigned)c.num_kv_heads, (unsigned)batch), dim3(512), spin_fused_lds(ctx), \
               (hipStream_t)stream, scores, part_offsets, seq_lens, dir, (const uint16_t *)q, c.num_kv_heads,      \
               ctx->fused_splits, ctx->group, c.num_q_heads, ctx->dir_stride, a)
 #define SPIN_SD_LAUNCH(KPT, TILES)                                                                \
   do {                                                                                            \
-    if (c.partition_tokens == SPIN_PAGE_TOKENS && leaf_log >= 2) SPIN_SD_LAUNCH1(KPT, true, TILES); \
-    else SPIN_SD_LAUNCH1(KPT, false, TILES);                                                      \
+    if (!TILES && ctx->var.count) SPIN_SD_LAUNCH1(KPT, false, false, true);                       \
+    else if (c.partition_tokens == SPIN_PAGE_TOKENS && leaf_log >= 2) SPIN_SD_LAUNCH1(KPT, true, TILES, false); \
+    else SPIN_SD_LAUNCH1(KPT, false, TILES, false);                                               \
   } while (0)
   if (ctx->max_parts <= 2048) SPIN_SD_LAUNCH(4, false);
   else if (ctx->max_parts <= 4096) SPIN_SD_LAUNCH(8, false);
@@ -346,7 +349,7 @@ extern "C" int spin_decode_step(spin_ctx *ctx, int32_t batch, const void *q, con
                                 void *stream) {
   // refuse before stage 1 is issued what the second launch would refuse
   if (!ctx || batch < 0 || batch > ctx->cfg.max_batch || leaf_chunks <= 0 || pool_slots <= 0) return SPIN_ERR_INVALID;
-  if (ctx->fused_splits == 0 || ctx->var.count) return SPIN_ERR_UNSUPPORTED;
+  if (ctx->fused_splits == 0) return SPIN_ERR_UNSUPPORTED;
   if (batch == 0) return SPIN_OK;
   if (!sel || !nsel || !dir || !leaf_pool || !slots || !page_ids || !valid_mask || !npages || !kv_pool || !out)
     return SPIN_ERR_INVALID;

@@ -521,9 +521,22 @@ __device__ __forceinline__ spin_var_span block_var_span(const spin_var &var, siz
     return e;
   };
   entry held[HELD];
-  if (HELD == KPT) {
+  if constexpr (HELD == KPT) {                         // four at a time, and without a branch (see spin_buffer)
+    const __amdgpu_buffer_rsrc_t first = spin_buffer(var.first_page + vbase, (uint32_t)max(PP, 0) * sizeof(int32_t));
+    const __amdgpu_buffer_rsrc_t tokens = spin_buffer(var.tokens + vbase, (uint32_t)max(PP, 0) * sizeof(int32_t));
+    int4 f[KPT / 4], t[KPT / 4];
 #pragma unroll
-    for (int k = 0; k < HELD; ++k) held[k] = load(k);
+    for (int k = 0; k < KPT / 4; ++k) {
+      f[k] = __builtin_bit_cast(int4, spin_buffer_load_kept(first, (uint32_t)(c0 + 4 * k) * sizeof(int32_t)));
+      t[k] = __builtin_bit_cast(int4, spin_buffer_load_kept(tokens, (uint32_t)(c0 + 4 * k) * sizeof(int32_t)));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < KPT / 4; ++k) {
+      const int fs[4] = {f[k].x, f[k].y, f[k].z, f[k].w}, ts[4] = {t[k].x, t[k].y, t[k].z, t[k].w};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) held[4 * k + i] = entry{fs[i], fs[i] + ((ts[i] + 15) >> 4)};
+    }
   }
   w.P = min(min(max(var.count[row], 0), PP), BLOCK * KPT);
   if (w.P == 0 && threadIdx.x == 0) s_pages = 0;

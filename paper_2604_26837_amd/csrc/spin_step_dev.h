@@ -19,6 +19,7 @@ struct spin_step_args {
   int lists_at;                       // floats of dynamic LDS ahead of the row's lists
   const float *maxima;                // of the scores' tiles, 2^gs_log partitions each (rows beyond a workgroup's registers)
   int max_stride, gs_log;
+  spin_var var;                       // variable-length partitions (count NULL: uniform ones)
   float scale_log2e;
 };
 

@@ -156,7 +156,7 @@ class LayerState:
         """The step in as few launches as the context allows (what ``bench.py`` times): stage 1, then stages 2-4 in
         one; or stages 1-3 in two, with the sink / recent pages attended beside stages 2+3 where that applies, then
         attention."""
-        if self.spin.fused_splits and self.layouts_none:
+        if self.spin.fused_splits:
             self.step2(q, summaries)
         elif self.spin.forced_split_supported and self.layouts_none:
             self.step3f(q, summaries)

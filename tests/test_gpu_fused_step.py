@@ -101,6 +101,26 @@ def test_rows_beyond_the_registers(kw, splits):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("kw", [
+    dict(lens=(100, 1, 17, 5000), part=64, topk=5),                   # rows as short as the windows
+    dict(lens=(20000, 31001), part=256, topk=32, incl=False, recent=16),    # 4 scores per thread
+    dict(lens=(65536, 9000), part=16, topk=100),                      # 8: partitions of at most a page
+    dict(lens=(131072, 70000), part=32, topk=60, incl=False, sink=0, recent=0),    # 16
+    dict(lens=(262144,), part=64, topk=40, incl=False, sink=9, recent=30, kv=1, heads=16),    # 32; 16 heads to a group
+    dict(lens=(30000,), part=128, topk=700, score=synth.SCORE_REPMAX),
+])
+@pytest.mark.parametrize("splits", [0, 1, 3])
+def test_variable_length_partitions(kw, splits):
+    w = _workload(**kw)
+    dd = synth.generate_on_device(w)
+    layer = runner.LayerState.from_natural_pool(w, dd.slot_of, dd.pool, layouts=synth.variable_layouts(w, 5),
+                                                decode_splits=splits)
+    layer.build_summaries()
+    assert layer.spin.fused_splits >= 1
+    _same_as_stage_calls(layer, dd.q)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
     dict(lens=(30000, 8000), topk=64),
     dict(lens=(30000, 8000), topk=500, part=1, score=synth.SCORE_SKETCH),
     dict(lens=(9000, 8000), topk=300, part=1, score=synth.SCORE_SKETCH),
@@ -183,8 +203,9 @@ def test_contexts_that_it_does_not_take():
     assert binding.Spin(**dict(base, partition_tokens=8)).fused_splits == 1
     assert binding.Spin(**dict(base, partition_tokens=1, topk=1024, max_context=65536, max_batch=32)).fused_splits == 4
     assert binding.Spin(**dict(base, topk=256, max_context=2097152)).fused_splits == 16
-    for other in (dict(lru_timestamps=8), dict(variable_partitions=1), dict(decode_waves=4), dict(decode_depth=3),
-                  dict(max_context=2097153), dict(partition_tokens=1, max_context=131073),
+    assert binding.Spin(**dict(base, partition_tokens=64, variable_partitions=1)).fused_splits == 1
+    for other in (dict(lru_timestamps=8), dict(decode_waves=4), dict(decode_depth=3), dict(max_context=2097153),
+                  dict(partition_tokens=64, variable_partitions=1, max_context=262145), dict(partition_tokens=1, max_context=131073),
                   dict(topk=2305, max_context=65536)):
         sp = binding.Spin(**dict(base, **other))
         assert sp.fused_splits == 0, other
