@@ -372,7 +372,7 @@ int spin_select_resolve_decode(spin_ctx *ctx, int32_t batch, const float *scores
                                uint16_t *valid_mask, int32_t *npages, const void *q, const void *kv_pool,
                                int64_t pool_slots, void *out, float *lse, void *workspace, void *stream);
 int32_t spin_fused_splits(const spin_ctx *ctx);
-/* spin_score_partitions and the above in one call (two launches; rows of more than 16384 partitions are selected from
+/* spin_score_partitions and the above in one call (two launches, or one where the contexts are small; rows of more than 16384 partitions are selected from
  * the maxima that stage 1 takes of its tiles).  Same results, same conditions. */
 int spin_decode_step(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries, const int32_t *chan_idx,
                      const int32_t *part_offsets, const int32_t *seq_lens, float *scores, int32_t *sel, int32_t *nsel,

@@ -20,6 +20,9 @@ struct spin_step_args {
   const float *maxima;                // of the scores' tiles, 2^gs_log partitions each (rows beyond a workgroup's registers)
   int max_stride, gs_log;
   spin_var var;                       // variable-length partitions (count NULL: uniform ones)
+  const uint4 *summ;                  // stage 1 in the same launch: its summaries, where its scores go,
+  float *scores_out;
+  int reps;                           // and summary rows per partition
   float scale_log2e;
 };
 

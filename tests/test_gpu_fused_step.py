@@ -1,6 +1,7 @@
 """Stages 2 to 4 in one launch: the page lists have the bits of the separate stage calls, the attention is theirs to the
 tolerance of a bf16 output of two summation orders, whatever the number of workgroups per row."""
-import numpy as np
+import dataclasses
+
 import pytest
 import torch
 
@@ -59,6 +60,27 @@ def test_equals_the_stage_calls(kw, splits):
     layer, _ = runner.build_device_layer(_workload(**kw), decode_splits=splits)
     assert layer.spin.fused_splits >= 1
     _same_as_stage_calls(layer, layer.q0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
+    dict(lens=(1, 15, 16, 17, 257, 1000, 4096)),                      # up to two tiles per wavefront, rows without any
+    dict(lens=(4096, 4081) * 20, heads=10, topk=20),                  # and where the rows are more
+    dict(lens=(1024, 1000, 3) * 25, heads=32),
+    dict(lens=(8192, 8177, 700), score=synth.SCORE_REPMAX, sink=0, recent=0),
+    dict(lens=(4096, 2049), score=synth.SCORE_REPMAX, reps=2, leaf=4),
+    dict(lens=(2048, 2033, 99), score=synth.SCORE_REPMAX, reps=4),
+])
+@pytest.mark.parametrize("splits", [0, 2])
+def test_stage_1_in_the_same_launch(kw, splits):
+    w = dataclasses.replace(_workload(**{k: v for k, v in kw.items() if k != "reps"}), reps_per_partition=kw.get("reps", 1))
+    layer, _ = runner.build_device_layer(w, decode_splits=splits)
+    layer.step(layer.q0)
+    want = layer.scores.clone()
+    _same_as_stage_calls(layer, layer.q0)
+    layer.scores.fill_(7.0)
+    layer.step2(layer.q0)
+    assert torch.equal(want, layer.scores)
 
 
 @pytest.mark.gpu
