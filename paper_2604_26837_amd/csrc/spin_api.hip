@@ -108,15 +108,24 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   }
   x->pstride = splits + (x->side_wgs > 1 ? x->side_wgs : 1);
 
-  // rows beyond 16384 partitions go by the maxima of their score tiles
+  // Rows beyond 16384 partitions go by the maxima of their score tiles.  In the launch of stages 2 to 4 so do those beyond
+  // 8192, 32 of which to a thread take it long, where no more tiles than there are need be read, and of whole pages where
+  // rows are few (a batch of many has short ones as well, which are selected faster from their scores, and stage 1 writes
+  // the maxima of all).  Steps, us, from scores / maxima: 64 rows of 9000 tokens, 512 attended 26.9 / 22.8, of 16000 30.4 /
+  // 25.9, with 2048 attended 35.4 / 38.7; 8 rows of 16384 pages 28.1 / 27.0, 32 rows 61.2 / 59.1; 64 ragged rows 42.8 / 43.6, 256
+  // 133.5 / 137.4.
   x->tile_log = x->rows_per_part == 4 ? 2 : x->rows_per_part == 2 ? 3 : 4;
-  if (x->max_parts > 16384 && x->max_parts <= 131072 && !c->variable_partitions)
+  const bool maxima = x->max_parts <= 131072 && !c->variable_partitions;
+  x->step_tiles = maxima && (x->max_parts > 16384 ||
+                             (x->max_parts > 8192 && c->lru_timestamps == 0 && ((int64_t)c->topk << x->tile_log) <= x->max_parts &&
+                              (tp < SPIN_PAGE_TOKENS || x->max_rows <= 32)));
+  if (maxima && (x->max_parts > 16384 || x->step_tiles))
     x->max_stride = ((cdiv32(x->max_parts, 16) * 16 >> x->tile_log) + 3) & ~3;
 
   // stages 2 to 4 in one launch, where the shape of stage 4's launch is left to the library
   x->fused_splits = 0;
   if (c->lru_timestamps == 0 &&
-      (x->max_parts <= 16384 || (x->max_stride && x->max_stride <= 8192)) && x->sel_stride <= SPIN_SEL_HELD &&
+      (x->max_parts <= 16384 || x->step_tiles) && x->max_stride <= 8192 && x->sel_stride <= SPIN_SEL_HELD &&
       !c->decode_waves && !c->decode_depth && x->max_rows <= 65535 && spin_fused_lds(x) <= SPIN_FUSED_LDS) {
     int32_t s = c->decode_splits;
     if (s == 0) {
@@ -139,7 +148,7 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   off += (size_t)x->max_rows * sizeof(int32_t);
   off = (off + 255) & ~(size_t)255;
   x->ws_zero_bytes = off;
-  // stage 2 of rows beyond 16384 partitions: the maxima of the rows' score tiles
+  // the maxima of the rows' score tiles
   if (x->max_stride) {
     x->ws_max_off = off;
     off += (size_t)x->max_rows * x->max_stride * sizeof(float);

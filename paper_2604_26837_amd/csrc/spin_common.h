@@ -58,6 +58,7 @@ struct spin_ctx {
   size_t ws_ticket_off, ws_ml_off, ws_acc_off;
   size_t ws_max_off;      // maxima of the rows' score tiles, [max_rows][max_stride]; 0 = not used
   int32_t max_stride;     // tiles of the longest row, rounded up to a multiple of 4
+  int32_t step_tiles;     // whether the launch of stages 2 to 4 goes by them
   int32_t tile_log;       // log2 of the partitions in a summary tile of 16 rows
   size_t ws_zero_bytes;   // leading part of the workspace that spin_workspace_init clears
   size_t ws_skip_off;     // [max_rows][2] list positions attended by the launch of stages 2+3 (always-attended pages)
@@ -93,7 +94,7 @@ static inline bool spin_forced_split_supported(const spin_ctx *ctx) { return ctx
 // page) the wavefronts' token lists and the row's selection.
 static inline size_t spin_fused_front(const spin_ctx *ctx) {
   const size_t merge = (size_t)8 * ctx->group * (SPIN_HEAD_DIM + 2) * sizeof(float);
-  return ctx->max_parts > 16384 && merge < SPIN_TILES_LDS ? SPIN_TILES_LDS : merge;
+  return ctx->step_tiles && merge < SPIN_TILES_LDS ? SPIN_TILES_LDS : merge;
 }
 static inline size_t spin_fused_lds(const spin_ctx *ctx) {
   return spin_fused_front(ctx) +

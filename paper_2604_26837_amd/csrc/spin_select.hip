@@ -174,7 +174,7 @@ extern "C" int spin_score_select_topk(spin_ctx *ctx, int32_t batch, const void *
   if (batch == 0) return SPIN_OK;
   if (!sel || !nsel) return SPIN_ERR_INVALID;
   // (same condition as in stage 2)
-  const bool fuse = ctx->ws_max_off && workspace && batch * ctx->cfg.num_kv_heads <= 65535;
+  const bool fuse = ctx->max_parts > 16384 && ctx->ws_max_off && workspace && batch * ctx->cfg.num_kv_heads <= 65535;
   float *maxima = fuse ? (float *)((char *)workspace + ctx->ws_max_off) : nullptr;
   const int st = spin_score_impl(ctx, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, workspace, stream,
                                  maxima);

@@ -373,7 +373,7 @@ static int select_resolve_decode_impl(spin_ctx *ctx, int32_t batch, const float 
   const spin_config &c = ctx->cfg;
   char *ws = (char *)workspace;
   const int leaf_log = (c.leaf_entries & (c.leaf_entries - 1)) ? -1 : 31 - __builtin_clz((unsigned)c.leaf_entries);
-  const bool tiles = ctx->max_parts > 16384;
+  const bool tiles = ctx->step_tiles != 0;
   float *maxima = tiles ? (float *)(ws + ctx->ws_max_off) : nullptr;
   if (tiles && !maxima_ready) spin_take_maxima(ctx, batch * c.num_kv_heads, scores, part_offsets, maxima, stream);
   const spin_step_args a = {leaf_pool, leaf_chunks, sel, nsel, slots, page_ids, valid_mask, npages, (const uint4 *)kv_pool,
@@ -399,12 +399,14 @@ static int select_resolve_decode_impl(spin_ctx *ctx, int32_t batch, const float 
   if (summaries) {
     if (c.score_kind == SPIN_SCORE_MINMAX) SPIN_SD_LAUNCH1(4, true, false, false, SPIN_SCORE_MINMAX + 1);
     else SPIN_SD_LAUNCH1(4, true, false, false, SPIN_SCORE_REPMAX + 1);
+  } else if (tiles) {
+    if (ctx->max_stride <= 2048) SPIN_SD_LAUNCH(4, true);
+    else if (ctx->max_stride <= 4096) SPIN_SD_LAUNCH(8, true);
+    else SPIN_SD_LAUNCH(16, true);
   } else if (ctx->max_parts <= 2048) SPIN_SD_LAUNCH(4, false);
   else if (ctx->max_parts <= 4096) SPIN_SD_LAUNCH(8, false);
   else if (ctx->max_parts <= 8192) SPIN_SD_LAUNCH(16, false);
-  else if (!tiles) SPIN_SD_LAUNCH(32, false);
-  else if (ctx->max_stride <= 4096) SPIN_SD_LAUNCH(8, true);
-  else SPIN_SD_LAUNCH(16, true);
+  else SPIN_SD_LAUNCH(32, false);
 #undef SPIN_SD_LAUNCH1
 #undef SPIN_SD_LAUNCH
   return spin_launch_status();
@@ -441,7 +443,7 @@ extern "C" int spin_decode_step(spin_ctx *ctx, int32_t batch, const void *q, con
                                       slots, page_ids, valid_mask, npages, q, kv_pool, pool_slots, out, lse, workspace,
                                       stream, false, summaries, scores);
   }
-  const bool tiles = ctx->max_parts > 16384;
+  const bool tiles = ctx->step_tiles != 0;
   const int st = spin_score_impl(ctx, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, workspace, stream,
                                  tiles ? (float *)((char *)workspace + ctx->ws_max_off) : nullptr);
   if (st != SPIN_OK) return st;

@@ -259,7 +259,7 @@ extern "C" int spin_score_select_resolve(spin_ctx *ctx, int32_t batch, const voi
   const bool long_rows = ctx->max_parts > 16384;
   // refuse before stage 1 is issued what the second launch would refuse
   if (c.lru_timestamps > 0 || (long_rows && !(ctx->ws_max_off && rows <= 65535))) return SPIN_ERR_UNSUPPORTED;
-  const bool fuse = ctx->ws_max_off != 0 && rows <= 65535;
+  const bool fuse = long_rows && ctx->ws_max_off != 0 && rows <= 65535;
   float *maxima = fuse ? (float *)((char *)workspace + ctx->ws_max_off) : nullptr;
   const int st = spin_score_impl(ctx, batch, q, summaries, chan_idx, part_offsets, seq_lens, scores, workspace, stream,
                                  maxima);

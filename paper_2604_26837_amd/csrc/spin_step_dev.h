@@ -17,7 +17,7 @@ struct spin_step_args {
   int tp, topk, includes_forced, sink_pages, recent_pages, sel_stride, page_stride, leaf_entries;
   int leaf_log;                       // log2 of leaf_entries, or -1
   int lists_at;                       // floats of dynamic LDS ahead of the row's lists
-  const float *maxima;                // of the scores' tiles, 2^gs_log partitions each (rows beyond a workgroup's registers)
+  const float *maxima;                // of the scores' tiles, 2^gs_log partitions each (step_tiles)
   int max_stride, gs_log;
   spin_var var;                       // variable-length partitions (count NULL: uniform ones)
   const uint4 *summ;                  // stage 1 in the same launch: its summaries, where its scores go,

@@ -90,7 +90,9 @@ def test_stage_1_in_the_same_launch(kw, splits):
     dict(lens=(4096, 3001), topk=300),                                # 8
     dict(lens=(8192, 5000), topk=1025, sink=1, recent=2),             # 16; more entries than threads
     dict(lens=(16384, 16001, 9), topk=2048),                          # 32
-    dict(lens=(16385, 40000, 65536, 20), topk=1024, sink=0, recent=0),    # by the tiles' maxima: 8 per thread
+    dict(lens=(8193, 9000, 3), topk=512),                             # by the tiles' maxima: 4 per thread
+    dict(lens=(8193, 9000, 3), topk=514),                             # 32 scores per thread: more tiles wanted than there are
+    dict(lens=(16385, 40000, 65536, 20), topk=1024, sink=0, recent=0),    # 8 maxima per thread
     dict(lens=(131072, 70001), topk=333),                             # 16
     dict(lens=(17000, 20000), topk=2048, heads=32),                   # walked whole; 16 heads to a group
     dict(lens=(9001, 30), part=2, topk=200, score=synth.SCORE_MINMAX),
@@ -108,7 +110,9 @@ def test_partitions_smaller_than_a_page(kw, splits):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("kw", [
-    dict(lens=(262145, 400000, 5, 70000), topk=128),                  # 8 maxima per thread
+    dict(lens=(131073, 262144, 50000), topk=200),                     # 4 maxima per thread, and 32 scores where rows are many:
+    dict(lens=(131073,) + (5000,) * 16, topk=200),
+    dict(lens=(600000, 262145, 5, 70000), topk=128),                  # 8
     dict(lens=(1048576, 1100001), topk=256, sink=4, recent=8, kv=1, heads=4),    # 16
     dict(lens=(300000,), topk=2000, sink=100, recent=200),            # walked whole; windows of more than a page a wavefront
     dict(lens=(300000, 280001), topk=64, leaf=6),                     # leaves that are no power of two
