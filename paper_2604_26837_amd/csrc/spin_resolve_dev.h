@@ -96,14 +96,15 @@ __device__ inline void emit_invalid(const OUT &o, int pos, int page_stride, int3
 // Resolves one row with the calling workgroup of RES_BLOCK threads; `ns` = the
 // row's selection count.  `known`: the row's windows, where the caller has them
 // (variable-length partitions).  HELD_DIR, HELD_SEL: the calling launch has staged the row's directory, or its selection,
-// in `held`.  Returns the length of the page list.
-template <int RES_BLOCK, bool LOOKUP = true, bool HELD_DIR = false, bool HELD_SEL = false, typename OUT>
+// in `held`.  TABLES > 0: so are the row's partition tables in `tables`, first pages [TABLES] and then tokens.  Returns the
+// length of the page list.
+template <int RES_BLOCK, bool LOOKUP = true, bool HELD_DIR = false, bool HELD_SEL = false, int TABLES = 0, typename OUT>
 __device__ __forceinline__ int resolve_row(
     int row, int ns, const int32_t *__restrict__ sel, const int32_t *__restrict__ seq_lens,
     const int32_t *dir, const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks, int Hkv, int tp,
     int sink_pages, int recent_pages, int sel_stride, int page_stride, int dir_stride, int leaf_entries, const OUT &o,
     int32_t *status, spin_var var, const spin_var_span *known = nullptr,
-    held_row<HELD_SEL> *held = nullptr) {
+    held_row<HELD_SEL> *held = nullptr, const int32_t *tables = nullptr) {
   constexpr int RES_WAVES = RES_BLOCK / 64;
   __shared__ int s_wave[RES_WAVES];
   __shared__ int s_flagA, s_flagB, s_cntB;
@@ -144,18 +145,20 @@ __device__ __forceinline__ int resolve_row(
     const int P = w.P;
     // selection entry i: partition (-1: names none of the row), first page, tokens
     struct part { int s, first, tokens; };
+    auto first_of = [&](int p) { return TABLES ? tables[p] : var.first_page[vb + p]; };
+    auto tokens_of = [&](int p) { return TABLES ? tables[TABLES + p] : var.tokens[vb + p]; };
     auto entry = [&](int i) {
       part e = {sel_at(i), 0, 0};
       if (e.s < 0 || e.s >= P) e.s = -1;
-      else { e.first = var.first_page[vb + e.s]; e.tokens = var.tokens[vb + e.s]; }
+      else { e.first = first_of(e.s); e.tokens = tokens_of(e.s); }
       return e;
     };
     part mine = {-1, 0, 0};
     if (tid < ns) mine = entry(tid);
     // partition A straddles the end of the sink pages, B the beginning of the recent ones
     part pa = {w.sink_end > 0 ? w.at_sink : -1, 0, 0}, pb = {w.recent_begin < w.pages ? w.at_recent : -1, 0, 0};
-    if (pa.s >= 0) { pa.first = var.first_page[vb + pa.s]; pa.tokens = var.tokens[vb + pa.s]; }
-    if (pb.s >= 0) { pb.first = var.first_page[vb + pb.s]; pb.tokens = var.tokens[vb + pb.s]; }
+    if (pa.s >= 0) { pa.first = first_of(pa.s); pa.tokens = tokens_of(pa.s); }
+    if (pb.s >= 0) { pb.first = first_of(pb.s); pb.tokens = tokens_of(pb.s); }
     const int endA = pa.first + ((pa.tokens + 15) >> 4), endB = pb.first + ((pb.tokens + 15) >> 4);
     const int A = pa.s >= 0 && endA > w.sink_end ? pa.s : -1, B = pb.s >= 0 && pb.first < w.recent_begin ? pb.s : -1;
     if (tid == 0) { s_flagA = 0; s_flagB = 0; s_sumA = 0; s_sumB = 0; }
@@ -193,7 +196,7 @@ __device__ __forceinline__ int resolve_row(
         s_part[tid] = e;
         __syncthreads();
         for (int x = tid; x < tot; x += RES_BLOCK) {
-          int lo = 0, hi = RES_BLOCK - 1;                // the last entry that begins at or before x: it has page x
+          int lo = 0, hi = min(ns - i0, RES_BLOCK) - 1;   // the last entry that begins at or before x: it has page x
           while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
             if (s_before[mid] <= x) lo = mid; else hi = mid - 1;

@@ -502,10 +502,11 @@ __device__ __forceinline__ void emit_forced(const sel_plan &pl, const ROW &rsel,
 // The windows of a row of at most BLOCK * KPT variable-length partitions, and its forced prefix and suffix
 // [0, nf_lo) and [first_hi, P).  Every thread holds the table entries of its KPT partitions, so one round of loads and
 // two barriers stand for four binary searches of a dozen dependent loads each.  (With more than 16 per thread, which
-// the registers would not hold beside the scores, the entries are read where they are used.)
-template <int BLOCK, int KPT>
+// the registers would not hold beside the scores, the entries are read where they are used.)  TABLES: they also go to
+// `tables`, first pages [BLOCK * KPT] and then tokens, for the stage that looks the selection up.
+template <int BLOCK, int KPT, bool TABLES>
 __device__ __forceinline__ spin_var_span block_var_span(const spin_var &var, size_t vbase, int row, int PP, int sink_pages,
-                                               int recent_pages, int &nf_lo, int &first_hi) {
+                                               int recent_pages, int &nf_lo, int &first_hi, int32_t *tables) {
   constexpr int NW = BLOCK / 64, HELD = KPT <= 16 ? KPT : 1;
   __shared__ int s_pages;
   __shared__ int4 s_cnt[NW];
@@ -533,6 +534,10 @@ __device__ __forceinline__ spin_var_span block_var_span(const spin_var &var, siz
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < KPT / 4; ++k) {
+      if (TABLES) {
+        *(int4 *)(tables + c0 + 4 * k) = f[k];
+        *(int4 *)(tables + BLOCK * KPT + c0 + 4 * k) = t[k];
+      }
       const int fs[4] = {f[k].x, f[k].y, f[k].z, f[k].w}, ts[4] = {t[k].x, t[k].y, t[k].z, t[k].w};
 #pragma unroll
       for (int i = 0; i < 4; ++i) held[4 * k + i] = entry{fs[i], fs[i] + ((ts[i] + 15) >> 4)};
@@ -586,13 +591,13 @@ __device__ __forceinline__ spin_var_span block_var_span(const spin_var &var, siz
 // thread keeps KPT consecutive scores in registers, so they are read once.
 // Returns the number of selected partitions (and, with variable-length partitions, the row's windows in `span`).
 // `meanwhile` issues what the caller wants under way beside the scores.
-template <int BLOCK, int KPT, typename ROW, typename MEANWHILE>
+template <int BLOCK, int KPT, bool TABLES = false, typename ROW, typename MEANWHILE>
 __device__ __forceinline__ int select_reg_row(
     const float *__restrict__ scores, const int32_t *__restrict__ part_offsets,
     const int32_t *__restrict__ seq_lens, int Hkv, int tp, int topk, int includes_forced, int sink_pages,
     int recent_pages, const ROW &rsel, int32_t *__restrict__ nsel, int row, spin_var var,
     spin_var_span &span, reg_row_lds<BLOCK> &s,
-    MEANWHILE meanwhile) {
+    MEANWHILE meanwhile, int32_t *tables = nullptr) {
   typedef typename key_bits<KPT>::type M;
   const int b = row / Hkv, h = row - b * Hkv;
   const int N = seq_lens[b];
@@ -616,7 +621,7 @@ __device__ __forceinline__ int select_reg_row(
   sel_plan pl;
   if (var.count) {
     int nf_lo, first_hi;
-    span = block_var_span<BLOCK, KPT>(var, vbase, row, PP, sink_pages, recent_pages, nf_lo, first_hi);
+    span = block_var_span<BLOCK, KPT, TABLES>(var, vbase, row, PP, sink_pages, recent_pages, nf_lo, first_hi, tables);
     pl = plan_of(span.P, nf_lo, first_hi, topk, includes_forced, sel_stride);
   } else {
     pl = select_plan(N, PP, tp, topk, includes_forced, sink_pages, recent_pages, sel_stride);
