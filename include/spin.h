@@ -12,6 +12,7 @@
  * Around them:
  *   spin_pack_kv_pages, spin_build_summaries, spin_append_kv   Offload's layout and Index (Section 4.1)
  *   spin_gather_misses, spin_copy_misses_host                  Retrieve steps 3-4 (Sections 5.2, 5.5)
+ *   spin_gather_decode                                         the same beside stage 4 over the pages that were there
  *   spin_offload_pages                                         Offload's copy, slot -> host page (Table 1)
  *   spin_select_resolve                                        stages 2+3 in one launch, same results
  *   spin_select_resolve_forced, spin_sparse_decode_rest        the same, the sink / recent pages attended beside 2+3
@@ -379,6 +380,17 @@ int spin_decode_step(spin_ctx *ctx, int32_t batch, const void *q, const void *su
                      const int32_t *dir, const int32_t *leaf_pool, int64_t leaf_chunks, int32_t *slots, int32_t *page_ids,
                      uint16_t *valid_mask, int32_t *npages, const void *kv_pool, int64_t pool_slots, void *out, float *lse,
                      void *workspace, void *stream);
+
+/* spin_gather_misses and stage 4 in two launches: the first copies the missed pages and meanwhile attends the others of the
+ * row's list, the second attends the missed ones.  slots, page_ids, valid_mask, npages, nmiss, miss_pages and miss_slots as
+ * spin_resolve_slots left them (both lists ascend by page, and every missed page is in the page list); the slots hold what
+ * spin_gather_misses would have left, out and lse are stage 4's results to its tolerance (another summation order),
+ * identical from run to run.  miss_mask: DEVICE uint16 [rows][page_stride], scratch: the token masks of the missed pages.
+ * SPIN_ERR_UNSUPPORTED with partitions smaller than a page, before anything is launched. */
+int spin_gather_decode(spin_ctx *ctx, int32_t batch, const void *q, const void *host_kv, const int64_t *row_base,
+                       const int32_t *nmiss, const int32_t *miss_pages, const int32_t *miss_slots, void *kv_pool,
+                       int64_t pool_slots, const int32_t *slots, const int32_t *page_ids, const uint16_t *valid_mask,
+                       const int32_t *npages, uint16_t *miss_mask, void *out, float *lse, void *workspace, void *stream);
 
 /* Buffer elasticity, mechanism only (Section 5.3: buffer pages are reclaimed from
  * the tail of a request's GPU page table).  Sets the slot count of every row to

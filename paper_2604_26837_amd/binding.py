@@ -30,7 +30,7 @@ EXPORTS = [
     "spin_set_partition_tables", "spin_probe_stream_read", "spin_offload_pages", "spin_score_select_topk", "spin_score_select_resolve", "spin_pin_partitions",
     "spin_set_host_page_table", "spin_set_step", "spin_advance_step", "spin_sparse_decode_static",
     "spin_select_resolve_forced", "spin_sparse_decode_rest", "spin_split_hits_misses", "spin_sparse_decode_begin",
-    "spin_sparse_decode_finish", "spin_select_resolve_decode", "spin_fused_splits", "spin_decode_step",
+    "spin_sparse_decode_finish", "spin_select_resolve_decode", "spin_fused_splits", "spin_decode_step", "spin_gather_decode",
 ]
 
 
@@ -91,6 +91,7 @@ def load_library() -> C.CDLL:
     lib.spin_sparse_decode.argtypes = [vp, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     lib.spin_sparse_decode_static.argtypes = [vp, i32, vp, vp, i64, vp, vp, vp, vp, vp, vp, vp]
     lib.spin_select_resolve_forced.argtypes = [vp, i32] + [vp] * 7 + [i64] + [vp] * 6 + [i64, vp, vp]
+    lib.spin_gather_decode.argtypes = [vp, i32] + [vp] * 7 + [i64] + [vp] * 9
     lib.spin_decode_step.argtypes = [vp, i32] + [vp] * 9 + [i64] + [vp] * 5 + [i64] + [vp] * 4
     lib.spin_select_resolve_decode.argtypes = [vp, i32] + [vp] * 7 + [i64] + [vp] * 6 + [i64] + [vp] * 4
     lib.spin_split_hits_misses.argtypes = [vp, i32] + [vp] * 8
@@ -341,6 +342,15 @@ class Spin:
         self._check(_call.spin_gather_misses(
             self._ctx, batch, host_kv.data_ptr(), row_base, nmiss, miss_pages, miss_slots, kv_pool,
             ws), "spin_gather_misses")
+
+    def gather_decode(self, batch, q, host_kv, row_base, nmiss, miss_pages, miss_slots, kv_pool, slots, page_ids,
+                      valid_mask, npages, miss_mask, out, lse, ws):
+        """gather_misses, with stage 4 over the pages that were there beside it, then stage 4 over the others."""
+        if not host_kv.is_pinned():
+            raise ValueError("host_kv must be pinned host memory")
+        self._check(_call.spin_gather_decode(
+            self._ctx, batch, q, host_kv.data_ptr(), row_base, nmiss, miss_pages, miss_slots, kv_pool, slots, page_ids,
+            valid_mask, npages, miss_mask, out, lse, ws), "spin_gather_decode")
 
     def offload_pages(self, batch, kv_pool, host_kv, row_base, count, pages, slots, ws):
         """host_kv: pinned CPU tensor (written by the kernel); the lists are DEVICE tensors."""

@@ -27,9 +27,6 @@
 
 #include "spin_token_tiles_dev.h"
 
-#define SPIN_DECODE_FROM_PARTIAL 1   // the row's first wavefront starts from the partial at index nsplit
-#define SPIN_DECODE_TO_PARTIAL 2     // the row's merged result goes there instead of to `out`
-
 template <int WAVES, int DEPTH>
 __global__ __launch_bounds__(WAVES * 64) void spin_decode_kernel(
     const uint16_t *__restrict__ q, const uint4 *__restrict__ pool, int64_t pool_slots,
@@ -38,81 +35,9 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_kernel(
     const int32_t *__restrict__ skip, int mode, int nside, float scale_log2e, float *part_ml, float *part_acc, int32_t *tickets,
     uint16_t *__restrict__ out, float *__restrict__ lse, int32_t *status) {
   const int row = blockIdx.x / nsplit;
-  const int split = blockIdx.x - row * nsplit;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform, and so are its page count and its loops
-  const int n = lane & 15;   // column: query head of the group (logits), channel-in-block (output)
-  const int c = lane >> 4;   // token quad (logits) / head quad (output)
-  const int b = row / Hkv;
-  const int h = row - b * Hkv;
-
-  // Pages are dealt round-robin: page p belongs to split p % nsplit and, inside
-  // it, to wavefront (p / nsplit) % WAVES.  The addresses of this wavefront's
-  // slot entries therefore do not depend on the row's page count, and their
-  // load is issued together with it.
-  const int32_t *rslots = slots + (size_t)row * page_stride;
-  const uint16_t *rmask = masks + (size_t)row * page_stride;
-  const int first = wave * nsplit + split, stride = WAVES * nsplit;
-  int np = npages[row];
-  np = np < 0 ? 0 : (np > page_stride ? page_stride : np);
-  // list positions [0, skip_lo) and [np - skip_hi, np) were attended by an earlier launch (the row's
-  // always-attended pages): they keep their place in the dealing but are not fetched or attended here
-  const int32_t *skip_at = skip ? skip + 2 * row : npages + row;   // read either way, in one round trip with the count
-  const int skip_0 = skip_at[0], skip_1 = skip_at[skip ? 1 : 0];
-  const int skip_lo = skip ? skip_0 : 0, skip_hi = skip ? skip_1 : 0;
-  const int keep_end = np - (skip_hi > 0 ? skip_hi : 0);
-
-  // this wavefront's pages: first + i * stride, i < nw; the entries of the first 64 are asked for ahead of all else
-  int p = first + lane * stride;
-  int next_slot = rslots[min(p, page_stride - 1)];
-  unsigned next_mask = rmask[min(p, page_stride - 1)];
-
-  spin_bf16x8 qf[4];
-  load_queries(qf, q, b, h, G, Hq, n, c);
-  softmax_state st;
-  softmax_reset(st);
-
-  // The first wavefront of split s < nside starts from the s-th partial (m, l, O) an earlier launch left for
-  // the row (its always-attended pages, or the first of two passes over the page list) instead of from the
-  // empty state: that partial then is part of the ordinary merge.
-  if ((mode & SPIN_DECODE_FROM_PARTIAL) && split < nside && wave == 0) {
-    const size_t pf = ((size_t)row * pstride + nsplit + split) * G;
-    if (n < G) {
-      st.m = part_ml[(pf + n) * 2];
-      if (c == 0) st.l = part_ml[(pf + n) * 2 + 1];   // the lanes' denominators are summed over c at the end
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (4 * c + i < G) {
-#pragma unroll
-        for (int jn = 0; jn < 8; ++jn) st.acc[jn][i] = part_acc[(pf + 4 * c + i) * SPIN_HEAD_DIM + 16 * jn + n];
-      }
-    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): waited for here, or every page's turn would wait as if they were under way
-  }
-
-  const int nw = np > first ? (np - first + stride - 1) / stride : 0;
-  for (int base = 0; base == 0 || base < nw; base += 64) {
-    const int cnt = min(nw - base, 64);
-    int myslot = 0;
-    unsigned mymask = 0;
-    if (lane < cnt && p >= skip_lo && p < keep_end) {   // the others are attended elsewhere, or past the end of the list
-      if (next_slot < 0 || (int64_t)next_slot >= pool_slots) {
-        spin_raise(status, SPIN_ERR_SLOT_RANGE);        // attends to none of it
-      } else {
-        myslot = next_slot;
-        mymask = next_mask;
-      }
-    }
-    p += 64 * stride;
-    if (base + 64 < nw) {
-      next_slot = rslots[min(p, page_stride - 1)];
-      next_mask = rmask[min(p, page_stride - 1)];
-    }
-    attend_lane_pages<DEPTH>(st, pool, myslot, mymask, cnt, lane, c, qf, scale_log2e);
-  }
-
-  decode_finish<WAVES>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, pstride, part_ml, part_acc, tickets, out,
-                       lse, (mode & SPIN_DECODE_TO_PARTIAL) != 0);
+  decode_row<WAVES, DEPTH>(row, blockIdx.x - row * nsplit, q, pool, pool_slots, slots, masks, npages, page_stride, G, Hq, Hkv,
+                           nsplit, pstride, skip, mode, nside, scale_log2e, part_ml, part_acc, tickets, out, lse, status,
+                           [](int, unsigned mask) { return mask; });
 }
 
 // ---------------------------------------------------------------------------
@@ -210,10 +135,10 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_tokens_kernel(
 // accumulators of the workgroup partials) and the status word are handed in by the two entry points.
 // skip != NULL: the row's always-attended pages were attended by the launch of stages 2+3, whose partial sits
 // behind the splits' partials and whose list positions are named in skip[row][2].
-static int decode_launch(spin_ctx *ctx, int32_t batch, const void *q, const void *kv_pool, int64_t pool_slots,
-                         const int32_t *slots, const uint16_t *valid_mask, const int32_t *npages, void *out,
-                         float *lse, float *part_ml, float *part_acc, int32_t *tickets, int32_t *status,
-                         const int32_t *skip, int mode, int nside, void *stream) {
+int decode_launch(spin_ctx *ctx, int32_t batch, const void *q, const void *kv_pool, int64_t pool_slots,
+                  const int32_t *slots, const uint16_t *valid_mask, const int32_t *npages, void *out, float *lse,
+                  float *part_ml, float *part_acc, int32_t *tickets, int32_t *status, const int32_t *skip, int mode,
+                  int nside, void *stream) {
   const int rows = batch * ctx->cfg.num_kv_heads;
   const int G = ctx->group, nsplit = ctx->splits;
   const int pstride = ctx->pstride;

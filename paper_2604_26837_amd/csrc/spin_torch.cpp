@@ -242,6 +242,8 @@ struct entry<int(A...)> {
     "scores,part_offsets,seq_lens,sel,nsel,dir,leaf_pool," STEP_LISTS ",q,kv_pool,out,lse,workspace")                  \
   E(spin_decode_step, "nnbaiiifiiiL#iisiP#bfaS",                                                                       \
     "q,summaries,chan_idx,part_offsets,seq_lens,scores,sel,nsel,dir,leaf_pool," STEP_LISTS ",kv_pool,out,lse,workspace") \
+  E(spin_gather_decode, "nnbnliiiP#iisisbfaS",                                                                         \
+    "q,row_base,nmiss,miss_pages,miss_slots,kv_pool,slots,page_ids,valid_mask,npages,miss_mask,out,lse,workspace")     \
   E(spin_gather_misses, "nnnliiiP#aS", "row_base,nmiss,miss_pages,miss_slots,kv_pool,workspace")                       \
   E(spin_offload_pages, "nnP#nliiiaS", "kv_pool,row_base,count,pages,slots,workspace")                                 \
   E(spin_split_hits_misses, "nnisiiissS", "page_ids,valid_mask,npages,miss_pages,nmiss,mask_hits,mask_misses")         \

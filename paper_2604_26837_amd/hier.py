@@ -166,11 +166,16 @@ class HierLayer:
             sp.sparse_decode_finish(w.batch, q, self.kv_pool, self.slots, self.mask_misses, self.npages, self.out,
                                     self.lse, self.ws)
             copied = None
+        elif w.partition_tokens >= w.page_tokens:
+            sp.gather_decode(w.batch, q, self.host_kv, self.host_row_base_dev, self.nmiss, self.miss_pages,
+                             self.miss_slots, self.kv_pool, self.slots, self.page_ids, self.valid_mask, self.npages,
+                             self.mask_misses, self.out, self.lse, self.ws)
+            copied = None
         else:
             sp.gather_misses(w.batch, self.host_kv, self.host_row_base_dev, self.nmiss, self.miss_pages,
                              self.miss_slots, self.kv_pool, self.ws)
             copied = None
-        if not self.overlap_hits:
+        if self.copy_mode == "memcpy" or (not self.overlap_hits and w.partition_tokens < w.page_tokens):
             sp.sparse_decode(w.batch, q, self.kv_pool, self.slots, self.valid_mask, self.npages, self.out, self.lse,
                              self.ws)
         if device_step:

@@ -1,0 +1,44 @@
+"""The copy of the missed pages with stage 4 beside it, against the copy and then stage 4: the same lists and slots, the
+attention to the tolerance of a bf16 output of two summation orders."""
+import pytest
+import torch
+
+from paper_2604_26837_amd import hier, synth
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
+    dict(lens=(5000, 9001, 700), topk=40),
+    dict(lens=(20000,), topk=200, kv=1, heads=16),                    # several splits, one row, 16 heads
+    dict(lens=(9000, 4000), part=64, topk=9, score=synth.SCORE_REPMAX, incl=False, recent=6),
+    dict(lens=(300, 40), topk=30),                                    # every page attended
+])
+@pytest.mark.parametrize("over", [dict(), dict(lru_policy=1), dict(decode_splits=3, decode_waves=4)])
+def test_equals_the_copy_and_then_stage_4(kw, over):
+    part = kw.get("part", 16)
+    w = synth.Workload(name="budget", seq_lens=kw["lens"], num_q_heads=kw.get("heads", 8), num_kv_heads=kw.get("kv", 2),
+                       partition_tokens=part, score_kind=kw.get("score", synth.SCORE_MINMAX),
+                       reps_per_partition=4 if part == 64 else 1, topk=kw["topk"], topk_includes_forced=kw.get("incl", True),
+                       sink_pages=1, recent_pages=kw.get("recent", 2), planted_frac=0.0, seed=part + kw["topk"])
+    a, b = (hier.HierLayer(w, copy_mode="gather", **over) for _ in range(2))
+    sp = b.spin
+    qs = [a.q0, a.q0] + [synth.make_queries_on_device(w, s, "cuda:0") for s in range(3)]     # all missed, none, some
+    some = 0
+    for t, q in enumerate(qs):
+        a.step(q, t, count=False)
+        sp.score_partitions(w.batch, q, b.summaries, None, b.part_offsets, b.seq_lens, b.scores, b.ws)
+        sp.select_topk(w.batch, b.scores, b.part_offsets, b.seq_lens, b.sel, b.nsel, b.ws)
+        sp.resolve_slots(w.batch, t, b.sel, b.nsel, b.seq_lens, b.dir, b.leaf_pool, b.slots, b.page_ids, b.valid_mask,
+                         b.npages, b.ws, rev_table=b.rev, slot_base=b.slot_base, miss_pages=b.miss_pages,
+                         miss_slots=b.miss_slots, nmiss=b.nmiss)
+        sp.gather_misses(w.batch, b.host_kv, b.host_row_base_dev, b.nmiss, b.miss_pages, b.miss_slots, b.kv_pool, b.ws)
+        sp.sparse_decode(w.batch, q, b.kv_pool, b.slots, b.valid_mask, b.npages, b.out, b.lse, b.ws)
+        torch.cuda.synchronize()
+        assert a.status() == 0 and b.status() == 0
+        for n in ("slots", "page_ids", "valid_mask", "npages", "nmiss", "miss_pages", "miss_slots", "kv_pool"):
+            assert torch.equal(getattr(a, n), getattr(b, n)), (t, n)
+        # probabilities rounded to bf16, and the output once more; lse sums them unrounded
+        assert (a.out.float() - b.out.float()).abs().max() <= 2 ** -6 * b.out.float().abs().max(), t
+        assert (a.lse - b.lse).abs().max() <= 4e-5, t
+        some += int(a.nmiss.sum()) > 0
+    assert int(a.nmiss.numel()) and some >= 1
