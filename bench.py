@@ -816,8 +816,9 @@ def main():
         # the fused launch's instantiation: scores (beyond 16384 partitions tile maxima) per thread, one-page partitions, tiles
         tiles = parts > 16384
         per_thread = next((k for k in (4, 8, 16, 32) if parts <= 512 * k), 8 if parts <= 65536 else 16)
+        one_page = str(w.partition_tokens == 16).lower()
         kernel = f"spin_select_decode_tokens_kernel<{per_thread}, {str(tiles).lower()}>" if fused_24 and w.partition_tokens < 16 else \
-            f"spin_select_decode_kernel<{per_thread}, {str(w.partition_tokens == 16).lower()}, {str(tiles).lower()}>" if fused_24 else \
+            f"spin_select_decode_kernel<{per_thread}, {one_page}, {str(tiles).lower()}, false, 0>" if fused_24 else \
             "spin_decode_tokens_kernel<8>" if w.partition_tokens < 16 else \
             f"spin_decode_kernel<{args.decode_waves or 8}, {args.decode_depth or 2}>"
         traffic, traffic_note = read_traffic(os.path.join(ROOT, "profiles", f"{args.workload}_stage_kernels_pmc.txt"),

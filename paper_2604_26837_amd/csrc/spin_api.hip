@@ -111,8 +111,8 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   // Rows beyond 16384 partitions go by the maxima of their score tiles.  In the launch of stages 2 to 4 so do those beyond
   // 8192, 32 of which to a thread take it long, where no more tiles than there are need be read, and of whole pages where
   // rows are few (a batch of many has short ones as well, which are selected faster from their scores, and stage 1 writes
-  // the maxima of all).  Steps, us, from scores / maxima: 64 rows of 9000 tokens, 512 attended 26.9 / 22.8, of 16000 30.4 /
-  // 25.9, with 2048 attended 35.4 / 38.7; 8 rows of 16384 pages 28.1 / 27.0, 32 rows 61.2 / 59.1; 64 ragged rows 42.8 / 43.6, 256
+  // the maxima of all).  Steps, us, from scores / maxima: 64 rows of 9000 tokens, 512 attended 26.9 / 23.9, of 16000 30.4 /
+  // 26.2, with 2048 attended 35.4 / 38.7; 8 rows of 16384 pages 28.1 / 27.0, 32 rows 61.2 / 59.1; 64 ragged rows 42.8 / 43.6, 256
   // 133.5 / 137.4.
   x->tile_log = x->rows_per_part == 4 ? 2 : x->rows_per_part == 2 ? 3 : 4;
   const bool maxima = x->max_parts <= 131072 && !c->variable_partitions;

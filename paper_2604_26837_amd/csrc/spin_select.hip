@@ -58,9 +58,7 @@ __global__ __launch_bounds__(256) void spin_tile_max_kernel(const float *__restr
 // One workgroup per row.  MPT: maxima per thread.  RESOLVE: the workgroup goes on to stage 3 for its row (same device
 // function as the stage call).
 // Latency bounds it: a dependent load each for maxima, scores and leaf entries, about 14 barriers, and whatever every
-// wavefront does for itself.  Tiles and listed candidates are chosen by select_elements (8 rows of 62500 and 64 of 65536:
-// as fast as by radix digits here, but it reads no tile too many: 1024 tiles and a slack were two rounds of loads, not
-// one, where 512 threads fetch them).  With a chip-wide histogram of the leading 12 key bits in its place one compute unit
+// wavefront does for itself.  With a chip-wide histogram of the leading 12 key bits in its place one compute unit
 // walked the row's scores, and rows with many scores in the threshold's bin were searched whole: stages 2+3, 8 rows
 // of 62500, k' = 244: 28.8 -> 12.7 us; 64 rows of 65536, k' = 1024: 22.8 -> 20.0; and stage 1, which counted the
 // histogram in LDS, 42.7 -> 39.5 us on 8 rows of 62500.

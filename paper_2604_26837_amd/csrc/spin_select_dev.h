@@ -265,6 +265,52 @@ __device__ inline float key_floor_score(uint32_t K, bool low_end) {
 }
 #define SPIN_KEY_MINUS_INF 0x007fffffu
 
+// the candidates that are left, in partition order
+template <int BLOCK, int CAP>
+struct elements_lds {
+  kth_lds<BLOCK> kth;
+  uint2 wtot[BLOCK / 64];
+  uint32_t key[CAP];
+  int32_t id[CAP];
+};
+
+// The kprime best of the `total` entries of an ordered list in LDS, stored ascending at rsel[first ..].
+template <int BLOCK, int CAP, typename ROW>
+__device__ __forceinline__ void pick_from_list(int total, int kprime, int first, const ROW &rsel,
+                                      elements_lds<BLOCK, CAP> &s) {
+  const int tid = threadIdx.x;
+  auto pick_list = [&](auto entries) {
+    constexpr int E = decltype(entries)::value;  // list entries per thread
+    uint32_t T;
+    unsigned need_eq;
+    uint32_t key[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) key[j] = tid * E + j < total ? s.key[tid * E + j] : 0u;
+    const uint32_t have = range_bits<E>(tid * E, 0, total);
+    block_kth<BLOCK, E>(key, have, kprime, 0, s.kth, T, need_eq);
+    uint32_t gt = 0, eq = 0;
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      gt |= key[j] > T ? 1u << j : 0u;
+      eq |= key[j] == T ? 1u << j : 0u;
+    }
+    int pos, picked, eq_picked;
+    uint32_t pick = ordered_picks<BLOCK>(gt & have, eq & have, need_eq, s.wtot, pos, picked, eq_picked);
+    pos += first;
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+      if ((pick >> j) & 1u) {
+        rsel.put(pos, s.id[tid * E + j]);
+        ++pos;
+      }
+  };
+  constexpr int LPT = CAP / BLOCK;
+  if (total <= BLOCK) pick_list(std::integral_constant<int, 1>());
+  else if (LPT > 2 && total <= 2 * BLOCK) pick_list(std::integral_constant<int, 2>());
+  else if (LPT > 4 && total <= 4 * BLOCK) pick_list(std::integral_constant<int, 4>());
+  else pick_list(std::integral_constant<int, LPT>());
+}
+
 // ---------------------------------------------------------------------------
 // Rows whose scores a workgroup holds in registers.
 #define TAIL_BINS 512
@@ -657,12 +703,7 @@ __device__ __forceinline__ int select_reg_row(
 #define ROW_BINS 4096
 #define ROW_LIST 2048
 template <int BLOCK, int CAP>
-struct tiles_lds {
-  reg_row_lds<BLOCK> row;
-  uint2 wtot[BLOCK / 64];
-  float least[BLOCK / 64];
-  alignas(16) float score[CAP];   // the candidates that are left, in partition order
-  int32_t id[CAP];
+struct tiles_lds : elements_lds<BLOCK, CAP> {
   uint16_t tile[TILE_LIST];
 };
 // LDS of select_whole_row
@@ -844,33 +885,35 @@ __device__ __forceinline__ void select_whole_row(const float *__restrict__ rs, u
 }
 
 // False (for the whole workgroup, nothing stored): more scores than the list holds.
-// `top`: the calling thread's MPT maxima, `cand` those of tiles of candidates only.
 template <int BLOCK, int MPT, int CAP, typename ROW>
-__device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs, float (&top)[MPT],
+__device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs, const uint32_t (&top)[MPT],
                                            typename key_bits<MPT>::type cand, int t_lo, int t_hi, int gs_log,
-                                           const sel_plan &pl, const ROW &rsel, tiles_lds<BLOCK, CAP> &s) {
+                                           int slack, const sel_plan &pl, const ROW &rsel, tiles_lds<BLOCK, CAP> &s) {
   constexpr int NW = BLOCK / 64;
+  typedef typename key_bits<MPT>::type M;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gs = 1 << gs_log, kprime = pl.kprime, m0 = tid * MPT;
+  uint32_t T0 = 0;
+  unsigned need_eq = 0;
+  if (t_hi - t_lo >= kprime) block_kth<BLOCK, MPT>(top, cand, kprime, slack, s.kth, T0, need_eq);
   // ascending list of the tiles to read, the one that straddles either end of the candidates among them (both
   // ends in one tile: that one)
   const int has_lo = (pl.nf_lo & (gs - 1)) ? 1 : 0, has_hi = (pl.first_hi & (gs - 1)) && t_hi >= t_lo ? 1 : 0;
-  const bool bound = t_hi - t_lo >= kprime;            // uniform
-  int ntiles = has_lo + (bound ? kprime : max(t_hi - t_lo, 0));
-  float least = __builtin_inff();
-  if (bound) {
-    select_elements<BLOCK, MPT>(top, cand, 0, m0, t_lo, t_hi, kprime, s.row, [&](int pos, int k) {
-      if (has_lo + pos < TILE_LIST) s.tile[has_lo + pos] = (uint16_t)(m0 + k);
-      float f = top[0];                                // (k is no constant where a thread has many)
+  M gt = 0, eq = 0;
 #pragma unroll
-      for (int j = 1; j < MPT; ++j) f = k == j ? top[j] : f;
-      least = fminf(least, f);
-    });
-    least = -spin_wave_max(-least);
-    if (lane == 0) s.least[wave] = least;
-  } else {
-    for (int t = t_lo + tid; t < t_hi; t += BLOCK)
-      if (has_lo + t - t_lo < TILE_LIST) s.tile[has_lo + t - t_lo] = (uint16_t)t;
+  for (int j = 0; j < MPT; ++j) {
+    gt |= top[j] > T0 ? (M)1 << j : (M)0;
+    eq |= top[j] == T0 ? (M)1 << j : (M)0;
+  }
+  int pos, ntiles, eq_tiles;
+  M pick = ordered_picks<BLOCK>((M)(gt & cand), (M)(eq & cand), need_eq, s.wtot, pos, ntiles, eq_tiles);
+  ntiles += has_lo;
+  pos += has_lo;
+  while (pick) {
+    const int j = ffs_bits(pick) - 1;
+    pick &= pick - 1;
+    if (pos < TILE_LIST) s.tile[pos] = (uint16_t)(m0 + j);
+    ++pos;
   }
   if (tid == 0) {
     if (has_lo) s.tile[0] = (uint16_t)(t_lo - 1);
@@ -878,8 +921,8 @@ __device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs
   }
   ntiles = min(ntiles + has_hi, TILE_LIST);
   __syncthreads();
-  const float bf = bound ? -spin_wave_max(-s.least[lane % NW]) : -__builtin_inff();
-  const bool all = bf == -__builtin_inff();            // (NaN scores rank at -inf and would fail the comparison)
+  const bool all = T0 <= SPIN_KEY_MINUS_INF;           // (NaN scores rank at -inf and would fail the comparison)
+  const float bf = key_floor_score(T0, true);
   const int q_log = gs_log - 2, nquads = ntiles << q_log;
   // Four scores (a quad) per lane and load, neighbouring lanes neighbouring quads: a wavefront's load touches as few
   // lines as there are, which matters because the one compute unit that fetches k' scattered lines is bound by them
@@ -942,7 +985,7 @@ __device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           if ((keep[j] >> e) & 1u) {
-            s.score[to] = f[e];
+            s.key[to] = score_key(f[e]);
             s.id[to] = p[j] + e;
             ++to;
           }
@@ -955,21 +998,7 @@ __device__ __forceinline__ bool list_by_tile_maxima(const float *__restrict__ rs
   else if (nquads <= BLOCK * 5) gather(std::integral_constant<int, 5>());
   else gather(std::integral_constant<int, 9>());
   if (total > CAP) return false;
-  auto pick = [&](auto entries) {
-    constexpr int E = decltype(entries)::value;        // list entries per thread
-    const int c0 = tid * E;
-    float f[E];
-#pragma unroll
-    for (int j = 0; j < E; j += 4) {                   // (what lies past the list's end is masked)
-      const float4 v = *(const float4 *)(s.score + c0 + j);
-      f[j] = v.x; f[j + 1] = v.y; f[j + 2] = v.z; f[j + 3] = v.w;
-    }
-    select_elements<BLOCK, E>(f, range_bits<E>(c0, 0, total), 0, c0, 0, total, kprime, s.row,
-                              [&](int pos, int k) { rsel.put(pl.nf_lo + pos, s.id[c0 + k]); });
-  };
-  static_assert(CAP / BLOCK == 4 || CAP / BLOCK == 8, "one or two quads per thread");
-  if (CAP == 4 * BLOCK || total <= 4 * BLOCK) pick(std::integral_constant<int, 4>());
-  else pick(std::integral_constant<int, CAP / BLOCK>());
+  pick_from_list<BLOCK, CAP>(total, kprime, pl.nf_lo, rsel, s);
   return true;
 }
 
@@ -993,31 +1022,43 @@ __device__ __forceinline__ void select_by_tile_maxima(const float *__restrict__ 
   const int gs = 1 << gs_log, kprime = pl.kprime;
   const int t_lo = (pl.nf_lo + gs - 1) >> gs_log, t_hi = pl.first_hi >> gs_log;   // tiles of candidates only
   const int m0 = tid * MPT;
-  float top[MPT];
+  uint32_t top[MPT];
 #pragma unroll
   for (int j = 0; j < MPT / 4; ++j) {
-    top[4 * j] = maxima[j].x; top[4 * j + 1] = maxima[j].y; top[4 * j + 2] = maxima[j].z; top[4 * j + 3] = maxima[j].w;
+    top[4 * j] = score_key(maxima[j].x);
+    top[4 * j + 1] = score_key(maxima[j].y);
+    top[4 * j + 2] = score_key(maxima[j].z);
+    top[4 * j + 3] = score_key(maxima[j].w);
   }
   const M cand = range_bits<MPT>(m0, t_lo, t_hi);
   // Scores above the bound: all candidates where there is none, else a share of 1 - k'/T of the T tiles holds none, so
-  // that there are about T ln(T / (T - k')) where scores come in no order.
+  // that there are about T ln(T / (T - k')) where scores come in no order.  The search for the bound is shorter with a
+  // slack of an eighth (1152 tiles instead of 1024: one round of loads either way), which is left out where the list
+  // would not hold the scores of so many (64 rows of 9000, k' 512: step 26.3 -> 23.9 us; stage 2 of 2 rows of 65536, k'
+  // 2560: 26.2 -> 22.0).
   const int T = t_hi - t_lo;
-  const bool whole = pl.first_hi - pl.nf_lo > CAP &&                               // block-uniform
-      (kprime >= T || kprime + 2 > TILE_LIST ||
-       (float)T * (__builtin_amdgcn_logf((float)T) - __builtin_amdgcn_logf((float)(T - kprime))) > CAP * 1.4427f);
-  if (!whole && list_by_tile_maxima<BLOCK, MPT, CAP>(rs, top, cand, t_lo, t_hi, gs_log, pl, rsel, s)) return;
-  // from the least to the greatest of the tiles' maxima; the candidates of the tiles that straddle either end may be greater
-  uint32_t kmx = 0u, kmn = 0xffffffffu;
+  auto fits = [&](int tiles) {                                                     // block-uniform
+    return tiles < T && tiles + 2 <= TILE_LIST &&
+           (float)T * (__builtin_amdgcn_logf((float)T) - __builtin_amdgcn_logf((float)(T - tiles))) <= CAP * 1.4427f;
+  };
+  const int slack = fits(kprime + (kprime >> 3)) ? kprime >> 3 : 0;
+  const bool whole = pl.first_hi - pl.nf_lo > CAP && !fits(kprime);
+  if (whole) {
+    uint32_t kmx = 0u, kmn = 0xffffffffu;
 #pragma unroll
-  for (int j = 0; j < MPT; ++j)
-    if ((cand >> j) & 1u) { kmx = max(kmx, score_key(top[j])); kmn = min(kmn, score_key(top[j])); }
-  kmx = spin_wave_max_u32(kmx);
-  kmn = spin_wave_min_u32(kmn);
-  __syncthreads();                                     // (the list's scratch may still be read)
-  if (lane == 0) s.wtot[wave] = make_uint2(kmx, kmn);
+    for (int j = 0; j < MPT; ++j)
+      if ((cand >> j) & 1u) { kmx = max(kmx, top[j]); kmn = min(kmn, top[j]); }
+    kmx = spin_wave_max_u32(kmx);
+    kmn = spin_wave_min_u32(kmn);
+    if (lane == 0) { s.kth.wmax[wave] = kmx; s.kth.wmin[wave] = kmn; }
+  } else if (list_by_tile_maxima<BLOCK, MPT, CAP>(rs, top, cand, t_lo, t_hi, gs_log, slack, pl, rsel, s)) {
+    return;
+  }
   __syncthreads();
-  kmx = spin_wave_max_u32(s.wtot[lane % NW].x);
-  kmn = spin_wave_min_u32(s.wtot[lane % NW].y);
+  // from the least to the greatest of the tiles' maxima, which block_kth leaves in LDS as well; the candidates of the
+  // tiles that straddle either end may be greater
+  uint32_t kmx = spin_wave_max_u32(s.kth.wmax[lane % NW]);
+  const uint32_t kmn = spin_wave_min_u32(s.kth.wmin[lane % NW]);
   const int p = ((lane & 16 ? t_hi : t_lo - 1) << gs_log) + (lane & (gs - 1));
   kmx = max(kmx, spin_wave_max_u32(p >= pl.nf_lo && p < pl.first_hi ? score_key(rs[p]) : 0u));
   __syncthreads();
