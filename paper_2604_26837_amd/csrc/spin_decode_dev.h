@@ -334,6 +334,7 @@ __device__ __forceinline__ bool decode_finish(softmax_state &st, int row, int sp
 
 #define SPIN_DECODE_FROM_PARTIAL 1   // the row's first wavefront starts from the partial at index nsplit
 #define SPIN_DECODE_TO_PARTIAL 2     // the row's merged result goes there instead of to `out`
+#define SPIN_DECODE_LISTED 4         // rows without a page in the list are left alone
 
 // The part of a row's pages that workgroup `split` of it attends (the kernel's arguments, see the header of stage 4).
 // only(position, mask): what of the page at that position of the list is attended.
@@ -360,6 +361,7 @@ __device__ __forceinline__ void decode_row(
   const int first = wave * nsplit + split, stride = WAVES * nsplit;
   int np = npages[row];
   np = np < 0 ? 0 : (np > page_stride ? page_stride : np);
+  if ((mode & SPIN_DECODE_LISTED) && np == 0) return;
   // list positions [0, skip_lo) and [np - skip_hi, np) were attended by an earlier launch (the row's
   // always-attended pages): they keep their place in the dealing but are not fetched or attended here
   const int32_t *skip_at = skip ? skip + 2 * row : npages + row;   // read either way, in one round trip with the count

@@ -4,9 +4,12 @@
 // The host link bounds the copy, which a few workgroups keep busy; the rest of the chip waited for it, and all of stage 4
 // came behind.  The workgroups that copy come first in the launch and wait for nothing; those that attend leave the row's
 // merged partial, as the first of two passes over one page list does, and write down the masks of the row's missed pages,
-// which the second launch has as a list of its own: a few pages to a row, not the whole list under masks.
+// which the second launch has as a list of its own: a few pages to a row, not the whole list under masks.  Rows that miss
+// none have their output from the first.
 // Step of 64 rows, 128 pages attended, about 1010 pages missed in all: 207.6 -> 196.9 us (stage 4 behind the copy 16.7 ->
 // 7.1; the copy as before, 160).  With the 64 copying wavefronts in 8 workgroups instead of 16 the copy took 165.
+// 8 rows, 64 pages attended, 82 missed 39.0 -> 35.6; 8 rows, 128 attended, none missed 28.1 -> 28.1 (32.0 with a second pass
+// over empty lists).
 #include "spin_decode_dev.h"
 #include "spin_fetch_dev.h"
 
@@ -19,7 +22,7 @@ __global__ __launch_bounds__(512) void spin_gather_decode_kernel(
     int nsplit, int pstride, int rows, const int32_t *__restrict__ page_ids, uint4 *__restrict__ host_kv,
     const int64_t *__restrict__ row_base, const int32_t *__restrict__ nmiss, const int32_t *__restrict__ miss_pages,
     const int32_t *__restrict__ miss_slots, uint16_t *__restrict__ miss_mask, host_map hm, float scale_log2e, float *part_ml,
-    float *part_acc, int32_t *tickets, int32_t *status) {
+    float *part_acc, int32_t *tickets, uint16_t *__restrict__ out, float *__restrict__ lse, int32_t *status) {
   if (blockIdx.x < COPY_WGS) {
     if (threadIdx.x >= COPY_WAVES * 64) return;          // whole wavefronts: a barrier does not wait for those that have ended
     copy_pages<false, COPY_WAVES>(blockIdx.x, COPY_WGS, host_kv, row_base, nmiss, miss_pages, miss_slots, pool, pool_slots, page_stride,
@@ -33,6 +36,7 @@ __global__ __launch_bounds__(512) void spin_gather_decode_kernel(
   const int32_t *missed = miss_pages + list;
   // both lists ascend by page
   auto hits = [&](int p, unsigned mask) {
+    if (nm == 0) return mask;                            // uniform
     const int32_t page = page_ids[list + p];
     int lo = 0, hi = nm;
     while (lo < hi) {
@@ -44,7 +48,7 @@ __global__ __launch_bounds__(512) void spin_gather_decode_kernel(
     return 0u;
   };
   decode_row<8, 2>(row, at - row * nsplit, q, pool, pool_slots, slots, masks, npages, page_stride, G, Hq, Hkv, nsplit, pstride,
-                   nullptr, SPIN_DECODE_TO_PARTIAL, 0, scale_log2e, part_ml, part_acc, tickets, nullptr, nullptr, status, hits);
+                   nullptr, nm ? SPIN_DECODE_TO_PARTIAL : 0, 0, scale_log2e, part_ml, part_acc, tickets, out, lse, status, hits);
 }
 
 extern "C" int spin_gather_decode(spin_ctx *ctx, int32_t batch, const void *q, const void *host_kv, const int64_t *row_base,
@@ -70,9 +74,9 @@ extern "C" int spin_gather_decode(spin_ctx *ctx, int32_t batch, const void *q, c
               ctx->page_stride, ctx->group, c.num_q_heads, c.num_kv_heads, ctx->splits, ctx->pstride, rows, page_ids,
               (uint4 *)const_cast<void *>(host_kv), row_base, nmiss, miss_pages, miss_slots, miss_mask,
               host_map{ctx->cpu_table, ctx->cpu_table_entries, ctx->cpu_pages}, ctx->scale * 1.4426950408889634f, ml, acc,
-              tickets, status);
+              tickets, (uint16_t *)out, lse, status);
   const int st = spin_launch_status();
   if (st != SPIN_OK) return st;
   return decode_launch(ctx, batch, q, kv_pool, pool_slots, miss_slots, miss_mask, nmiss, out, lse, ml, acc, tickets, status,
-                       nullptr, SPIN_DECODE_FROM_PARTIAL, 1, stream);
+                       nullptr, SPIN_DECODE_FROM_PARTIAL | SPIN_DECODE_LISTED, 1, stream);
 }
