@@ -320,7 +320,7 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
       if (found >= 0 && (int64_t)found < a.pool_slots) {
         myslot = found;
         mymask = found_mask;
-      } else if (v >= nf) {
+      } else if (found >= 0) {                            // (one that is missing has been reported)
         spin_raise(a.status, SPIN_ERR_SLOT_RANGE);        // attends to none of it
       }
     }

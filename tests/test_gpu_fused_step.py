@@ -200,6 +200,33 @@ def test_pages_that_are_missing_or_outside_the_pool(kw):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
+    dict(lens=(5000, 3000)),                                          # stage 1 in the same launch
+    dict(lens=(40000, 3000)),                                         # the first forced pages asked for ahead
+    dict(lens=(9000, 3000), part=64, topk=9, incl=False),
+    dict(lens=(300000, 3000)),                                        # by the tiles' maxima
+    dict(lens=(9000, 3000), part=4, topk=90),
+])
+def test_forced_pages_that_are_missing_or_outside_the_pool(kw):
+    for page in (0, 1, -5, -1):                                       # of the sink's two and the window's five
+        for slot, code in ((-1, -6), (1 << 30, -7)):
+            layer, _ = runner.build_device_layer(_workload(**dict(dict(topk=30), **kw)))
+            layer.step(layer.q0)
+            page %= -(-kw["lens"][0] // 16)
+            chunk = int(layer.dir[1, page // layer.w.leaf_entries])   # row 1: request 0, head 1
+            layer.leaf_pool[chunk, page % layer.w.leaf_entries] = slot
+            layer.step(layer.q0)
+            want = {n: getattr(layer, n).clone() for n in LISTS + ("out",)}
+            assert layer.status() == code
+            layer.spin.workspace_init(layer.ws)
+            layer.step2(layer.q0)
+            assert layer.status() == code, (page, slot)
+            for n in LISTS:
+                assert torch.equal(want[n], getattr(layer, n)), (page, slot, n)
+            assert (layer.out.float() - want["out"].float()).abs().max() <= 2 ** -6 * want["out"].float().abs().max()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kw", [dict(lens=(9001, 4000)), dict(lens=(20001, 4000), part=1, score=synth.SCORE_SKETCH)])
 def test_replays_of_a_graph(kw):
     layer, _ = runner.build_device_layer(_workload(topk=64, **kw))
