@@ -202,12 +202,14 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
   spin_bf16x8 qf[4];
   page_regs rf;
   unsigned rf_mask = 0;
+  int rf_slot = 0;
   auto ask_ahead = [&](const asked_page &p) {
     const int32_t slot = __builtin_amdgcn_readfirstlane(a.leaf_pool[p.leaf]);
     const bool ok = p.there && slot >= 0 && (int64_t)slot < a.pool_slots;
     rf_mask = ok ? page_mask(p.page, N) : 0u;
-    load_k_tile(rf, a.pool, ok ? slot : 0, lane, rf_mask);
-    load_v_tile(rf, a.pool, ok ? slot : 0, lane, rf_mask);
+    rf_slot = ok ? slot : 0;
+    load_k_tile(rf, a.pool, rf_slot, lane, rf_mask);
+    load_v_tile(rf, a.pool, rf_slot, lane, rf_mask);
     __builtin_amdgcn_sched_barrier(0);
   };
 
@@ -281,10 +283,12 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
   }
   __syncthreads();
 
-  // The sink pages open the list and the recent ones close it.
+  // The sink pages open the list and the recent ones close it (but for a row longer than its partition table, whose list
+  // may be without the recent ones).
   softmax_state st;
   softmax_reset(st);
-  const int nf = min(fs.nlo + fs.nhi, np);
+  const bool whole = fs.nlo + fs.nhi <= np;
+  const int nlo = whole ? fs.nlo : 0, nf = whole ? fs.nlo + fs.nhi : 0;
   const int cnt_all = np > first ? (np - first + stride - 1) / stride : 0;
   const res_out out = res_row_out(a.slots, a.page_ids, a.valid_mask, a.npages, row, a.page_stride);
   for (int base = 0; base == 0 || base < cnt_all; base += 64) {
@@ -295,7 +299,7 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     [[maybe_unused]] unsigned found_mask = 0;
     if (lane < cnt) {
       const int v = first + (base + lane) * stride;
-      at = v < nf ? (v < fs.nlo ? v : max(np - fs.nhi + (v - fs.nlo), 0)) : fs.nlo + (v - nf);
+      at = v < nf ? (v < nlo ? v : np - nf + v) : nlo + (v - nf);
       if constexpr (PAGES) {
         page = l_page[at];
         if (with_leaf) {
@@ -324,7 +328,9 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
         spin_raise(a.status, SPIN_ERR_SLOT_RANGE);        // attends to none of it
       }
     }
-    const int from = base == 0 && asked ? 1 : 0;          // the first one was asked for already
+    // the first one was asked for already, if it is the listed one
+    const int from = base == 0 && asked && __builtin_amdgcn_readlane(myslot, 0) == rf_slot &&
+                     __builtin_amdgcn_readlane((int)mymask, 0) == (int)rf_mask ? 1 : 0;
     attend_lane_pages<2>(st, a.pool, myslot, mymask, from, cnt, lane, c, qf, a.scale_log2e, [&] {
       if (from && cnt > 0) tile_attend(st, tile_logits(rf, qf), rf, rf_mask, c, a.scale_log2e);
       if constexpr (PAGES) {                              // the row's lists: its own entries from every wavefront

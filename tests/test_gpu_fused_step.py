@@ -227,6 +227,30 @@ def test_forced_pages_that_are_missing_or_outside_the_pool(kw):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
+    dict(lens=(40000, 3000), topk=30),                                # its recent pages are not in the list
+    dict(lens=(40000, 3000), topk=300, sink=100, recent=200),         # nor are there as many pages as the windows have
+    dict(lens=(9000, 3000), part=64, topk=9),
+    dict(lens=(9000, 3000), part=64, topk=20, sink=30, recent=60),
+    dict(lens=(300000, 3000), topk=30),
+    dict(lens=(5000, 300), topk=30, sink=10, recent=30),
+])
+@pytest.mark.parametrize("splits", [0, 1, 3])
+def test_a_row_longer_than_its_partition_table(kw, splits):
+    layer, _ = runner.build_device_layer(_workload(**kw), decode_splits=splits)
+    layer.seq_lens[1] = kw["lens"][0] - 100
+    layer.step(layer.q0)
+    lists = {n: getattr(layer, n).clone() for n in LISTS}
+    out, code = layer.out.clone(), layer.status()
+    layer.spin.workspace_init(layer.ws)
+    layer.step2(layer.q0)
+    assert layer.status() == code
+    for n in LISTS:
+        assert torch.equal(lists[n], getattr(layer, n)), n
+    assert (layer.out.float() - out.float()).abs().max() <= 2 ** -6 * out.float().abs().max()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kw", [dict(lens=(9001, 4000)), dict(lens=(20001, 4000), part=1, score=synth.SCORE_SKETCH)])
 def test_replays_of_a_graph(kw):
     layer, _ = runner.build_device_layer(_workload(topk=64, **kw))
