@@ -232,8 +232,10 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
       if (tid < RES_DIR_LDS) held_words[tid] = mydir;
     } else {
       // the selection's plan: partitions are pages
-      const int P = min(min((N + 15) >> 4, PP), BLOCK * KPT);
-      const sel_plan pl = plan_of(P, min(fs.nlo, P), min(fs.recent_begin, P), a.topk, a.includes_forced, a.sel_stride);
+      const int pages = min((N + 15) >> 4, PP), P = min(pages, BLOCK * KPT);
+      // (of a row beyond the context's longest the first BLOCK * KPT pages are kept, but all its forced ones count, as in stage 2)
+      const int beyond = a.includes_forced ? pages - max(min(fs.recent_begin, pages), P) : 0;
+      const sel_plan pl = plan_of(P, min(fs.nlo, P), min(fs.recent_begin, P), a.topk - beyond, a.includes_forced, a.sel_stride);
       with_leaf = ahead && P <= 8 * BLOCK;
       if constexpr (SCORE != 0) {
         score_row<SCORE == SPIN_SCORE_MINMAX + 1>(qf, a.summ, (size_t)Hkv * off + (size_t)h * PP, PP, a.reps, G, wave, lane, s_scores,

@@ -17,6 +17,10 @@ def _workload(lens, part=16, topk=40, incl=True, sink=2, recent=5, heads=8, kv=2
 
 
 def _same_as_stage_calls(layer, q):
+    _same(layer, q, layer.step, layer.step2)
+
+
+def _same(layer, q, stage_calls, one_launch):
     def run(step):
         for n in LISTS:
             getattr(layer, n).fill_(77)
@@ -27,7 +31,7 @@ def _same_as_stage_calls(layer, q):
         assert layer.status() == 0
         return {n: getattr(layer, n).clone() for n in LISTS + ("out", "lse")}
 
-    want, got, again = run(layer.step), run(layer.step2), run(layer.step2)
+    want, got, again = run(stage_calls), run(one_launch), run(one_launch)
     for n in LISTS:
         assert torch.equal(want[n], got[n]), n
     for n in LISTS + ("out", "lse"):                                  # (the second: the row tickets are left cleared)
@@ -248,6 +252,36 @@ def test_a_row_longer_than_its_partition_table(kw, splits):
     for n in LISTS:
         assert torch.equal(lists[n], getattr(layer, n)), n
     assert (layer.out.float() - out.float()).abs().max() <= 2 ** -6 * out.float().abs().max()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw,longest", [
+    (dict(lens=(40000, 3000), topk=30, leaf=4096), 32000),            # 2500 pages, of which 4 per thread are 2048
+    (dict(lens=(40000, 3000), topk=30, leaf=4096, incl=False), 32000),
+    (dict(lens=(32800, 3000), topk=30, leaf=4096, recent=9), 32000),  # 2050: some of the recent ones are kept
+    (dict(lens=(70000, 66000), topk=300, leaf=8192, sink=100, recent=250), 60000),    # 8
+    (dict(lens=(40000, 3000), topk=30, leaf=4096, part=32), 16 * 2048),
+])
+def test_a_row_longer_than_its_context(kw, longest):
+    w = _workload(**kw)
+    dd = synth.generate_on_device(w)
+    layer = runner.LayerState.from_natural_pool(w, dd.slot_of, dd.pool, max_context=longest)
+    sp, gen = layer.spin, torch.Generator(device="cuda:0")
+    gen.manual_seed(3)
+    layer.scores.normal_(generator=gen)
+
+    def stage_calls(q):
+        sp.select_topk(w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.ws)
+        sp.resolve_slots(w.batch, 0, layer.sel, layer.nsel, layer.seq_lens, layer.dir, layer.leaf_pool, layer.slots,
+                         layer.page_ids, layer.valid_mask, layer.npages, layer.ws)
+        sp.sparse_decode(w.batch, q, layer.kv_pool, layer.slots, layer.valid_mask, layer.npages, layer.out, layer.lse, layer.ws)
+
+    def one_launch(q):
+        sp.select_resolve_decode(w.batch, layer.scores, layer.part_offsets, layer.seq_lens, layer.sel, layer.nsel, layer.dir,
+                                 layer.leaf_pool, layer.slots, layer.page_ids, layer.valid_mask, layer.npages, q,
+                                 layer.kv_pool, layer.out, layer.lse, layer.ws)
+
+    _same(layer, dd.q, stage_calls, one_launch)
 
 
 @pytest.mark.gpu
