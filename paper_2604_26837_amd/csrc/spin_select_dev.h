@@ -377,6 +377,11 @@ __device__ __forceinline__ int tail_bin_of_rank(const int *bins, int &rank, int 
 // with k 1500 13.3 -> 10.2.  Slower where many scores tie at the threshold (128 rows of 2048 with steps of a quarter of their
 // deviation 6.7 -> 8.4, 64 of 8192 9.3 -> 10.8) or more outliers than there are parts are a million times the others
 // (256 of 16384 10.8 -> 16.2).
+// Pinned partitions (scores of +inf) may leave no part of the row without one.  Then the upper end is the greatest finite
+// score, and with more of them than are wanted they are the only candidates.  Stage 2 alone, us, with 10 / 64 / 200 of them
+// in each row, against a search over the whole row: 128 rows of 2048, k' 116 5.2 / 5.6 / 6.3 -> 4.0 / 4.4 / 4.1; 256 of 16384
+// 16.7 / 17.2 / 13.1 -> 8.2 / 8.6 / 8.5 (none: 7.6).  Few of few, where that search is short as well: 8 rows of 256, k' 20,
+// 2 / 10 4.4 / 4.6 -> 3.8 / 3.8.
 template <int BLOCK, int KPT, typename PUT>
 __device__ __forceinline__ void select_elements(float (&f)[KPT], typename key_bits<KPT>::type cand,
                                                 typename key_bits<KPT>::type forced, int c0, int nf_lo, int first_hi,
@@ -449,30 +454,59 @@ __device__ __forceinline__ void select_elements(float (&f)[KPT], typename key_bi
     top = -spin_wave_max(-counts(top));
   }
   lo = spin_readlane(lo, 0);
-  const float spread = spin_readlane(top, 0) - lo;
+  top = spin_readlane(top, 0);
+  M member = kprime > 0 ? cand : 0;
+  if (__builtin_expect(kprime > 0 && top == inf && lo < inf, 0)) {   // uniform: pinned partitions in every part
+    float finite = -inf;
+    M pinned = 0;
+#pragma unroll
+    for (int k = 0; k < KPT; ++k) {
+      pinned |= f[k] == inf ? (M)1 << k : (M)0;
+      finite = fmaxf(finite, f[k] == inf ? -inf : f[k]);
+    }
+    finite = spin_wave_max(finite);
+    int pins = spin_wave_inclusive_scan(popc_bits(pinned));
+    __syncthreads();                             // the maxima have been read
+    if (lane == 63) {
+      s.top[wave] = finite;
+      s.wtot[wave].x = (uint32_t)pins;
+    }
+    __syncthreads();
+    (void)spin_waves_before<NW>((int)s.wtot[lane % NW].x, wave, pins);
+    if (pins < kprime) top = spin_wave_max(s.top[lane % NW]);    // the greatest finite one: the last step holds little else
+    else member &= pinned;                       // more of them than are wanted: the first ones
+  }
+  const float spread = top - lo;
   // (no group that counts: lo = inf; below 2^-100 the scale might overflow)
   const bool usable = kprime > 0 && spread > 0x1p-100f && spread < inf;
   const float scale = (float)(TAIL_BINS - 1) * __builtin_amdgcn_rcpf(spread);
   int bin = -1, need = kprime, in_bin = 0;
-  int b[KPT];
-  M sure = forced, member = kprime > 0 ? cand : 0;
+  // (64 scores leave no registers for their steps, which are taken twice then: 32 rows of 40000 20.6 -> 18.1 us)
+  constexpr bool KEPT = KPT <= 32;
+  auto step_of = [&](float v, float by) { return (int)fminf((v - lo) * by, (float)(TAIL_BINS - 1)); };
+  int b[KEPT ? KPT : 1];
+  M sure = forced;
   if (usable) {
 #pragma unroll
     for (int k = 0; k < KPT; ++k) {
-      b[k] = -1;
+      int at = -1;
       if (f[k] >= lo) {
-        b[k] = (int)fminf((f[k] - lo) * scale, (float)(TAIL_BINS - 1));
-        atomicAdd(&s.bins[tail_word(b[k])], 1);
+        at = step_of(f[k], scale);
+        atomicAdd(&s.bins[tail_word(at)], 1);
       }
+      if (KEPT) b[KEPT ? k : 0] = at;
     }
     __syncthreads();
     bin = tail_bin_of_rank(s.bins, need, in_bin);
     if (bin >= 0) {
+      float again = scale;
+      if (!KEPT) asm volatile("" : "+v"(again));   // (or the compiler would keep them all the same)
       member = 0;
 #pragma unroll
       for (int k = 0; k < KPT; ++k) {
-        sure |= b[k] > bin ? (M)1 << k : (M)0;
-        member |= b[k] == bin ? (M)1 << k : (M)0;
+        const int at = KEPT ? b[KEPT ? k : 0] : f[k] >= lo ? step_of(f[k], again) : -1;
+        sure |= at > bin ? (M)1 << k : (M)0;
+        member |= at == bin ? (M)1 << k : (M)0;
       }
     }
   }

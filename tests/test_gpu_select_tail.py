@@ -1,6 +1,7 @@
 """Stage 2 of rows held in registers, against a sort: the tail's histogram (scores of any spread, few and many outliers, rows
-as long as they may be), more than 64 scores in the threshold's step, scores that are not finite, at the sizes where the
-scores per thread, the groups and the interleaved parts change."""
+as long as they may be), more than 64 scores in the threshold's step, scores that are not finite, pins in every part of the
+row (fewer and more than are wanted), at the sizes where the scores per thread, the groups and the interleaved parts
+change."""
 import numpy as np
 import pytest
 import torch
@@ -25,6 +26,13 @@ def _scores(kind, n, rng):
     elif kind == "inf":
         x[rng.random(n) < 0.01] = np.inf
         x[rng.random(n) < 0.5] = -np.inf
+    elif kind == "pins":
+        x[rng.random(n) < 0.03] = np.inf
+    elif kind == "pins and outliers":
+        x[rng.random(n) < 0.01] *= 1e6
+        x[rng.random(n) < 0.01] = np.inf
+    elif kind == "zeros":
+        x = np.where(rng.random(n) < 0.02, x, np.where(rng.random(n) < 0.5, 0.0, -0.0))
     elif kind == "nan":
         x[rng.random(n) < 0.97] = np.nan
     elif kind == "tiny":
@@ -32,7 +40,8 @@ def _scores(kind, n, rng):
     return x.astype(np.float32)
 
 
-@pytest.mark.parametrize("kind", ["normal", "ties", "spread", "outliers", "close", "rising", "inf", "nan", "tiny"])
+@pytest.mark.parametrize("kind", ["normal", "ties", "spread", "outliers", "close", "rising", "inf", "nan", "tiny", "pins",
+                                  "pins and outliers", "zeros"])
 @pytest.mark.parametrize("pages,topk", [(40, 5), (256, 32), (2048, 62), (2048, 63), (2048, 128), (2047, 1300), (4096, 511),
                                         (4096, 527), (8192, 140), (8191, 4100), (16384, 200), (16384, 3000)])
 def test_against_a_sort(pages, topk, kind):
