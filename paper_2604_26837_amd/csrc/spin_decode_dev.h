@@ -358,10 +358,16 @@ __device__ __forceinline__ void decode_row(
   // load is issued together with it.
   const int32_t *rslots = slots + (size_t)row * page_stride;
   const uint16_t *rmask = masks + (size_t)row * page_stride;
-  const int first = wave * nsplit + split, stride = WAVES * nsplit;
+  // A list of missed pages is short more often than not: it is dealt to a split's wavefronts before the next split's, and
+  // the splits without a page end, so that one of at most WAVES pages is attended by one workgroup, which has nothing to
+  // merge.  (Dealt as a whole row is, 5 missed pages of 8 rows: both launches 15.0 -> 12.9 us, of
+  // 64 rows 21.6 -> 19.7, 50 of 24 rows 17.5 -> 15.6.)
+  const bool listed = (mode & SPIN_DECODE_LISTED) != 0;
+  const int first = listed ? split * WAVES + wave : wave * nsplit + split, stride = WAVES * nsplit;
   int np = npages[row];
   np = np < 0 ? 0 : (np > page_stride ? page_stride : np);
-  if ((mode & SPIN_DECODE_LISTED) && np == 0) return;
+  if (listed && np <= split * WAVES) return;
+  const int parts = listed ? min((np + WAVES - 1) / WAVES, nsplit) : nsplit;
   // list positions [0, skip_lo) and [np - skip_hi, np) were attended by an earlier launch (the row's
   // always-attended pages): they keep their place in the dealing but are not fetched or attended here
   const int32_t *skip_at = skip ? skip + 2 * row : npages + row;   // read either way, in one round trip with the count
@@ -418,7 +424,7 @@ __device__ __forceinline__ void decode_row(
     attend_lane_pages<DEPTH>(st, pool, myslot, mymask, cnt, lane, c, qf, scale_log2e);
   }
 
-  decode_finish<WAVES>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, pstride, part_ml, part_acc, tickets, out,
+  decode_finish<WAVES>(st, row, split, b, h, lane, wave, n, c, G, Hq, parts, pstride, part_ml, part_acc, tickets, out,
                        lse, (mode & SPIN_DECODE_TO_PARTIAL) != 0);
 }
 

@@ -10,6 +10,12 @@
 // 7.1; the copy as before, 160).  With the 64 copying wavefronts in 8 workgroups instead of 16 the copy took 165.
 // 8 rows, 64 pages attended, 82 missed 39.0 -> 35.6; 8 rows, 128 attended, none missed 28.1 -> 28.1 (32.0 with a second pass
 // over empty lists).
+// Copy and stage 4 alone, replayed from a graph, us, one after the other / these two launches, with 0, 5, 20, 50 and 200
+// pages missed in all: 8 rows, 128 attended 10.6 / 10.3, 12.9 / 13.0, 15.3 / 13.3, 20.1 / 15.6, 42.7 / 39.9; 64 rows
+// 15.2 / 15.6, 17.4 / 19.6, 19.9 / 21.0, 24.7 / 24.7, 47.7 / 38.3; 128 rows 26.6 / 26.7, 29.0 / 30.4, 31.3 / 30.7, 36.0 /
+// 32.9, 58.4 / 44.7.  So the few pages of a step that hardly misses cost 64 rows and more 1 to 2 us: their workgroups fill
+// the chip, and those that take the place of the copying ones start behind them.  (At most 168 registers, so that they
+// would fit beside these, spill: 64 rows, none missed 21.3.)
 #include "spin_decode_dev.h"
 #include "spin_fetch_dev.h"
 

@@ -42,3 +42,35 @@ def test_equals_the_copy_and_then_stage_4(kw, over):
         assert (a.lse - b.lse).abs().max() <= 4e-5, t
         some += int(a.nmiss.sum()) > 0
     assert int(a.nmiss.numel()) and some >= 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("over", [dict(), dict(decode_splits=1), dict(decode_splits=5), dict(decode_splits=3, decode_waves=4)])
+def test_lists_of_missed_pages_of_any_length(over):
+    """The missed pages are dealt to the wavefronts of a workgroup before the next workgroup's: lists around the multiples
+    of 4 and 8."""
+    w = synth.Workload(name="budget", seq_lens=(9000, 5000, 2000, 1500), num_q_heads=12, num_kv_heads=3, partition_tokens=16,
+                       score_kind=synth.SCORE_MINMAX, reps_per_partition=1, topk=70, topk_includes_forced=True,
+                       sink_pages=1, recent_pages=2, planted_frac=0.0, seed=11)
+    a = hier.HierLayer(w, copy_mode="gather", **over)
+    sp = a.spin
+    a.step(a.q0, 0, count=False)
+    sp.sparse_decode(w.batch, a.q0, a.kv_pool, a.slots, a.valid_mask, a.npages, a.out, a.lse, a.ws)
+    out, lse, pool = a.out.float(), a.lse.clone(), a.kv_pool.clone()
+    gen = torch.Generator().manual_seed(5)
+    for lens in ([0, 1, 3, 4, 5, 7, 8, 9, 15, 16, 17, 70], [24, 25, 31, 32, 33, 39, 40, 41, 63, 64, 65, 0], [0] * 12):
+        a.nmiss.copy_(torch.tensor(lens, dtype=torch.int32))
+        a.miss_pages.fill_(-1)
+        a.miss_slots.fill_(-1)
+        for r, n in enumerate(lens):                                  # what is said to have been missed is fetched once more
+            at = torch.randperm(70, generator=gen)[:n].sort().values.cuda()
+            a.miss_pages[r, :n], a.miss_slots[r, :n] = a.page_ids[r, at], a.slots[r, at]
+            a.kv_pool[a.slots[r, at].long()] = 7.0
+        a.mask_misses.fill_(-1)
+        a.out.fill_(3.0)
+        sp.gather_decode(w.batch, a.q0, a.host_kv, a.host_row_base_dev, a.nmiss, a.miss_pages, a.miss_slots, a.kv_pool,
+                         a.slots, a.page_ids, a.valid_mask, a.npages, a.mask_misses, a.out, a.lse, a.ws)
+        torch.cuda.synchronize()
+        assert a.status() == 0 and torch.equal(a.kv_pool, pool)
+        assert (a.out.float() - out).abs().max() <= 2 ** -6 * out.abs().max(), lens
+        assert (a.lse - lse).abs().max() <= 4e-5, lens
