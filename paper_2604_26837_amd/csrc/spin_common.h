@@ -16,7 +16,8 @@
 
 #define SPIN_SEL_HELD 2304    // longest selection handed over in LDS: a top 2048 with 256 forced ones; with these the launch by
                               // tile maxima stays under 64 KiB
-#define SPIN_FUSED_LDS (96 * 1024)   // dynamic LDS the launch that runs stages 2 to 4 may use beside some 25 KiB of its own
+#define SPIN_FUSED_LDS (96 * 1024)   // dynamic LDS the launch that runs stages 2 to 4 may use beside its own: 2 to 30 KiB, 62
+                              // with the tables of up to 4096 variable-length partitions (160 KiB in all, see the tests)
 
 #define SPIN_TILES_LDS (54 * 1024)           // scratch of the selection by tile maxima in that launch
 #define SPIN_STEP_TOKENS_LDS (8 * 1024)      // token lists of its 8 wavefronts
