@@ -812,13 +812,7 @@ def main():
                         pct_peak=round(100 * kv_bytes / (dec_us + side_us) / 1e3 / PEAK_HBM_GBPS, 2),
                         side_bytes=side_bytes, side_us=round(side_us, 3))
         ach = dec_bytes / dec_us / 1e3                                 # GB/s
-        parts = max(w.partitions(b) for b in range(w.batch))
-        # the fused launch's instantiation: scores (beyond 16384 partitions tile maxima) per thread, one-page partitions, tiles
-        tiles = parts > 16384
-        per_thread = next((k for k in (4, 8, 16, 32) if parts <= 512 * k), 8 if parts <= 65536 else 16)
-        one_page = str(w.partition_tokens == 16).lower()
-        kernel = f"spin_select_decode_tokens_kernel<{per_thread}, {str(tiles).lower()}>" if fused_24 and w.partition_tokens < 16 else \
-            f"spin_select_decode_kernel<{per_thread}, {one_page}, {str(tiles).lower()}, false, 0>" if fused_24 else \
+        kernel = sp.step_kernel()[1] if fused_24 else \
             "spin_decode_tokens_kernel<8>" if w.partition_tokens < 16 else \
             f"spin_decode_kernel<{args.decode_waves or 8}, {args.decode_depth or 2}>"
         traffic, traffic_note = read_traffic(os.path.join(ROOT, "profiles", f"{args.workload}_stage_kernels_pmc.txt"),
@@ -883,8 +877,9 @@ def main():
         "attended_kv_pct_peak": attended["pct_peak"] if attended else None,
         "attended_kv": attended,
         "step_launches": "four stage calls" if args.four_calls else (
-            "stages 1-3 in one call (stage 1 stores its tiles' maxima for stage 2, stage 2's launch resolves), attention (3 launches)" if fused_12
-            else "score, then select+resolve+attention in one launch (2 launches)" if fused_24
+            ("all four stages in one launch" if sp.step_kernel()[0] == 1
+             else "score, then select+resolve+attention in one launch (2 launches)") if fused_24
+            else "stages 1-3 in one call (stage 1 stores its tiles' maxima for stage 2, stage 2's launch resolves), attention (3 launches)" if fused_12
             else ("score, select+resolve with the sink / recent pages attended on the side, attention over the "
                   "other pages (3 launches)" if forced_split else "score, select+resolve, attention (3 launches)")),
         "kernels_plain_three_launch_step": plain_kernels or None,

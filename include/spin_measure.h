@@ -37,6 +37,11 @@ int spin_profile_read(spin_ctx *ctx, int32_t which, int32_t *count, float *mean_
  * the yardstick the stage kernels are compared with. */
 int spin_probe_stream_read(spin_ctx *ctx, const void *buf, size_t bytes, void *workspace, void *stream);
 
+/* The kernel that runs stages 2 to 4 of spin_decode_step in this context, as a profiler names it, in `name` (at most `size`
+ * bytes, ended by a zero).  Returns the call's launches: 2, or 1 where that kernel does stage 1 as well; 0 where the context
+ * does not support the call. */
+int32_t spin_step_kernel(const spin_ctx *ctx, char *name, int32_t size);
+
 #ifdef __cplusplus
 }
 #endif

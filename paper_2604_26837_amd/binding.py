@@ -31,6 +31,7 @@ EXPORTS = [
     "spin_set_host_page_table", "spin_set_step", "spin_advance_step", "spin_sparse_decode_static",
     "spin_select_resolve_forced", "spin_sparse_decode_rest", "spin_split_hits_misses", "spin_sparse_decode_begin",
     "spin_sparse_decode_finish", "spin_select_resolve_decode", "spin_fused_splits", "spin_decode_step", "spin_gather_decode",
+    "spin_step_kernel",
 ]
 
 
@@ -71,6 +72,8 @@ def load_library() -> C.CDLL:
     for n in ("spin_sel_stride", "spin_page_stride", "spin_dir_stride", "spin_decode_splits", "spin_fused_splits"):
         getattr(lib, n).argtypes = [vp]
         getattr(lib, n).restype = i32
+    lib.spin_step_kernel.argtypes = [vp, C.c_char_p, i32]
+    lib.spin_step_kernel.restype = i32
     lib.spin_summary_bytes.argtypes = [vp, i64]
     lib.spin_summary_bytes.restype = C.c_size_t
     lib.spin_workspace_init.argtypes = [vp, vp, vp]
@@ -202,6 +205,12 @@ class Spin:
 
     def summary_bytes(self, padded_partitions: int) -> int:
         return self.lib.spin_summary_bytes(self.h, padded_partitions)
+
+    def step_kernel(self):
+        """(launches of decode_step, name of the one that runs stages 2 to 4); (0, "") where it does not apply."""
+        name = C.create_string_buffer(128)
+        launches = self.lib.spin_step_kernel(self.h, name, len(name))
+        return launches, name.value.decode()
 
     KERNEL_IDS = dict(score=0, select=1, resolve=2, decode=3, merge=4, index=5, pack=6, gather=7, probe=8, select_hist=9, offload=10, append=11,
                       meta=12, select_decode=13)

@@ -14,6 +14,8 @@
 //
 // The row's always-attended pages are known before its scores are: each wavefront asks for the first of its own ahead of
 // the selection and attends it when the first selected ones are under way.
+#include <cstdio>
+
 #include "spin_score_dev.h"
 #include "spin_step_dev.h"
 
@@ -353,6 +355,12 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
                        a.lse);
 }
 
+// partitions of one page, leaves of four entries and more, in powers of two: the kernel's PAGES
+static bool step_one_page(const spin_ctx *ctx) {
+  const int32_t leaf = ctx->cfg.leaf_entries;
+  return ctx->cfg.partition_tokens == SPIN_PAGE_TOKENS && leaf >= 4 && (leaf & (leaf - 1)) == 0;
+}
+
 // Contexts whose stage 1 the launch of stages 2 to 4 does as well (score_row): a row's summaries fill two tiles of 8 KiB per
 // wavefront at most, or one where the rows are enough for a launch of stage 1 to stream.  Steps, us, two launches / one:
 // MINMAX, 64 pages to a row: 2 rows 10.8 / 9.5, 32 rows 14.0 / 12.1, 256 rows 26.4 / 25.4; 128 pages 12.9 / 11.6, 14.6 / 13.3,
@@ -361,9 +369,8 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
 static bool score_in_step(const spin_ctx *ctx) {
   const spin_config &c = ctx->cfg;
   const int64_t row_bytes = (int64_t)((ctx->max_parts + 15) / 16 * 16) * ctx->rows_per_part * ctx->kd * 2;
-  return c.partition_tokens == SPIN_PAGE_TOKENS && c.score_kind != SPIN_SCORE_SKETCH && !ctx->var.count &&
-         ctx->max_parts <= 2048 && row_bytes <= (ctx->max_rows <= 128 ? 128 : 64) * 1024 &&
-         c.leaf_entries >= 4 && (c.leaf_entries & (c.leaf_entries - 1)) == 0;
+  return step_one_page(ctx) && c.score_kind != SPIN_SCORE_SKETCH && !ctx->var.count && ctx->max_parts <= 2048 &&
+         row_bytes <= (ctx->max_rows <= 128 ? 128 : 64) * 1024;
 }
 
 // maxima_ready: stage 1 of this step has left its tiles' maxima in the workspace.  summaries: stage 1 has not run, its scores
@@ -396,6 +403,8 @@ static int select_resolve_decode_impl(spin_ctx *ctx, int32_t batch, const float 
                             (const uint4 *)summaries, scores_out, ctx->rows_per_part,
                             ctx->scale * 1.4426950408889634f};
   if (ctx->k_token_major) return spin_step_tokens_launch(ctx, batch, scores, part_offsets, seq_lens, dir, q, a, stream);
+  const int per_thread = spin_step_per_thread(ctx);
+  const bool one_page = step_one_page(ctx);
 #define SPIN_SD_LAUNCH1(KPT, PAGES, TILES, VAR, SCORE)                                                                   \
   spin_launch(ctx, SPIN_K_SELECT_DECODE, spin_select_decode_kernel<KPT, PAGES, TILES, VAR, SCORE>,                           \
               dim3((unsigned)ctx->fused_splits, (unsigned)c.num_kv_heads, (unsigned)batch), dim3(512), spin_fused_lds(ctx), \
@@ -404,19 +413,19 @@ static int select_resolve_decode_impl(spin_ctx *ctx, int32_t batch, const float 
 #define SPIN_SD_LAUNCH(KPT, TILES)                                                                \
   do {                                                                                            \
     if (!TILES && ctx->var.count) SPIN_SD_LAUNCH1(KPT, false, false, true, 0);                       \
-    else if (c.partition_tokens == SPIN_PAGE_TOKENS && leaf_log >= 2) SPIN_SD_LAUNCH1(KPT, true, TILES, false, 0); \
+    else if (one_page) SPIN_SD_LAUNCH1(KPT, true, TILES, false, 0);                                  \
     else SPIN_SD_LAUNCH1(KPT, false, TILES, false, 0);                                               \
   } while (0)
   if (summaries) {
     if (c.score_kind == SPIN_SCORE_MINMAX) SPIN_SD_LAUNCH1(4, true, false, false, SPIN_SCORE_MINMAX + 1);
     else SPIN_SD_LAUNCH1(4, true, false, false, SPIN_SCORE_REPMAX + 1);
   } else if (tiles) {
-    if (ctx->max_stride <= 2048) SPIN_SD_LAUNCH(4, true);
-    else if (ctx->max_stride <= 4096) SPIN_SD_LAUNCH(8, true);
+    if (per_thread == 4) SPIN_SD_LAUNCH(4, true);
+    else if (per_thread == 8) SPIN_SD_LAUNCH(8, true);
     else SPIN_SD_LAUNCH(16, true);
-  } else if (ctx->max_parts <= 2048) SPIN_SD_LAUNCH(4, false);
-  else if (ctx->max_parts <= 4096) SPIN_SD_LAUNCH(8, false);
-  else if (ctx->max_parts <= 8192) SPIN_SD_LAUNCH(16, false);
+  } else if (per_thread == 4) SPIN_SD_LAUNCH(4, false);
+  else if (per_thread == 8) SPIN_SD_LAUNCH(8, false);
+  else if (per_thread == 16) SPIN_SD_LAUNCH(16, false);
   else SPIN_SD_LAUNCH(32, false);
 #undef SPIN_SD_LAUNCH1
 #undef SPIN_SD_LAUNCH
@@ -464,3 +473,18 @@ extern "C" int spin_decode_step(spin_ctx *ctx, int32_t batch, const void *q, con
 }
 
 extern "C" int32_t spin_fused_splits(const spin_ctx *c) { return c ? c->fused_splits : 0; }
+
+extern "C" int32_t spin_step_kernel(const spin_ctx *ctx, char *name, int32_t size) {
+  if (!ctx || !name || size < 1) return SPIN_ERR_INVALID;
+  if (ctx->fused_splits == 0) return 0;
+  const spin_config &c = ctx->cfg;
+  const bool one = score_in_step(ctx), var = ctx->var.count != nullptr;
+  const char *tiles = ctx->step_tiles ? "true" : "false";
+  if (ctx->k_token_major)
+    snprintf(name, size, "spin_select_decode_tokens_kernel<%d, %s>", spin_step_per_thread(ctx), tiles);
+  else
+    snprintf(name, size, "spin_select_decode_kernel<%d, %s, %s, %s, %d>", one ? 4 : spin_step_per_thread(ctx),
+             step_one_page(ctx) && !var ? "true" : "false", tiles, var ? "true" : "false",
+             one ? (c.score_kind == SPIN_SCORE_MINMAX ? SPIN_SCORE_MINMAX : SPIN_SCORE_REPMAX) + 1 : 0);
+  return one ? 1 : 2;
+}

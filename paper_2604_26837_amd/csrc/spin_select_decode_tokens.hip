@@ -170,13 +170,14 @@ int spin_step_tokens_launch(spin_ctx *ctx, int32_t batch, const float *scores, c
               dim3((unsigned)(rows * ctx->fused_splits)), dim3(512), spin_fused_lds(ctx), (hipStream_t)stream,    \
               scores, part_offsets, seq_lens, dir, (const uint16_t *)q, c.num_kv_heads, rows,                     \
               ctx->fused_splits, ctx->group, c.num_q_heads, ctx->dir_stride, a)
+  const int per_thread = spin_step_per_thread(ctx);
   if (ctx->step_tiles) {
-    if (ctx->max_stride <= 2048) SPIN_SDT_LAUNCH(4, true);
-    else if (ctx->max_stride <= 4096) SPIN_SDT_LAUNCH(8, true);
+    if (per_thread == 4) SPIN_SDT_LAUNCH(4, true);
+    else if (per_thread == 8) SPIN_SDT_LAUNCH(8, true);
     else SPIN_SDT_LAUNCH(16, true);
-  } else if (ctx->max_parts <= 2048) SPIN_SDT_LAUNCH(4, false);
-  else if (ctx->max_parts <= 4096) SPIN_SDT_LAUNCH(8, false);
-  else if (ctx->max_parts <= 8192) SPIN_SDT_LAUNCH(16, false);
+  } else if (per_thread == 4) SPIN_SDT_LAUNCH(4, false);
+  else if (per_thread == 8) SPIN_SDT_LAUNCH(8, false);
+  else if (per_thread == 16) SPIN_SDT_LAUNCH(16, false);
   else SPIN_SDT_LAUNCH(32, false);
 #undef SPIN_SDT_LAUNCH
   return spin_launch_status();

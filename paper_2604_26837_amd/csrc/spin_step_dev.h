@@ -32,6 +32,12 @@ struct spin_step_args {
 typedef tiles_row_lds<512, STEP_CAP> step_tiles_lds;
 static_assert(sizeof(step_tiles_lds) <= SPIN_TILES_LDS, "the selection by tile maxima fits");
 
+// scores, or tile maxima, that a thread of the launch holds
+static inline int spin_step_per_thread(const spin_ctx *ctx) {
+  if (ctx->step_tiles) return ctx->max_stride <= 2048 ? 4 : ctx->max_stride <= 4096 ? 8 : 16;
+  return ctx->max_parts <= 2048 ? 4 : ctx->max_parts <= 4096 ? 8 : ctx->max_parts <= 8192 ? 16 : 32;
+}
+
 // Which row and split a workgroup is.  Workgroups go to the chip's 8 dies in turn; the splits of a row, which all read its
 // scores, are 8 workgroups apart, on the same die, whose cache then asks for them once.
 struct step_place {

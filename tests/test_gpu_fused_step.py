@@ -324,3 +324,37 @@ def test_contexts_that_it_does_not_take():
         import ctypes as C
         assert sp.lib.spin_select_resolve_decode(sp.h, 1, fake, fake, fake, fake, fake, fake, fake, C.c_int64(1), fake, fake,
                                                  fake, fake, fake, fake, C.c_int64(1), fake, fake, fake, None) == -2
+
+
+@pytest.mark.parametrize("kw,launches,kernel", [
+    (dict(max_context=32768), 2, "spin_select_decode_kernel<4, true, false, false, 0>"),
+    (dict(max_context=4096), 1, "spin_select_decode_kernel<4, true, false, false, 1>"),
+    (dict(max_context=4096, score_kind=synth.SCORE_REPMAX, reps_per_partition=1), 1,
+     "spin_select_decode_kernel<4, true, false, false, 3>"),
+    (dict(max_context=65536), 2, "spin_select_decode_kernel<8, true, false, false, 0>"),
+    (dict(max_context=131072), 2, "spin_select_decode_kernel<16, true, false, false, 0>"),
+    (dict(max_context=262144), 2, "spin_select_decode_kernel<4, true, true, false, 0>"),
+    (dict(max_context=262144, max_batch=17), 2, "spin_select_decode_kernel<32, true, false, false, 0>"),
+    (dict(max_context=262144, leaf_entries=6), 2, "spin_select_decode_kernel<4, false, true, false, 0>"),
+    (dict(max_context=1000000), 2, "spin_select_decode_kernel<8, true, true, false, 0>"),
+    (dict(max_context=65536, partition_tokens=64), 2, "spin_select_decode_kernel<4, false, false, false, 0>"),
+    (dict(max_context=65536, partition_tokens=1, topk=1024), 2, "spin_select_decode_tokens_kernel<8, true>"),
+    (dict(max_context=8192, partition_tokens=1), 2, "spin_select_decode_tokens_kernel<16, false>"),
+    (dict(max_context=4096, lru_timestamps=8), 0, ""),
+])
+def test_the_kernel_that_a_context_takes(kw, launches, kernel):
+    assert binding.Spin(**dict(dict(max_batch=2, num_q_heads=8, num_kv_heads=2, topk=8), **kw)).step_kernel() == (launches, kernel)
+
+
+@pytest.mark.gpu
+def test_the_launches_are_as_many_as_it_says():
+    for kw in (dict(lens=(3000, 4000)), dict(lens=(40000, 3000)), dict(lens=(140000, 3000)), dict(lens=(9000,), part=64, topk=9),
+               dict(lens=(20000, 900), part=1, score=synth.SCORE_SKETCH)):
+        layer, _ = runner.build_device_layer(_workload(**kw))
+        sp = layer.spin
+        sp.profile_enable(8)
+        layer.step2(layer.q0)
+        torch.cuda.synchronize()
+        ran = {name: sp.profile_read(name)[0] for name in sp.KERNEL_IDS}
+        sp.profile_enable(0)
+        assert {n: c for n, c in ran.items() if c} == {"select_decode": 1, **({"score": 1} if sp.step_kernel()[0] == 2 else {})}
