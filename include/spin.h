@@ -362,7 +362,8 @@ int spin_sparse_decode_rest(spin_ctx *ctx, int32_t batch, const void *q, const v
                             const int32_t *npages, void *out, float *lse, void *workspace, void *stream);
 
 /* Stages 2, 3 and 4 in one launch: every workgroup that attends a part of a row's pages selects and
- * resolves the row for itself.  Arguments as in the stage calls; sel, nsel, slots, page_ids, valid_mask and
+ * resolves the row for itself.  (Two launches where the context's rows are selected by the maxima of their score tiles, see
+ * below: the first takes them.)  Arguments as in the stage calls; sel, nsel, slots, page_ids, valid_mask and
  * npages are exactly theirs, out and lse are stage 4's results to its tolerance (the pages are summed in another
  * order), identical from run to run and whatever else is in the call.  spin_fused_splits says whether a context
  * supports it: the number of those workgroups per row, or 0, and then the call is SPIN_ERR_UNSUPPORTED before
@@ -373,8 +374,10 @@ int spin_select_resolve_decode(spin_ctx *ctx, int32_t batch, const float *scores
                                uint16_t *valid_mask, int32_t *npages, const void *q, const void *kv_pool,
                                int64_t pool_slots, void *out, float *lse, void *workspace, void *stream);
 int32_t spin_fused_splits(const spin_ctx *ctx);
-/* spin_score_partitions and the above in one call (two launches, or one where the contexts are small; rows of more than 16384 partitions are selected from
- * the maxima that stage 1 takes of its tiles).  Same results, same conditions. */
+/* spin_score_partitions and the above in one call: two launches, or one where the contexts are small.  Rows are selected by
+ * the maxima that stage 1 takes of its tiles in contexts of uniform partitions, more than 16384 to a row, and from 8193 on
+ * where topk tiles of 16 summary rows are no more than a row has and the partitions are smaller than a page or the rows at
+ * most 32.  Same results, same conditions. */
 int spin_decode_step(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries, const int32_t *chan_idx,
                      const int32_t *part_offsets, const int32_t *seq_lens, float *scores, int32_t *sel, int32_t *nsel,
                      const int32_t *dir, const int32_t *leaf_pool, int64_t leaf_chunks, int32_t *slots, int32_t *page_ids,

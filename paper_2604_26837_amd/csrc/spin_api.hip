@@ -26,7 +26,8 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   if (c->variable_partitions && tp < 16) return SPIN_ERR_UNSUPPORTED;
   // the key sketch is one row per token: every SKETCH kernel takes summary row == token
   if (c->score_kind == SPIN_SCORE_SKETCH && tp != 1) return SPIN_ERR_UNSUPPORTED;
-  if (c->score_tiles_per_wg < 0 || (c->score_waves != 0 && c->score_waves != 1 && c->score_waves != 2 && c->score_waves != 4 && c->score_waves != 8))
+  if (c->score_tiles_per_wg < 0 ||
+      (c->score_waves != 0 && c->score_waves != 1 && c->score_waves != 2 && c->score_waves != 4 && c->score_waves != 8))
     return SPIN_ERR_INVALID;
 
   spin_ctx *x = new (std::nothrow) spin_ctx;
@@ -84,7 +85,7 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
     return SPIN_ERR_INVALID;
   }
   x->waves = c->decode_waves ? c->decode_waves : 8;
-  x->depth = c->decode_depth ? c->decode_depth : 2;   // (partitions smaller than a page: the gathered tiles have two of their own)
+  x->depth = c->decode_depth ? c->decode_depth : 2;   // (partitions smaller than a page: gathered tiles have two of their own)
   int32_t splits = c->decode_splits;
   if (splits == 0) {
     // about one 8-wave workgroup on each of the 256 compute units, all resident
@@ -117,7 +118,8 @@ extern "C" int spin_create(const spin_config *c, spin_ctx **out) {
   x->tile_log = x->rows_per_part == 4 ? 2 : x->rows_per_part == 2 ? 3 : 4;
   const bool maxima = x->max_parts <= 131072 && !c->variable_partitions;
   x->step_tiles = maxima && (x->max_parts > 16384 ||
-                             (x->max_parts > 8192 && c->lru_timestamps == 0 && ((int64_t)c->topk << x->tile_log) <= x->max_parts &&
+                             (x->max_parts > 8192 && c->lru_timestamps == 0 &&
+                              ((int64_t)c->topk << x->tile_log) <= x->max_parts &&
                               (tp < SPIN_PAGE_TOKENS || x->max_rows <= 32)));
   if (maxima && (x->max_parts > 16384 || x->step_tiles))
     x->max_stride = ((cdiv32(x->max_parts, 16) * 16 >> x->tile_log) + 3) & ~3;

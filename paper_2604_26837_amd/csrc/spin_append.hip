@@ -15,7 +15,9 @@
 // other: token 0 / 3 / 15 / 64 / 127 of it 2.9 / 3.7 / 6.8 / 19.9 / 36.5 -> 2.9 / 3.8 / 3.8 / 4.9 / 5.9 us.
 #include "spin_common.h"
 
-__device__ inline size_t k_elem(int token_major, int t, int d) { return ((size_t)spin_k_unit(token_major, t, d >> 3) << 3) + (d & 7); }
+__device__ inline size_t k_elem(int token_major, int t, int d) {
+  return ((size_t)spin_k_unit(token_major, t, d >> 3) << 3) + (d & 7);
+}
 __device__ inline size_t v_elem(int token_major, int t, int d) {
   if (token_major) return (size_t)t * SPIN_HEAD_DIM + d;
   return (((size_t)((d >> 5) * 64 + (t >> 2) * 16 + (d & 15)) * 2 + ((d >> 4) & 1)) << 2) + (t & 3);

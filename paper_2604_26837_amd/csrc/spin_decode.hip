@@ -127,8 +127,8 @@ __global__ __launch_bounds__(WAVES * 64) void spin_decode_tokens_kernel(
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // before the next batch overwrites the list
   }
   __syncthreads();   // the merge buffers are separate from the lists, but keep the phases apart
-  decode_finish<WAVES, false, true>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, pstride, part_ml, part_acc, tickets, out,
-                       lse);
+  decode_finish<WAVES, false, true>(st, row, split, b, h, lane, wave, n, c, G, Hq, nsplit, pstride, part_ml, part_acc,
+                                    tickets, out, lse);
 }
 
 // Host side of stage 4: checks, then the launch; the split-K scratch (row tickets, (m, l) pairs and

@@ -87,10 +87,10 @@ __device__ __forceinline__ void tile_attend(softmax_state &st, const spin_f32x4 
 }
 
 // Attends `cnt` (<= 64) pages whose slot and mask are held one per lane (lane i: the i-th page; a slot inside the pool
-// in every lane), in lane order from page `from` on, through a ring of DEPTH register buffers.  A tile's registers are loaded again as soon
-// as it has been consumed, and what lies past the end is loaded as an empty page, so that the loop is straight-line
-// code that waits for exactly the tile it is about to read (see spin_buffer).  `asked` runs once the first DEPTH pages
-// have been asked for.
+// in every lane), in lane order from page `from` on, through a ring of DEPTH register buffers.  A tile's registers are
+// loaded again as soon as it has been consumed, and what lies past the end is loaded as an empty page, so that the loop
+// is straight-line code that waits for exactly the tile it is about to read (see spin_buffer).  `asked` runs once the
+// first DEPTH pages have been asked for.
 template <int DEPTH, typename ASKED>
 __device__ __forceinline__ void attend_lane_pages(softmax_state &st, const uint4 *__restrict__ pool, int myslot,
                                                   unsigned mymask, int from, int cnt, int lane, int c,
@@ -161,8 +161,8 @@ __device__ inline void write_out(uint16_t *__restrict__ out, float *__restrict__
 
 // After a workgroup's wavefronts have consumed their tiles: merge the wavefront partials through
 // LDS and, with several splits, the workgroup partials through the workspace (see the header).
-// Partial `s` of a row lives at index row * pstride + s (pstride = splits + the partials earlier launches may leave); the row's output is
-// the merge, in index order, of the partials 0 .. nsplit-1 of the calling launch.
+// Partial `s` of a row lives at index row * pstride + s (pstride = splits + the partials earlier launches may leave); the
+// row's output is the merge, in index order, of the partials 0 .. nsplit-1 of the calling launch.
 // ONLY_PARTIAL (then `split` is the index j of the calling workgroup among those that attend a row's
 // always-attended pages): the workgroup only stores its partial, at index nsplit + j, for a later
 // launch on the same stream to start from.

@@ -31,8 +31,8 @@ __global__ __launch_bounds__(512) void spin_gather_decode_kernel(
     float *part_acc, int32_t *tickets, uint16_t *__restrict__ out, float *__restrict__ lse, int32_t *status) {
   if (blockIdx.x < COPY_WGS) {
     if (threadIdx.x >= COPY_WAVES * 64) return;          // whole wavefronts: a barrier does not wait for those that have ended
-    copy_pages<false, COPY_WAVES>(blockIdx.x, COPY_WGS, host_kv, row_base, nmiss, miss_pages, miss_slots, pool, pool_slots, page_stride,
-                         rows, status, hm);
+    copy_pages<false, COPY_WAVES>(blockIdx.x, COPY_WGS, host_kv, row_base, nmiss, miss_pages, miss_slots, pool, pool_slots,
+                                  page_stride, rows, status, hm);
     return;
   }
   const int at = blockIdx.x - COPY_WGS, row = at / nsplit;

@@ -134,10 +134,10 @@ extern "C" int spin_alloc_leaves(spin_ctx *ctx, int32_t batch, const int32_t *se
   if (ctx->var.count) return SPIN_ERR_UNSUPPORTED;
   const spin_config &c = ctx->cfg;
   const int rows = batch * c.num_kv_heads;
-  spin_launch(ctx, SPIN_K_META, spin_alloc_leaves_kernel, dim3((unsigned)rows), dim3(META_BLOCK), 0, (hipStream_t)stream, sel, nsel,
-                     seq_lens, dir, leaf_pool, leaf_chunks, leaf_bitmap, c.num_kv_heads, c.partition_tokens,
-                     c.sink_pages, c.recent_pages, ctx->sel_stride, ctx->dir_stride, c.leaf_entries,
-                     (int32_t *)workspace);
+  spin_launch(ctx, SPIN_K_META, spin_alloc_leaves_kernel, dim3((unsigned)rows), dim3(META_BLOCK), 0, (hipStream_t)stream, sel,
+              nsel, seq_lens, dir, leaf_pool, leaf_chunks, leaf_bitmap, c.num_kv_heads, c.partition_tokens,
+              c.sink_pages, c.recent_pages, ctx->sel_stride, ctx->dir_stride, c.leaf_entries,
+              (int32_t *)workspace);
   return spin_launch_status();
 }
 

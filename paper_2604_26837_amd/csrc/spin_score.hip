@@ -109,7 +109,8 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch_kernel(
     __builtin_amdgcn_sched_barrier(0);
   }
   // A operand: row n = head, k = sketched channels 4c..4c+3
-  const spin_s16x4 qf = __builtin_bit_cast(spin_s16x4, n < G ? make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16)) : make_uint2(0u, 0u));
+  const spin_s16x4 qf =
+      __builtin_bit_cast(spin_s16x4, n < G ? make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16)) : make_uint2(0u, 0u));
   spin_f32x4 start;
 #pragma unroll
   for (int i = 0; i < 4; ++i) start[i] = 4 * c + i < G ? 0.f : -__builtin_inff();
@@ -195,7 +196,8 @@ __global__ __launch_bounds__(SCORE_WAVES * 64) void spin_score_sketch4_kernel(
   spin_s16x4 qa[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j)
-    qa[j] = __builtin_bit_cast(spin_s16x4, (n >> 2) == j && (n & 3) < G ? make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16)) : make_uint2(0u, 0u));
+    qa[j] = __builtin_bit_cast(spin_s16x4, (n >> 2) == j && (n & 3) < G ? make_uint2(e[0] | (e[1] << 16), e[2] | (e[3] << 16))
+                                                                       : make_uint2(0u, 0u));
   for (int t0 = t_begin + wave * 4 * U; t0 < t_end; t0 += ROUND) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {

@@ -77,8 +77,9 @@ __global__ __launch_bounds__(BLOCK) void spin_select_tiles_kernel(
   // (with 32 maxima per thread there is no register to hold it in)
   if (RESOLVE && MPT < 32) mydir = row_dir_entry(ra.dir, dir_stride, row);
   const sel_row<HELD> rsel = {sel + (size_t)row * sel_stride, sel_stride, (spin_lds_i32 *)s_held.sel};
-  const int take = select_tiles_row<BLOCK, MPT, CAP, HELD>(scores, maxima, max_stride, gs_log, part_offsets, seq_lens, Hkv, tp, topk,
-                                                           includes_forced, sink_pages, recent_pages, sel, rsel, nsel, row, s);
+  const int take = select_tiles_row<BLOCK, MPT, CAP, HELD>(scores, maxima, max_stride, gs_log, part_offsets, seq_lens, Hkv,
+                                                           tp, topk, includes_forced, sink_pages, recent_pages, sel, rsel,
+                                                           nsel, row, s);
   if (RESOLVE) {
     if (MPT >= 32) mydir = row_dir_entry(ra.dir, dir_stride, row);
     resolve_selected<BLOCK>(s_held, rsel, mydir, row, take, sel, seq_lens, ra.dir, ra.leaf_pool, ra.leaf_chunks, Hkv,

@@ -70,8 +70,9 @@ __device__ __forceinline__ asked_page page_ahead(bool mine, int first, const for
   return p;
 }
 
-// The selection of a row of partitions of one page, KPT of them per thread (`scores` gives a quad of theirs): the chosen pages in order to l_page, and with
-// `with_leaf` their leaf entries, which came with the scores, to l_slot (a thread's pages are quads of one leaf).
+// The selection of a row of partitions of one page, KPT of them per thread (`scores` gives a quad of theirs): the chosen
+// pages in order to l_page, and with `with_leaf` their leaf entries, which came with the scores, to l_slot (a thread's pages
+// are quads of one leaf).
 template <int BLOCK, int KPT, typename SCORES, typename ASK>
 __device__ __forceinline__ void select_pages(SCORES scores, const sel_plan &pl, bool with_leaf,
                                              int32_t lane_dir, int dir_stride, const spin_step_args &a, spin_lds_i32 *l_page,
@@ -94,7 +95,8 @@ __device__ __forceinline__ void select_pages(SCORES scores, const sel_plan &pl, 
         const int p = c0 + 4 * j, ci = p >> a.leaf_log;
         const int32_t chunk = __shfl(lane_dir, min(ci, dir_stride - 1));
         there[j] = ci < dir_stride && chunk >= 0 && (int64_t)chunk < a.leaf_chunks;
-        leaf[j] = *(const spin_i32x4_at4 *)(a.leaf_pool + (there[j] ? ((size_t)chunk << a.leaf_log) + (p & (a.leaf_entries - 1)) : 0));
+        const size_t at = there[j] ? ((size_t)chunk << a.leaf_log) + (p & (a.leaf_entries - 1)) : 0;
+        leaf[j] = *(const spin_i32x4_at4 *)(a.leaf_pool + at);
       }
     }
   }
@@ -223,7 +225,8 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     load_queries(qf, q, b, h, G, Hq, n, c);
     __builtin_amdgcn_sched_barrier(0);
     auto ask = [&] {
-      if constexpr (!SCORE) ask_ahead(page_ahead(asked, first, fs, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
+      if constexpr (!SCORE)
+        ask_ahead(page_ahead(asked, first, fs, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
       if (!with_leaf && tid < RES_DIR_LDS) held_words[tid] = mydir;
     };
     if constexpr (TILES) {
@@ -235,24 +238,30 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     } else {
       // the selection's plan: partitions are pages
       const int pages = min((N + 15) >> 4, PP), P = min(pages, BLOCK * KPT);
-      // (of a row beyond the context's longest the first BLOCK * KPT pages are kept, but all its forced ones count, as in stage 2)
+      // (of a row beyond the context's longest the first BLOCK * KPT pages are kept, but all its forced ones count, as in
+      // stage 2)
       const int beyond = a.includes_forced ? pages - max(min(fs.recent_begin, pages), P) : 0;
       const sel_plan pl = plan_of(P, min(fs.nlo, P), min(fs.recent_begin, P), a.topk - beyond, a.includes_forced, a.sel_stride);
       with_leaf = ahead && P <= 8 * BLOCK;
       if constexpr (SCORE != 0) {
-        score_row<SCORE == SPIN_SCORE_MINMAX + 1>(qf, a.summ, (size_t)Hkv * off + (size_t)h * PP, PP, a.reps, G, wave, lane, s_scores,
-                                              BLOCK * KPT, store ? a.scores_out : nullptr);
+        score_row<SCORE == SPIN_SCORE_MINMAX + 1>(qf, a.summ, (size_t)Hkv * off + (size_t)h * PP, PP, a.reps, G, wave, lane,
+                                                  s_scores, BLOCK * KPT, store ? a.scores_out : nullptr);
         __syncthreads();
         select_pages<BLOCK, KPT>([&](int at) { return *(const float4 *)(s_scores + at); }, pl, with_leaf, lane_dir, dir_stride, a,
                                  l_page, l_slot, s, ask);
       } else {
         // zeros past the row's end
-        const __amdgpu_buffer_rsrc_t buf = spin_buffer(scores + (size_t)Hkv * off + (size_t)h * PP, (uint32_t)max(PP, 0) * sizeof(float));
+        const __amdgpu_buffer_rsrc_t buf =
+            spin_buffer(scores + (size_t)Hkv * off + (size_t)h * PP, (uint32_t)max(PP, 0) * sizeof(float));
         auto quad = [&](int at) { return __builtin_bit_cast(float4, spin_buffer_load_kept(buf, (uint32_t)at * sizeof(float))); };
-        if (KPT == 4 || P <= 4 * BLOCK) select_pages<BLOCK, 4>(quad, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
-        else if (KPT == 8 || P <= 8 * BLOCK) select_pages<BLOCK, 8>(quad, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
-        else if (KPT == 16 || P <= 16 * BLOCK) select_pages<BLOCK, 16>(quad, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
-        else select_pages<BLOCK, 32>(quad, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+        if (KPT == 4 || P <= 4 * BLOCK)
+          select_pages<BLOCK, 4>(quad, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+        else if (KPT == 8 || P <= 8 * BLOCK)
+          select_pages<BLOCK, 8>(quad, pl, with_leaf, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+        else if (KPT == 16 || P <= 16 * BLOCK)
+          select_pages<BLOCK, 16>(quad, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
+        else
+          select_pages<BLOCK, 32>(quad, pl, false, lane_dir, dir_stride, a, l_page, l_slot, s, ask);
       }
       np = min(pl.take, a.page_stride);
     }
@@ -263,7 +272,8 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
     const step_sel rsel = {a.sel + (size_t)row * a.sel_stride, a.sel_stride, (spin_lds_i32 *)s_held.sel, store};
     auto ask = [&] {
       mydir = row_dir_entry(dir, dir_stride, row);
-      if constexpr (!VAR && !TILES) ask_ahead(page_ahead(asked, first, fs, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
+      if constexpr (!VAR && !TILES)
+        ask_ahead(page_ahead(asked, first, fs, lane_dir, dir_stride, a.leaf_chunks, a.leaf_entries, a.leaf_log));
     };
     int take;
     spin_var_span span;
@@ -273,8 +283,9 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
                                                           a.tp, a.topk, a.includes_forced, a.sink_pages, a.recent_pages,
                                                           a.sel, rsel, a.nsel, row, *(step_tiles_lds *)smem);
     } else {
-      take = select_reg_row<BLOCK, KPT, (TABLES > 0)>(scores, part_offsets, seq_lens, Hkv, a.tp, a.topk, a.includes_forced, a.sink_pages,
-                                        a.recent_pages, rsel, a.nsel, row, VAR ? a.var : spin_var{}, span, s, ask, s_tables);
+      take = select_reg_row<BLOCK, KPT, (TABLES > 0)>(scores, part_offsets, seq_lens, Hkv, a.tp, a.topk, a.includes_forced,
+                                                      a.sink_pages, a.recent_pages, rsel, a.nsel, row,
+                                                      VAR ? a.var : spin_var{}, span, s, ask, s_tables);
     }
     if (tid < RES_DIR_LDS) s_held.dir[tid] = mydir;
     __syncthreads();                   // the selection and the directory are whole
@@ -282,8 +293,9 @@ __global__ __launch_bounds__(512) void spin_select_decode_kernel(
       for (int i = tid; i < take; i += BLOCK) rsel.out[i] = rsel.lds[i];
     const step_pages list = {res_row_out(a.slots, a.page_ids, a.valid_mask, a.npages, row, a.page_stride), l_slot, l_mask, store};
     np = resolve_row<BLOCK, true, true, true, TABLES>(row, take, a.sel, seq_lens, dir, a.leaf_pool, a.leaf_chunks, Hkv, a.tp,
-                                              a.sink_pages, a.recent_pages, a.sel_stride, a.page_stride, dir_stride,
-                                              a.leaf_entries, list, a.status, VAR ? a.var : spin_var{}, VAR ? &span : nullptr, &s_held, s_tables);
+                                                      a.sink_pages, a.recent_pages, a.sel_stride, a.page_stride, dir_stride,
+                                                      a.leaf_entries, list, a.status, VAR ? a.var : spin_var{},
+                                                      VAR ? &span : nullptr, &s_held, s_tables);
   }
   __syncthreads();
 
@@ -442,8 +454,8 @@ extern "C" int spin_select_resolve_decode(spin_ctx *ctx, int32_t batch, const fl
                                     stream, false, nullptr, nullptr);
 }
 
-// Stages 1 to 4 in one call, two launches (small contexts: one): stage 1 (for rows of more than 16384 partitions with its tiles' maxima), then
-// the above.
+// Stages 1 to 4 in one call, two launches (small contexts: one): stage 1 (with its tiles' maxima in contexts whose rows are
+// selected by them, see step_tiles), then the above.
 extern "C" int spin_decode_step(spin_ctx *ctx, int32_t batch, const void *q, const void *summaries, const int32_t *chan_idx,
                                 const int32_t *part_offsets, const int32_t *seq_lens, float *scores, int32_t *sel,
                                 int32_t *nsel, const int32_t *dir, const int32_t *leaf_pool, int64_t leaf_chunks,

@@ -135,8 +135,8 @@ __global__ __launch_bounds__(512) void spin_select_resolve_forced_kernel(
     int32_t *__restrict__ npages, int32_t *status, spin_forced_args fa) {
   if ((int)blockIdx.x >= rows) {
     const int idx = (int)blockIdx.x - rows, srow = idx / fa.nside;
-    attend_forced_row<8>(srow, idx - srow * fa.nside, fa.nside, fa.q, fa.pool, fa.pool_slots, seq_lens, dir, leaf_pool, leaf_chunks, Hkv,
-                         fa.G, fa.Hq, sink_pages, recent_pages, dir_stride, leaf_entries, fa.nsplit, fa.pstride,
+    attend_forced_row<8>(srow, idx - srow * fa.nside, fa.nside, fa.q, fa.pool, fa.pool_slots, seq_lens, dir, leaf_pool, leaf_chunks,
+                         Hkv, fa.G, fa.Hq, sink_pages, recent_pages, dir_stride, leaf_entries, fa.nsplit, fa.pstride,
                          fa.scale_log2e, fa.part_ml, fa.part_acc, fa.skip);
     return;
   }
@@ -225,7 +225,8 @@ static int select_resolve_impl(spin_ctx *ctx, int32_t batch, const float *scores
   } while (0)
   if (ctx->max_parts <= 2048) SPIN_SR_LAUNCH1(512, 4, true);   // no selection of so few partitions is longer
   else if (ctx->max_parts <= 4096) SPIN_SR_LAUNCH(512, 8);
-  else if (ctx->max_parts <= 8192) SPIN_SR_LAUNCH(512, 16);   // against 1024 x 8 and 1024 x 16, stages 2+3 of 8 rows: 9.0 / 10.4 / 11.8 us
+  // against 1024 x 8 and 1024 x 16, stages 2+3 of 8 rows: 9.0 / 10.4 / 11.8 us
+  else if (ctx->max_parts <= 8192) SPIN_SR_LAUNCH(512, 16);
   else SPIN_SR_LAUNCH(1024, 16);
 #undef SPIN_SR_LAUNCH
 #undef SPIN_SR_LAUNCH1

@@ -30,9 +30,9 @@ __device__ __forceinline__ int32_t row_dir_entry(const int32_t *__restrict__ dir
 // HELD is a variant of the kernel: told apart at every store it cost what it gained (2 rows of 256: 13.6 -> 13.9).
 template <int BLOCK, bool HELD>
 __device__ __forceinline__ void resolve_selected(
-    held_row<HELD> &held, const sel_row<HELD> &rsel, int32_t mydir, int row, int take, int32_t *sel, const int32_t *__restrict__ seq_lens,
-    const int32_t *dir, const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks, int Hkv, int tp, int sink_pages,
-    int recent_pages, int page_stride, int dir_stride, int leaf_entries, int32_t *__restrict__ slots,
+    held_row<HELD> &held, const sel_row<HELD> &rsel, int32_t mydir, int row, int take, int32_t *sel,
+    const int32_t *__restrict__ seq_lens, const int32_t *dir, const int32_t *__restrict__ leaf_pool, int64_t leaf_chunks,
+    int Hkv, int tp, int sink_pages, int recent_pages, int page_stride, int dir_stride, int leaf_entries, int32_t *__restrict__ slots,
     int32_t *__restrict__ page_ids, uint16_t *__restrict__ valid_mask, int32_t *__restrict__ npages, int32_t *status,
     spin_var var, const spin_var_span *known) {
   static_assert(BLOCK >= RES_DIR_LDS, "an entry per thread");
