@@ -285,6 +285,23 @@ def test_a_row_longer_than_its_context(kw, longest):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("kw", [
+    dict(lens=(3000, 4000, 100)),                                     # stage 1 in the same launch
+    dict(lens=(40000, 3000, 100)),
+    dict(lens=(300000, 3000, 50)),
+    dict(lens=(9000, 3000, 70), part=64, topk=9),
+    dict(lens=(20000, 900, 8), part=1, score=synth.SCORE_SKETCH),
+    dict(lens=(5000, 300, 8), part=4, topk=60),
+])
+@pytest.mark.parametrize("splits", [0, 3])
+def test_rows_without_a_token(kw, splits):
+    layer, _ = runner.build_device_layer(_workload(**kw), decode_splits=splits)
+    layer.seq_lens[1] = 0
+    _same_as_stage_calls(layer, layer.q0)
+    assert (layer.out[1] == 0).all() and (layer.lse[1] == float("-inf")).all()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("kw", [dict(lens=(9001, 4000)), dict(lens=(20001, 4000), part=1, score=synth.SCORE_SKETCH)])
 def test_replays_of_a_graph(kw):
     layer, _ = runner.build_device_layer(_workload(topk=64, **kw))
